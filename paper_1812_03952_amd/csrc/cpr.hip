@@ -233,11 +233,12 @@ static hipStream_t side_stream() {
   return ss[dev];
 }
 
-// The second-stage set-up (block Jacobi or layer RAS) reads only the
+// The second-stage set-up (block Jacobi, DILU or layer RAS) reads only the
 // decoupled blocks, the AMG set-up only the pressure matrix: the former runs
 // on a side stream while the latter (many small launches and host reads)
-// runs on the caller's stream.  The global DILU set-up stays on the
-// caller's stream (its workgroups wait on each other).  Both streams are
+// runs on the caller's stream.  (The DILU set-up's workgroups wait on each
+// other, but only on workgroups that took their ticket before them and so
+// are already running, whatever else the device runs.)  Both streams are
 // idle again when this returns, on every path.
 extern "C" rs_status rs_cpr_setup(rs_bsr A, rs_dcpl D, const rs_cpr_opts *o, void *stream, rs_cpr *out) {
   if (!A || !D || !out || D->A != A) return RS_E_ARG;
@@ -253,7 +254,7 @@ extern "C" rs_status rs_cpr_setup(rs_bsr A, rs_dcpl D, const rs_cpr_opts *o, voi
       opts.max_row_sum != opts.max_row_sum)
     return RS_E_ARG;
   hipStream_t s = rs_stream(stream);
-  hipStream_t ss = opts.smoother == RS_SM_DILU ? nullptr : side_stream();
+  hipStream_t ss = side_stream();
   hipEvent_t ev = nullptr;
   if (ss && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) { ev = nullptr; ss = nullptr; }
   if (!ss) ss = s;
@@ -289,13 +290,12 @@ extern "C" rs_status rs_cpr_setup(rs_bsr A, rs_dcpl D, const rs_cpr_opts *o, voi
       if (hipGetLastError() != hipSuccess) { st = RS_E_HIP; break; }
     } else if (ras) {
       if ((st = rs_ras_setup_run(M, flag.as<int>(), ss)) != RS_OK) break;
+    } else {
+      if ((st = rs_dilu_prepare(M, ss)) != RS_OK) break;
+      if ((st = rs_dilu_setup_run(M, flag.as<int>(), ss)) != RS_OK) break;
     }
     if ((st = rs_amg_level0(M, s)) != RS_OK) break;
     if ((st = rs_amg_build(M, s)) != RS_OK) break;
-    if (opts.smoother == RS_SM_DILU) {
-      if ((st = rs_dilu_prepare(M)) != RS_OK) break;
-      if ((st = rs_dilu_setup_run(M, flag.as<int>(), s)) != RS_OK) break;
-    }
   } while (0);
   if (split && launched) {
     // join: the caller's stream waits for the side stream; the read of the

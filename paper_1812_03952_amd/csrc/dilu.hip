@@ -32,14 +32,16 @@
 #include "rs_internal.h"
 #include <math.h>
 #include <algorithm>
-#include <stdlib.h>
+#include <type_traits>
 
 namespace {
 #pragma clang fp contract(off)
 #include "block4.h"
 #pragma clang fp contract(fast)
 #include "quad4.h"
+#include "quadinv.h"
 
+constexpr int FL = 32;                  // a brick's level count has a cache line of its own
 constexpr int SPIN_LIMIT = 1 << 22;     // about a quarter of a second of polling
 constexpr int XSPIN_LIMIT = 1 << 20;    // face-word polls (each a device-scope load): about a second
 
@@ -62,28 +64,17 @@ __device__ __forceinline__ void st_dev(T *p, T v) { __hip_atomic_store(p, v, __A
 template <class T>
 __device__ __forceinline__ T ld_dev(const T *p) { return __hip_atomic_load(const_cast<T *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// cell slot of a brick: faces first (so that they all land in wave 0).
-// fwd: outgoing faces are jl == B-1 and kl == B-1; bwd: jl == 0 and kl == 0.
-template <int B, bool FWD>
-__device__ __forceinline__ void cell_of(int cl, int &jl, int &kl) {
-  int f = FWD ? B - 1 : 0;
-  if (cl < B) { jl = f; kl = cl; return; }
-  if (cl < 2 * B - 1) {
-    int t = cl - B;                         // 0 .. B-2
-    kl = f;
-    jl = FWD ? t : t + 1;
-    return;
-  }
-  int m = cl - (2 * B - 1);                 // interior (B-1)^2
-  jl = m % (B - 1);
-  kl = m / (B - 1);
-  if (!FWD) { jl += 1; kl += 1; }
-}
-
 __global__ void k_pipe_reset(int nb, int *__restrict__ done, int *__restrict__ ticket) {
   int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < nb) done[t] = 0;
+  if (t < nb) done[FL * t] = 0;
   if (t == 0) *ticket = 0;
+}
+
+// exchange words without a tag, no error
+__global__ void k_pipe_clear(int64_t words, uint64_t *__restrict__ x, int *__restrict__ ctl) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < 2) ctl[t] = 0;
+  if (t < words) x[t] = 0;
 }
 
 template <class T>
@@ -371,108 +362,228 @@ __global__ __launch_bounds__(64 * NW) void k_bwd_pipe(
 }
 
 // ---- factorisation: D_c = A~_cc - sum_{lower k} A~_ck D_k^{-1} A~_kc ----------
-// one thread per cell (B*B threads: one wave for B = 8); the previous level's
-// D^{-1} blocks of the brick in an LDS ring
-template <class T, int B>
-__global__ __launch_bounds__(B * B) void k_setup_pipe(
-    int nx, int ny, int nz, int NJ, const int *__restrict__ ord, int *__restrict__ ticket,
-    int *__restrict__ done, int *__restrict__ err, const T *__restrict__ t7, T *__restrict__ dinv2,
-    int *__restrict__ flag) {
-#pragma clang fp contract(off)
-  __shared__ T ring[2][B][B][16];
-  __shared__ int s_b;
+// Bricks of 8 x 8 x-lines, one workgroup each, walked by hyperplanes like the
+// sweeps' bricks: 4 compute waves with a quad of lanes per cell (lane r holds
+// block row r), a writer wave and a poller wave, one barrier per level.
+//   - compute: the D^{-1} rows of the three lower neighbours come from the
+//     previous level in an LDS ring (which has a slot for each line just
+//     outside the brick), the seven block rows of the next two levels are in
+//     flight in registers;
+//   - writer: copies the previous level from the ring to dinv2, the brick's
+//     outgoing faces with device-scope stores, waits for them and publishes
+//     the level count;
+//   - poller: waits for the two bricks before (bounded), loads their face
+//     blocks two levels ahead and puts them into the ring.
+// What bounds it is the chain nx + ny + nz of levels: a level is a cell's
+// dependency chain (three Schur products, then four pivot steps with a
+// division each), so the cells of a level are spread over as many SIMDs as
+// the brick has waves, and the brick is as large as keeps one compute wave
+// per SIMD: the step from a brick to the next costs the brick edge in levels
+// plus the face's way through memory, and larger bricks have fewer of them.
+// Measured: 1.45 ms in FP32 at 200x200x100 (5.83 ms with bricks of 4 x 4 lines
+// and one thread per cell), 0.74 ms in FP64 at 100x100x50 (2.05); a level of a
+// lone brick takes 1.85 us in FP32 (about 760 instructions in a compute
+// wave), 2.1 in FP64.  Each level count has a cache line of its own: packed
+// counts, polled by one brick and written by another, cost 15 % more.
+constexpr int SB = 8;                    // brick edge
+constexpr int SG = SB + 1;               // ring lines per side: one outside the brick
+
+// brick of ticket t in an order where every brick comes after the bricks
+// before it in j and in k: by J + K, then by K
+__device__ __forceinline__ int64_t diag_count(int64_t d, int64_t NJ, int64_t NK) {   // bricks with J + K < d
+  auto tri = [](int64_t x) { return x > 0 ? x * (x + 1) / 2 : (int64_t)0; };
+  return tri(d) - tri(d - NJ) - tri(d - NK) + tri(d - NJ - NK);
+}
+__device__ __forceinline__ void brick_of(int t, int NJ, int NK, int &J, int &K) {
+  int lo = 0, hi = NJ + NK - 2;          // the largest d with diag_count(d) <= t
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (diag_count(mid, NJ, NK) <= t) lo = mid; else hi = mid - 1;
+  }
+  K = max(0, lo - (NJ - 1)) + (int)(t - diag_count(lo, NJ, NK));
+  J = lo - K;
+}
+
+__device__ __forceinline__ void st4v(float *p, const float *v) { *(float4 *)p = make_float4(v[0], v[1], v[2], v[3]); }
+__device__ __forceinline__ void st4v(double *p, const double *v) {
+  ((double2 *)p)[0] = make_double2(v[0], v[1]);
+  ((double2 *)p)[1] = make_double2(v[2], v[3]);
+}
+template <class T> __device__ __forceinline__ void st_dev16(T *p, const T (&v)[16]) {   // 16 values, 8 bytes a store
+  constexpr int PER = 8 / sizeof(T);
+#pragma unroll
+  for (int e = 0; e < 16; e += PER) {
+    uint64_t w;
+    __builtin_memcpy(&w, &v[e], 8);
+    st_dev((uint64_t *)(p + e), w);
+  }
+}
+
+template <class T>
+__global__ __launch_bounds__(6 * 64) void k_setup_pipe(int nx, int ny, int nz, int NJ, int NK, int *__restrict__ ticket,
+                                                       int *done, int *__restrict__ err, const T *__restrict__ t7,
+                                                       T *dinv2, int *__restrict__ flag) {
+  constexpr int B = SB, NC = 4 * B * B;                 // compute lanes
+  __shared__ __align__(16) T ring[2][SG * SG][16];      // line (jl, kl) at (kl + 1) SG + jl + 1
+  __shared__ int s_t;
   const int tid = threadIdx.x;
-  int jl, kl;
-  cell_of<B, true>(tid, jl, kl);
-  if (tid == 0) s_b = ord[atomicAdd(ticket, 1)];
+  if (tid == 0) s_t = atomicAdd(ticket, 1);
   __syncthreads();
-  const int b = s_b, J = b % NJ, K = b / NJ;
-  const int j = J * B + jl, k = K * B + kl;
-  const bool line = j < ny && k < nz;
+  int J, K;
+  brick_of(s_t, NJ, NK, J, K);
+  const int b = J + NJ * K;
   const int64_t nxy = (int64_t)nx * ny, n = nxy * nz;
-  const int L = nx + 2 * B - 2;
-  const bool face = (jl == B - 1) || (kl == B - 1);
-  int seenJ = 0, seenK = 0, bad = 0;
-  bool failed = false;
-  for (int lam = 0; lam < L; ++lam) {
-    const int i = lam - jl - kl;
-    const bool act = line && i >= 0 && i < nx;
-    const int64_t c = act ? i + nx * (j + (int64_t)ny * k) : 0;
-    if (tid == 0) {
-      if (J > 0) seenJ = poll_until(done + b - 1, min(lam + B, L), seenJ, err, failed);
-      if (K > 0) seenK = poll_until(done + b - NJ, min(lam + B, L), seenK, err, failed);
+  const int L = nx + 2 * (B - 1);
+  if (tid >= NC + 64) {
+    // poller: lane (line of a face, row): the y face before the brick (lines
+    // kl), then the z face (lines jl)
+    const int lane = tid - NC - 64, r = lane & 3, pos = (lane >> 2) & 7;
+    const bool yf = lane < 32;
+    const int j = yf ? J * B - 1 : J * B + pos, k = yf ? K * B + pos : K * B - 1;
+    const bool has = yf ? J > 0 && k < nz : K > 0 && j < ny;
+    const int gs = yf ? (pos + 1) * SG : pos + 1;
+    const T *base = dinv2 + (has ? ((int64_t)k * nxy + (int64_t)j * nx) * 16 : 0) + 4 * r;
+    constexpr int NW = 4 * sizeof(T) / 8;               // 8-byte words of a block row
+    // the lanes of each face read their own predecessor's count, both in one
+    // round trip
+    const int *fl = done + FL * (yf ? b - 1 : b - NJ);
+    const bool pred = yf ? J > 0 : K > 0;
+    int seen = pred ? 0 : L;
+    bool failed = false;
+    auto issue = [&](int h, uint64_t (&w)[NW]) {
+      if (h >= L) return;
+      const int need = min(h + B, L);                   // the face cell of level h is at level h + B - 1 of its brick
+      int spins = 0;
+      while (__ballot(seen < need) != 0 && !failed) {
+        if (pred) seen = ld_dev(fl);
+        if (++spins > SPIN_LIMIT) { atomicOr(err, 1); failed = true; }
+      }
+      asm volatile("" ::: "memory");                    // the loads stay behind the polls
+      const int i = h - pos;
+      if (!has || i < 0 || i >= nx) return;
+#pragma unroll
+      for (int e = 0; e < NW; ++e) w[e] = ld_dev((const uint64_t *)(base + (int64_t)i * 16) + e);
+    };
+    auto put = [&](int h, const uint64_t (&w)[NW]) {
+      const int i = h - pos;
+      if (!has || h >= L || i < 0 || i >= nx) return;
+#pragma unroll
+      for (int e = 0; e < NW; ++e) *((uint64_t *)&ring[(h + 1) & 1][gs][4 * r] + e) = w[e];
+    };
+    uint64_t w[2][NW];
+    issue(0, w[0]);
+    put(0, w[0]);
+    issue(1, w[1]);
+    for (int h = 0; h < L; h += 2) {
+      __syncthreads();
+      put(h + 1, w[1]);
+      issue(h + 2, w[0]);
+      if (h + 1 >= L) break;
+      __syncthreads();
+      put(h + 2, w[0]);
+      issue(h + 3, w[1]);
     }
     __syncthreads();
-    const int prev = (lam + 1) & 1, cur = lam & 1;
-    if (act) {
-      double D[4][4];
-#pragma unroll
-      for (int e = 0; e < 16; ++e) D[e >> 2][e & 3] = (double)t7[(3 * n + c) * 16 + e];
-#pragma unroll
-      for (int s = 0; s < 3; ++s) {
-        bool has = s == 0 ? k > 0 : (s == 1 ? j > 0 : i > 0);
-        if (!has) continue;
-        int64_t q = c - (s == 0 ? nxy : (s == 1 ? (int64_t)nx : 1));
-        double Dq[4][4], Aqc[4][4], Acq[4][4], T1[4][4];
-        if (s == 0 && kl == 0) {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) Dq[e >> 2][e & 3] = (double)ld_dev(dinv2 + q * 16 + e);
-        } else if (s == 1 && jl == 0) {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) Dq[e >> 2][e & 3] = (double)ld_dev(dinv2 + q * 16 + e);
-        } else {
-          int rk = s == 0 ? kl - 1 : kl, rj = s == 1 ? jl - 1 : jl;
-#pragma unroll
-          for (int e = 0; e < 16; ++e) Dq[e >> 2][e & 3] = (double)ring[prev][rk][rj][e];
-        }
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          Aqc[e >> 2][e & 3] = (double)t7[((int64_t)(6 - s) * n + q) * 16 + e];
-          Acq[e >> 2][e & 3] = (double)t7[((int64_t)s * n + c) * 16 + e];
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int cc = 0; cc < 4; ++cc) {
-            double v = 0.0;
-#pragma unroll
-            for (int m = 0; m < 4; ++m) v = v + Dq[r][m] * Aqc[m][cc];
-            T1[r][cc] = v;
-          }
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int cc = 0; cc < 4; ++cc) {
-            double v = 0.0;
-#pragma unroll
-            for (int m = 0; m < 4; ++m) v = v + Acq[r][m] * T1[m][cc];
-            D[r][cc] = D[r][cc] - v;
-          }
-      }
-      double R[4][4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) R[r][qq] = (r == qq) ? 1.0 : 0.0;
-      bad |= gje4<4>(D, R);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        T v = (T)R[e >> 2][e & 3];
-        ring[cur][kl][jl][e] = v;
-        if (face) st_dev(dinv2 + c * 16 + e, v);
-        else dinv2[c * 16 + e] = v;
-      }
-    }
-    __builtin_amdgcn_s_waitcnt(0);
-    if (tid == 0) st_dev(done + b, lam + 1);
+    return;
   }
+  if (tid >= NC) {
+    // writer: line `lane` of the brick
+    const int lane = tid - NC, jl = lane & 7, kl = lane >> 3;
+    const int j = J * B + jl, k = K * B + kl;
+    const bool line = j < ny && k < nz, face = jl == B - 1 || kl == B - 1;
+    T *base = dinv2 + (line ? ((int64_t)k * nxy + (int64_t)j * nx) * 16 : 0);
+    auto write_level = [&](int h) {
+      const int i = h - jl - kl;
+      if (line && i >= 0 && i < nx) {
+        T v[16];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          T t4[4];
+          ld4v(&ring[h & 1][(kl + 1) * SG + jl + 1][4 * q], t4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[4 * q + e] = t4[e];
+        }
+        if (face) {
+          st_dev16(base + (int64_t)i * 16, v);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 16; e += 4) st4v(base + (int64_t)i * 16 + e, v + e);
+        }
+      }
+    };
+    // the stores of a level have a level's time to complete before its count
+    // is published
+    auto publish = [&](int cnt) {
+      __builtin_amdgcn_s_waitcnt(0);
+      asm volatile("" ::: "memory");
+      if (lane == 0) st_dev(done + FL * b, cnt);
+    };
+    for (int h = 0; h < L; ++h) {
+      __syncthreads();
+      if (h > 1) publish(h - 1);
+      if (h > 0) write_level(h - 1);
+    }
+    __syncthreads();
+    write_level(L - 1);
+    publish(L);
+    return;
+  }
+  const int r = tid & 3, q = tid >> 2, jl = q & 7, kl = q >> 3, wq = (tid & 63) & ~3;
+  const int j = J * B + jl, k = K * B + kl;
+  const bool line = j < ny && k < nz, hz = k > 0, hy = j > 0;
+  const int slot = (kl + 1) * SG + jl + 1;
+  const int64_t c0 = line ? (int64_t)k * nxy + (int64_t)j * nx : 0;
+  // this lane's rows of A~_cc, A~_cq and A~_qc for q before c in z, y, x
+  struct rows { T d[4], lo[3][4], up[3][4]; };
+  auto load = [&](int h, rows &p) {
+    int i = min(max(h - jl - kl, 0), nx - 1);
+    const int64_t c = c0 + i;
+    const int64_t qz = line && hz ? c - nxy : c, qy = line && hy ? c - nx : c, qx = i > 0 ? c - 1 : c;
+    ld4v(t7 + (3 * n + c) * 16 + 4 * r, p.d);
+    ld4v(t7 + c * 16 + 4 * r, p.lo[0]);
+    ld4v(t7 + (n + c) * 16 + 4 * r, p.lo[1]);
+    ld4v(t7 + (2 * n + c) * 16 + 4 * r, p.lo[2]);
+    ld4v(t7 + (6 * n + qz) * 16 + 4 * r, p.up[0]);
+    ld4v(t7 + (5 * n + qy) * 16 + 4 * r, p.up[1]);
+    ld4v(t7 + (4 * n + qx) * 16 + 4 * r, p.up[2]);
+  };
+  int bad = 0;
+  auto level = [&](int h, rows &p) {
+    __syncthreads();
+    const int i = h - jl - kl;
+    if (line && i >= 0 && i < nx) {                     // the same for the four lanes of the cell
+      const T(*prev)[16] = ring[(h + 1) & 1];
+      double Lr[4], Rr[4];
+#pragma unroll
+      for (int cc = 0; cc < 4; ++cc) Lr[cc] = (double)p.d[cc];
+      T dq[4];
+      if (hz) { ld4v(&prev[slot - SG][4 * r], dq); quad_schur<T>(Lr, dq, p.up[0], p.lo[0]); }
+      if (hy) { ld4v(&prev[slot - 1][4 * r], dq); quad_schur<T>(Lr, dq, p.up[1], p.lo[1]); }
+      if (i > 0) { ld4v(&prev[slot][4 * r], dq); quad_schur<T>(Lr, dq, p.up[2], p.lo[2]); }
+      int mine;
+      bad |= quad_inverse(Lr, Rr, r, wq, mine);
+      T *o = &ring[h & 1][slot][4 * mine];
+#pragma unroll
+      for (int cc = 0; cc < 4; ++cc) o[cc] = (T)Rr[cc];
+    }
+    load(h + 2, p);
+  };
+  rows p0, p1;
+  load(0, p0);
+  load(1, p1);
+  for (int h = 0; h < L; h += 2) {
+    level(h, p0);
+    if (h + 1 >= L) break;
+    level(h + 1, p1);
+  }
+  __syncthreads();
   if (bad) atomicOr(flag, bad);
 }
 
 }  // namespace
 
 // ---------------------------------------------------------------------------
-rs_status rs_dilu_prepare(rs_cpr_s *M) {
+rs_status rs_dilu_prepare(rs_cpr_s *M, hipStream_t s) {
   const grid3 &g = M->A->g;
   int B = BR;
   int NJ = (g.ny + B - 1) / B, NK = (g.nz + B - 1) / B, nb = NJ * NK;
@@ -485,16 +596,16 @@ rs_status rs_dilu_prepare(rs_cpr_s *M) {
     return da < db;
   });
   RS_TRY(M->pord.alloc(sizeof(int) * nb));
-  RS_TRY(M->pdone.alloc(sizeof(int) * (nb + 1)));
+  RS_TRY(M->pdone.alloc(sizeof(int) * FL * (size_t)nb));
   RS_TRY(M->pctl.alloc(sizeof(int) * 2));     // [0] ticket, [1] error
   // face exchange: 2 faces x B lines x nx cells x 4 values x (1 or 2) words
   size_t words = (size_t)nb * 2 * B * g.nx * 4 * (M->prec == 64 ? 2 : 1);
   if (sizeof(uint64_t) * words >= 0xffffffffull) return RS_E_ARG;   // one buffer resource covers it
   RS_TRY(M->pxch.alloc(sizeof(uint64_t) * words));
-  RS_HIP(hipMemset(M->pxch.p, 0, sizeof(uint64_t) * words));
+  k_pipe_clear<<<rs_grid(words), RS_BLOCK, 0, s>>>((int64_t)words, M->pxch.as<uint64_t>(), M->pctl.as<int>());
+  RS_HIP(hipGetLastError());
   M->pepoch = 0;
   RS_HIP(hipMemcpy(M->pord.p, ord.data(), sizeof(int) * nb, hipMemcpyHostToDevice));
-  RS_HIP(hipMemset(M->pctl.p, 0, sizeof(int) * 2));
   return RS_OK;
 }
 
@@ -505,16 +616,15 @@ static void pipe_reset(rs_cpr_s *M, hipStream_t s) {
 
 rs_status rs_dilu_setup_run(rs_cpr_s *M, int *flag, hipStream_t s) {
   const grid3 &g = M->A->g;
-  int nb = M->pnj * M->pnk;
+  const int NJ = (g.ny + SB - 1) / SB, NK = (g.nz + SB - 1) / SB;
   int *ctl = M->pctl.as<int>();
   pipe_reset(M, s);
-#define RS_SETUP(T, BB)                                                                            \
-  k_setup_pipe<T, BB><<<nb, BB * BB, 0, s>>>(g.nx, g.ny, g.nz, M->pnj, M->pord.as<int>(), ctl,      \
-                                             M->pdone.as<int>(), ctl + 1, M->D->t7.as<T>(),        \
-                                             M->dinv2.as<T>(), flag)
-  if (M->prec == 64) RS_SETUP(double, BR);
-  else RS_SETUP(float, BR);
-#undef RS_SETUP
+  if (M->prec == 64)
+    k_setup_pipe<double><<<NJ * NK, 6 * 64, 0, s>>>(g.nx, g.ny, g.nz, NJ, NK, ctl, M->pdone.as<int>(), ctl + 1,
+                                                    M->D->t7.as<double>(), M->dinv2.as<double>(), flag);
+  else
+    k_setup_pipe<float><<<NJ * NK, 6 * 64, 0, s>>>(g.nx, g.ny, g.nz, NJ, NK, ctl, M->pdone.as<int>(), ctl + 1,
+                                                   M->D->t7.as<float>(), M->dinv2.as<float>(), flag);
   RS_HIP(hipGetLastError());
   return RS_OK;
 }
