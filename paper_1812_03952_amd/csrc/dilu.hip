@@ -5,23 +5,21 @@
 // The recurrences run over hyperplanes i+j+k = const.  One launch per
 // hyperplane costs a few microseconds of launch and drain each (about 1000
 // launches per application at 200x200x100), so instead the grid is cut into
-// bricks of B x B x-lines (j, k) running along the whole x extent, and one
-// workgroup walks its brick hyperplane by hyperplane (local level
-// lambda = i + j_local + k_local): four lanes per cell (one block row each),
-// the previous level of the brick in an LDS ring, one barrier per level.
-// A brick needs, at level lambda, the face values of the bricks before it in
-// j and in k at their level lambda + B - 1, published through per-brick
-// progress counters.
+// bricks of x-lines (j, k) running along the whole x extent, and one workgroup
+// walks its brick hyperplane by hyperplane (local level h = i + jl + kl): a
+// quad of lanes per cell (one block row each), the previous level of the brick
+// in an LDS ring, one barrier per level.  A brick needs, at level h, the face
+// values that the bricks before it in j and in k computed at their level
+// h + edge - 1.
 //
 // Progress and visibility across workgroups (and across XCDs, whose L2 caches
 // are not coherent with each other):
-//   - the only values other bricks read are the brick's outgoing faces; all
-//     of them are mapped into wave 0 and stored with device-scope stores;
-//   - wave 0 waits for its stores to complete (s_waitcnt vmcnt(0)), then
-//     lane 0 stores the level counter with a device-scope store;
-//   - a consumer polls the counter with device-scope loads and reads the
-//     face values with device-scope loads, after a barrier that follows the
-//     poll.
+//   - the only values other bricks read are the brick's outgoing faces, stored
+//     with device-scope stores by a wave that does nothing but store;
+//   - the sweeps' values carry a tag; the factorisation's blocks are followed,
+//     once they are complete, by a level count;
+//   - a wave of its own in each brick reads them with device-scope loads, as
+//     often as it takes, and puts them into the ring.
 //   - bricks are handed out by a ticket counter in an order where every
 //     brick comes after the bricks it waits on, so a waiting workgroup only
 //     ever waits on workgroups that are already running: no deadlock,
@@ -42,48 +40,20 @@ namespace {
 #include "quadinv.h"
 
 constexpr int FL = 32;                  // a brick's level count has a cache line of its own
-constexpr int SPIN_LIMIT = 1 << 22;     // about a quarter of a second of polling
-constexpr int XSPIN_LIMIT = 1 << 20;    // face-word polls (each a device-scope load): about a second
-
-// Wait until *flag >= need.  After one time-out in a workgroup (recorded in
-// *err and in `failed`) it stops waiting altogether, so a failure costs one
-// time-out, not one per level.
-__device__ __forceinline__ int poll_until(const int *flag, int need, int seen, int *err, bool &failed) {
-  int spins = 0;
-  while (seen < need && !failed) {
-    seen = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (seen >= need) break;
-    __builtin_amdgcn_s_sleep(2);
-    if (++spins > SPIN_LIMIT) { atomicOr(err, 1); failed = true; }
-  }
-  return seen;
-}
+constexpr int SPIN_LIMIT = 1 << 20;     // polls (each a device-scope load): about a second
 
 template <class T>
 __device__ __forceinline__ void st_dev(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 template <class T>
 __device__ __forceinline__ T ld_dev(const T *p) { return __hip_atomic_load(const_cast<T *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-__global__ void k_pipe_reset(int nb, int *__restrict__ done, int *__restrict__ ticket) {
-  int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < nb) done[FL * t] = 0;
-  if (t == 0) *ticket = 0;
-}
-
-// exchange words without a tag, no error
-__global__ void k_pipe_clear(int64_t words, uint64_t *__restrict__ x, int *__restrict__ ctl) {
+// exchange words without a tag, no level done, no error
+__global__ void k_pipe_clear(int64_t words, uint64_t *__restrict__ x, int nb, int *__restrict__ done,
+                             int *__restrict__ ctl) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < 2) ctl[t] = 0;
+  if (t < 4) ctl[t] = 0;
+  if (t < nb) done[FL * t] = 0;
   if (t < words) x[t] = 0;
-}
-
-template <class T>
-__device__ __forceinline__ T group_mv(const T *__restrict__ Mrow, T v) {
-  int base = (threadIdx.x & 63) & ~3;
-  T out = 0;
-#pragma unroll
-  for (int m = 0; m < 4; ++m) out = fma(Mrow[m], __shfl(v, base + m, 64), out);
-  return out;
 }
 
 // ---- tagged exchange of brick faces ------------------------------------------
@@ -98,18 +68,9 @@ template <> struct xw<float> {
   __device__ static void put(uint64_t *p, float v, uint32_t tag) {
     st_dev(p, (uint64_t)(((uint64_t)tag << 32) | (uint64_t)__float_as_uint(v)));
   }
-  // spins until the tag matches; returns false on time-out
-  __device__ static bool get(const uint64_t *p, uint64_t &w0, uint64_t &, uint32_t tag, float &v, bool &failed) {
-    int spins = 0;
-    while ((uint32_t)(w0 >> 32) != tag && !failed) {
-      if (++spins > XSPIN_LIMIT) { failed = true; return false; }
-      __builtin_amdgcn_s_sleep(1);
-      w0 = ld_dev(p);
-    }
-    v = __uint_as_float((uint32_t)w0);
-    return true;
-  }
-  __device__ static void pre(const uint64_t *p, uint64_t &w0, uint64_t &) { w0 = ld_dev(p); }
+  __device__ static void get(const uint64_t *p, uint64_t (&w)[W]) { w[0] = ld_dev(p); }
+  __device__ static bool ready(const uint64_t (&w)[W], uint32_t tag) { return (uint32_t)(w[0] >> 32) == tag; }
+  __device__ static float value(const uint64_t (&w)[W]) { return __uint_as_float((uint32_t)w[0]); }
 };
 template <> struct xw<double> {
   static constexpr int W = 2;
@@ -118,247 +79,523 @@ template <> struct xw<double> {
     st_dev(p, (uint64_t)(((uint64_t)tag << 32) | (b & 0xffffffffull)));
     st_dev(p + 1, (uint64_t)(((uint64_t)tag << 32) | (b >> 32)));
   }
-  __device__ static bool get(const uint64_t *p, uint64_t &w0, uint64_t &w1, uint32_t tag, double &v, bool &failed) {
-    int spins = 0;
-    while (((uint32_t)(w0 >> 32) != tag || (uint32_t)(w1 >> 32) != tag) && !failed) {
-      if (++spins > XSPIN_LIMIT) { failed = true; return false; }
-      __builtin_amdgcn_s_sleep(1);
-      w0 = ld_dev(p);
-      w1 = ld_dev(p + 1);
-    }
-    v = __longlong_as_double((long long)(((w1 & 0xffffffffull) << 32) | (w0 & 0xffffffffull)));
-    return true;
+  __device__ static void get(const uint64_t *p, uint64_t (&w)[W]) { w[0] = ld_dev(p); w[1] = ld_dev(p + 1); }
+  __device__ static bool ready(const uint64_t (&w)[W], uint32_t tag) {
+    return (uint32_t)(w[0] >> 32) == tag && (uint32_t)(w[1] >> 32) == tag;
   }
-  __device__ static void pre(const uint64_t *p, uint64_t &w0, uint64_t &w1) { w0 = ld_dev(p); w1 = ld_dev(p + 1); }
+  __device__ static double value(const uint64_t (&w)[W]) {
+    return __longlong_as_double((long long)(((w[1] & 0xffffffffull) << 32) | (w[0] & 0xffffffffull)));
+  }
 };
 
-// word offset of the value (row r) of face cell (face f, position pos, i) of brick b
-template <class T, int B>
+__device__ __forceinline__ void st4v(float *p, const float *v) { *(float4 *)p = make_float4(v[0], v[1], v[2], v[3]); }
+__device__ __forceinline__ void st4v(double *p, const double *v) {
+  ((double2 *)p)[0] = make_double2(v[0], v[1]);
+  ((double2 *)p)[1] = make_double2(v[2], v[3]);
+}
+
+// A sweep's brick: BJ x BK x-lines in j and in k, BK = 4 or 8 (see
+// rs_dilu_prepare).  One poller wave covers both incoming faces, and a face
+// has BJ lines of exchange words.
+constexpr int BJ = 8;
+constexpr int RG = BJ + 2;               // ring row: the brick's lines, one outside, one to spread the LDS banks
+template <int BK> constexpr int ring_lines = RG * (BK + 1);
+
+// word of the value of block row r of face cell (face f, position pos, i) of brick b
+template <class T>
 __device__ __forceinline__ int64_t xslot(int b, int f, int pos, int i, int nx, int r) {
-  return ((((int64_t)b * 2 + f) * B + pos) * nx + i) * (4 * xw<T>::W) + r * xw<T>::W;
+  return ((((int64_t)b * 2 + f) * BJ + pos) * nx + i) * (4 * xw<T>::W) + r * xw<T>::W;
 }
 
-// ---- forward sweep: y_c = D_c^{-1} (r~2_c - sum_{lower k} A~_ck y_k) --------
-// Bricks of 4 x 4 x-lines, so one level of a brick is 16 cells x 4 block rows
-// = one wave.  The workgroup's NW waves take the levels in turn: wave w
-// computes levels w, w+NW, ...; right after computing a level it issues
-// every load of its next one (blocks, D^{-1} row, residual and correction
-// terms, and the neighbour bricks' face values).  A wave therefore only ever
-// has its own next level's loads in flight, which get NW-1 level-times to
-// land.  The previous level passes between waves through an LDS ring; one
-// barrier per level.  The per-level critical path is kept short: addresses
-// are a uniform per-array base plus one 32-bit lane offset, the 4-vectors of
-// neighbours are read whole from LDS (or were prefetched whole from the
-// exchange buffer), and the 4x4 products gather the other rows of the cell
-// with quad-broadcast DPP moves instead of LDS permutes.
-constexpr int BR = 4;                    // brick edge (x-lines per side)
-
-template <class T> __device__ __forceinline__ const T *at(const T *base, uint32_t byte_off) {
-  return (const T *)((const char *)base + byte_off);
+// brick of ticket t in an order where every brick comes after the bricks
+// before it in j and in k: by J + K, then by K
+__device__ __forceinline__ int64_t diag_count(int64_t d, int64_t NJ, int64_t NK) {   // bricks with J + K < d
+  auto tri = [](int64_t x) { return x > 0 ? x * (x + 1) / 2 : (int64_t)0; };
+  return tri(d) - tri(d - NJ) - tri(d - NK) + tri(d - NJ - NK);
+}
+__device__ __forceinline__ void brick_of(int t, int NJ, int NK, int &J, int &K) {
+  int lo = 0, hi = NJ + NK - 2;          // the largest d with diag_count(d) <= t
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (diag_count(mid, NJ, NK) <= t) lo = mid; else hi = mid - 1;
+  }
+  K = max(0, lo - (NJ - 1)) + (int)(t - diag_count(lo, NJ, NK));
+  J = lo - K;
 }
 
-typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+// ---- brick order -----------------------------------------------------------------
+// What the sweeps read and hand on is stored brick by brick, each brick level
+// by level (h = i + jl + kl), the lines of a level by jl + kl, then kl.  Lines
+// start in that order and end in it, so the lines active at a level are a run
+// of it and the storage has no gaps.  A level is then one contiguous run per
+// plane: in the grid's own order its 64 cells lie whole x-lines apart, in
+// FP32 half of every cache line fetched for them is the next level's, they
+// crowd into a few L2 channels for many nx, and the sweeps ran at half the
+// speed at 200x200x100.
+template <int BK> struct brick_geo {
+  static constexpr int BS = BJ + BK - 2;   // levels between the first and the last line of a full brick
+  int nx, bj, bk, nl;      // lines in j, in k, in all
+  int64_t base;            // cells stored before the brick
+  __device__ static int tri(int x) { return x > 0 ? x * (x + 1) / 2 : 0; }
+  __device__ static int tet(int x) { return x > 0 ? x * (x + 1) * (x + 2) / 6 : 0; }
+  // lines with jl + kl <= x, and their sum over the levels before x
+  __device__ int started(int x) const { return x >= bj + bk - 2 ? nl : tri(x + 1) - tri(x + 1 - bj) - tri(x + 1 - bk); }
+  __device__ int64_t begun(int64_t x) const {
+    const int e = bj + bk - 1;                          // from level e - 1 on every line has started
+    if (x > e) return (int64_t)(tet(e) - tet(e - bj) - tet(e - bk)) + (x - e) * nl;
+    return tet((int)x) - tet((int)x - bj) - tet((int)x - bk);
+  }
+  // index in brick order of rank 0's cell at level h, were it active there
+  // (lines that have ended are left out of the level's run)
+  __device__ int64_t rank0(int h) const { return base + begun(h) - begun(h - nx) - (h >= nx ? started(h - nx) : 0); }
+  __device__ int rank(int jl, int kl) const {
+    const int s = jl + kl;
+    return (s > 0 ? started(s - 1) : 0) + kl - max(0, s - (bj - 1));
+  }
+  // line of rank q
+  __device__ void line(int q, int &jl, int &kl) const {
+    int s = 0;
+    while (s < bj + bk - 2 && started(s) <= q) ++s;
+    kl = max(0, s - (bj - 1)) + q - (s > 0 ? started(s - 1) : 0);
+    jl = s - kl;
+  }
+};
+template <int BK> __device__ __forceinline__ brick_geo<BK> geo_of(int J, int K, int nx, int ny, int nz) {
+  brick_geo<BK> g;
+  g.nx = nx;
+  g.bj = min(BJ, ny - J * BJ);
+  g.bk = min(BK, nz - K * BK);
+  g.nl = g.bj * g.bk;
+  g.base = ((int64_t)K * BK * ny + (int64_t)g.bk * J * BJ) * nx;
+  return g;
+}
+// a wave-uniform value that the compiler cannot see to be one
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// all 4 values of a neighbour cell from the exchange buffer (words prefetched
-// in w[]; re-polled while the tag is stale)
-// The exchange buffer is read through a buffer resource: 16-byte loads with
-// device scope (sc1), which return zero instead of faulting out of range.
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-constexpr int RS_CPOL_SC1 = 16;          // cache policy: device scope
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t xrsrc(const uint64_t *base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc((void *)base, (short)0, (int)bytes, 0x00020000);
+// The two passes below take 16 cells of each line of a brick per workgroup, 16
+// consecutive cells of a line per wave, and read in the grid's order in whole
+// cache lines.  tab[h - i0]: rank0 of the levels that the 16 cells are on.
+constexpr int CH = 16;
+template <int BK> __device__ __forceinline__ void level_table(const brick_geo<BK> &g, int i0, int64_t *tab) {
+  const int t = threadIdx.x;
+  if (t < CH + brick_geo<BK>::BS) tab[t] = g.rank0(i0 + t);
+  __syncthreads();
 }
 
-template <class T> struct xcell {
-  static constexpr int NWD = 4 * xw<T>::W;
-  // words w[] of the cell starting at word index `word` (16-byte aligned):
-  // each 64-bit word is read whole, tag and data together
-  __device__ static void pre(__amdgpu_buffer_rsrc_t r, int64_t word, uint64_t (&w)[NWD]) {
+// The sweeps' operands in brick order, planes -z -y -x D^{-1} +x +y +z of each
+// level one after another (so that the forward sweep reads the first four and
+// the backward sweep the last four), after the factorisation.
+template <class T, int BK>
+__global__ __launch_bounds__(256) void k_dilu_order(int nx, int ny, int nz, int NJ, int NC, int64_t n,
+                                                     const T *__restrict__ t7, const T *__restrict__ dinv2,
+                                                     T *__restrict__ pb) {
+  __shared__ int64_t tab[CH + BJ + BK];
+  const int b = blockIdx.x / NC, i0 = (int)(blockIdx.x - (unsigned)b * NC) * CH;
+  const int J = b % NJ, K = b / NJ;
+  const brick_geo<BK> g = geo_of<BK>(J, K, nx, ny, nz);
+  level_table(g, i0, tab);
+  const int row = threadIdx.x & 3, i = i0 + ((threadIdx.x >> 2) & 15);
+  if (i >= nx) return;
+  for (int l = threadIdx.x >> 6; l < g.nl; l += 4) {
+    const int kl = l / g.bj, jl = l - kl * g.bj;
+    const int h = i + jl + kl, q = g.rank(jl, kl);
+    const int64_t c = (((int64_t)(K * BK + kl) * ny + J * BJ + jl) * nx + i) * 16 + 4 * row;
+    // the level's active lines, and the index of its first one
+    const int ended = h >= nx ? g.started(h - nx) : 0, act = g.started(h) - ended;
+    const int64_t r0 = tab[h - i0], f = r0 + ended;
+    T *o = pb + (7 * f + r0 + q - f) * 16 + 4 * row;
+    T v[7][4];
 #pragma unroll
-    for (int e = 0; e < NWD; e += 2) {
-      u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(r, (uint32_t)((word + e) * 8), 0, RS_CPOL_SC1);
-      w[e] = ((uint64_t)q.y << 32) | q.x;
-      w[e + 1] = ((uint64_t)q.w << 32) | q.z;
+    for (int s = 0; s < 7; ++s) ld4v(s == 3 ? dinv2 + c : t7 + s * n * 16 + c, v[s]);
+#pragma unroll
+    for (int s = 0; s < 7; ++s) st4v(o + (int64_t)s * act * 16, v[s]);
+  }
+}
+
+// Right-hand side of the forward sweep, v = r~ - A~[:,0] x_p, and x_p, in brick
+// order: apart from the sweep, whose levels depend on each other and would
+// have to stream 144 bytes a cell more (in FP32).  x_p carries nx*ny zero
+// guard entries on each side and off-grid column-0 entries are zero.  The
+// results go through LDS and out level by level, as runs of up to a level
+// (133 us in FP32 at 200x200x100, 5.3 TB/s; 195 written cell by cell).  Also zeroes the two sweeps' tickets.
+template <class T, int BK>
+__global__ __launch_bounds__(256) void k_dilu_rhs(int nx, int ny, int nz, int NJ, int NC, const T *__restrict__ rt,
+                                                   const T *__restrict__ col0, const T *__restrict__ xp,
+                                                   T *__restrict__ rhs, T *__restrict__ xpb, int *__restrict__ ctl) {
+  __shared__ int64_t tab[CH + BJ + BK];
+  __shared__ T sv[BJ * BK][CH][4], sx[BJ * BK][CH];     // by rank of the line
+  if (blockIdx.x == 0 && threadIdx.x < 2) ctl[2 * threadIdx.x] = 0;
+  const int b = blockIdx.x / NC, i0 = (int)(blockIdx.x - (unsigned)b * NC) * CH;
+  const int J = b % NJ, K = b / NJ;
+  const brick_geo<BK> g = geo_of<BK>(J, K, nx, ny, nz);
+  level_table(g, i0, tab);
+  const int row = threadIdx.x & 3, ii = (threadIdx.x >> 2) & 15, i = min(i0 + ii, nx - 1);
+  const int64_t nxy = (int64_t)nx * ny;
+  const int64_t nb[7] = {-nxy, -(int64_t)nx, -1, 0, 1, (int64_t)nx, nxy};
+#pragma unroll 2
+  for (int l = threadIdx.x >> 6; l < g.nl; l += 4) {
+    const int kl = l / g.bj, jl = l - kl * g.bj;
+    const int64_t c = ((int64_t)(K * BK + kl) * ny + J * BJ + jl) * nx + i;
+    T col[8], x[7];
+    ld8v(col0 + c * 32 + 8 * row, col);
+#pragma unroll
+    for (int s = 0; s < 7; ++s) x[s] = xp[c + nb[s]];
+    T v = rt[4 * c + row];
+#pragma unroll
+    for (int s = 0; s < 7; ++s) v = v - col[s] * x[s];
+    const int q = g.rank(jl, kl);
+    sv[q][ii][row] = v;
+    if (row == 0) sx[q][ii] = x[3];
+  }
+  __syncthreads();
+  constexpr int NL = BJ * BK, ST = 64 / NL;             // lines of a full brick, levels per step
+  const int q = (threadIdx.x >> 2) % NL;
+  if (q >= g.nl) return;
+  int jl, kl;
+  g.line(q, jl, kl);
+  for (int d = (threadIdx.x >> 2) / NL; d < CH + brick_geo<BK>::BS; d += ST) {
+    const int e = d - jl - kl;
+    if (e < 0 || e >= CH || i0 + e >= nx) continue;
+    const int64_t o = tab[d] + q;
+    rhs[4 * o + row] = sv[q][e][row];
+    if (row == 0) xpb[o] = sx[q][e];
+  }
+}
+
+// ---- sweeps ------------------------------------------------------------------
+//   forward   y_c = D_c^{-1} (v_c - sum_{lower k} A~_ck y_k)
+//   backward  z_c = y_c - D_c^{-1} sum_{upper k} A~_ck z_k, output z + Pi_p x_p
+// A brick of 8 x 4 or 8 x 8 x-lines per workgroup, one barrier per level: 2 or
+// 4 compute waves with a quad of lanes per cell (lane r owns block row r), a
+// writer wave and a poller wave.
+//   - compute: the neighbours' 4-vectors come from the previous level in an
+//     LDS ring with a slot for each line just outside the brick; the operands
+//     of the next P levels (five loads a level) are in flight in registers;
+//   - writer: copies the previous level from LDS to global memory, the values
+//     of the outgoing faces as tagged words as well (a wave's loads and stores
+//     complete in order, so that stores in a compute wave would make its loads
+//     wait for the slow device-scope ones);
+//   - poller: one lane per value of the incoming faces (16 lines x 4); loads
+//     the words D levels ahead, checks a level's tags when it is due, re-reads
+//     the ones that are not there yet (bounded), puts the values into the ring.
+// What bounds the sweeps is the chain of nx + ny + nz levels, a level taking
+// as long as its CU takes to bring the operands in (about 45 GB/s a CU from
+// HBM: 0.39 us in FP32 and 0.75 in FP64 with 64 cells), and for every brick on
+// the way from corner to corner the way of a face value through memory, 2 to
+// 3 us.  Forward and backward, FP32 at 200x200x100: 480 and 520 us (1395 and
+// 1206 with bricks of 4 x 4 lines whose waves took the levels in turn, polled
+// their faces themselves and read the grid's order; 690 and 740 with these
+// waves on the grid's order); FP64 at 100x100x50: 210 and 217 (567 and 577).
+template <class T> __device__ __forceinline__ void poll_faces(
+    int lane, int L, int nx, bool has, int shift, const uint64_t *__restrict__ src, bool rev, T *__restrict__ slot0,
+    T *__restrict__ slot1, uint32_t tag, int *__restrict__ err) {
+  // level m of this lane's line is cell m - shift along x (from the far end
+  // with rev); src: words of cell 0, 4 W a cell; slot0/1: ring entries of the
+  // line for odd and even m
+  constexpr int W = xw<T>::W, D = 8;
+  bool failed = false;
+  uint64_t w[D][W];
+  auto at = [&](int m, int &i) {
+    i = rev ? nx - 1 - (m - shift) : m - shift;
+    return has && i >= 0 && i < nx;
+  };
+  // issued by every lane, at a clamped cell: then the number of younger loads
+  // is known where a word is tested, and only its own load is waited for
+  auto issue = [&](int m, uint64_t (&x)[W]) {
+    int i;
+    at(m, i);
+    xw<T>::get(src + (int64_t)min(max(i, 0), nx - 1) * 4 * W, x);
+  };
+  auto deliver = [&](int m, uint64_t (&x)[W]) {
+    // the words loaded D levels ago are tested outside the loop that reads
+    // them again: in one loop the test would wait for every load in flight
+    int i;
+    const bool in = at(m, i);
+    T v = xw<T>::value(x);
+    if (__ballot(in && !xw<T>::ready(x, tag)) != 0) {
+      uint64_t z[W];
+      int spins = 0;
+      do {
+        if (in) xw<T>::get(src + (int64_t)i * 4 * W, z);
+        if (++spins > SPIN_LIMIT) { atomicOr(err, 1); failed = true; }
+      } while (__ballot(in && !xw<T>::ready(z, tag)) != 0 && !failed);
+      v = xw<T>::value(z);
+    }
+    if (in) *((m & 1) ? slot0 : slot1) = v;
+  };
+#pragma unroll
+  for (int d = 0; d < D; ++d) issue(d, w[d]);
+  for (int m0 = 0; m0 < L; m0 += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      deliver(m0 + d, w[d]);
+      issue(m0 + d + D, w[d]);
+      __syncthreads();
     }
   }
-  __device__ static bool get(__amdgpu_buffer_rsrc_t r, int64_t word, uint64_t (&w)[NWD], uint32_t tag, T (&out)[4],
-                             bool &failed) {
-    int spins = 0;
-    for (;;) {
-      bool ok = true;
-#pragma unroll
-      for (int e = 0; e < NWD; ++e) ok = ok && (uint32_t)(w[e] >> 32) == tag;
-      if (ok || failed) break;
-      if (++spins > XSPIN_LIMIT) { failed = true; return false; }
-      __builtin_amdgcn_s_sleep(1);
-      pre(r, word, w);
+  __syncthreads();
+}
+
+// the writer wave: level m is in LDS after the barrier that starts level m + 1
+template <class T, class F> __device__ __forceinline__ void write_levels(int L, F &&write) {
+  __syncthreads();
+  for (int m = 0; m < L; ++m) {
+    __syncthreads();
+    write(m);
+  }
+}
+
+// refills of a level's registers stay behind the level's last use of them
+// (see the layer sweeps)
+template <class T> __device__ __forceinline__ void after(int &idx, T tok) { asm volatile("" : "+v"(idx) : "v"(tok)); }
+
+// Walks a brick's levels up (from level 0) or down (from level `top`), with a
+// wave-uniform pointer to the level's vectors and one to its blocks: in the
+// middle of the brick, where every line is active, a step adds constants.
+template <class T, int BK> struct walk {
+  const T *v, *o;          // 4-vectors and blocks of level h
+  int h, first, act;       // lines ended, lines active
+  __device__ void at_level(const brick_geo<BK> &g) {
+    first = 0;
+    act = g.nl;
+    if (h < g.BS || h >= g.nx) {
+      first = h >= g.nx ? g.started(h - g.nx) : 0;
+      act = max((h >= 0 ? g.started(h) : 0) - first, 0);
     }
+  }
+  __device__ void begin(const brick_geo<BK> &g, const T *v0, const T *pb) {
+    v = v0 + 4 * g.base;
+    o = pb + 112 * g.base;
+    h = 0;
+    at_level(g);
+  }
+  __device__ void up(const brick_geo<BK> &g) {
+    v += 4 * act;
+    o += 112 * act;
+    ++h;
+    at_level(g);
+  }
+  __device__ void begin_top(const brick_geo<BK> &g, const T *v0, const T *pb, int top) {
+    h = top;
+    at_level(g);
+    const int64_t off = g.base + (int64_t)g.nl * g.nx - act;
+    v = v0 + 4 * off;
+    o = pb + 112 * off;
+  }
+  __device__ void down(const brick_geo<BK> &g) {
+    --h;
+    at_level(g);
+    v -= 4 * act;
+    o -= 112 * act;
+  }
+  // index within the level for the lane of rank q; lanes without an active
+  // line take a cell that is in the brick (past the last level the one before)
+  __device__ int lane(int q) const { return act > 0 ? min(max(q - first, 0), act - 1) : (h < 0 ? 0 : -1); }
+};
+
+// p + e at a wave-uniform p and a 32-bit lane offset
+template <class T> __device__ __forceinline__ const T *at(const T *p, int e) {
+  return (const T *)((const char *)p + (int64_t)e * (int)sizeof(T));
+}
+
+template <class T> struct sweep_pre { T v, a[3][4], dv[4]; };
+
+template <class T, int P, int BK>
+__global__ __launch_bounds__(4 * BJ * BK + 128) void k_fwd_pipe(int nx, int ny, int nz, int NJ, int NK, int *__restrict__ ticket,
+                                                  int *__restrict__ err, uint32_t tag, uint64_t *__restrict__ xch,
+                                                  const T *__restrict__ pb, const T *__restrict__ rhs,
+                                                  T *__restrict__ y) {
+  constexpr int NC = 4 * BJ * BK, RN = ring_lines<BK>, BS = brick_geo<BK>::BS;
+  __shared__ __align__(32) T ring[2][RN][4];       // line (jl, kl) at (kl + 1) RG + jl + 1
+  __shared__ int s_t;
+  const int tid = threadIdx.x;
+  if (tid == 0) s_t = atomicAdd(ticket, 1);
+  __syncthreads();
+  int J, K;
+  brick_of(uni(s_t), NJ, NK, J, K);
+  const int b = J + NJ * K;
+  const brick_geo<BK> g = geo_of<BK>(J, K, nx, ny, nz);
+  const int L = (nx + BS + 7) / 8 * 8;                  // levels, a multiple of P and of the poller's lead
+  if (tid >= NC + 64) {
+    // the y face before the brick (lines kl), then the z face (lines jl)
+    const int lane = tid - NC - 64, r = lane & 3;
+    const bool yf = lane < 4 * BK;
+    const int pos = yf ? lane >> 2 : (lane >> 2) - BK;   // (lanes beyond the faces: past bj)
+    const bool has = yf ? J > 0 && pos < g.bk : K > 0 && pos < g.bj;
+    const int gs = !has ? 0 : (yf ? (pos + 1) * RG : pos + 1);
+    // lanes without a face to read load words of their own brick
+    const uint64_t *src = xch + (has ? xslot<T>(yf ? b - 1 : b - NJ, yf ? 0 : 1, pos, 0, nx, r) : xslot<T>(b, 0, 0, 0, nx, r));
+    poll_faces<T>(lane, L, nx, has, pos, src, false, &ring[0][gs][r], &ring[1][gs][r], tag, err);
+    return;
+  }
+  if (tid >= NC) {
+    const int lane = tid - NC;
+    const bool yf = lane < 4 * BK;
+    const int pos = yf ? lane >> 2 : min((lane >> 2) - BK, BJ - 1), fj = yf ? BJ - 1 : pos, fk = yf ? pos : BK - 1;
+    const bool pub = lane < 4 * (BJ + BK) && (yf ? J + 1 < NJ && pos < g.bk : K + 1 < NK && pos < g.bj);
+    int jl = 0, kl = 0;
+    if (lane < g.nl) g.line(lane, jl, kl);
+    const T *f0 = &ring[0][(fk + 1) * RG + fj + 1][lane & 3], *o0 = &ring[0][(kl + 1) * RG + jl + 1][0];
+    uint64_t *dst = xch + xslot<T>(b, yf ? 0 : 1, pos, 0, nx, lane & 3);
+    walk<T, BK> w;
+    w.begin(g, y, y);
+    write_levels<T>(L, [&](int m) {
+      const int i = m - fj - fk, c = m - jl - kl;
+      const T fv = f0[(m & 1) * RN * 4];
+      T ov[4];
+      ld4v(o0 + (m & 1) * RN * 4, ov);
+      if (pub && i >= 0 && i < nx) xw<T>::put(dst + (int64_t)i * 4 * xw<T>::W, fv, tag);
+      if (lane < g.nl && c >= 0 && c < nx) st4v(const_cast<T *>(at(w.v, 4 * (lane - w.first))), ov);
+      w.up(g);
+    });
+    return;
+  }
+  const int row = tid & 3, q = tid >> 2;
+  int jl = 0, kl = 0;
+  if (q < g.nl) g.line(q, jl, kl);
+  const bool hz = K * BK + kl > 0, hy = J * BJ + jl > 0;
+  const int slot = (kl + 1) * RG + jl + 1;
+  walk<T, BK> lw;                                           // the level that loads next
+  lw.begin(g, rhs, pb);
+  auto load = [&](sweep_pre<T> &p, T tok) {
+    int e = lw.lane(q);
+    after(e, tok);
+    p.v = *at(lw.v, 4 * e + row);
+    e = 16 * e + 4 * row;
+    ld4v(at(lw.o, e), p.a[0]);
+    ld4v(at(lw.o + lw.act * 16, e), p.a[1]);
+    ld4v(at(lw.o + lw.act * 32, e), p.a[2]);
+    ld4v(at(lw.o + lw.act * 48, e), p.dv);
+    lw.up(g);
+  };
+  sweep_pre<T> R[P];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      if (xw<T>::W == 1) {
-        out[m] = (T)__uint_as_float((uint32_t)w[m]);
-      } else {
-        uint64_t lo = w[2 * m] & 0xffffffffull, hi = w[2 * m + 1] & 0xffffffffull;
-        out[m] = (T)__longlong_as_double((long long)((hi << 32) | lo));
+  for (int d = 0; d < P; ++d) load(R[d], (T)0);
+  for (int h0 = 0; h0 < L; h0 += P) {
+#pragma unroll
+    for (int d = 0; d < P; ++d) {
+      const int h = h0 + d, i = h - jl - kl;
+      const bool act = q < g.nl && i >= 0 && i < nx;
+      __syncthreads();
+      const T(*prev)[4] = ring[(h + 1) & 1];
+      T yz[4], yy[4], yx[4];
+      ld4v(&prev[slot - RG][0], yz);
+      ld4v(&prev[slot - 1][0], yy);
+      ld4v(&prev[slot][0], yx);
+      const T tz = dot4(R[d].a[0], yz), ty = dot4(R[d].a[1], yy), tx = dot4(R[d].a[2], yx);
+      T v = R[d].v;
+      v = hz ? v - tz : v;
+      v = hy ? v - ty : v;
+      v = i > 0 ? v - tx : v;
+      const T o = quad_mv<T>(R[d].dv, v);
+      if (act) ring[h & 1][slot][row] = o;
+      load(R[d], o);
+    }
+  }
+  __syncthreads();
+}
+
+template <class T, int P, int BK>
+__global__ __launch_bounds__(4 * BJ * BK + 128) void k_bwd_pipe(int nx, int ny, int nz, int NJ, int NK, int *__restrict__ ticket,
+                                                  int *__restrict__ err, uint32_t tag, uint64_t *__restrict__ xch,
+                                                  const T *__restrict__ pb, const T *__restrict__ y,
+                                                  const T *__restrict__ xpb, T *__restrict__ out) {
+  constexpr int NC = 4 * BJ * BK, RN = ring_lines<BK>, BS = brick_geo<BK>::BS;
+  __shared__ __align__(32) T ring[2][RN][4];       // line (jl, kl) at kl RG + jl
+  __shared__ __align__(32) T oring[2][BJ * BK][4];        // the level's output: z + Pi_p x_p, by rank
+  __shared__ int s_t;
+  const int tid = threadIdx.x;
+  if (tid == 0) s_t = atomicAdd(ticket, 1);
+  __syncthreads();
+  int J, K;
+  brick_of(NJ * NK - 1 - uni(s_t), NJ, NK, J, K);
+  const int b = J + NJ * K;
+  const brick_geo<BK> g = geo_of<BK>(J, K, nx, ny, nz);
+  const int L = (nx + BS + 7) / 8 * 8;                  // levels, a multiple of P and of the poller's lead
+  const int top = nx - 1 + BS;                 // step m handles level top - m
+  if (tid >= NC + 64) {
+    // the y face after the brick (lines kl), then the z face (lines jl)
+    const int lane = tid - NC - 64, r = lane & 3;
+    const bool yf = lane < 4 * BK;
+    const int pos = yf ? lane >> 2 : (lane >> 2) - BK;   // (lanes beyond the faces: past bj)
+    const bool has = yf ? J + 1 < NJ && pos < g.bk : K + 1 < NK && pos < g.bj;
+    const int gs = !has ? 0 : (yf ? pos * RG + BJ : BK * RG + pos);
+    // lanes without a face to read load words of their own brick
+    const uint64_t *src = xch + (has ? xslot<T>(yf ? b + 1 : b + NJ, yf ? 0 : 1, pos, 0, nx, r) : xslot<T>(b, 0, 0, 0, nx, r));
+    poll_faces<T>(lane, L, nx, has, (yf ? BK : BJ) - 1 - pos, src, true, &ring[0][gs][r], &ring[1][gs][r], tag, err);
+    return;
+  }
+  if (tid >= NC) {
+    const int lane = tid - NC;
+    const bool yf = lane < 4 * BK;
+    const int pos = yf ? lane >> 2 : min((lane >> 2) - BK, BJ - 1), fj = yf ? 0 : pos, fk = yf ? pos : 0;
+    const bool pub = lane < 4 * (BJ + BK) && (yf ? J > 0 && pos < g.bk : K > 0 && pos < g.bj);
+    int jl = 0, kl = 0;
+    if (lane < g.nl) g.line(lane, jl, kl);
+    const T *f0 = &ring[0][fk * RG + fj][lane & 3], *o0 = &oring[0][min(lane, BJ * BK - 1)][0];
+    uint64_t *dst = xch + xslot<T>(b, yf ? 0 : 1, pos, 0, nx, lane & 3);
+    T *o = out + 4 * ((int64_t)(K * BK + kl) * ny + J * BJ + jl) * nx;
+    write_levels<T>(L, [&](int m) {
+      const int i = top - m - fj - fk, c = top - m - jl - kl;
+      const T fv = f0[(m & 1) * RN * 4];
+      T ov[4];
+      ld4v(o0 + (m & 1) * BJ * BK * 4, ov);
+      if (pub && i >= 0 && i < nx) xw<T>::put(dst + (int64_t)i * 4 * xw<T>::W, fv, tag);
+      if (lane < g.nl && c >= 0 && c < nx) st4v(o + 4 * c, ov);
+    });
+    return;
+  }
+  const int row = tid & 3, q = tid >> 2;
+  int jl = 0, kl = 0;
+  if (q < g.nl) g.line(q, jl, kl);
+  const bool hz = K * BK + kl < nz - 1, hy = J * BJ + jl < ny - 1;
+  const int slot = kl * RG + jl;
+  T xpc[P];
+  walk<T, BK> lw;                                           // the level that loads next
+  lw.begin_top(g, y, pb, top);
+  const T *xl = xpb + (lw.v - y) / 4;
+  auto load = [&](sweep_pre<T> &p, T &x, T tok) {
+    int e = lw.lane(q);
+    after(e, tok);
+    p.v = *at(lw.v, 4 * e + row);
+    x = *at(xl, e);
+    e = 16 * e + 4 * row;
+    ld4v(at(lw.o + lw.act * 48, e), p.dv);
+    ld4v(at(lw.o + lw.act * 64, e), p.a[0]);
+    ld4v(at(lw.o + lw.act * 80, e), p.a[1]);
+    ld4v(at(lw.o + lw.act * 96, e), p.a[2]);
+    lw.down(g);
+    xl -= lw.act;
+  };
+  sweep_pre<T> R[P];
+#pragma unroll
+  for (int d = 0; d < P; ++d) load(R[d], xpc[d], (T)0);
+  for (int m0 = 0; m0 < L; m0 += P) {
+#pragma unroll
+    for (int d = 0; d < P; ++d) {
+      const int m = m0 + d, i = top - m - jl - kl;
+      const bool act = q < g.nl && i >= 0 && i < nx;
+      __syncthreads();
+      const T(*prev)[4] = ring[(m + 1) & 1];
+      T zx[4], zy[4], zz[4];
+      ld4v(&prev[slot][0], zx);
+      ld4v(&prev[slot + 1][0], zy);
+      ld4v(&prev[slot + RG][0], zz);
+      const T tx = dot4(R[d].a[0], zx), ty = dot4(R[d].a[1], zy), tz = dot4(R[d].a[2], zz);
+      T v = 0;
+      v = i < nx - 1 ? v + tx : v;
+      v = hy ? v + ty : v;
+      v = hz ? v + tz : v;
+      const T w = quad_mv<T>(R[d].dv, v);
+      const T zc = R[d].v - w;
+      if (act) {
+        ring[m & 1][slot][row] = zc;
+        oring[m & 1][q][row] = row == 0 ? zc + xpc[d] : zc;
       }
+      load(R[d], xpc[d], zc);
     }
-    return true;
   }
-};
-
-template <class T> struct fwd_pre {
-  T rt, col[8], xq[7], a[3][4], dv[4];
-  uint64_t ez[4 * xw<T>::W], ey[4 * xw<T>::W];      // face words (-z, -y)
-};
-
-template <class T, int NW>
-__global__ __launch_bounds__(64 * NW) void k_fwd_pipe(
-    int nx, int ny, int nz, int NJ, const int *__restrict__ ord, int *__restrict__ ticket,
-    int *__restrict__ err, uint32_t tag, uint64_t *__restrict__ xch, uint32_t xbytes, const T *__restrict__ t7,
-    const T *__restrict__ dinv2, const T *__restrict__ rt, const T *__restrict__ col0,
-    const T *__restrict__ xp, T *__restrict__ y) {
-  constexpr int B = BR;
-  __shared__ T ring[2][B][B][4];
-  __shared__ int s_b;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int row = lane & 3, cl = lane >> 2;
-  const int jl = cl % B, kl = cl / B;
-  if (tid == 0) s_b = ord[atomicAdd(ticket, 1)];
   __syncthreads();
-  const int b = s_b, J = b % NJ, K = b / NJ;
-  const int j = J * B + jl, k = K * B + kl;
-  const bool line = j < ny && k < nz;
-  const int64_t nxy = (int64_t)nx * ny, n = nxy * nz;
-  const int L = nx + 2 * B - 2;
-  const bool ext_z = kl == 0 && k > 0, ext_y = jl == 0 && j > 0;
-  const uint32_t c0 = line ? (uint32_t)(nx * (j + (int64_t)ny * k)) : 0u;
-  const int64_t off[7] = {-nxy, -(int64_t)nx, -1, 0, 1, (int64_t)nx, nxy};
-  const __amdgpu_buffer_rsrc_t xr = xrsrc(xch, xbytes);
-  bool failed = false;
-  auto load = [&](int lam, fwd_pre<T> &P) {
-    const int i = lam - jl - kl;
-    const uint32_t c = c0 + (uint32_t)min(max(i, 0), nx - 1);
-    const uint32_t o4 = c * 4u * sizeof(T), o16 = c * 16u * sizeof(T), o1 = c * (uint32_t)sizeof(T);
-    const uint32_t r1 = row * (uint32_t)sizeof(T), r4 = row * 4u * (uint32_t)sizeof(T);
-    P.rt = *at(rt, o4 + r1);
-    ld8v(at(col0, 2 * o16 + 2 * r4), P.col);
-#pragma unroll
-    for (int s = 0; s < 7; ++s) P.xq[s] = *at(xp + off[s], o1);   // x_p carries zero guard planes
-#pragma unroll
-    for (int s = 0; s < 3; ++s) ld4v(at(t7 + (int64_t)s * n * 16, o16 + r4), P.a[s]);
-    ld4v(at(dinv2, o16 + r4), P.dv);
-    const bool act = line && i >= 0 && i < nx;
-    // lanes without an external neighbour load their own brick's face words
-    // instead (distinct addresses, never used) so that the load count stays fixed
-    const int ic = min(max(i, 0), nx - 1);
-    xcell<T>::pre(xr, (act && ext_z) ? xslot<T, B>(b - NJ, 1, jl, i, nx, 0) : xslot<T, B>(b, 1, jl, ic, nx, 0), P.ez);
-    xcell<T>::pre(xr, (act && ext_y) ? xslot<T, B>(b - 1, 0, kl, i, nx, 0) : xslot<T, B>(b, 0, kl, ic, nx, 0), P.ey);
-  };
-  fwd_pre<T> P;
-  if (wave < L) load(wave, P);
-  for (int lam = 0; lam < L; ++lam) {
-    __syncthreads();
-    if (lam % NW != wave) continue;            // wave-uniform
-    const int prev = (lam + 1) & 1, cur = lam & 1;
-    const int i = lam - jl - kl;
-    const bool act = line && i >= 0 && i < nx;
-    T v = P.rt;
-#pragma unroll
-    for (int s = 0; s < 7; ++s) v = v - P.col[s] * P.xq[s];
-    T yz[4], yy[4], yx[4];
-    if (kl > 0) ld4(&ring[prev][kl - 1][jl][0], yz);
-    else if (act && k > 0 && !xcell<T>::get(xr, xslot<T, B>(b - NJ, 1, jl, i, nx, 0), P.ez, tag, yz, failed)) atomicOr(err, 1);
-    if (jl > 0) ld4(&ring[prev][kl][jl - 1][0], yy);
-    else if (act && j > 0 && !xcell<T>::get(xr, xslot<T, B>(b - 1, 0, kl, i, nx, 0), P.ey, tag, yy, failed)) atomicOr(err, 1);
-    ld4(&ring[prev][kl][jl][0], yx);
-    if (act && k > 0) v = v - dot4(P.a[0], yz);
-    if (act && j > 0) v = v - dot4(P.a[1], yy);
-    if (act && i > 0) v = v - dot4(P.a[2], yx);
-    const T o = quad_mv<T>(P.dv, v);
-    if (act) {
-      const uint32_t c = c0 + (uint32_t)i;
-      ring[cur][kl][jl][row] = o;
-      y[(int64_t)4 * c + row] = o;
-      if (jl == B - 1) xw<T>::put(xch + xslot<T, B>(b, 0, kl, i, nx, row), o, tag);
-      if (kl == B - 1) xw<T>::put(xch + xslot<T, B>(b, 1, jl, i, nx, row), o, tag);
-    }
-    if (lam + NW < L) load(lam + NW, P);
-  }
-}
-
-// ---- backward sweep: z_c = y_c - D_c^{-1} sum_{upper k} A~_ck z_k ------------
-template <class T> struct bwd_pre {
-  T yc, xpc, a[3][4], dv[4];
-  uint64_t ey[4 * xw<T>::W], ez[4 * xw<T>::W];      // face words (+y, +z)
-};
-
-template <class T, int NW>
-__global__ __launch_bounds__(64 * NW) void k_bwd_pipe(
-    int nx, int ny, int nz, int NJ, int NK, const int *__restrict__ ord, int *__restrict__ ticket,
-    int *__restrict__ err, uint32_t tag, uint64_t *__restrict__ xch, uint32_t xbytes, const T *__restrict__ t7,
-    const T *__restrict__ dinv2, const T *__restrict__ y, const T *__restrict__ xp, T *__restrict__ out) {
-  constexpr int B = BR;
-  __shared__ T ring[2][B][B][4];
-  __shared__ int s_b;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int row = lane & 3, cl = lane >> 2;
-  const int jl = cl % B, kl = cl / B;
-  const int nb = NJ * NK;
-  if (tid == 0) s_b = ord[nb - 1 - atomicAdd(ticket, 1)];
-  __syncthreads();
-  const int b = s_b, J = b % NJ, K = b / NJ;
-  const int j = J * B + jl, k = K * B + kl;
-  const bool line = j < ny && k < nz;
-  const int64_t nxy = (int64_t)nx * ny, n = nxy * nz;
-  const int L = nx + 2 * B - 2;
-  const bool ext_y = jl == B - 1 && j < ny - 1, ext_z = kl == B - 1 && k < nz - 1;
-  const uint32_t c0 = line ? (uint32_t)(nx * (j + (int64_t)ny * k)) : 0u;
-  const __amdgpu_buffer_rsrc_t xr = xrsrc(xch, xbytes);
-  bool failed = false;
-  auto load = [&](int step, bwd_pre<T> &P) {
-    const int i = L - 1 - step - jl - kl;
-    const uint32_t c = c0 + (uint32_t)min(max(i, 0), nx - 1);
-    const uint32_t o4 = c * 4u * sizeof(T), o16 = c * 16u * sizeof(T), o1 = c * (uint32_t)sizeof(T);
-    const uint32_t r1 = row * (uint32_t)sizeof(T), r4 = row * 4u * (uint32_t)sizeof(T);
-    P.yc = *at(y, o4 + r1);
-    P.xpc = *at(xp, o1);
-#pragma unroll
-    for (int s = 0; s < 3; ++s) ld4v(at(t7 + (int64_t)(s + 4) * n * 16, o16 + r4), P.a[s]);
-    ld4v(at(dinv2, o16 + r4), P.dv);
-    const bool act = line && i >= 0 && i < nx;
-    const int ic = min(max(i, 0), nx - 1);
-    xcell<T>::pre(xr, (act && ext_y) ? xslot<T, B>(b + 1, 0, kl, i, nx, 0) : xslot<T, B>(b, 0, kl, ic, nx, 0), P.ey);
-    xcell<T>::pre(xr, (act && ext_z) ? xslot<T, B>(b + NJ, 1, jl, i, nx, 0) : xslot<T, B>(b, 1, jl, ic, nx, 0), P.ez);
-  };
-  bwd_pre<T> P;
-  if (wave < L) load(wave, P);
-  for (int step = 0; step < L; ++step) {
-    __syncthreads();
-    if (step % NW != wave) continue;           // wave-uniform
-    const int prev = (step + 1) & 1, cur = step & 1;
-    const int i = L - 1 - step - jl - kl;
-    const bool act = line && i >= 0 && i < nx;
-    T zx[4], zy[4], zz[4];
-    ld4(&ring[prev][kl][jl][0], zx);
-    if (jl < B - 1) ld4(&ring[prev][kl][jl + 1][0], zy);
-    else if (act && j < ny - 1 && !xcell<T>::get(xr, xslot<T, B>(b + 1, 0, kl, i, nx, 0), P.ey, tag, zy, failed)) atomicOr(err, 1);
-    if (kl < B - 1) ld4(&ring[prev][kl + 1][jl][0], zz);
-    else if (act && k < nz - 1 && !xcell<T>::get(xr, xslot<T, B>(b + NJ, 1, jl, i, nx, 0), P.ez, tag, zz, failed)) atomicOr(err, 1);
-    T v = 0;
-    if (act && i < nx - 1) v = v + dot4(P.a[0], zx);
-    if (act && j < ny - 1) v = v + dot4(P.a[1], zy);
-    if (act && k < nz - 1) v = v + dot4(P.a[2], zz);
-    const T w = quad_mv<T>(P.dv, v);
-    if (act) {
-      const uint32_t c = c0 + (uint32_t)i;
-      const T zc = P.yc - w;
-      ring[cur][kl][jl][row] = zc;
-      out[(int64_t)4 * c + row] = row == 0 ? zc + P.xpc : zc;
-      if (jl == 0) xw<T>::put(xch + xslot<T, B>(b, 0, kl, i, nx, row), zc, tag);
-      if (kl == 0) xw<T>::put(xch + xslot<T, B>(b, 1, jl, i, nx, row), zc, tag);
-    }
-    if (step + NW < L) load(step + NW, P);
-  }
 }
 
 // ---- factorisation: D_c = A~_cc - sum_{lower k} A~_ck D_k^{-1} A~_kc ----------
@@ -388,27 +625,6 @@ __global__ __launch_bounds__(64 * NW) void k_bwd_pipe(
 constexpr int SB = 8;                    // brick edge
 constexpr int SG = SB + 1;               // ring lines per side: one outside the brick
 
-// brick of ticket t in an order where every brick comes after the bricks
-// before it in j and in k: by J + K, then by K
-__device__ __forceinline__ int64_t diag_count(int64_t d, int64_t NJ, int64_t NK) {   // bricks with J + K < d
-  auto tri = [](int64_t x) { return x > 0 ? x * (x + 1) / 2 : (int64_t)0; };
-  return tri(d) - tri(d - NJ) - tri(d - NK) + tri(d - NJ - NK);
-}
-__device__ __forceinline__ void brick_of(int t, int NJ, int NK, int &J, int &K) {
-  int lo = 0, hi = NJ + NK - 2;          // the largest d with diag_count(d) <= t
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (diag_count(mid, NJ, NK) <= t) lo = mid; else hi = mid - 1;
-  }
-  K = max(0, lo - (NJ - 1)) + (int)(t - diag_count(lo, NJ, NK));
-  J = lo - K;
-}
-
-__device__ __forceinline__ void st4v(float *p, const float *v) { *(float4 *)p = make_float4(v[0], v[1], v[2], v[3]); }
-__device__ __forceinline__ void st4v(double *p, const double *v) {
-  ((double2 *)p)[0] = make_double2(v[0], v[1]);
-  ((double2 *)p)[1] = make_double2(v[2], v[3]);
-}
 template <class T> __device__ __forceinline__ void st_dev16(T *p, const T (&v)[16]) {   // 16 values, 8 bytes a store
   constexpr int PER = 8 / sizeof(T);
 #pragma unroll
@@ -585,73 +801,78 @@ __global__ __launch_bounds__(6 * 64) void k_setup_pipe(int nx, int ny, int nz, i
 // ---------------------------------------------------------------------------
 rs_status rs_dilu_prepare(rs_cpr_s *M, hipStream_t s) {
   const grid3 &g = M->A->g;
-  int B = BR;
-  int NJ = (g.ny + B - 1) / B, NK = (g.nz + B - 1) / B, nb = NJ * NK;
-  M->pb = B; M->pnj = NJ; M->pnk = NK;
-  // bricks by increasing J + K (then K): every brick after the ones it waits on
-  std::vector<int> ord(nb);
-  for (int t = 0; t < nb; ++t) ord[t] = t;
-  std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) {
-    int da = a % NJ + a / NJ, db = b % NJ + b / NJ;
-    return da < db;
-  });
-  RS_TRY(M->pord.alloc(sizeof(int) * nb));
-  RS_TRY(M->pdone.alloc(sizeof(int) * FL * (size_t)nb));
-  RS_TRY(M->pctl.alloc(sizeof(int) * 2));     // [0] ticket, [1] error
-  // face exchange: 2 faces x B lines x nx cells x 4 values x (1 or 2) words
-  size_t words = (size_t)nb * 2 * B * g.nx * 4 * (M->prec == 64 ? 2 : 1);
-  if (sizeof(uint64_t) * words >= 0xffffffffull) return RS_E_ARG;   // one buffer resource covers it
+  // Bricks of 8 x 4 lines while they are few enough for one a CU, 8 x 8 beyond:
+  // a CU takes in about 45 GB/s, whatever its brick's size, so that thinner
+  // bricks walk their levels faster, but a grid has more of them between its
+  // corners.  Forward sweep with 8 x 4 and with 8 x 8 lines, us, FP32 and FP64:
+  // 100x100x50 (169 thin bricks) 168 and 177, 212 and 287; 128x128x64 (256)
+  // 226 and 264, 323 and 402; 150x150x75 (361) 316 and 300, 554 and 491;
+  // 200x200x100 (650) 580 and 480, 878 and 806.
+  M->pnj = (g.ny + BJ - 1) / BJ;
+  M->pbk = (int64_t)M->pnj * ((g.nz + 3) / 4) <= 256 ? 4 : 8;
+  M->pnk = (g.nz + M->pbk - 1) / M->pbk;
+  const size_t nb = (size_t)M->pnj * M->pnk, nbs = (size_t)((g.ny + SB - 1) / SB) * ((g.nz + SB - 1) / SB);
+  RS_TRY(M->pdone.alloc(sizeof(int) * FL * nbs));
+  const size_t es = M->prec == 64 ? sizeof(double) : sizeof(float);
+  RS_TRY(M->pblk.alloc(es * 7 * 16 * (size_t)g.n));
+  RS_TRY(M->pxp.alloc(es * (size_t)g.n));
+  RS_TRY(M->pctl.alloc(sizeof(int) * 4));     // [0] ticket, [1] error, [2] second ticket
+  // face exchange: 2 faces x 8 lines x nx cells x 4 values x (1 or 2) words
+  const size_t words = nb * 2 * BJ * g.nx * 4 * (M->prec == 64 ? 2 : 1);
+  // grids beyond this are refused
+  const size_t nb4 = (size_t)((g.ny + 3) / 4) * ((g.nz + 3) / 4);
+  if (sizeof(uint64_t) * nb4 * 8 * g.nx * 4 * (M->prec == 64 ? 2 : 1) >= 0xffffffffull) return RS_E_ARG;
   RS_TRY(M->pxch.alloc(sizeof(uint64_t) * words));
-  k_pipe_clear<<<rs_grid(words), RS_BLOCK, 0, s>>>((int64_t)words, M->pxch.as<uint64_t>(), M->pctl.as<int>());
+  const size_t most = std::max(words, nbs);
+  k_pipe_clear<<<rs_grid(most), RS_BLOCK, 0, s>>>((int64_t)words, M->pxch.as<uint64_t>(), (int)nbs, M->pdone.as<int>(),
+                                                  M->pctl.as<int>());
   RS_HIP(hipGetLastError());
   M->pepoch = 0;
-  RS_HIP(hipMemcpy(M->pord.p, ord.data(), sizeof(int) * nb, hipMemcpyHostToDevice));
   return RS_OK;
 }
 
-static void pipe_reset(rs_cpr_s *M, hipStream_t s) {
-  int nb = M->pnj * M->pnk;
-  k_pipe_reset<<<rs_grid(nb), RS_BLOCK, 0, s>>>(nb, M->pdone.as<int>(), M->pctl.as<int>());
+template <class T>
+static rs_status dilu_setup_t(rs_cpr_s *M, int *flag, hipStream_t s) {
+  const grid3 &g = M->A->g;
+  const int SJ = (g.ny + SB - 1) / SB, SK = (g.nz + SB - 1) / SB;
+  int *ctl = M->pctl.as<int>();
+  const T *t7 = M->D->t7.as<T>();
+  T *dinv2 = M->dinv2.as<T>(), *pb = M->pblk.as<T>();
+  k_setup_pipe<T><<<SJ * SK, 6 * 64, 0, s>>>(g.nx, g.ny, g.nz, SJ, SK, ctl, M->pdone.as<int>(), ctl + 1, t7, dinv2, flag);
+  // the sweeps' operands in brick order
+  const int NC = (g.nx + CH - 1) / CH;
+  const unsigned ng = (unsigned)(M->pnj * M->pnk) * NC;
+  if (M->pbk == 4) k_dilu_order<T, 4><<<ng, 256, 0, s>>>(g.nx, g.ny, g.nz, M->pnj, NC, g.n, t7, dinv2, pb);
+  else k_dilu_order<T, 8><<<ng, 256, 0, s>>>(g.nx, g.ny, g.nz, M->pnj, NC, g.n, t7, dinv2, pb);
+  RS_HIP(hipGetLastError());
+  return RS_OK;
 }
 
 rs_status rs_dilu_setup_run(rs_cpr_s *M, int *flag, hipStream_t s) {
+  return M->prec == 64 ? dilu_setup_t<double>(M, flag, s) : dilu_setup_t<float>(M, flag, s);
+}
+
+template <class T, int BK>
+static rs_status dilu_apply_t(rs_cpr_s *M, const T *xp, T *out, hipStream_t s) {
   const grid3 &g = M->A->g;
-  const int NJ = (g.ny + SB - 1) / SB, NK = (g.nz + SB - 1) / SB;
+  const int NJ = M->pnj, NK = M->pnk, NC = (g.nx + CH - 1) / CH, NT = 4 * BJ * BK + 128;
   int *ctl = M->pctl.as<int>();
-  pipe_reset(M, s);
-  if (M->prec == 64)
-    k_setup_pipe<double><<<NJ * NK, 6 * 64, 0, s>>>(g.nx, g.ny, g.nz, NJ, NK, ctl, M->pdone.as<int>(), ctl + 1,
-                                                    M->D->t7.as<double>(), M->dinv2.as<double>(), flag);
-  else
-    k_setup_pipe<float><<<NJ * NK, 6 * 64, 0, s>>>(g.nx, g.ny, g.nz, NJ, NK, ctl, M->pdone.as<int>(), ctl + 1,
-                                                   M->D->t7.as<float>(), M->dinv2.as<float>(), flag);
+  uint64_t *xch = M->pxch.as<uint64_t>();
+  T *rhs = M->zt.as<T>(), *y = M->yv.as<T>(), *pb = M->pblk.as<T>(), *xpb = M->pxp.as<T>();
+  constexpr int P = sizeof(T) == 4 ? 8 : 4;   // levels in flight (6 to 12 and 3 to 6 measure the same)
+  k_dilu_rhs<T, BK><<<(unsigned)(NJ * NK) * NC, 256, 0, s>>>(g.nx, g.ny, g.nz, NJ, NC, M->rt.as<T>(),
+                                                            M->D->col0.as<T>(), xp, rhs, xpb, ctl);
+  uint32_t tag = ++M->pepoch;
+  k_fwd_pipe<T, P, BK><<<NJ * NK, NT, 0, s>>>(g.nx, g.ny, g.nz, NJ, NK, ctl, ctl + 1, tag, xch, pb, rhs, y);
+  tag = ++M->pepoch;
+  k_bwd_pipe<T, P, BK><<<NJ * NK, NT, 0, s>>>(g.nx, g.ny, g.nz, NJ, NK, ctl + 2, ctl + 1, tag, xch, pb, y, xpb, out);
   RS_HIP(hipGetLastError());
   return RS_OK;
 }
 
 template <class T>
 rs_status rs_dilu_apply_run(rs_cpr_s *M, const T *xp, T *out, hipStream_t s) {
-  const grid3 &g = M->A->g;
-  int nb = M->pnj * M->pnk;
-  int *ctl = M->pctl.as<int>();
-  const rs_dcpl_s *D = M->D;
-  uint64_t *xch = M->pxch.as<uint64_t>();
-  uint32_t xbytes = (uint32_t)M->pxch.bytes;
-  const int nw = 6;                   // waves per brick workgroup
-  pipe_reset(M, s);
-  uint32_t tag = ++M->pepoch;
-#define RS_FWD(NW) k_fwd_pipe<T, NW><<<nb, 64 * NW, 0, s>>>(g.nx, g.ny, g.nz, M->pnj, M->pord.as<int>(), ctl, ctl + 1, \
-      tag, xch, xbytes, D->t7.as<T>(), M->dinv2.as<T>(), M->rt.as<T>(), D->col0.as<T>(), xp, M->yv.as<T>())
-  if (nw == 4) RS_FWD(4); else if (nw == 8) RS_FWD(8); else RS_FWD(6);
-#undef RS_FWD
-  pipe_reset(M, s);
-  tag = ++M->pepoch;
-#define RS_BWD(NW) k_bwd_pipe<T, NW><<<nb, 64 * NW, 0, s>>>(g.nx, g.ny, g.nz, M->pnj, M->pnk, M->pord.as<int>(), ctl, \
-      ctl + 1, tag, xch, xbytes, D->t7.as<T>(), M->dinv2.as<T>(), M->yv.as<T>(), xp, out)
-  if (nw == 4) RS_BWD(4); else if (nw == 8) RS_BWD(8); else RS_BWD(6);
-#undef RS_BWD
-  RS_HIP(hipGetLastError());
-  return RS_OK;
+  return M->pbk == 4 ? dilu_apply_t<T, 4>(M, xp, out, s) : dilu_apply_t<T, 8>(M, xp, out, s);
 }
 
 template rs_status rs_dilu_apply_run<double>(rs_cpr_s *, const double *, double *, hipStream_t);

@@ -137,10 +137,12 @@ struct rs_cpr_s {
   dbuf cinv;          // dense inverse of the coarsest level (double)
   dbuf cb, cx;        // coarsest rhs / solution in double
   dbuf dinv2;         // second-stage block inverses [n][16], prec
-  // pipelined DILU sweeps: brick size, brick grid, ticket order, progress
-  int pb = 0, pnj = 0, pnk = 0;
-  uint32_t pepoch = 0;       // tag of the last pipelined sweep
-  dbuf pord, pdone, pctl, pxch;
+  // DILU sweeps' bricks: lines in k, brick grid, tag of the last sweep, level counts of the
+  // factorisation, [ticket, error, second ticket], face exchange words, the
+  // sweeps' blocks and x_p in brick order
+  int pbk = 8, pnj = 0, pnk = 0;
+  uint32_t pepoch = 0;
+  dbuf pdone, pctl, pxch, pblk, pxp;
   // RAS sweeps: scaled blocks and x_p in wavefront order; strips per layer,
   // their boundary exchange words, [fwd ticket, bwd ticket, error] and the
   // tag of the last sweep
