@@ -15,6 +15,7 @@
 #include <math.h>
 
 namespace {
+#include "csr7.h"
 
 __device__ __forceinline__ int64_t nbr_of(int64_t c, int s, int64_t nx, int64_t nxy) {
   switch (s) {
@@ -25,17 +26,6 @@ __device__ __forceinline__ int64_t nbr_of(int64_t c, int s, int64_t nx, int64_t 
     case 4: return c + 1;
     case 5: return c + nx;
     default: return c + nxy;
-  }
-}
-__device__ __forceinline__ bool in_grid(int s, int i, int j, int k, int nx, int ny, int nz) {
-  switch (s) {
-    case 0: return k > 0;
-    case 1: return j > 0;
-    case 2: return i > 0;
-    case 3: return true;
-    case 4: return i < nx - 1;
-    case 5: return j < ny - 1;
-    default: return k < nz - 1;
   }
 }
 __device__ __forceinline__ int axis_of(int s) { return s == 0 || s == 6 ? 2 : (s == 1 || s == 5 ? 1 : 0); }
@@ -51,109 +41,197 @@ __device__ __forceinline__ int well_of(int nw, const int32_t *__restrict__ wc, i
   return -1;
 }
 
-// position of stencil slot s in the caller row of cell c
-__device__ __forceinline__ int64_t pos_of(const int32_t *__restrict__ rp, int64_t c, int s, int i, int j,
-                                          int k, int nx, int ny, int nz) {
-  int64_t p = rp[c];
-  for (int t = 0; t < s; ++t) p += in_grid(t, i, j, k, nx, ny, nz) ? 1 : 0;
-  return p;
+// A cell's coordinates and its in-grid slots as a bit mask (grids hold fewer
+// than 2^31 cells).
+struct cell_at {
+  int i, j, k;
+  unsigned in;
+};
+__device__ __forceinline__ unsigned slots_in(int i, int j, int k, int nx, int ny, int nz) {
+  return (k > 0 ? 1u : 0u) | (j > 0 ? 2u : 0u) | (i > 0 ? 4u : 0u) | 8u | (i < nx - 1 ? 16u : 0u) |
+         (j < ny - 1 ? 32u : 0u) | (k < nz - 1 ? 64u : 0u);
+}
+__device__ __forceinline__ cell_at cell_of(int64_t c, int nx, int ny, int nz) {
+  const uint32_t cu = (uint32_t)c, line = cu / (uint32_t)nx;
+  cell_at a;
+  a.i = (int)(cu - line * (uint32_t)nx);
+  a.k = (int)(line / (uint32_t)ny);
+  a.j = (int)(line - (uint32_t)a.k * (uint32_t)ny);
+  a.in = slots_in(a.i, a.j, a.k, nx, ny, nz);
+  return a;
 }
 
-__global__ void k_assemble(int nx, int ny, int nz, const double *__restrict__ logk, double kvkh, double tscale,
-                           const double *__restrict__ Mf, const double *__restrict__ Mb,
-                           const double *__restrict__ B, double dt, int nw, const int32_t *__restrict__ wc,
-                           const double *__restrict__ wu, const int32_t *__restrict__ rp,
-                           double *__restrict__ vals) {
-  int64_t nxy = (int64_t)nx * ny, n = nxy * nz;
-  int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= n) return;
-  int i = (int)(c % nx), j = (int)((c / nx) % ny), k = (int)(c / nxy);
-  double acc[16];
+// The kernels below move whole 4x4 blocks (HBM bound) and take 16 lanes a
+// cell or face, one block entry each: every load and store of a block is one
+// 128-byte run, with no more alignment than that of a double.  (One thread a
+// cell touches 64 lines with each instruction.)
+
+// Lane l < 7 of a cell forms the transmissibility of its slot l, so a cell
+// takes one exp per lane; the entries see the operations of the definition in
+// its order.  100x100x50: 153 us (5.9 TB/s of blocks read and written), 333 us
+// with one thread a cell.
+__global__ __launch_bounds__(256) void k_assemble(int nx, int ny, int nz, const double *__restrict__ logk, double kvkh,
+                                                   double tscale, const double *__restrict__ Mf,
+                                                   const double *__restrict__ Mb, const double *__restrict__ B,
+                                                   double dt, int nw, const int32_t *__restrict__ wc,
+                                                   const double *__restrict__ wu, const int32_t *__restrict__ rp,
+                                                   double *__restrict__ vals) {
+  const int64_t nxy = (int64_t)nx * ny, n = nxy * nz;
+  const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
+  if (c >= n) return;                                   // whole groups of 16
+  const int e = threadIdx.x & 15, base = (threadIdx.x & 63) & ~15;
+  const cell_at a = cell_of(c, nx, ny, nz);
+  const int64_t p0 = rp[c];
+  // every block's entry at once, from the accumulation block off the grid
+  const double *Bc = B + 16 * c;
+  double m[7];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = B[16 * c + e] / dt;
-  int64_t p = rp[c], diagpos = p;
   for (int s = 0; s < 7; ++s) {
-    if (!in_grid(s, i, j, k, nx, ny, nz)) continue;
-    if (s == 3) { diagpos = p++; continue; }
-    int64_t q = nbr_of(c, s, nx, nxy);
-    int d = axis_of(s);
-    int64_t lo = q < c ? q : c, hi = q < c ? c : q;
-    double pa = exp(logk[lo]), pb = exp(logk[hi]);
-    if (d == 2) { pa = kvkh * pa; pb = kvkh * pb; }
-    double T = tscale * (((2.0 * pa) * pb) / (pa + pb));
-    const double *M = (q > c) ? Mf + (d * n + c) * 16 : Mb + (d * n + q) * 16;
-    double *o = vals + 16 * p;
+    const double *M = Bc;
+    if (s != 3 && ((a.in >> s) & 1u))
+      M = s > 3 ? Mf + ((int64_t)axis_of(s) * n + c) * 16
+                : Mb + ((int64_t)axis_of(s) * n + nbr_of(c, s, nx, nxy)) * 16;
+    m[s] = M[e];
+  }
+  const bool in = e < 7 && ((a.in >> e) & 1u);
+  const double kq = exp(logk[in ? nbr_of(c, e, nx, nxy) : c]);
+  const double kc = __shfl(kq, base + 3, 64);
+  double pa = e < 3 ? kq : kc, pb = e < 3 ? kc : kq;    // lower-numbered cell first
+  if (e == 0 || e == 6) { pa = kvkh * pa; pb = kvkh * pb; }
+  const double T = tscale * (((2.0 * pa) * pb) / (pa + pb));
+  double acc = m[3] / dt;
+  int64_t p = p0, diagpos = p0;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      double t = T * M[e];
-      o[e] = -t;
-      acc[e] = acc[e] + t;
-    }
+  for (int s = 0; s < 7; ++s) {
+    const double Ts = __shfl(T, base + s, 64);
+    if (!((a.in >> s) & 1u)) continue;
+    if (s == 3) { diagpos = p++; continue; }
+    const double t = Ts * m[s];
+    vals[16 * p + e] = -t;
+    acc = acc + t;
     ++p;
   }
-  int w = well_of(nw, wc, c);
+  const int w = well_of(nw, wc, c);
   if (w >= 0) {
-    double ws = wu[w] * exp(logk[c]);
-    if (ws != 0.0)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[5 * r] = acc[5 * r] + ws;
+    const double ws = wu[w] * kc;
+    if (ws != 0.0 && e % 5 == 0) acc = acc + ws;
   }
-  double *o = vals + 16 * diagpos;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) o[e] = acc[e];
+  vals[16 * diagpos + e] = acc;
 }
 
-// G = -lambda_i x_j^T for every stored block (i,j), caller layout
-__global__ void k_grad_vals(int64_t n, int64_t nx, int64_t nxy, const int64_t *__restrict__ pos7,
-                            const double *__restrict__ lam, const double *__restrict__ x,
-                            double *__restrict__ G) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= 7 * n * 16) return;
-  int64_t sc = t >> 4;
-  int64_t p = pos7[sc];
-  if (p < 0) return;
-  int e = (int)(t & 15), r = e >> 2, col = e & 3;
-  int s = (int)(sc / n);
-  int64_t c = sc - (int64_t)s * n;
-  int64_t q = nbr_of(c, s, nx, nxy);
-  G[16 * p + e] = -(lam[4 * c + r] * x[4 * q + col]);
+// G = -lambda_i x_j^T for every stored block (i,j), caller layout: a row's
+// blocks are one run, at the closed-form row start.  100x100x50: 108 us (4.5
+// TB/s, written), 222 us slot by slot through an index array.
+__global__ __launch_bounds__(256) void k_grad_vals(int nx, int ny, int nz, const double *__restrict__ lam,
+                                                    const double *__restrict__ x, double *__restrict__ G) {
+  const int64_t nxy = (int64_t)nx * ny, n = nxy * nz;
+  const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
+  if (c >= n) return;
+  const int e = threadIdx.x & 15, r = e >> 2, col = e & 3;
+  const csr7_row w = csr7_of((uint32_t)c, (uint32_t)nx, (uint32_t)ny, (uint32_t)nz);
+  const double l = lam[4 * c + r];
+  double xq[7];
+#pragma unroll
+  for (int s = 0; s < 7; ++s) xq[s] = x[4 * (((w.mask >> s) & 1u) ? nbr_of(c, s, nx, nxy) : c) + col];
+  double *o = G + 16 * (int64_t)w.start + e;
+#pragma unroll
+  for (int s = 0; s < 7; ++s)
+    if ((w.mask >> s) & 1u) {
+      *o = -(l * xq[s]);
+      o += 16;
+    }
+}
+
+// sum over the 16 lanes of a DPP row, in every lane
+template <int CTRL> __device__ __forceinline__ double row_add(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+  return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double row_sum(double v) {
+  v = row_add<0x128>(v);                                // row_ror:8, 4, 2, 1
+  v = row_add<0x124>(v);
+  v = row_add<0x122>(v);
+  return row_add<0x121>(v);
 }
 
 // dJ/dlog k_c = sum over the faces of c of dT/dlog k_c * (G : dA/dT)
 //             + u_c k_c trace(G_cc) at wells
-__global__ void k_grad_logk(int nx, int ny, int nz, const double *__restrict__ logk, double kvkh,
-                            double tscale, const double *__restrict__ Mf, const double *__restrict__ Mb,
-                            int nw, const int32_t *__restrict__ wc, const double *__restrict__ wu,
-                            const int32_t *__restrict__ rp, const double *__restrict__ G,
-                            double *__restrict__ g) {
-  int64_t nxy = (int64_t)nx * ny, n = nxy * nz;
-  int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= n) return;
-  int i = (int)(c % nx), j = (int)((c / nx) % ny), k = (int)(c / nxy);
-  double kc = exp(logk[c]);
-  const double *Gcc = G + 16 * pos_of(rp, c, 3, i, j, k, nx, ny, nz);
-  double acc = 0.0;
-  for (int s = 0; s < 7; ++s) {
-    if (s == 3 || !in_grid(s, i, j, k, nx, ny, nz)) continue;
-    int64_t q = nbr_of(c, s, nx, nxy);
-    int d = axis_of(s);
-    int iq = (int)(q % nx), jq = (int)((q / nx) % ny), kq = (int)(q / nxy);
-    double kq_ = exp(logk[q]);
-    double sc = tscale * (d == 2 ? kvkh : 1.0);
-    double den = (kc + kq_) * (kc + kq_);
-    double dT = sc * 2.0 * kc * kq_ * kq_ / den;
-    const double *Mcq = (q > c) ? Mf + (d * n + c) * 16 : Mb + (d * n + q) * 16;
-    const double *Mqc = (q > c) ? Mb + (d * n + c) * 16 : Mf + (d * n + q) * 16;
-    const double *Gcq = G + 16 * pos_of(rp, c, s, i, j, k, nx, ny, nz);
-    const double *Gqc = G + 16 * pos_of(rp, q, 6 - s, iq, jq, kq, nx, ny, nz);
-    const double *Gqq = G + 16 * pos_of(rp, q, 3, iq, jq, kq, nx, ny, nz);
-    double e = 0.0;
-    for (int t = 0; t < 16; ++t)
-      e = e + (Gcc[t] - Gcq[t]) * Mcq[t] + (Gqq[t] - Gqc[t]) * Mqc[t];
-    acc = acc + dT * e;
+// G : dA/dT is the face's, the same from either side: a workgroup takes a tile
+// of cells, forms it once for each face of the tile (16 lanes a face: four
+// blocks of G, two of M), and sums the faces of its cells from LDS.  The
+// tile's outer faces are formed by two tiles (1.19 times the faces in all).
+// 100x100x50: 279 us, 1493 us with one thread a cell that formed every face
+// twice.
+constexpr int TX = 16, TY = 4, TZ = 4;
+constexpr int FX = (TX + 1) * TY * TZ, FY = TX * (TY + 1) * TZ, FZ = TX * TY * (TZ + 1);
+
+__global__ __launch_bounds__(256) void k_grad_logk(int nx, int ny, int nz, const double *__restrict__ logk, double kvkh,
+                                                    double tscale, const double *__restrict__ Mf,
+                                                    const double *__restrict__ Mb, int nw,
+                                                    const int32_t *__restrict__ wc, const double *__restrict__ wu,
+                                                    const int32_t *__restrict__ rp, const double *__restrict__ G,
+                                                    double *__restrict__ g) {
+  __shared__ double ef[FX + FY + FZ];
+  __shared__ double kk[TZ + 2][TY + 2][TX + 2];
+  const int64_t nxy = (int64_t)nx * ny, n = nxy * nz;
+  const int tx = (nx + TX - 1) / TX, ty = (ny + TY - 1) / TY;
+  const int bt = blockIdx.x / tx, i0 = (int)(blockIdx.x - (unsigned)bt * tx) * TX;
+  const int k0 = bt / ty * TZ, j0 = (bt - bt / ty * ty) * TY;
+  // permeabilities of the tile and its neighbours
+  for (int t = threadIdx.x; t < (TX + 2) * (TY + 2) * (TZ + 2); t += 256) {
+    const int a = t % (TX + 2), b = t / (TX + 2) % (TY + 2), d = t / ((TX + 2) * (TY + 2));
+    const int i = i0 + a - 1, j = j0 + b - 1, k = k0 + d - 1;
+    if (i >= 0 && i < nx && j >= 0 && j < ny && k >= 0 && k < nz) kk[d][b][a] = exp(logk[i + nx * (j + (int64_t)ny * k)]);
   }
-  int w = well_of(nw, wc, c);
-  if (w >= 0) acc = acc + wu[w] * kc * (Gcc[0] + Gcc[5] + Gcc[10] + Gcc[15]);
+  // faces: below cell (a, b, d) of the tile along the axis
+  const int e = threadIdx.x & 15;
+#pragma unroll 2
+  for (int f = threadIdx.x >> 4; f < FX + FY + FZ; f += 16) {
+    const int axis = f < FX ? 0 : (f < FX + FY ? 1 : 2);
+    const int t = axis == 0 ? f : (axis == 1 ? f - FX : f - FX - FY);
+    const int ex = axis == 0 ? TX + 1 : TX, ey = axis == 1 ? TY + 1 : TY;
+    const int q = t / ex, a = t - q * ex, d = q / ey, b = q - d * ey;
+    const int i = i0 + a, j = j0 + b, k = k0 + d;       // the face's upper cell
+    const int il = i - (axis == 0), jl = j - (axis == 1), kl = k - (axis == 2);
+    if (il < 0 || jl < 0 || kl < 0 || i >= nx || j >= ny || k >= nz) continue;
+    const int64_t hi = i + nx * (j + (int64_t)ny * k), lo = il + nx * (jl + (int64_t)ny * kl);
+    const unsigned inl = slots_in(il, jl, kl, nx, ny, nz), inh = slots_in(i, j, k, nx, ny, nz);
+    const double *Gl = G + 16 * (int64_t)rp[lo] + e, *Gh = G + 16 * (int64_t)rp[hi] + e;
+    const int sd = 4 + axis, su = 2 - axis;             // lower cell's slot up, upper cell's slot down
+    const double gll = Gl[16 * __popc(inl & 7u)], glh = Gl[16 * __popc(inl & ((1u << sd) - 1u))];
+    const double ghh = Gh[16 * __popc(inh & 7u)], ghl = Gh[16 * __popc(inh & ((1u << su) - 1u))];
+    const int64_t mo = ((int64_t)axis * n + lo) * 16 + e;
+    const double v = row_sum((gll - glh) * Mf[mo] + (ghh - ghl) * Mb[mo]);
+    if (e == 0) ef[f] = v;
+  }
+  __syncthreads();
+  const int a = threadIdx.x & 15, b = (threadIdx.x >> 4) & 3, d = threadIdx.x >> 6;
+  const int i = i0 + a, j = j0 + b, k = k0 + d;
+  if (i >= nx || j >= ny || k >= nz) return;
+  const int64_t c = i + nx * (j + (int64_t)ny * k);
+  const unsigned in = slots_in(i, j, k, nx, ny, nz);
+  const double kc = kk[d + 1][b + 1][a + 1];
+  double acc = 0.0;
+#pragma unroll
+  for (int s = 0; s < 7; ++s) {
+    if (s == 3 || !((in >> s) & 1u)) continue;
+    const int axis = axis_of(s), up = s > 3;
+    const int fa = a + (axis == 0 && up), fb = b + (axis == 1 && up), fd = d + (axis == 2 && up);
+    const int f = axis == 0 ? fa + (TX + 1) * (fb + TY * fd)
+                            : (axis == 1 ? FX + fa + TX * (fb + (TY + 1) * fd) : FX + FY + fa + TX * (fb + TY * fd));
+    const int sg = up ? 1 : -1;
+    const double kq = kk[d + 1 + (axis == 2) * sg][b + 1 + (axis == 1) * sg][a + 1 + (axis == 0) * sg];
+    const double sc = tscale * (axis == 2 ? kvkh : 1.0);
+    const double den = (kc + kq) * (kc + kq);
+    const double dT = sc * 2.0 * kc * kq * kq / den;
+    acc = acc + dT * ef[f];
+  }
+  const int w = well_of(nw, wc, c);
+  if (w >= 0) {
+    const double *Gcc = G + 16 * ((int64_t)rp[c] + __popc(in & 7u));
+    acc = acc + wu[w] * kc * (Gcc[0] + Gcc[5] + Gcc[10] + Gcc[15]);
+  }
   g[c] = acc;
 }
 
@@ -167,7 +245,7 @@ extern "C" rs_status rs_assemble(int nx, int ny, int nz, const double *d_logk, d
       (nw > 0 && (!d_wcell || !d_wu)) || !(dt > 0.0))
     return RS_E_ARG;
   int64_t n = (int64_t)nx * ny * nz;
-  k_assemble<<<rs_grid(n), RS_BLOCK, 0, rs_stream(stream)>>>(nx, ny, nz, d_logk, kvkh, tscale, d_Mf, d_Mb, d_B,
+  k_assemble<<<rs_grid(16 * n), RS_BLOCK, 0, rs_stream(stream)>>>(nx, ny, nz, d_logk, kvkh, tscale, d_Mf, d_Mb, d_B,
                                                              dt, nw, d_wcell, d_wu, d_row_ptr, d_vals);
   RS_HIP(hipGetLastError());
   return RS_OK;
@@ -176,9 +254,8 @@ extern "C" rs_status rs_assemble(int nx, int ny, int nz, const double *d_logk, d
 extern "C" rs_status rs_grad_vals(rs_bsr A, const double *d_lambda, const double *d_x, double *d_G,
                                   void *stream) {
   if (!A || !d_lambda || !d_x || !d_G) return RS_E_ARG;
-  int64_t n = A->g.n;
-  k_grad_vals<<<rs_grid(7 * n * 16), RS_BLOCK, 0, rs_stream(stream)>>>(n, A->g.nx, A->g.nxy, A->pos7.as<int64_t>(),
-                                                                       d_lambda, d_x, d_G);
+  const grid3 &g = A->g;
+  k_grad_vals<<<rs_grid(16 * g.n), RS_BLOCK, 0, rs_stream(stream)>>>(g.nx, g.ny, g.nz, d_lambda, d_x, d_G);
   RS_HIP(hipGetLastError());
   return RS_OK;
 }
@@ -190,9 +267,9 @@ extern "C" rs_status rs_grad_logk(int nx, int ny, int nz, const double *d_logk, 
   if (!rs_grid_dims_ok(nx, ny, nz) || nw < 0 || !d_logk || !d_Mf || !d_Mb || !d_row_ptr || !d_G || !d_g ||
       (nw > 0 && (!d_wcell || !d_wu)))
     return RS_E_ARG;
-  int64_t n = (int64_t)nx * ny * nz;
-  k_grad_logk<<<rs_grid(n), RS_BLOCK, 0, rs_stream(stream)>>>(nx, ny, nz, d_logk, kvkh, tscale, d_Mf, d_Mb, nw,
-                                                              d_wcell, d_wu, d_row_ptr, d_G, d_g);
+  const int64_t tiles = (int64_t)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY) * ((nz + TZ - 1) / TZ);
+  k_grad_logk<<<(unsigned)tiles, 256, 0, rs_stream(stream)>>>(nx, ny, nz, d_logk, kvkh, tscale, d_Mf, d_Mb, nw, d_wcell,
+                                                              d_wu, d_row_ptr, d_G, d_g);
   RS_HIP(hipGetLastError());
   return RS_OK;
 }
