@@ -10,17 +10,19 @@
 // upstream fluid part); the model, its constants and their sources are
 // listed with rs_thermal_assemble in rsolve.h.
 //
-// One thread per cell: it evaluates its own properties and those of each
-// neighbour across its six faces, and writes its whole block row (diagonal,
-// up to six off-diagonal blocks) and its residual, so no two threads write
-// the same place.  The face flow seen from either side is the same number
-// (up to sign): the upstream cell is the one of higher pressure, on a tie
-// the lower-numbered one, whichever cell computes it.
+// A workgroup takes a tile of 8 x 4 x 2 cells: it evaluates the properties of
+// the tile's cells and of the cells around it once, into LDS, and then forms
+// the block rows and the residual with a quad of lanes per cell, lane r for
+// equation r, so that a block is written as one 128-byte run.  No two lanes
+// write the same place.  The face flow seen from either side is the same
+// number (up to sign): the upstream cell is the one of higher pressure, on a
+// tie the lower-numbered one, whichever cell computes it.
 #include "rs_internal.h"
 #include <math.h>
 
 namespace {
 #include "csr7.h"
+#include "quad4.h"
 
 // Fig. rela-swt of the paper: S_w, k_rw, k_row
 __constant__ double kSwt[12][3] = {
@@ -43,56 +45,89 @@ __constant__ double kWvis[28][2] = {
     {325.0, 8.4075e-2},  {350.0, 7.7437e-2}, {375.0, 7.2818e-2}, {400.0, 7.2818e-2}, {500.0, 7.2818e-2},
     {600.0, 7.2818e-2},  {700.0, 7.2818e-2}, {800.0, 7.2818e-2}};
 
-// piecewise-linear table value and slope at x (columns of a row-major table
-// of `cols` columns; constant beyond the first and last abscissa)
-template <int ROWS, int COLS>
-__device__ double table_lin(const double (&tab)[ROWS][COLS], int col, double x, double &slope) {
-  if (x <= tab[0][0]) { slope = 0.0; return tab[0][col]; }
-  if (x >= tab[ROWS - 1][0]) { slope = 0.0; return tab[ROWS - 1][col]; }
-  int lo = 0, hi = ROWS - 1;                 // tab[lo][0] <= x < tab[hi][0]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (x < tab[mid][0]) hi = mid; else lo = mid;
+// Tables in LDS: rows of COLS values, abscissa first, then the slopes of the
+// following interval.  find: the interval at x, or -1 below the first and -2
+// beyond the last abscissa, where the table is constant.
+template <int ROWS, int COLS> struct lds_table {
+  static constexpr int W = 2 * COLS - 1;
+  double v[ROWS][W];
+  __device__ __forceinline__ void fill(const double (&tab)[ROWS][COLS], int t) {
+    if (t >= ROWS * W) return;
+    const int r = t / W, c = t - r * W;
+    if (c < COLS) v[r][c] = tab[r][c];
+    else v[r][c] = r + 1 < ROWS ? (tab[r + 1][c - COLS + 1] - tab[r][c - COLS + 1]) / (tab[r + 1][0] - tab[r][0]) : 0.0;
   }
-  const double x0 = tab[lo][0], x1 = tab[hi][0], y0 = tab[lo][col], y1 = tab[hi][col];
-  slope = (y1 - y0) / (x1 - x0);
-  return y0 + (y1 - y0) * (x - x0) / (x1 - x0);
-}
+  __device__ __forceinline__ int find(double x) const {
+    if (x <= v[0][0]) return -1;
+    if (x >= v[ROWS - 1][0]) return -2;
+    int lo = 0, hi = ROWS - 1;               // v[lo][0] <= x < v[hi][0]
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (x < v[mid][0]) hi = mid; else lo = mid;
+    }
+    return lo;
+  }
+  // value and slope of column col
+  __device__ __forceinline__ double at(int col, int lo, double x, double &slope) const {
+    slope = lo < 0 ? 0.0 : v[lo][COLS + col - 1];
+    if (lo < 0) return v[lo == -1 ? 0 : ROWS - 1][col];
+    return v[lo][col] + slope * (x - v[lo][0]);
+  }
+};
+typedef lds_table<12, 3> swt_t;
+typedef lds_table<28, 2> wvis_t;
+static_assert(12 * swt_t::W <= 128 && 28 * wvis_t::W <= 128, "filled by half a workgroup each");
 
-// everything the flows, the accumulation and the constraint need of a cell
-struct tcell {
-  double p, t;
-  double lw, lo, lw_u[4], lo_u[4];   // mole mobilities k_r rho / mu and their u-gradients
-  double hw, hw_t, ho;               // enthalpies (Btu/lbmole); dH_o/dT = cpl_o
-  double kt, kt_u[4];                // thermal conductivity
-  double e, e_u[4];                  // energy per bulk volume
-  double vol, vol_u[4];              // phi - N_w/rho_w - N_o/rho_o
+// What the flows need of a cell: pressure, temperature, thermal conductivity,
+// the mobilities of water, oil (k_r rho / mu) and energy (their sum times the
+// enthalpies), and the u-gradients of the mobilities and the conductivity.
+enum { C_P, C_T, C_KT, C_L, C_LU = C_L + 3, C_KTU = C_LU + 12, C_N = C_KTU + 4 };
+// What the cell itself needs besides: gradients of the energy and of the
+// volume constraint, their values, the phase terms of a producer.
+enum { O_EU, O_VU = 4, O_E = 8, O_VOL, O_EOLD, O_N };
+
+// The parameters with what follows from them alone (formed on the host: a
+// division in FP64 is 15 instructions for every lane)
+struct tpar : rs_thermal_params {
+  double acc;                // V / dt
+  double gc[3];              // area / length of a face along x, y, z
+  double ch[5], href;        // coefficients of the water enthalpy's integral, its value at t_ref
+  explicit tpar(const rs_thermal_params &q) : rs_thermal_params(q) {
+    acc = dx * dy * dz / dt;
+    gc[0] = dy * dz / dx;
+    gc[1] = dx * dz / dy;
+    gc[2] = dx * dy / dz;
+    const double tr = (t_ref - 32.0) / 1.8;
+    href = 0.0;
+    double pr = tr;
+    for (int k = 0; k < 5; ++k) {
+      ch[k] = cpg[k] / (k + 1);
+      href += ch[k] * pr;
+      pr *= tr;
+    }
+  }
 };
 
-__device__ double water_h(const rs_thermal_params &q, double t, double &dh) {
-  const double tc = (t - 32.0) / 1.8, tr = (q.t_ref - 32.0) / 1.8;
+__device__ double water_h(const tpar &q, double t, double &dh) {
+  const double tc = (t - 32.0) * (1.0 / 1.8);
   // integral of c0 + c1 s + ... + c4 s^4 from tr to tc, and the integrand at tc
-  double h = 0.0, cp = 0.0;
-  double pc = tc, pr = tr, pw = 1.0;
-  for (int k = 0; k < 5; ++k) {
-    h += q.cpg[k] * (pc - pr) / (k + 1);
-    cp += q.cpg[k] * pw;
-    pc *= tc; pr *= tr; pw *= tc;
-  }
+  const double h = ((((q.ch[4] * tc + q.ch[3]) * tc + q.ch[2]) * tc + q.ch[1]) * tc + q.ch[0]) * tc - q.href;
+  const double cp = (((q.cpg[4] * tc + q.cpg[3]) * tc + q.cpg[2]) * tc + q.cpg[1]) * tc + q.cpg[0];
   double hv = 0.0, dhv = 0.0;              // heat of vaporisation, zero above T_crit
   if (tc < q.tcrit_w) {
     const double g = pow(q.tcrit_w - tc, q.ev_w - 1.0);
     hv = q.hvr_w * g * (q.tcrit_w - tc);
     dhv = -q.hvr_w * q.ev_w * g;
   }
-  dh = (cp - dhv) * q.jmol_btu / 1.8;
+  dh = (cp - dhv) * q.jmol_btu * (1.0 / 1.8);
   return (h - hv) * q.jmol_btu;
 }
 
-__device__ void cell_eval(const rs_thermal_params &q, const double *__restrict__ u4, tcell &c) {
+__device__ void cell_eval(const tpar &q, const double *__restrict__ u4, const swt_t &swt,
+                          const wvis_t &wvis, double *__restrict__ c, double *__restrict__ own) {
   const double p = u4[0], nw = u4[1], no = u4[2], t = u4[3];
   const double dp = p - q.p_ref, dT = t - q.t_ref;
-  c.p = p; c.t = t;
+  c[C_P] = p; c[C_T] = t;
   const double phi = q.por_ref * (1.0 + q.cpor * dp), phi_p = q.por_ref * q.cpor;
   const double rw = q.rhow_ref * exp(q.cpw * dp - q.ct1w * dT - 0.5 * q.ct2w * dT * dT + q.cptw * dp * dT);
   const double rw_p = rw * (q.cpw + q.cptw * dT), rw_t = rw * (q.cptw * dp - q.ct1w - q.ct2w * dT);
@@ -100,58 +135,71 @@ __device__ void cell_eval(const rs_thermal_params &q, const double *__restrict__
   const double ro_p = ro * (q.cpo + q.cpto * dT), ro_t = ro * (q.cpto * dp - q.ct1o - q.ct2o * dT);
   // S = N / (phi rho): gradients in (p, N_w, N_o, T)
   const double aw = phi * rw, ao = phi * ro;
-  const double sw = nw / aw, so = no / ao;
-  const double sw_u[4] = {-sw * (phi_p * rw + phi * rw_p) / aw, 1.0 / aw, 0.0, -sw * phi * rw_t / aw};
-  const double so_u[4] = {-so * (phi_p * ro + phi * ro_p) / ao, 0.0, 1.0 / ao, -so * phi * ro_t / ao};
-  // relative permeabilities: k_rw, and Stone II with no gas (S_l = 1)
-  double dkrw, dkrow, dkrg, dkrog, d0;
-  const double krw = table_lin(kSwt, 1, sw, dkrw), krow = table_lin(kSwt, 2, sw, dkrow);
-  const double krg = table_lin(kSlt, 1, 1.0, dkrg), krog = table_lin(kSlt, 2, 1.0, dkrog);
-  const double krocw = table_lin(kSwt, 2, kSwt[0][0], d0);
-  double kro = krocw * ((krow / krocw + krw) * (krog / krocw + krg) - krw - krg);
-  double dkro = krocw * ((dkrow / krocw + dkrw) * (krog / krocw + krg) - dkrw);
+  const double iaw = 1.0 / aw, iao = 1.0 / ao, irw = 1.0 / rw, iro = 1.0 / ro;   // a division is 15 instructions
+  const double sw = nw * iaw, so = no * iao;
+  const double sw_u[4] = {-sw * (phi_p * rw + phi * rw_p) * iaw, iaw, 0.0, -sw * phi * rw_t * iaw};
+  const double so_u[4] = {-so * (phi_p * ro + phi * ro_p) * iao, 0.0, iao, -so * phi * ro_t * iao};
+  // relative permeabilities: k_rw, and Stone II with no gas (S_l = 1, the
+  // last entry of that table)
+  double dkrw, dkrow;
+  const int is = swt.find(sw);
+  const double krw = swt.at(1, is, sw, dkrw), krow = swt.at(2, is, sw, dkrow);
+  const double krg = kSlt[18][1], krog = kSlt[18][2], krocw = kSwt[0][2];
+  const double ikr = 1.0 / krocw, kg = krog * ikr + krg;
+  double kro = krocw * ((krow * ikr + krw) * kg - krw - krg);
+  double dkro = krocw * ((dkrow * ikr + dkrw) * kg - dkrw);
   if (kro < 0.0) { kro = 0.0; dkro = 0.0; }
   // viscosities
   double dmw;
-  const double mw = table_lin(kWvis, 1, (t - 32.0) / 1.8, dmw);
-  dmw /= 1.8;
-  const double ta = t + 459.67;
-  const double mo = q.avisc_o * exp(q.bvisc_o / ta), dmo = -mo * q.bvisc_o / (ta * ta);
-  c.lw = krw * rw / mw;
-  c.lo = kro * ro / mo;
+  const double tc = (t - 32.0) * (1.0 / 1.8), mw = wvis.at(1, wvis.find(tc), tc, dmw);
+  dmw *= 1.0 / 1.8;
+  const double ita = 1.0 / (t + 459.67);
+  const double mo = q.avisc_o * exp(q.bvisc_o * ita), dmo = -mo * q.bvisc_o * ita * ita;
+  const double imw = 1.0 / mw, imo = 1.0 / mo;
+  const double lw = krw * rw * imw, lo = kro * ro * imo;
+  // enthalpies
+  double hw_t;
+  const double hw = water_h(q, t, hw_t), ho = q.cpl_o * dT;
+  c[C_L] = lw;
+  c[C_L + 1] = lo;
+  c[C_L + 2] = lw * hw + lo * ho;
   for (int m = 0; m < 4; ++m) {
     const double drw = m == 0 ? rw_p : (m == 3 ? rw_t : 0.0), dro = m == 0 ? ro_p : (m == 3 ? ro_t : 0.0);
     const double dmuw = m == 3 ? dmw : 0.0, dmuo = m == 3 ? dmo : 0.0;
-    c.lw_u[m] = (dkrw * sw_u[m] * rw + krw * drw) / mw - krw * rw * dmuw / (mw * mw);
-    c.lo_u[m] = (dkro * sw_u[m] * ro + kro * dro) / mo - kro * ro * dmuo / (mo * mo);
+    const double lwm = (dkrw * sw_u[m] * rw + krw * drw - lw * dmuw) * imw;
+    const double lom = (dkro * sw_u[m] * ro + kro * dro - lo * dmuo) * imo;
+    const double hwm = m == 3 ? hw_t : 0.0, hom = m == 3 ? q.cpl_o : 0.0;
+    c[C_LU + m] = lwm;
+    c[C_LU + 4 + m] = lom;
+    c[C_LU + 8 + m] = lwm * hw + lw * hwm + lom * ho + lo * hom;
   }
-  // enthalpies, internal energies U = H - p/rho, energy per bulk volume
-  c.hw = water_h(q, t, c.hw_t);
-  c.ho = q.cpl_o * dT;
-  const double uw = c.hw - q.pv_btu * p / rw, uo = c.ho - q.pv_btu * p / ro;
-  const double uw_p = -q.pv_btu * (1.0 / rw - p * rw_p / (rw * rw)), uw_t = c.hw_t + q.pv_btu * p * rw_t / (rw * rw);
-  const double uo_p = -q.pv_btu * (1.0 / ro - p * ro_p / (ro * ro)), uo_t = q.cpl_o + q.pv_btu * p * ro_t / (ro * ro);
-  c.e = nw * uw + no * uo + (1.0 - q.por_ref) * q.cp_rock * dT;
-  c.e_u[0] = nw * uw_p + no * uo_p;
-  c.e_u[1] = uw;
-  c.e_u[2] = uo;
-  c.e_u[3] = nw * uw_t + no * uo_t + (1.0 - q.por_ref) * q.cp_rock;
-  // conductivity (linear mixing) and the saturation constraint
+  // conductivity (linear mixing)
   const double mix = sw * q.kw + so * q.ko;
-  c.kt = phi * mix + (1.0 - phi) * q.kr;
+  c[C_KT] = phi * mix + (1.0 - phi) * q.kr;
   for (int m = 0; m < 4; ++m) {
     const double dphi = m == 0 ? phi_p : 0.0;
-    c.kt_u[m] = dphi * (mix - q.kr) + phi * (sw_u[m] * q.kw + so_u[m] * q.ko);
+    c[C_KTU + m] = dphi * (mix - q.kr) + phi * (sw_u[m] * q.kw + so_u[m] * q.ko);
   }
-  c.vol = phi - nw / rw - no / ro;
-  c.vol_u[0] = phi_p + nw * rw_p / (rw * rw) + no * ro_p / (ro * ro);
-  c.vol_u[1] = -1.0 / rw;
-  c.vol_u[2] = -1.0 / ro;
-  c.vol_u[3] = nw * rw_t / (rw * rw) + no * ro_t / (ro * ro);
+  if (!own) return;
+  // internal energies U = H - p/rho, energy per bulk volume
+  const double uw = hw - q.pv_btu * p * irw, uo = ho - q.pv_btu * p * iro;
+  const double uw_p = -q.pv_btu * (irw - p * rw_p * irw * irw), uw_t = hw_t + q.pv_btu * p * rw_t * irw * irw;
+  const double uo_p = -q.pv_btu * (iro - p * ro_p * iro * iro), uo_t = q.cpl_o + q.pv_btu * p * ro_t * iro * iro;
+  own[O_E] = nw * uw + no * uo + (1.0 - q.por_ref) * q.cp_rock * dT;
+  own[O_EU] = nw * uw_p + no * uo_p;
+  own[O_EU + 1] = uw;
+  own[O_EU + 2] = uo;
+  own[O_EU + 3] = nw * uw_t + no * uo_t + (1.0 - q.por_ref) * q.cp_rock;
+  // the saturation constraint
+  own[O_VOL] = phi - nw * irw - no * iro;
+  own[O_VU] = phi_p + nw * rw_p * irw * irw + no * ro_p * iro * iro;
+  own[O_VU + 1] = -irw;
+  own[O_VU + 2] = -iro;
+  own[O_VU + 3] = nw * rw_t * irw * irw + no * ro_t * iro * iro;
 }
 
 // energy per bulk volume only (the previous time step's state)
-__device__ double cell_energy(const rs_thermal_params &q, const double *__restrict__ u4) {
+__device__ double cell_energy(const tpar &q, const double *__restrict__ u4) {
   const double p = u4[0], nw = u4[1], no = u4[2], t = u4[3];
   const double dp = p - q.p_ref, dT = t - q.t_ref;
   const double rw = q.rhow_ref * exp(q.cpw * dp - q.ct1w * dT - 0.5 * q.ct2w * dT * dT + q.cptw * dp * dT);
@@ -161,120 +209,209 @@ __device__ double cell_energy(const rs_thermal_params &q, const double *__restri
   return nw * (hw - q.pv_btu * p / rw) + no * (ho - q.pv_btu * p / ro) + (1.0 - q.por_ref) * q.cp_rock * dT;
 }
 
-__global__ __launch_bounds__(128) void k_thermal(int nx, int ny, int nz, rs_thermal_params q,
+// Tile of a workgroup, and the LDS index of its cells and the ones around it:
+// own cells, then the faces -x, +x, -y, +y, -z, +z.
+constexpr int TX = 8, TY = 4, TZ = 2, TN = TX * TY * TZ;
+constexpr int HX = TN, HY = HX + 2 * TY * TZ, HZ = HY + 2 * TX * TZ, HN = HZ + 2 * TX * TY;
+static_assert(HN + TN + TY * TZ <= 256 && 4 * TN == 256, "one evaluation or search and one block row per thread");
+__device__ __forceinline__ void tile_cell(int t, int &a, int &b, int &d) {
+  if (t < HX) {
+    a = t % TX; b = t / TX % TY; d = t / (TX * TY);
+  } else if (t < HY) {
+    const int f = t - HX, e = f % (TY * TZ);
+    a = f < TY * TZ ? -1 : TX; b = e % TY; d = e / TY;
+  } else if (t < HZ) {
+    const int f = t - HY, e = f % (TX * TZ);
+    b = f < TX * TZ ? -1 : TY; a = e % TX; d = e / TX;
+  } else {
+    const int f = t - HZ, e = f % (TX * TY);
+    d = f < TX * TY ? -1 : TZ; a = e % TX; b = e / TX;
+  }
+}
+
+// 2300 instructions per 16 cells and a chain of loads, evaluation, faces and
+// stores; the blocks written (441 MB at 100x100x50) would take 90 us.  There:
+// 169 us, 426 us with one thread per cell that evaluated its six neighbours
+// as well and searched the tables in constant memory.
+__global__ __launch_bounds__(256) void k_thermal(int nx, int ny, int nz, tpar q,
                                                  const double *__restrict__ kx, const double *__restrict__ ky,
                                                  const double *__restrict__ kz, const double *__restrict__ u,
                                                  const double *__restrict__ uold, int nw,
                                                  const int32_t *__restrict__ wcell, const int32_t *__restrict__ wkind,
                                                  const double *__restrict__ wval, double *__restrict__ vals,
                                                  double *__restrict__ res) {
-  const int64_t n = (int64_t)nx * ny * nz, nxy = (int64_t)nx * ny;
-  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= n) return;
-  tcell A;
-  cell_eval(q, u + 4 * c, A);
-  const double acc = q.dx * q.dy * q.dz / q.dt;
-  double D[16], R[4];
-  for (int e = 0; e < 16; ++e) D[e] = 0.0;
-  R[0] = acc * (u[4 * c + 1] - uold[4 * c + 1]);
-  R[1] = acc * (u[4 * c + 2] - uold[4 * c + 2]);
-  R[2] = acc * (A.e - cell_energy(q, uold + 4 * c));
-  R[3] = acc * A.vol;
-  D[1] = acc;                                  // row 0, column N_w
-  D[6] = acc;                                  // row 1, column N_o
-  for (int m = 0; m < 4; ++m) { D[8 + m] = acc * A.e_u[m]; D[12 + m] = acc * A.vol_u[m]; }
+  __shared__ double prop[HN][C_N + 1], own[TN][O_N];
+  __shared__ int first_well[TY * TZ];
+  __shared__ swt_t swt;
+  __shared__ wvis_t wvis;
+  const int64_t nxy = (int64_t)nx * ny;
+  const int tid = threadIdx.x, tx = (nx + TX - 1) / TX, ty = (ny + TY - 1) / TY;
+  const int bt = blockIdx.x / tx, i0 = (int)(blockIdx.x - (unsigned)bt * tx) * TX;
+  const int k0 = bt / ty * TZ, j0 = (bt - bt / ty * ty) * TY;
+  // What the second half needs of global memory is asked for first: the
+  // workgroup's time is latencies one after another.
+  const int r = tid & 3, l = tid >> 2, a = l % TX, b = l / TX % TY, d = l / (TX * TY);
+  const int i = i0 + a, j = j0 + b, k = k0 + d;
+  const bool cell = i < nx && j < ny && k < nz;
+  const int64_t c = cell ? i + nx * (j + (int64_t)ny * k) : 0;
   const csr7_row w = csr7_of((uint32_t)c, (uint32_t)nx, (uint32_t)ny, (uint32_t)nz);
-  const int64_t off[7] = {-nxy, -(int64_t)nx, -1, 0, 1, (int64_t)nx, nxy};
-  for (int s = 0; s < 7; ++s) {
-    if (s == 3 || !((w.mask >> s) & 1u)) continue;
-    const int64_t b = c + off[s];
-    tcell B;
-    cell_eval(q, u + 4 * b, B);
-    const int ax = s == 2 || s == 4 ? 0 : (s == 1 || s == 5 ? 1 : 2);
+  // lane r of a quad takes the permeabilities of faces r and r + 4 (in the
+  // order -z -y -x +x +y +z)
+  double k1[2], k2[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int f = min(r + 4 * h, 5);
+    const int ax = h ? (f == 4 ? 1 : 2) : (f == 3 ? 0 : 2 - f);
+    const bool in = (w.mask >> (f < 3 ? f : f + 1)) & 1u;
+    const int64_t st = ax == 0 ? 1 : (ax == 1 ? (int64_t)nx : nxy);
     const double *kk = ax == 0 ? kx : (ax == 1 ? ky : kz);
-    const double area = ax == 0 ? q.dy * q.dz : (ax == 1 ? q.dx * q.dz : q.dx * q.dy);
-    const double len = ax == 0 ? q.dx : (ax == 1 ? q.dy : q.dz);
-    const double k1 = kk[c], k2 = kk[b];
-    const double G = q.ctrans * area / len * ((k1 + k2 > 0.0) ? 2.0 * k1 * k2 / (k1 + k2) : 0.0);
-    const double Gc = area / len;
+    k1[h] = kk[c];
+    k2[h] = kk[in ? (f < 3 ? c - st : c + st) : c];
+  }
+  const int mo = min(1 + r, 3);
+  const double un = u[4 * c + mo], uo = uold[4 * c + mo];
+  if (tid < 128) swt.fill(kSwt, tid);
+  else wvis.fill(kWvis, tid - 128);
+  double u4[4];
+  bool eval = false;
+  const bool old = tid >= HN;
+  {
+    int ta, tb, td;
+    tile_cell(old ? min(tid - HN, TN - 1) : tid, ta, tb, td);
+    const int ti = i0 + ta, tj = j0 + tb, tk = k0 + td;
+    if (ti >= 0 && ti < nx && tj >= 0 && tj < ny && tk >= 0 && tk < nz && tid < HN + TN) {
+      eval = true;
+      ld4v((old ? uold : u) + 4 * (ti + nx * (tj + (int64_t)ny * tk)), u4);
+    }
+  }
+  __syncthreads();
+  if (eval) {
+    if (old) own[tid - HN][O_EOLD] = cell_energy(q, u4);
+    else cell_eval(q, u4, swt, wvis, prop[tid], tid < TN ? own[tid] : nullptr);
+  } else if (tid >= HN + TN && tid < HN + TN + TY * TZ) {
+    // threads without an evaluation: where the wells of each of the tile's
+    // lines start (cells ascending and unique)
+    const int t = tid - HN - TN;
+    const int64_t c0 = i0 + nx * (j0 + t % TY + (int64_t)ny * (k0 + t / TY));
+    int lo = 0, hi = nw;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (wcell[mid] < c0) lo = mid + 1; else hi = mid;
+    }
+    first_well[t] = lo;
+  }
+  __syncthreads();
+  if (!cell) return;
+  const double *A = prop[l], *W = own[l];
+  const double acc = q.acc;
+  // this equation's residual and row of the diagonal block
+  double R, D[4];
+  if (r < 2) {
+    R = acc * (un - uo);
+    for (int m = 0; m < 4; ++m) D[m] = m == 1 + r ? acc : 0.0;
+  } else {
+    R = r == 2 ? acc * (W[O_E] - W[O_EOLD]) : acc * W[O_VOL];
+    for (int m = 0; m < 4; ++m) D[m] = acc * W[(r == 2 ? O_EU : O_VU) + m];
+  }
+  const int rr = min(r, 2);                             // the constraint has no flows: its terms are dropped below
+  // LDS index of the neighbour across each face (-z -y -x +x +y +z)
+  int nb[6];
+  nb[0] = d > 0 ? l - TX * TY : HZ + a + TX * b;
+  nb[1] = b > 0 ? l - TX : HY + a + TX * d;
+  nb[2] = a > 0 ? l - 1 : HX + b + TY * d;
+  nb[3] = a < TX - 1 ? l + 1 : HX + TY * TZ + b + TY * d;
+  nb[4] = b < TY - 1 ? l + TX : HY + TX * TZ + a + TX * d;
+  nb[5] = d < TZ - 1 ? l + TX * TY : HZ + TX * TY + a + TX * b;
+  // Face factors that are the same for the four equations, handed on within
+  // the quad by DPP: the transmissibility and 1 / (sum of the conductivities)
+  double Gf[2], If[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int f = min(r + 4 * h, 5);
+    const bool in = (w.mask >> (f < 3 ? f : f + 1)) & 1u;
+    const double ks = k1[h] + k2[h];
+    Gf[h] = ks > 0.0 ? q.ctrans * q.gc[h ? (f == 4 ? 1 : 2) : (f == 3 ? 0 : 2 - f)] * 2.0 * k1[h] * k2[h] / ks : 0.0;
+    const int nf = h ? (f == 4 ? nb[4] : nb[5]) : (f == 0 ? nb[0] : f == 1 ? nb[1] : f == 2 ? nb[2] : nb[3]);
+    const double ksum = A[C_KT] + prop[in ? nf : l][C_KT];
+    If[h] = ksum > 0.0 ? 1.0 / ksum : 0.0;
+  }
+#pragma unroll
+  for (int f = 0; f < 6; ++f) {
+    const int s = f < 3 ? f : f + 1, ax = f < 3 ? 2 - f : f - 3, fl = f & 3;
+    const double gh = f < 4 ? Gf[0] : Gf[1], ih = f < 4 ? If[0] : If[1];
+    const double G = fl == 0 ? qb<0>(gh) : fl == 1 ? qb<1>(gh) : fl == 2 ? qb<2>(gh) : qb<3>(gh);
+    const double ik = fl == 0 ? qb<0>(ih) : fl == 1 ? qb<1>(ih) : fl == 2 ? qb<2>(ih) : qb<3>(ih);
+    if (!((w.mask >> s) & 1u)) continue;                // the same for the quad
+    const double *B = prop[nb[f]];
     // upstream: the higher pressure, on a tie the lower-numbered cell
-    const bool up_b = c < b ? (B.p > A.p) : !(A.p > B.p);
-    const tcell &U = up_b ? B : A;
-    const double dp = B.p - A.p;                // flow into c is positive for dp > 0
-    const double fw = G * U.lw * dp, fo = G * U.lo * dp;
-    const double hflux = U.lw * U.hw + U.lo * U.ho;
-    const double ksum = A.kt + B.kt;
-    const double kh = ksum > 0.0 ? 2.0 * A.kt * B.kt / ksum : 0.0;
-    const double fe = G * hflux * dp + Gc * kh * (B.t - A.t);
-    R[0] -= fw; R[1] -= fo; R[2] -= fe;
-    double O[16];                                // -dF/du_b, this face's off-diagonal block
-    for (int side = 0; side < 2; ++side) {      // 0: derivatives in u_c, 1: in u_b
-      const tcell &X = side ? B : A;
-      const bool up = side ? up_b : !up_b;
-      const double sg = side ? 1.0 : -1.0;
-      const double kother = side ? A.kt : B.kt;
-      const double dkh_dk = ksum > 0.0 ? 2.0 * kother * kother / (ksum * ksum) : 0.0;
+    const double pa = A[C_P], pb = B[C_P];
+    const bool up_b = f >= 3 ? (pb > pa) : !(pa > pb);
+    const double *U = up_b ? B : A;
+    const double dp = pb - pa, gdp = G * dp;            // flow into c is positive for dp > 0
+    const double gl = G * U[C_L + rr];
+    // -dF/du in u_c and in u_b: the mobility's part falls to the upstream cell
+    double O[4], F = gl * dp;
+    for (int m = 0; m < 4; ++m) {
+      const double t = gdp * U[C_LU + 4 * rr + m], tb = up_b ? t : 0.0;
+      if (r < 3) D[m] -= t - tb;
+      O[m] = 0.0 - tb;
+    }
+    if (r < 3) D[0] += gl;
+    O[0] -= gl;
+    if (r == 2) {                                       // conduction, harmonic mean of the conductivities
+      const double Gc = q.gc[ax];
+      const double ka = A[C_KT] * ik, kb = B[C_KT] * ik, dt = B[C_T] - A[C_T];
+      const double gk = Gc * 2.0 * ka * B[C_KT], gd = Gc * dt * 2.0, da = gd * kb * kb, db = gd * ka * ka;
+      F = F + gk * dt;
       for (int m = 0; m < 4; ++m) {
-        const double ddp = m == 0 ? sg : 0.0;
-        const double lwm = up ? U.lw_u[m] : 0.0, lom = up ? U.lo_u[m] : 0.0;
-        const double hwm = (up && m == 3) ? U.hw_t : 0.0, hom = (up && m == 3) ? q.cpl_o : 0.0;
-        const double dfw = G * (lwm * dp + U.lw * ddp);
-        const double dfo = G * (lom * dp + U.lo * ddp);
-        const double dfe = G * ((lwm * U.hw + U.lw * hwm + lom * U.ho + U.lo * hom) * dp + hflux * ddp) +
-                           Gc * (dkh_dk * X.kt_u[m] * (B.t - A.t) + kh * (m == 3 ? sg : 0.0));
-        if (side == 0) {
-          D[m] -= dfw; D[4 + m] -= dfo; D[8 + m] -= dfe;
-        } else {
-          O[m] = -dfw; O[4 + m] = -dfo; O[8 + m] = -dfe; O[12 + m] = 0.0;
-        }
+        D[m] -= da * A[C_KTU + m];
+        O[m] -= db * B[C_KTU + m];
       }
+      D[3] += gk;
+      O[3] -= gk;
     }
+    if (r < 3) R -= F;
+    else O[0] = O[1] = O[2] = O[3] = 0.0;
     if (vals) {
-      double2 *ob = (double2 *)(vals + 16 * (int64_t)csr7_pos(w, s));
-      for (int e = 0; e < 8; ++e) ob[e] = make_double2(O[2 * e], O[2 * e + 1]);
+      double2 *ob = (double2 *)(vals + 16 * (int64_t)csr7_pos(w, s) + 4 * r);
+      ob[0] = make_double2(O[0], O[1]);
+      ob[1] = make_double2(O[2], O[3]);
     }
   }
-  // wells (cells ascending and unique): binary search for this cell
-  int lo = 0, hi = nw;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (wcell[mid] < c) lo = mid + 1; else hi = mid;
-  }
-  if (lo < nw && wcell[lo] == c) {
+  int lo = first_well[l / TX], wc = lo < nw ? wcell[lo] : -1;
+  while (wc >= 0 && wc < c) wc = ++lo < nw ? wcell[lo] : -1;
+  if (wc == c && r < 3) {
     if (wkind[lo] > 0) {                         // injector: water rate (bbl/day of cold water)
       double dh;
       const double qw = wval[lo] * q.bbl_ft3 * q.rhow_ref;
-      R[0] -= qw;
-      R[2] -= qw * water_h(q, q.t_inj, dh);
-    } else if (A.p > q.p_bh) {                   // producer at bottom-hole pressure
-      const double wi = q.ctrans * wval[lo], drive = A.p - q.p_bh;
-      const double qw = -wi * A.lw * drive, qo = -wi * A.lo * drive;
-      R[0] -= qw; R[1] -= qo; R[2] -= qw * A.hw + qo * A.ho;
+      if (r == 0) R -= qw;
+      if (r == 2) R -= qw * water_h(q, q.t_inj, dh);
+    } else if (A[C_P] > q.p_bh) {                // producer at bottom-hole pressure: Q = -WI lambda (p - p_bh)
+      const double wi = q.ctrans * wval[lo], drive = A[C_P] - q.p_bh;
+      R -= -wi * A[C_L + r] * drive;
       for (int m = 0; m < 4; ++m) {
         const double dd = m == 0 ? 1.0 : 0.0;
-        const double dqw = -wi * (A.lw_u[m] * drive + A.lw * dd), dqo = -wi * (A.lo_u[m] * drive + A.lo * dd);
-        D[m] -= dqw;
-        D[4 + m] -= dqo;
-        D[8 + m] -= dqw * A.hw + qw * (m == 3 ? A.hw_t : 0.0) + dqo * A.ho + qo * (m == 3 ? q.cpl_o : 0.0);
+        D[m] -= -wi * (A[C_LU + 4 * r + m] * drive + A[C_L + r] * dd);
       }
     }
   }
   if (vals) {
-    double2 *db = (double2 *)(vals + 16 * (int64_t)csr7_pos(w, 3));
-    for (int e = 0; e < 8; ++e) db[e] = make_double2(D[2 * e], D[2 * e + 1]);
+    double2 *db = (double2 *)(vals + 16 * (int64_t)csr7_pos(w, 3) + 4 * r);
+    db[0] = make_double2(D[0], D[1]);
+    db[1] = make_double2(D[2], D[3]);
   }
-  if (res) {
-    double2 *rr = (double2 *)(res + 4 * c);
-    rr[0] = make_double2(R[0], R[1]);
-    rr[1] = make_double2(R[2], R[3]);
-  }
+  if (res) res[4 * c + r] = R;
 }
 
-// wells must be ascending and unique, inside the grid
-__global__ void k_thermal_wells_check(int64_t n, int nw, const int32_t *__restrict__ wcell, int *__restrict__ bad) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nw) return;
-  if (wcell[t] < 0 || wcell[t] >= n || (t > 0 && wcell[t - 1] >= wcell[t])) atomicOr(bad, 1);
+// wells must be ascending and unique, inside the grid (one workgroup, which
+// writes the flag whatever it finds)
+__global__ __launch_bounds__(1024) void k_thermal_wells_check(int64_t n, int nw, const int32_t *__restrict__ wcell,
+                                                               int *__restrict__ bad) {
+  int b = 0;
+  for (int t = threadIdx.x; t < nw; t += 1024)
+    if (wcell[t] < 0 || wcell[t] >= n || (t > 0 && wcell[t - 1] >= wcell[t])) b = 1;
+  b = __syncthreads_or(b);
+  if (threadIdx.x == 0) *bad = b;
 }
 
 // (p, N_w, N_o, T) from (p, S_w, S_o, T): N = phi rho S
@@ -334,16 +471,15 @@ extern "C" rs_status rs_thermal_assemble(int nx, int ny, int nz, const rs_therma
   if (nw > 0) {
     dbuf flag;
     RS_TRY(flag.alloc(sizeof(int)));
-    RS_HIP(hipMemsetAsync(flag.p, 0, sizeof(int), s));
-    k_thermal_wells_check<<<rs_grid(nw), RS_BLOCK, 0, s>>>(n, nw, d_wcell, flag.as<int>());
+    k_thermal_wells_check<<<1, 1024, 0, s>>>(n, nw, d_wcell, flag.as<int>());
     int h = 0;
     RS_HIP(hipGetLastError());
-    RS_HIP(hipMemcpyAsync(&h, flag.p, sizeof(int), hipMemcpyDeviceToHost, s));
-    RS_HIP(hipStreamSynchronize(s));
+    RS_TRY(rs_wait_read(&h, flag.p, sizeof(int), s));
     if (h) return RS_E_ARG;
   }
-  k_thermal<<<rs_grid(n, 128), 128, 0, s>>>(nx, ny, nz, *q, d_kx, d_ky, d_kz, d_u, d_uold, nw, d_wcell, d_wkind,
-                                           d_wval, d_vals, d_res);
+  const int64_t tiles = (int64_t)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY) * ((nz + TZ - 1) / TZ);
+  k_thermal<<<(unsigned)tiles, 256, 0, s>>>(nx, ny, nz, tpar(*q), d_kx, d_ky, d_kz, d_u, d_uold, nw, d_wcell, d_wkind, d_wval,
+                                            d_vals, d_res);
   RS_HIP(hipGetLastError());
   return RS_OK;
 }
