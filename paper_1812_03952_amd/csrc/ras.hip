@@ -33,12 +33,14 @@
 #include <math.h>
 #include <algorithm>
 #include <functional>
+#include <type_traits>
 
 namespace {
 #pragma clang fp contract(off)
 #include "block4.h"
 #pragma clang fp contract(fast)
 #include "quad4.h"
+#include "quadinv.h"
 
 // ---- wavefront order --------------------------------------------------------
 // Number of cells (i, j) of an nx x ny layer with i + j < lambda.
@@ -179,13 +181,13 @@ template <class T> __device__ __forceinline__ void order_after(int &idx, T tok) 
 
 // ---- factorisation, per layer: D_c = A~_cc - sum_{q in {c-nx, c-1}} A~_cq D_q^{-1} A~_qc
 // A quad of lanes per cell, lane r holding block row r, computes in FP64
-// (lines j = q + LW*u for quad q, U passes).  Each lane forms row r of
-// T = D_q^{-1} A~_qc and of the Schur update; the other rows of A~_qc and T
-// come from the quad by DPP.  The inverse is the Gauss-Jordan elimination
-// with row pivoting of the single-thread form, element by element the same
-// operations: the quad tracks the row permutation instead of moving rows
-// (every lane takes the same pivot decision from the broadcast column), and
-// each lane scales the pivot row, read from its lane, itself.  D^{-1} blocks
+// (lines j = q + LW*u for quad q, U passes): the Schur terms and the inverse of
+// quadinv.h, element by element the operations of the single-thread form.
+// Bound by the chain of one cell: 1.6 us per level with one wave per SIMD, of
+// which the four pivot steps are most.  Reading the pivot rows by DPP took the
+// pass from 556 to 425 us at 100x100x50 and from 1388 to 1123 us at
+// 200x200x100 (FP32); loads two levels ahead, one barrier per level, and the
+// two Schur terms side by side gave nothing more.  D^{-1} blocks
 // are rounded to the stored precision before the next cells use them; both
 // neighbours' D^{-1} (cell before in x: same line, previous level; before in
 // y: line j-1) come from an LDS slot per line, with a barrier after the
@@ -261,91 +263,20 @@ __global__ __launch_bounds__(1024) void k_ras_setup(int nx, int ny, int64_t n, i
         load(lam, u, a);
       }
       if (j < ny && i >= 0 && i < nx) {                 // the same for the four lanes of the cell
-        double Lr[4];
+        double Lr[4], Rr[4];
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc) Lr[cc] = (double)a[0][cc];
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {                   // -y, then -x (ascending column)
-          if (s == 0 ? j == 0 : i == 0) continue;
-          const T *dq = ring + (s == 0 ? j - 1 : j) * 16 + 4 * r;
-          double Aqc[4][4], t[4], Tm[4][4];
-#pragma unroll
-          for (int cc = 0; cc < 4; ++cc) {
-            const T v = a[s == 0 ? 3 : 4][cc];
-            Aqc[0][cc] = (double)qb<0>(v); Aqc[1][cc] = (double)qb<1>(v);
-            Aqc[2][cc] = (double)qb<2>(v); Aqc[3][cc] = (double)qb<3>(v);
-          }
-#pragma unroll
-          for (int cc = 0; cc < 4; ++cc) {
-            double v = 0.0;
-#pragma unroll
-            for (int m = 0; m < 4; ++m) v = v + (double)dq[m] * Aqc[m][cc];
-            t[cc] = v;
-          }
-#pragma unroll
-          for (int cc = 0; cc < 4; ++cc) {
-            Tm[0][cc] = qb<0>(t[cc]); Tm[1][cc] = qb<1>(t[cc]);
-            Tm[2][cc] = qb<2>(t[cc]); Tm[3][cc] = qb<3>(t[cc]);
-          }
-#pragma unroll
-          for (int cc = 0; cc < 4; ++cc) {
-            double v = 0.0;
-#pragma unroll
-            for (int m = 0; m < 4; ++m) v = v + (double)a[s == 0 ? 1 : 2][m] * Tm[m][cc];
-            Lr[cc] = Lr[cc] - v;
-          }
+        T dq[4];                                        // -y, then -x (ascending column)
+        if (j > 0) {
+          ld4v(ring + (j - 1) * 16 + 4 * r, dq);
+          quad_schur<T>(Lr, dq, a[3], a[1]);
         }
-        // Gauss-Jordan on [L | I]; lane `mine` holds logical row `mine`
-        double Rr[4];
-#pragma unroll
-        for (int cc = 0; cc < 4; ++cc) Rr[cc] = cc == r ? 1.0 : 0.0;
-        double rmax = 0.0;
-#pragma unroll
-        for (int cc = 0; cc < 4; ++cc) rmax = fmax(rmax, fabs(Lr[cc]));
-        const double amax = fmax(fmax(fmax(fmax(0.0, qb<0>(rmax)), qb<1>(rmax)), qb<2>(rmax)), qb<3>(rmax));
-        int mine = r;
-        if (!isfinite(amax)) {
-          bad |= RSF_NONFINITE;
-        } else {
-          unsigned perm = 0xE4u;                        // 2 bits per logical row k: its lane
-          auto lane_of = [&](int k) { return (int)((perm >> (2 * k)) & 3u); };
-#pragma unroll
-          for (int p = 0; p < 4; ++p) {
-            const double c0 = qb<0>(Lr[p]), c1 = qb<1>(Lr[p]), c2 = qb<2>(Lr[p]), c3 = qb<3>(Lr[p]);
-            auto col = [&](int l) { return l == 0 ? c0 : (l == 1 ? c1 : (l == 2 ? c2 : c3)); };
-            int piv = p;
-            double best = fabs(col(lane_of(p)));
-#pragma unroll
-            for (int k = p + 1; k < 4; ++k)
-              if (fabs(col(lane_of(k))) > best) { best = fabs(col(lane_of(k))); piv = k; }
-            const unsigned lp = (unsigned)lane_of(p), lq = (unsigned)lane_of(piv);
-            perm = (perm & ~(3u << (2 * p)) & ~(3u << (2 * piv))) | (lq << (2 * p)) | (lp << (2 * piv));
-            mine = mine == p ? piv : (mine == piv ? p : mine);
-            const int src = wq + (int)lq;
-            double pv = col((int)lq);
-            if (fabs(pv) <= 1e-300 || fabs(pv) <= 1e-14 * amax) { bad |= RSF_SINGULAR; pv = 1.0; }
-            const double inv = 1.0 / pv;
-            double pL[4], pR[4];
-#pragma unroll
-            for (int cc = p + 1; cc < 4; ++cc) pL[cc] = __shfl(Lr[cc], src, 64) * inv;
-#pragma unroll
-            for (int cc = 0; cc < 4; ++cc) pR[cc] = __shfl(Rr[cc], src, 64) * inv;
-            if (mine == p) {
-#pragma unroll
-              for (int cc = p + 1; cc < 4; ++cc) Lr[cc] = pL[cc];
-#pragma unroll
-              for (int cc = 0; cc < 4; ++cc) Rr[cc] = pR[cc];
-              Lr[p] = 1.0;
-            } else {
-              const double f = Lr[p];
-#pragma unroll
-              for (int cc = p + 1; cc < 4; ++cc) Lr[cc] = Lr[cc] - f * pL[cc];
-#pragma unroll
-              for (int cc = 0; cc < 4; ++cc) Rr[cc] = Rr[cc] - f * pR[cc];
-              Lr[p] = 0.0;
-            }
-          }
+        if (i > 0) {
+          ld4v(ring + j * 16 + 4 * r, dq);
+          quad_schur<T>(Lr, dq, a[4], a[2]);
         }
+        int mine;
+        bad |= quad_inverse(Lr, Rr, r, wq, mine);
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc) orow[u][cc] = (T)Rr[cc];
         ok[u] = mine;
