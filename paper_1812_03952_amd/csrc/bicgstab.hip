@@ -5,25 +5,27 @@
 //   rho_i = (r^, r),  p = r + (rho_i / rho_{i-1})(alpha / omega)(p - omega v)
 //   v = A p^,  alpha = rho_i / (r^, v),  s = r - alpha v
 //   t = A s^,  omega = (t, s) / (t, t),  x += alpha p^ + omega s^,  r = s - omega t
-// One iteration is five launches besides the two CPR applications:
-//   k_bcg_p      p = r + beta (p - omega v)                       (beta from device scalars)
-//   SpMV         v = A p^  with the epilogue dot (r^, v)
+// One iteration is seven launches besides the two CPR applications:
+//   k_bcg_p      p = r + beta (p - omega v)    (beta from device scalars; not in a cycle's first)
+//   SpMV         v = A p^  with the epilogue dot (r^, v), and its sum
 //   k_bcg_s      s = r - alpha v in place of r, ||s||^2
-//   SpMV         t = A s^  with the epilogue dots (t, s), (t, t)
+//   SpMV         t = A s^  with the epilogue dots (t, s), (t, t), and their sums
 //   k_bcg_xr     x += alpha p^ + omega s^, r = s - omega t, (r^, r), ||r||^2
-// Every dot is reduced in two fixed-order stages, so a solve is bitwise
+// Every dot is reduced in two fixed-order stages, the second one by the last
+// workgroup of the launch that forms the first, so a solve is bitwise
 // reproducible.  alpha, beta and omega are formed on the device from the
-// reduced dots; the host reads a few doubles twice per iteration (after s and
-// after r) to test convergence and breakdown.  p^ and s^ are stored in the
+// reduced dots; the device posts a few doubles to the host twice per iteration
+// (after s and after r) to test convergence and breakdown.  p^ and s^ are stored in the
 // preconditioner's precision and read as stored, so v = A p^ and t = A s^
 // hold for the stored vectors.
 #include "rs_internal.h"
+#include <algorithm>
 #include <math.h>
 #include <string.h>
 
 namespace {
 
-constexpr int NBLK = 1024;   // blocks of the vector kernels (partials per dot)
+#include "reduce.h"
 
 // Device scalar block (doubles).
 enum {
@@ -36,62 +38,31 @@ enum {
   B_TS,          // (t, s)
   B_TT,          // (t, t)
   B_RN,          // ||r||^2
+  B_CNT,         // the reductions' workgroup count (an unsigned)
   B_TOTAL
 };
 
-// Two partials per workgroup (dots d0, d1) into part[k * NBLK + blockIdx.x].
+// out[k] = sum of part[k * nparts + b], b < nparts, in a fixed order, k < ND
+// (the SpMV's lists of one partial per workgroup).  With a post: out[0] and
+// whether a sweep's bounded wait has timed out go to the host.
 template <int ND>
-__device__ __forceinline__ void store_partials(double d0, double d1, double *__restrict__ part) {
-  __shared__ double sh[2][4];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  double d[2] = {d0, d1};
+__global__ __launch_bounds__(RED_T) void k_bcg_sums(int64_t nparts, const double *__restrict__ part,
+                                                    double *__restrict__ mid, unsigned *__restrict__ cnt,
+                                                    double *__restrict__ out, const int *__restrict__ err0,
+                                                    const int *__restrict__ err1, rs_post *__restrict__ post,
+                                                    uint64_t seq) {
+  double acc[ND], sum[1];
 #pragma unroll
-  for (int k = 0; k < ND; ++k) {
-    double v = d[k];
+  for (int k = 0; k < ND; ++k) acc[k] = 0.0;
+  for (int64_t b = (int64_t)blockIdx.x * RED_T + threadIdx.x; b < nparts; b += (int64_t)gridDim.x * RED_T)
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    if (lane == 0) sh[k][wv] = v;
+    for (int k = 0; k < ND; ++k) acc[k] += part[k * nparts + b];
+  if (!reduce_grid<ND>(acc, ND - 1, mid, cnt, sum)) return;
+  if ((threadIdx.x & 63) == 0 && threadIdx.x < 64 * ND) out[threadIdx.x >> 6] = sum[0];
+  if (post && threadIdx.x == 0) {
+    const double v[2] = {sum[0], ((err0 && *err0) || (err1 && *err1)) ? 1.0 : 0.0};
+    post_host(post, seq, v, 2);
   }
-  __syncthreads();
-  if ((int)threadIdx.x < ND)
-    part[(int64_t)threadIdx.x * NBLK + blockIdx.x] =
-        ((sh[threadIdx.x][0] + sh[threadIdx.x][1]) + sh[threadIdx.x][2]) + sh[threadIdx.x][3];
-}
-
-// out[k] = sum of part[k * stride + b], b < nparts, in a fixed order (one
-// workgroup per dot).
-__global__ __launch_bounds__(1024) void k_bcg_reduce(int nparts, int stride, const double *__restrict__ part,
-                                                     double *__restrict__ out) {
-  __shared__ double sh[1024];
-  const int k = blockIdx.x;
-  double s = 0.0;
-  for (int b = threadIdx.x; b < nparts; b += blockDim.x) s += part[(int64_t)k * stride + b];
-  sh[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[k] = sh[0];
-}
-
-// First stage for long partial lists (one per SpMV workgroup): block
-// (c, k) sums part[k * stride + b] over its contiguous chunk of b in a fixed
-// order, into mid[k * gridDim.x + c].
-__global__ __launch_bounds__(256) void k_bcg_reduce_chunks(int nparts, int stride, const double *__restrict__ part,
-                                                           double *__restrict__ mid) {
-  __shared__ double sh[256];
-  const int k = blockIdx.y, nc = gridDim.x, c = blockIdx.x;
-  const int chunk = (nparts + nc - 1) / nc, b0 = c * chunk, b1 = min(nparts, b0 + chunk);
-  double s = 0.0;
-  for (int b = b0 + threadIdx.x; b < b1; b += blockDim.x) s += part[(int64_t)k * stride + b];
-  sh[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) mid[k * nc + c] = sh[0];
 }
 
 // The vector kernels take two consecutive entries per thread and step
@@ -107,15 +78,22 @@ template <> struct pair_of<float> {
   }
 };
 
-// partial ||b||^2
-__global__ __launch_bounds__(256) void k_bcg_norm2(int64_t N, const double *__restrict__ b, double *__restrict__ part) {
-  double acc = 0.0;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < (N >> 1); t += (int64_t)NBLK * blockDim.x) {
-    const double2 v = pair_of<double>::ld(b, t);
-    acc = fma(v.x, v.x, acc);
-    acc = fma(v.y, v.y, acc);
-  }
-  store_partials<1>(acc, 0.0, part);
+// partials of ||b||^2 as the SpMV's epilogue forms them (one workgroup per 256
+// entries, the same tree): a norm and a dot of equal vectors are then equal,
+// and so are a solve from a stored x = 0 and one with zero_guess.  Also zeroes
+// the count of the later reductions.
+__global__ __launch_bounds__(256) void k_bcg_norm2(int64_t N, const double *__restrict__ b, double *__restrict__ part,
+                                                   unsigned *__restrict__ cnt) {
+  __shared__ double sh[4];
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const double x = t < N ? b[t] : 0.0;
+  double v = x * x;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) part[blockIdx.x] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
+  if (blockIdx.x == 0 && threadIdx.x == 0) *cnt = 0u;
 }
 
 __global__ void k_bcg_zero(int64_t N, double *__restrict__ x) {
@@ -123,17 +101,21 @@ __global__ void k_bcg_zero(int64_t N, double *__restrict__ x) {
   if (t < N) x[t] = 0.0;
 }
 
-// start of a cycle: p = v = 0, rho_{i-1} = alpha = omega = 1, rho = ||r||^2
-// (the shadow r^ is a copy of r, so (r^, r) = ||r||^2)
-__global__ void k_bcg_start(int64_t N, double *__restrict__ p, double *__restrict__ v, double *__restrict__ S) {
+// start of a cycle: r^ = p = r and rho = ||r||^2 (the shadow r^ is a copy of
+// r, so (r^, r) = ||r||^2); with b given, x = 0 and r = b first
+__global__ void k_bcg_start(int64_t N, const double *__restrict__ b, double *__restrict__ r, double *__restrict__ rh,
+                            double *__restrict__ p, double *__restrict__ x, double *__restrict__ S) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < N) { p[t] = 0.0; v[t] = 0.0; }
-  if (t == 0) {
-    S[B_RHO] = S[B_RN];
-    S[B_RHOP] = 1.0;
-    S[B_ALPHA] = 1.0;
-    S[B_OMEGA] = 1.0;
+  if (t < (N >> 1)) {
+    const double2 v = b ? ((const double2 *)b)[t] : ((const double2 *)r)[t];
+    if (b) {
+      ((double2 *)r)[t] = v;
+      ((double2 *)x)[t] = make_double2(0.0, 0.0);
+    }
+    ((double2 *)rh)[t] = v;
+    ((double2 *)p)[t] = v;
   }
+  if (t == 0) S[B_RHO] = S[B_RN];
 }
 
 // p = r + beta (p - omega v), beta = (rho / rho_prev) (alpha / omega)
@@ -150,23 +132,27 @@ __global__ __launch_bounds__(256) void k_bcg_p(int64_t N, const double *__restri
   }
 }
 
-// alpha = rho / (r^, v);  s = r - alpha v (in place);  partial ||s||^2
-__global__ __launch_bounds__(256) void k_bcg_s(int64_t N, double *__restrict__ r, const double *__restrict__ v,
-                                               double *__restrict__ S, double *__restrict__ part) {
-  const double alpha = S[B_RHO] / S[B_RV];
-  double acc = 0.0;
+// alpha = rho / (r^, v);  s = r - alpha v (in place);  ||s||^2
+__global__ __launch_bounds__(RED_T) void k_bcg_s(int64_t N, double *__restrict__ r, const double *__restrict__ v,
+                                                 double *__restrict__ S, double *__restrict__ part,
+                                                 rs_post *__restrict__ post, uint64_t seq) {
+  const double rv = S[B_RV], alpha = S[B_RHO] / rv;
+  double acc[1] = {0.0}, sum[1];
   double2 *r2 = (double2 *)r;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < (N >> 1); t += (int64_t)NBLK * blockDim.x) {
+  for (int64_t t = (int64_t)blockIdx.x * RED_T + threadIdx.x; t < (N >> 1); t += (int64_t)gridDim.x * RED_T) {
     const double2 vv = pair_of<double>::ld(v, t);
     double2 sv = r2[t];
     sv.x = sv.x - alpha * vv.x;
     sv.y = sv.y - alpha * vv.y;
     r2[t] = sv;
-    acc = fma(sv.x, sv.x, acc);
-    acc = fma(sv.y, sv.y, acc);
+    acc[0] = fma(sv.x, sv.x, acc[0]);
+    acc[0] = fma(sv.y, sv.y, acc[0]);
   }
-  store_partials<1>(acc, 0.0, part);
-  if (blockIdx.x == 0 && threadIdx.x == 0) S[B_ALPHA] = alpha;
+  if (!reduce_grid<1>(acc, 0, part, (unsigned *)(S + B_CNT), sum) || threadIdx.x != 0) return;
+  S[B_ALPHA] = alpha;
+  S[B_SN] = sum[0];
+  const double o[2] = {rv, sum[0]};
+  post_host(post, seq, o, 2);
 }
 
 // x += alpha p^ (the iteration stopped at s)
@@ -177,17 +163,19 @@ __global__ void k_bcg_xa(int64_t N, const TZ *__restrict__ ph, const double *__r
 }
 
 // omega = (t, s) / (t, t);  x += alpha p^ + omega s^;  r = s - omega t;
-// partials (r^, r) and ||r||^2.  (t, t) == 0 (breakdown) takes omega = 0:
-// x += alpha p^ and r = s.
+// (r^, r) and ||r||^2, and the scalars of the next iteration.  (t, t) == 0
+// (breakdown) takes omega = 0: x += alpha p^ and r = s.
 template <class TZ>
-__global__ __launch_bounds__(256) void k_bcg_xr(int64_t N, const TZ *__restrict__ ph, const TZ *__restrict__ sh,
-                                                const double *__restrict__ tv, const double *__restrict__ rh,
-                                                double *__restrict__ r, double *__restrict__ x,
-                                                const double *__restrict__ S, double *__restrict__ part) {
-  const double alpha = S[B_ALPHA], omega = S[B_TT] != 0.0 ? S[B_TS] / S[B_TT] : 0.0;
-  double a0 = 0.0, a1 = 0.0;
+__global__ __launch_bounds__(RED_T) void k_bcg_xr(int64_t N, const TZ *__restrict__ ph, const TZ *__restrict__ sh,
+                                                  const double *__restrict__ tv, const double *__restrict__ rh,
+                                                  double *__restrict__ r, double *__restrict__ x,
+                                                  double *__restrict__ S, double *__restrict__ part,
+                                                  rs_post *__restrict__ post, uint64_t seq) {
+  __shared__ double res[2];
+  const double alpha = S[B_ALPHA], tt2 = S[B_TT], omega = tt2 != 0.0 ? S[B_TS] / tt2 : 0.0;
+  double acc[2] = {0.0, 0.0}, sum[1];
   double2 *x2 = (double2 *)x, *r2 = (double2 *)r;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < (N >> 1); t += (int64_t)NBLK * blockDim.x) {
+  for (int64_t t = (int64_t)blockIdx.x * RED_T + threadIdx.x; t < (N >> 1); t += (int64_t)gridDim.x * RED_T) {
     const double2 pp = pair_of<TZ>::ld(ph, t), ss = pair_of<TZ>::ld(sh, t);
     const double2 tt = pair_of<double>::ld(tv, t), hh = pair_of<double>::ld(rh, t);
     double2 xv = x2[t], rv = r2[t];
@@ -197,21 +185,21 @@ __global__ __launch_bounds__(256) void k_bcg_xr(int64_t N, const TZ *__restrict_
     rv.y = rv.y - omega * tt.y;
     x2[t] = xv;
     r2[t] = rv;
-    a0 = fma(hh.x, rv.x, a0);
-    a0 = fma(hh.y, rv.y, a0);
-    a1 = fma(rv.x, rv.x, a1);
-    a1 = fma(rv.y, rv.y, a1);
+    acc[0] = fma(hh.x, rv.x, acc[0]);
+    acc[0] = fma(hh.y, rv.y, acc[0]);
+    acc[1] = fma(rv.x, rv.x, acc[1]);
+    acc[1] = fma(rv.y, rv.y, acc[1]);
   }
-  store_partials<2>(a0, a1, part);
-}
-
-// after k_bcg_xr's dots are reduced: omega stored, rho_prev = rho, rho = (r^, r)
-__global__ void k_bcg_next(double *__restrict__ S, const double *__restrict__ d) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  S[B_OMEGA] = S[B_TT] != 0.0 ? S[B_TS] / S[B_TT] : 0.0;
+  if (!reduce_grid<2>(acc, 1, part, (unsigned *)(S + B_CNT), sum)) return;
+  if ((threadIdx.x & 63) == 0 && threadIdx.x < 128) res[threadIdx.x >> 6] = sum[0];
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  S[B_OMEGA] = omega;
   S[B_RHOP] = S[B_RHO];
-  S[B_RHO] = d[0];
-  S[B_RN] = d[1];
+  S[B_RHO] = res[0];
+  S[B_RN] = res[1];
+  const double o[4] = {tt2, omega, res[0], res[1]};
+  post_host(post, seq, o, 4);
 }
 
 }  // namespace
@@ -223,24 +211,6 @@ extern "C" void rs_bicgstab_opts_default(rs_bicgstab_opts *o) {
   o->zero_guess = 0;
 }
 
-// out[k] = sum over b < nparts of part[k * stride + b], k < K, deterministic:
-// one workgroup per dot for short lists, two stages (64 chunks) for the
-// SpMV's one-partial-per-workgroup lists.
-constexpr int RED_CHUNKS = 64;
-static void bcg_reduce(int K, int nparts, int stride, const double *part, double *mid, double *out, hipStream_t s) {
-  if (nparts <= 4096) {
-    k_bcg_reduce<<<K, 1024, 0, s>>>(nparts, stride, part, out);
-  } else {
-    k_bcg_reduce_chunks<<<dim3(RED_CHUNKS, K), 256, 0, s>>>(nparts, stride, part, mid);
-    k_bcg_reduce<<<K, 1024, 0, s>>>(RED_CHUNKS, RED_CHUNKS, mid, out);
-  }
-}
-
-static rs_status bcg_read(double *h, const double *d, int cnt, hipStream_t s) {
-  RS_HIP(hipMemcpyAsync(h, d, sizeof(double) * cnt, hipMemcpyDeviceToHost, s));   // h is pinned
-  return rs_wait(s);
-}
-
 template <class TZ>
 static rs_status bicgstab_t(rs_bsr_s *A, rs_cpr_s *M, const double *b, double *x, const rs_bicgstab_opts &o,
                             rs_solve_info *info, hipStream_t s) {
@@ -249,16 +219,18 @@ static rs_status bicgstab_t(rs_bsr_s *A, rs_cpr_s *M, const double *b, double *x
   const int zp = sizeof(TZ) == 8 ? 64 : 32;
   if (M->bprec != zp || !M->bvec.p) {
     RS_TRY(M->bvec.alloc(sizeof(double) * N * 5 + sizeof(TZ) * N * 2));
-    RS_TRY(M->bpart.alloc(sizeof(double) * (2 * ((size_t)nsp > NBLK ? nsp : NBLK) + 2 * RED_CHUNKS)));
-    RS_TRY(M->bscal.alloc(sizeof(double) * (B_TOTAL + 4)));
+    RS_TRY(M->bpart.alloc(sizeof(double) * (2 * (size_t)nsp + 2 * RED_NB)));
+    RS_TRY(M->bscal.alloc(sizeof(double) * B_TOTAL));
     M->bprec = zp;
   }
   double *r = M->bvec.as<double>(), *rh = r + N, *p = rh + N, *v = p + N, *tv = v + N;
   TZ *ph = (TZ *)(tv + N), *shv = ph + N;
-  double *part = M->bpart.as<double>(), *S = M->bscal.as<double>(), *D = S + B_TOTAL;
-  double *mid = part + 2 * ((size_t)nsp > NBLK ? nsp : NBLK);
-  if (!M->bpin) RS_HIP(hipHostMalloc((void **)&M->bpin, sizeof(double) * B_TOTAL, hipHostMallocDefault));
-  double *hp = M->bpin;
+  double *sp = M->bpart.as<double>(), *part = sp + 2 * (size_t)nsp, *S = M->bscal.as<double>();
+  unsigned *cnt = (unsigned *)(S + B_CNT);
+  rs_post *post = nullptr;
+  RS_TRY(rs_post_slot(&post));
+  const int *err[2];
+  rs_sweep_errors(M, err);
   hipEvent_t e0, e1;
   RS_HIP(hipEventCreate(&e0));
   RS_HIP(hipEventCreate(&e1));
@@ -266,68 +238,74 @@ static rs_status bicgstab_t(rs_bsr_s *A, rs_cpr_s *M, const double *b, double *x
   rs_status st = RS_OK;
   int iters = 0, cycles = 0;
   double relres = 0.0, est = 0.0;
-  const unsigned gN = rs_grid(N);
-  // host copy of the scalar block, refreshed twice per iteration
-  double *h = hp;
-  auto read_scalars = [&]() -> rs_status { return bcg_read(h, S, B_TOTAL, s); };
-  // r = b - A x and ||r||^2 into S[B_RN]
-  auto residual = [&]() -> rs_status {
-    RS_TRY(rs_spmv_dots(A, x, 64, r, b, 1, nullptr, part, s));
-    bcg_reduce(1, nsp, nsp, part, mid, S + B_RN, s);
+  const unsigned gN = rs_grid(N), gP = (unsigned)std::min<int64_t>(1024, rs_grid(N >> 1)), nv = red_grid(N >> 1), ns = red_grid(nsp);
+  bool timed = false;                            // e1 is recorded after everything queued so far
+  bool sweeps_failed = false;
+  double rr = 0.0;                               // ||r||^2 of the last norm read
+  uint64_t seq = 0;
+  // the sum of the norm's partials into S[B_RN] and rr; e1 is recorded while
+  // the host would only wait, for the case that the solve ends here
+  auto read_norm = [&]() -> rs_status {
+    seq = rs_post_next(post);
+    k_bcg_sums<1><<<ns, RED_T, 0, s>>>(nsp, sp, part, cnt, S + B_RN, err[0], err[1], post, seq);
     RS_HIP(hipGetLastError());
-    return read_scalars();
+    RS_HIP(hipEventRecord(e1, s));
+    timed = true;
+    RS_TRY(rs_wait_post(post, seq, s));
+    rr = post->v[0];
+    sweeps_failed = post->v[1] != 0.0;
+    return RS_OK;
+  };
+  // r = b - A x and ||r||^2
+  auto residual = [&]() -> rs_status {
+    RS_TRY(rs_spmv_dots(A, x, 64, r, b, 1, nullptr, sp, s));
+    return read_norm();
   };
   do {
-    k_bcg_norm2<<<NBLK, 256, 0, s>>>(N, b, part);
-    bcg_reduce(1, NBLK, NBLK, part, mid, D, s);
-    if ((st = bcg_read(h, D, 1, s)) != RS_OK) break;
-    const double bnorm = sqrt(h[0]);
+    k_bcg_norm2<<<nsp, 256, 0, s>>>(N, b, sp, cnt);
+    if ((st = read_norm()) != RS_OK) break;
+    const double bnorm = sqrt(rr);
     if (!isfinite(bnorm)) { st = RS_E_NONFINITE; break; }
     if (bnorm == 0.0) {
       k_bcg_zero<<<gN, RS_BLOCK, 0, s>>>(N, x);
+      timed = false;
       relres = 0.0;
       break;
     }
     bool zero_start = o.zero_guess != 0;
     for (;;) {
-      if (zero_start) {
-        // x0 = 0: r = b and ||r||^2 = ||b||^2 (already reduced into D[0])
-        k_bcg_zero<<<gN, RS_BLOCK, 0, s>>>(N, x);
-        if (hipMemcpyAsync(r, b, sizeof(double) * N, hipMemcpyDeviceToDevice, s) != hipSuccess ||
-            hipMemcpyAsync(S + B_RN, D, sizeof(double), hipMemcpyDeviceToDevice, s) != hipSuccess) {
-          st = RS_E_HIP;
-          break;
-        }
-        if ((st = read_scalars()) != RS_OK) break;
-        zero_start = false;
-      } else if ((st = residual()) != RS_OK) {
-        break;
-      }
-      const double rn = sqrt(h[B_RN]);
+      // x0 = 0: r = b and ||r||^2 = ||b||^2 (already in S[B_RN])
+      if (!zero_start && (st = residual()) != RS_OK) break;
+      const double rn = sqrt(rr);
       relres = rn / bnorm;
-      if (!isfinite(rn)) { st = RS_E_NONFINITE; break; }
-      if (rn <= o.rtol * bnorm) { st = RS_OK; break; }
-      if (iters >= o.maxit) { st = RS_NOT_CONVERGED; break; }
-      ++cycles;
-      if (hipMemcpyAsync(rh, r, sizeof(double) * N, hipMemcpyDeviceToDevice, s) != hipSuccess) {
-        st = RS_E_HIP;
+      st = !isfinite(rn) ? RS_E_NONFINITE : (rn <= o.rtol * bnorm ? RS_OK : RS_NOT_CONVERGED);
+      if (st != RS_NOT_CONVERGED || iters >= o.maxit) {
+        if (zero_start) {
+          k_bcg_zero<<<gN, RS_BLOCK, 0, s>>>(N, x);
+          timed = false;
+        }
         break;
       }
-      k_bcg_start<<<gN, RS_BLOCK, 0, s>>>(N, p, v, S);
-      double rho = h[B_RN];                  // (r^, r) with r^ = r
+      st = RS_OK;
+      ++cycles;
+      timed = false;
+      k_bcg_start<<<rs_grid(N >> 1), RS_BLOCK, 0, s>>>(N, zero_start ? b : nullptr, r, rh, p, x, S);
+      zero_start = false;
+      double rho = rr;                       // (r^, r) with r^ = r
       bool first = true, stop_early = false;
       while (iters < o.maxit) {
         if (rho == 0.0) { stop_early = first; break; }
-        k_bcg_p<<<NBLK, 256, 0, s>>>(N, r, v, p, S);
+        if (!first) k_bcg_p<<<gP, 256, 0, s>>>(N, r, v, p, S);
         if ((st = rs_cpr_apply_any(M, p, ph, zp, s)) != RS_OK) break;
-        if ((st = rs_spmv_dots(A, ph, zp, v, nullptr, 1, rh, part, s)) != RS_OK) break;
-        bcg_reduce(1, nsp, nsp, part, mid, S + B_RV, s);
-        k_bcg_s<<<NBLK, 256, 0, s>>>(N, r, v, S, part);
-        bcg_reduce(1, NBLK, NBLK, part, mid, S + B_SN, s);
-        if ((st = read_scalars()) != RS_OK) break;
-        if (h[B_RV] == 0.0) { stop_early = first; break; }   // r now holds garbage; x is untouched
+        if ((st = rs_spmv_dots(A, ph, zp, v, nullptr, 1, rh, sp, s)) != RS_OK) break;
+        k_bcg_sums<1><<<ns, RED_T, 0, s>>>(nsp, sp, part, cnt, S + B_RV, nullptr, nullptr, nullptr, 0);
+        seq = rs_post_next(post);
+        k_bcg_s<<<nv, RED_T, 0, s>>>(N, r, v, S, part, post, seq);
+        if (hipGetLastError() != hipSuccess) { st = RS_E_HIP; break; }
+        if ((st = rs_wait_post(post, seq, s)) != RS_OK) break;
+        if (post->v[0] == 0.0) { stop_early = first; break; }   // r now holds garbage; x is untouched
         ++iters;
-        const double sn = sqrt(h[B_SN]);
+        const double sn = sqrt(post->v[1]);
         est = sn;
         if (!isfinite(sn)) { st = RS_E_NONFINITE; break; }
         if (sn <= o.rtol * bnorm) {
@@ -335,37 +313,34 @@ static rs_status bicgstab_t(rs_bsr_s *A, rs_cpr_s *M, const double *b, double *x
           break;
         }
         if ((st = rs_cpr_apply_any(M, r, shv, zp, s)) != RS_OK) break;
-        if ((st = rs_spmv_dots(A, shv, zp, tv, nullptr, 2, r, part, s)) != RS_OK) break;
-        bcg_reduce(2, nsp, nsp, part, mid, S + B_TS, s);
-        k_bcg_xr<TZ><<<NBLK, 256, 0, s>>>(N, ph, shv, tv, rh, r, x, S, part);
-        bcg_reduce(2, NBLK, NBLK, part, mid, D, s);
-        k_bcg_next<<<1, 64, 0, s>>>(S, D);
+        if ((st = rs_spmv_dots(A, shv, zp, tv, nullptr, 2, r, sp, s)) != RS_OK) break;
+        k_bcg_sums<2><<<ns, RED_T, 0, s>>>(nsp, sp, part, cnt, S + B_TS, nullptr, nullptr, nullptr, 0);
+        seq = rs_post_next(post);
+        k_bcg_xr<TZ><<<nv, RED_T, 0, s>>>(N, ph, shv, tv, rh, r, x, S, part, post, seq);
         if (hipGetLastError() != hipSuccess) { st = RS_E_HIP; break; }
-        if ((st = read_scalars()) != RS_OK) break;
-        if (h[B_TT] == 0.0) { stop_early = first; break; }   // x += alpha p^ was applied
-        const double rnn = sqrt(h[B_RN]);
+        if ((st = rs_wait_post(post, seq, s)) != RS_OK) break;
+        if (post->v[0] == 0.0) { stop_early = first; break; }   // x += alpha p^ was applied
+        const double rnn = sqrt(post->v[3]), omega = post->v[1];
         est = rnn;
-        rho = h[B_RHO];
+        rho = post->v[2];
         first = false;
         if (!isfinite(rnn)) break;
-        if (rnn <= o.rtol * bnorm || h[B_OMEGA] == 0.0) break;
+        if (rnn <= o.rtol * bnorm || omega == 0.0) break;
       }
       if (st != RS_OK) break;
       if (stop_early) {
         if ((st = residual()) != RS_OK) break;
-        relres = sqrt(h[B_RN]) / bnorm;
+        relres = sqrt(rr) / bnorm;
         st = relres <= o.rtol ? RS_OK : RS_NOT_CONVERGED;
         break;
       }
     }
     est = bnorm > 0.0 ? est / bnorm : 0.0;
   } while (0);
-  if (st == RS_OK || st == RS_NOT_CONVERGED) {
-    rs_status e = rs_dilu_check(M, s);
-    if (e != RS_OK) st = e;
-  }
+  // the last norm read came after every sweep of the solve
+  if ((st == RS_OK || st == RS_NOT_CONVERGED) && sweeps_failed) st = RS_E_HIP;
   float ms = 0.f;
-  (void)hipEventRecord(e1, s);
+  if (!timed) (void)hipEventRecord(e1, s);
   (void)hipEventSynchronize(e1);
   (void)hipEventElapsedTime(&ms, e0, e1);
   (void)hipEventDestroy(e0);

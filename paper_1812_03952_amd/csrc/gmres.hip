@@ -8,13 +8,14 @@
 //   pass 2  h2 = V^T (w - V h1)            (w - V h1 in registers only)
 //   pass 3  w = (w - V h1) - V h2;  ||w||^2
 // which is classical Gram-Schmidt applied twice, with the same operations
-// per entry as updating w in place after each pass.
-// followed by one single-thread kernel that forms h = h1 + h2, applies the
-// previous rotations, builds the new one and updates g, and a normalisation
-// v_{j+1} = w / h_{j+1,j} that reads h_{j+1,j} from device memory.  Every
-// dot is reduced in two deterministic stages (fixed per-block partials, then
-// a fixed-order sum), so a solve is bitwise reproducible.  The host reads
-// one 3-double status word per step to decide whether to stop.
+// per entry as updating w in place after each pass.  Each pass reduces its
+// dots itself (its last workgroup adds the partials in a fixed order), and the
+// last workgroup of pass 3 also forms h = h1 + h2, applies the previous
+// rotations, builds the new one and updates g: three launches where separate
+// reductions and rotations took seven.  The normalisation v_{j+1} = w /
+// h_{j+1,j} reads h_{j+1,j} from device memory.  The orders are functions of
+// the length alone, so a solve is bitwise reproducible.  The host reads one
+// posted status per step to decide whether to stop.
 // Z (the preconditioned vectors of flexible GMRES) is stored in the
 // preconditioner's precision; the SpMV and x += Z y read it as stored, so
 // A Z = V H holds for the stored Z and x stays consistent in FP32 mode.
@@ -24,41 +25,49 @@
 
 namespace {
 
-constexpr int NBLK = 1024;     // blocks of the dot kernels (partials per dot)
+#include "reduce.h"
 
-template <int MK, class TV>
-__device__ __forceinline__ void block_store_partials(double (&acc)[MK + 1], int K, bool norm,
-                                                     double *__restrict__ part) {
-  __shared__ double sh[4][MK + 1];
-  int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+// Device scalar block layout (doubles):
+enum {
+  S_H1 = 0,            // 64: pass-1 dots, [j+1] = ||w||^2 before orthogonalisation
+  S_H2 = 64,           // 64: pass-2 dots
+  S_HN = 129,          // h_{j+1,j}
+  S_BETA = 130,        // norm of the residual at the cycle start
+  S_STAT = 132,        // [0] |g_{j+1}|, [1] breakdown flag, [2] halt flag
+  S_G = 136,           // 65: rotated rhs g
+  S_CS = 208,          // 64
+  S_SN = 272,          // 64
+  S_Y = 336,           // 64
+  S_H = 400,           // (m+1) x m Hessenberg, row-major with leading dim 64
+  S_CNT = 400 + 65 * 64,   // the reductions' workgroup count (an unsigned)
+  S_TOTAL
+};
+
+// the grid's sums of acc[0 .. K) and acc[MK] into out[0 .. K]
+template <int MK>
+__device__ __forceinline__ void store_dots(const double (&acc)[MK + 1], int K, double *__restrict__ part,
+                                           unsigned *__restrict__ cnt, double *__restrict__ out) {
+  double sum[(MK + 8) / 8];
+  if (!reduce_grid<MK + 1>(acc, K, part, cnt, sum)) return;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-  for (int k = 0; k <= MK; ++k) {
-    double v = acc[k];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    if (lane == 0) sh[wv][k] = v;
-  }
-  __syncthreads();
-  int k = threadIdx.x;
-  if (k < K || (norm && k == MK)) {
-    double v = sh[0][k] + sh[1][k] + sh[2][k] + sh[3][k];
-    int slot = (k == MK) ? K : k;
-    part[(int64_t)slot * NBLK + blockIdx.x] = v;
-  }
+  for (int e = 0; e < (MK + 8) / 8; ++e)
+    if (lane == 0 && wv + 8 * e <= K) out[wv + 8 * e] = sum[e];
 }
 
-// pass 1: part[k] = V_k . w (k < K), part[K] = w . w.  Two consecutive
-// entries per thread and step (16-byte loads; N = 4n is even): at 1024
-// workgroups this streams about 1.5x faster than one entry per step.
+// pass 1: out[k] = V_k . w (k < K), out[K] = w . w.  Two consecutive
+// entries per thread and step (16-byte loads; N = 4n is even): this streams
+// about 1.5x faster than one entry per step.
 template <int MK>
-__global__ __launch_bounds__(256) void k_dots(int64_t N, int K, const double *__restrict__ V,
-                                               const double *__restrict__ w, double *__restrict__ part) {
+__global__ __launch_bounds__(RED_T) void k_dots(int64_t N, int K, const double *__restrict__ V,
+                                                const double *__restrict__ w, double *__restrict__ part,
+                                                unsigned *__restrict__ cnt, double *__restrict__ out) {
   double acc[MK + 1];
 #pragma unroll
   for (int k = 0; k <= MK; ++k) acc[k] = 0.0;
   const int64_t N2 = N >> 1;
   const double2 *w2 = (const double2 *)w;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < N2; t += (int64_t)NBLK * blockDim.x) {
+  for (int64_t t = (int64_t)blockIdx.x * RED_T + threadIdx.x; t < N2; t += (int64_t)gridDim.x * RED_T) {
     const double2 wv = w2[t];
 #pragma unroll
     for (int k = 0; k < MK; ++k)
@@ -70,32 +79,27 @@ __global__ __launch_bounds__(256) void k_dots(int64_t N, int K, const double *__
     acc[MK] = fma(wv.x, wv.x, acc[MK]);
     acc[MK] = fma(wv.y, wv.y, acc[MK]);
   }
-  block_store_partials<MK, double>(acc, K, true, part);
+  store_dots<MK>(acc, K, part, cnt, out);
 }
 
-// pass 2 (PASS3 = false): w' = w - sum_k h1[k] V_k formed in registers only,
-//   part[k] = V_k . w', part[K] = w' . w'  (read-only: w is not written)
-// pass 3 (PASS3 = true): w' formed again with the same operations, then
-//   w'' = w' - sum_k h2[k] V_k stored into w, part[0] = w'' . w''
-// Keeping pass 2 read-only saves a vector write per Arnoldi step, and a
-// kernel that both streams several vectors in and one out runs slower
-// than a read-only one; the arithmetic is that of updating w in place.
-template <int MK, bool PASS3>
-__global__ __launch_bounds__(256) void k_axpy_dots(int64_t N, int K, const double *__restrict__ V,
-                                                    const double *__restrict__ h1, const double *__restrict__ h2,
-                                                    double *__restrict__ w, double *__restrict__ part) {
+// pass 2: w' = w - sum_k h1[k] V_k formed in registers only,
+//   out[k] = V_k . w', out[K] = w' . w'  (read-only: w is not written, which
+//   saves a vector write per Arnoldi step, and a kernel that both streams
+//   several vectors in and one out runs slower than a read-only one)
+template <int MK>
+__global__ __launch_bounds__(RED_T) void k_axpy_dots(int64_t N, int K, const double *__restrict__ V,
+                                                     const double *__restrict__ h1, const double *__restrict__ w,
+                                                     double *__restrict__ part, unsigned *__restrict__ cnt,
+                                                     double *__restrict__ out) {
   double acc[MK + 1];
 #pragma unroll
   for (int k = 0; k <= MK; ++k) acc[k] = 0.0;
-  double g1[MK], g2[MK];
+  double g1[MK];
 #pragma unroll
-  for (int k = 0; k < MK; ++k) {
-    g1[k] = (k < K) ? h1[k] : 0.0;
-    g2[k] = (PASS3 && k < K) ? h2[k] : 0.0;
-  }
+  for (int k = 0; k < MK; ++k) g1[k] = (k < K) ? h1[k] : 0.0;
   const int64_t N2 = N >> 1;
-  double2 *w2 = (double2 *)w;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < N2; t += (int64_t)NBLK * blockDim.x) {
+  const double2 *w2 = (const double2 *)w;
+  for (int64_t t = (int64_t)blockIdx.x * RED_T + threadIdx.x; t < N2; t += (int64_t)gridDim.x * RED_T) {
     double2 vk[MK];
     double2 wv = w2[t];
 #pragma unroll
@@ -104,93 +108,143 @@ __global__ __launch_bounds__(256) void k_axpy_dots(int64_t N, int K, const doubl
       wv.x = fma(-g1[k], vk[k].x, wv.x);
       wv.y = fma(-g1[k], vk[k].y, wv.y);
     }
-    if (PASS3) {
 #pragma unroll
-      for (int k = 0; k < MK; ++k) {
-        wv.x = fma(-g2[k], vk[k].x, wv.x);
-        wv.y = fma(-g2[k], vk[k].y, wv.y);
+    for (int k = 0; k < MK; ++k)
+      if (k < K) {
+        acc[k] = fma(vk[k].x, wv.x, acc[k]);
+        acc[k] = fma(vk[k].y, wv.y, acc[k]);
       }
-      w2[t] = wv;
-    } else {
-#pragma unroll
-      for (int k = 0; k < MK; ++k)
-        if (k < K) {
-          acc[k] = fma(vk[k].x, wv.x, acc[k]);
-          acc[k] = fma(vk[k].y, wv.y, acc[k]);
-        }
-    }
     acc[MK] = fma(wv.x, wv.x, acc[MK]);
     acc[MK] = fma(wv.y, wv.y, acc[MK]);
   }
-  block_store_partials<MK, double>(acc, PASS3 ? 0 : K, true, part);
+  store_dots<MK>(acc, K, part, cnt, out);
 }
 
-// out[k] = sum over blocks of part[k] in a fixed order, k < K
-__global__ void k_reduce(int K, const double *__restrict__ part, double *__restrict__ out) {
-  __shared__ double sh[256];
-  int k = blockIdx.x;
-  if (k >= K) return;
-  double s = 0.0;
-  for (int b = threadIdx.x; b < NBLK; b += blockDim.x) s += part[(int64_t)k * NBLK + b];
-  sh[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[k] = sh[0];
-}
-
-// Device scalar block layout (doubles):
-enum {
-  S_H1 = 0,            // 64: pass-1 dots, [j+1] = ||w||^2 before orthogonalisation
-  S_H2 = 64,           // 64: pass-2 dots
-  S_NRM = 128,         // ||w||^2 after pass 3
-  S_HN = 129,          // h_{j+1,j}
-  S_BETA = 130,        // norm of the residual at the cycle start
-  S_STAT = 132,        // [0] |g_{j+1}|, [1] breakdown flag, [2] halt flag
-  S_G = 136,           // 65: rotated rhs g
-  S_CS = 208,          // 64
-  S_SN = 272,          // 64
-  S_Y = 336,           // 64
-  S_H = 400,           // (m+1) x m Hessenberg, row-major with leading dim 64
-  S_TOTAL = 400 + 65 * 64
-};
-
-// tol: the stopping bound on |g_{j+1}|; S_STAT[2] = 1 when the solve stops
-// after this step (converged, broken down or not finite), else 0
-__global__ void k_givens(int j, double *__restrict__ S, double tol) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  double *H = S + S_H, *g = S + S_G, *cs = S + S_CS, *sn = S + S_SN;
-  double wn0 = sqrt(S[S_H1 + j + 1]);
-  double hn = sqrt(S[S_NRM]);
-  for (int i = 0; i <= j; ++i) H[i * 64 + j] = (0.0 + S[S_H1 + i]) + S[S_H2 + i];
-  H[(j + 1) * 64 + j] = hn;
-  S[S_HN] = hn;
+// The rotations of step j by one wave, nrm2 = ||w||^2 after pass 3.  Lane i
+// holds entry i of the column and rotation i; the chain over them runs on
+// values read from their lanes.  Posts |g_{j+1}| and the breakdown flag.
+// S_STAT[2] = 1 when the solve stops after this step (converged within tol,
+// broken down or not finite), else 0.
+__device__ __forceinline__ void givens_step(int j, double nrm2, double *__restrict__ S, double tol,
+                                            rs_post *__restrict__ post, uint64_t seq) {
+  double *H = S + S_H, *g = S + S_G;
+  const int lane = threadIdx.x;
+  const int li = min(lane, j);
+  double h = (0.0 + S[S_H1 + li]) + S[S_H2 + li];
+  const double cl = S[S_CS + li], sl = S[S_SN + li], gj = g[j], wn0 = sqrt(S[S_H1 + j + 1]);
+  const double hn = sqrt(nrm2);
+  double a = lane_value(h, 0);
   for (int i = 0; i < j; ++i) {
-    double a = H[i * 64 + j], c = H[(i + 1) * 64 + j];
-    H[i * 64 + j] = cs[i] * a + sn[i] * c;
-    H[(i + 1) * 64 + j] = -sn[i] * a + cs[i] * c;
+    const double c = lane_value(h, i + 1), cs = lane_value(cl, i), sn = lane_value(sl, i);
+    const double u = cs * a + sn * c;
+    a = -sn * a + cs * c;
+    if (lane == i) h = u;
   }
-  double a = H[j * 64 + j], c = H[(j + 1) * 64 + j];
-  double d = hypot(a, c);
-  cs[j] = a / d;
-  sn[j] = c / d;
-  H[j * 64 + j] = d;
+  const double d = hypot(a, hn), cj = a / d, sj = hn / d;
+  if (lane == j) h = d;
+  if (lane <= j) H[lane * 64 + j] = h;
+  if (lane != 0) return;
+  S[S_HN] = hn;
   H[(j + 1) * 64 + j] = 0.0;
-  g[j + 1] = -sn[j] * g[j];
-  g[j] = cs[j] * g[j];
-  const double est = fabs(g[j + 1]);
+  S[S_CS + j] = cj;
+  S[S_SN + j] = sj;
+  const double gn = -sj * gj;
+  g[j + 1] = gn;
+  g[j] = cj * gj;
+  const double est = fabs(gn);
   const bool brk = hn <= 1e-14 * wn0;
   S[S_STAT + 0] = est;
   S[S_STAT + 1] = brk ? 1.0 : 0.0;
   S[S_STAT + 2] = (brk || !(est > tol) || isinf(est)) ? 1.0 : 0.0;
+  const double v[2] = {est, brk ? 1.0 : 0.0};
+  post_host(post, seq, v, 2);
 }
 
-__global__ void k_init_cycle(double *__restrict__ S, double beta) {
-  int t = threadIdx.x;
-  if (t < 65) S[S_G + t] = (t == 0) ? beta : 0.0;
-  if (t == 0) S[S_BETA] = beta;
+// pass 3: w' formed again with the operations of pass 2, then
+// w'' = w' - sum_k h2[k] V_k stored into w, ||w''||^2, and the rotations
+template <int MK>
+__global__ __launch_bounds__(RED_T) void k_axpy_norm(int64_t N, int K, const double *__restrict__ V,
+                                                     double *__restrict__ w, double *__restrict__ part,
+                                                     double *__restrict__ S, double tol,
+                                                     rs_post *__restrict__ post, uint64_t seq) {
+  double g1[MK], g2[MK];
+#pragma unroll
+  for (int k = 0; k < MK; ++k) {
+    g1[k] = (k < K) ? S[S_H1 + k] : 0.0;
+    g2[k] = (k < K) ? S[S_H2 + k] : 0.0;
+  }
+  double acc[1] = {0.0};
+  const int64_t N2 = N >> 1;
+  double2 *w2 = (double2 *)w;
+  for (int64_t t = (int64_t)blockIdx.x * RED_T + threadIdx.x; t < N2; t += (int64_t)gridDim.x * RED_T) {
+    double2 vk[MK];
+    double2 wv = w2[t];
+#pragma unroll
+    for (int k = 0; k < MK; ++k) {
+      vk[k] = (k < K) ? ((const double2 *)(V + (int64_t)k * N))[t] : make_double2(0.0, 0.0);
+      wv.x = fma(-g1[k], vk[k].x, wv.x);
+      wv.y = fma(-g1[k], vk[k].y, wv.y);
+    }
+#pragma unroll
+    for (int k = 0; k < MK; ++k) {
+      wv.x = fma(-g2[k], vk[k].x, wv.x);
+      wv.y = fma(-g2[k], vk[k].y, wv.y);
+    }
+    w2[t] = wv;
+    acc[0] = fma(wv.x, wv.x, acc[0]);
+    acc[0] = fma(wv.y, wv.y, acc[0]);
+  }
+  double sum[1];
+  if (reduce_grid<1>(acc, 0, part, (unsigned *)(S + S_CNT), sum) && threadIdx.x < 64)
+    givens_step(K - 1, sum[0], S, tol, post, seq);
+}
+
+// partials of ||w||^2 for k_cycle
+__global__ __launch_bounds__(RED_T) void k_norm(int64_t N, const double *__restrict__ w, double *__restrict__ part) {
+  __shared__ double sh[RED_T / 64];
+  double acc = 0.0;
+  const int64_t N2 = N >> 1;
+  const double2 *w2 = (const double2 *)w;
+  for (int64_t t = (int64_t)blockIdx.x * RED_T + threadIdx.x; t < N2; t += (int64_t)gridDim.x * RED_T) {
+    const double2 wv = w2[t];
+    acc = fma(wv.x, wv.x, acc);
+    acc = fma(wv.y, wv.y, acc);
+  }
+  acc = wave_sum(acc);
+  if ((threadIdx.x & 63) == 63) sh[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double v = sh[0];
+#pragma unroll
+    for (int q = 1; q < RED_T / 64; ++q) v += sh[q];
+    part[blockIdx.x] = v;
+  }
+}
+
+// Start of a cycle, one workgroup: beta = the norm whose nb partials k_norm
+// left, g = beta e_1, and the words that the passes count on.  The halt flag
+// is set where there is nothing to iterate on.  Posts ||.||^2 and whether a
+// sweep's bounded wait has timed out (err0, err1, either may be null).
+__global__ __launch_bounds__(RED_T) void k_cycle(int nb, const double *__restrict__ part, double *__restrict__ S,
+                                                 double rtol, const int *__restrict__ err0,
+                                                 const int *__restrict__ err1, rs_post *__restrict__ post,
+                                                 uint64_t seq) {
+  __shared__ double sh[RED_T / 64];
+  const int t = threadIdx.x;
+  double s = wave_sum(t < nb ? part[t] : 0.0);
+  if ((t & 63) == 63) sh[t >> 6] = s;
+  __syncthreads();
+  double nrm2 = sh[0];
+#pragma unroll
+  for (int q = 1; q < RED_T / 64; ++q) nrm2 += sh[q];
+  const double beta = sqrt(nrm2);
+  if (t < 65) S[S_G + t] = t == 0 ? beta : 0.0;
+  if (t != 0) return;
+  S[S_BETA] = beta;
+  S[S_STAT + 2] = (beta == 0.0 || !isfinite(beta) || beta <= rtol * beta) ? 1.0 : 0.0;
+  *(unsigned *)(S + S_CNT) = 0u;
+  const double v[2] = {nrm2, ((err0 && *err0) || (err1 && *err1)) ? 1.0 : 0.0};
+  post_host(post, seq, v, 2);
 }
 
 __global__ void k_backsolve(int k, double *__restrict__ S) {
@@ -251,32 +305,15 @@ extern "C" const char *rs_status_string(int st) {
   }
 }
 
-// dots of V_0..V_{K-1} (K may be 0) with w, plus ||w||^2 into S[off + K]
-static rs_status run_dots(int64_t N, int K, const double *V, const double *w, double *part, double *S,
-                          int off, hipStream_t s) {
-  if (K <= 8) k_dots<8><<<NBLK, 256, 0, s>>>(N, K, V, w, part);
-  else if (K <= 16) k_dots<16><<<NBLK, 256, 0, s>>>(N, K, V, w, part);
-  else k_dots<32><<<NBLK, 256, 0, s>>>(N, K, V, w, part);
-  k_reduce<<<K + 1, 256, 0, s>>>(K + 1, part, S + off);
-  RS_HIP(hipGetLastError());
-  return RS_OK;
-}
-
-template <bool PASS3>
-static rs_status run_axpy(int64_t N, int K, const double *V, const double *h1, const double *h2, double *w,
-                          double *part, double *S, int off, hipStream_t s) {
-  if (K <= 8) k_axpy_dots<8, PASS3><<<NBLK, 256, 0, s>>>(N, K, V, h1, h2, w, part);
-  else if (K <= 16) k_axpy_dots<16, PASS3><<<NBLK, 256, 0, s>>>(N, K, V, h1, h2, w, part);
-  else k_axpy_dots<32, PASS3><<<NBLK, 256, 0, s>>>(N, K, V, h1, h2, w, part);
-  int nout = PASS3 ? 1 : K + 1;
-  k_reduce<<<nout, 256, 0, s>>>(nout, part, S + off);
-  RS_HIP(hipGetLastError());
-  return RS_OK;
-}
-
-static rs_status read_host(double *h, const double *d, int cnt, hipStream_t s) {
-  RS_HIP(hipMemcpyAsync(h, d, sizeof(double) * cnt, hipMemcpyDeviceToHost, s));   // h is pinned
-  return rs_wait(s);
+// Gram-Schmidt of step K - 1: w against V_0 .. V_{K-1}, and its rotations
+template <int MK>
+static void run_cgs2(int64_t N, int K, const double *V, double *w, double *part, double *S, double tol,
+                     rs_post *post, uint64_t seq, hipStream_t s) {
+  const unsigned nb = red_grid(N >> 1);
+  unsigned *cnt = (unsigned *)(S + S_CNT);
+  k_dots<MK><<<nb, RED_T, 0, s>>>(N, K, V, w, part, cnt, S + S_H1);
+  k_axpy_dots<MK><<<nb, RED_T, 0, s>>>(N, K, V, S + S_H1, w, part, cnt, S + S_H2);
+  k_axpy_norm<MK><<<nb, RED_T, 0, s>>>(N, K, V, w, part, S, tol, post, seq);
 }
 
 template <class TZ>
@@ -288,48 +325,76 @@ static rs_status gmres_t(rs_bsr_s *A, rs_cpr_s *M, const double *b, double *x, c
     RS_TRY(M->V.alloc(sizeof(double) * N * (m + 1)));
     RS_TRY(M->Z.alloc(sizeof(TZ) * N * m));
     RS_TRY(M->w.alloc(sizeof(double) * N));
-    RS_TRY(M->part.alloc(sizeof(double) * NBLK * 66));
+    RS_TRY(M->part.alloc(sizeof(double) * RED_NB * 33));
     RS_TRY(M->scal.alloc(sizeof(double) * S_TOTAL));
     M->m = m;
   }
   double *V = M->V.as<double>(), *w = M->w.as<double>(), *part = M->part.as<double>(), *S = M->scal.as<double>();
   TZ *Z = M->Z.as<TZ>();
-  if (!M->hpin) RS_HIP(hipHostMalloc((void **)&M->hpin, sizeof(double) * 8, hipHostMallocDefault));
-  struct { double *p; } hb = {M->hpin};
-  hipEvent_t e0, e1, es;
+  rs_post *post = nullptr;
+  RS_TRY(rs_post_slot(&post));
+  const int *err[2];
+  rs_sweep_errors(M, err);
+  hipEvent_t e0, e1;
   RS_HIP(hipEventCreate(&e0));
   RS_HIP(hipEventCreate(&e1));
-  RS_HIP(hipEventCreateWithFlags(&es, hipEventDisableTiming));
   RS_HIP(hipEventRecord(e0, s));
   rs_status st = RS_OK;
   int iters = 0, cycles = 0;
   double relres = 0.0, est = 0.0;
   unsigned gN = rs_grid(N);
+  bool timed = false;                            // e1 is recorded after everything queued so far
+  bool sweeps_failed = false;
+  // ||v||^2 and the start of a cycle from v; e1 is recorded while the host
+  // would only wait, for the case that the solve ends here
+  auto start_cycle = [&](const double *v, uint64_t *seq) -> rs_status {
+    *seq = rs_post_next(post);
+    k_norm<<<red_grid(N >> 1), RED_T, 0, s>>>(N, v, part);
+    k_cycle<<<1, RED_T, 0, s>>>((int)red_grid(N >> 1), part, S, o.rtol, err[0], err[1], post, *seq);
+    RS_HIP(hipGetLastError());
+    RS_HIP(hipEventRecord(e1, s));
+    timed = true;
+    return RS_OK;
+  };
+  auto read_norm = [&](uint64_t seq, double *nrm) -> rs_status {
+    RS_TRY(rs_wait_post(post, seq, s));
+    *nrm = sqrt(post->v[0]);
+    sweeps_failed = post->v[1] != 0.0;
+    return RS_OK;
+  };
   do {
-    // ||b||
-    if ((st = run_dots(N, 0, V, b, part, S, S_NRM, s)) != RS_OK) break;
-    if ((st = read_host(hb.p, S + S_NRM, 1, s)) != RS_OK) break;
-    double bnorm = sqrt(hb.p[0]);
+    // ||b||; from x0 = 0 the first step's first pass (V_0 = b / ||b||) is
+    // queued behind it, and does nothing where the cycle has nothing to do
+    uint64_t seq = 0;
+    bool zero_start = o.zero_guess != 0;
+    bool in_queued = false;                      // step j's first pass is already on the stream
+    if ((st = start_cycle(b, &seq)) != RS_OK) break;
+    if (zero_start && o.maxit > 0) {
+      if ((st = rs_cpr_apply_in(M, b, S + S_BETA, V, S + S_STAT + 2, s)) != RS_OK) break;
+      in_queued = true;
+      timed = false;
+    }
+    double bnorm = 0.0;
+    if ((st = read_norm(seq, &bnorm)) != RS_OK) break;
     if (!isfinite(bnorm)) { st = RS_E_NONFINITE; break; }
     if (bnorm == 0.0) {
       if (hipMemsetAsync(x, 0, sizeof(double) * N, s) != hipSuccess) st = RS_E_HIP;
+      timed = false;
       relres = 0.0;
       break;
     }
-    bool zero_start = o.zero_guess != 0;
     bool x_zero = false;                         // x = 0 is implied, not stored
     for (;;) {
       double beta;
       if (zero_start) {
-        // x0 = 0: r0 = b, ||r0|| = ||b||, V_0 = b / ||b|| (the k_scale below)
+        // x0 = 0: r0 = b, ||r0|| = ||b||, V_0 = b / ||b||
         x_zero = true;
         beta = bnorm;
       } else {
         // r = b - A x into V_0
         if ((st = rs_spmv_any(A, x, 64, V, b, s)) != RS_OK) break;
-        if ((st = run_dots(N, 0, V, V, part, S, S_NRM, s)) != RS_OK) break;
-        if ((st = read_host(hb.p, S + S_NRM, 1, s)) != RS_OK) break;
-        beta = sqrt(hb.p[0]);
+        if ((st = start_cycle(V, &seq)) != RS_OK) break;
+        if ((st = read_norm(seq, &beta)) != RS_OK) break;
       }
       relres = beta / bnorm;
       if (!isfinite(beta)) { st = RS_E_NONFINITE; break; }
@@ -339,14 +404,13 @@ static rs_status gmres_t(rs_bsr_s *A, rs_cpr_s *M, const double *b, double *x, c
       // forms it (with beta from S_BETA); a restart's residual is in V_0
       // itself and is scaled in place
       const bool v0_fused = zero_start;
+      timed = false;
       if (!v0_fused) k_scale<<<gN, RS_BLOCK, 0, s>>>(N, V, S, -1, beta, V);
       zero_start = false;
-      k_init_cycle<<<1, 128, 0, s>>>(S, beta);
       ++cycles;
       const double tol = o.rtol * bnorm;
       const int zp = sizeof(TZ) == 8 ? 64 : 32;
       int k = 0;
-      bool in_queued = false;                    // step j's first pass is already on the stream
       for (int j = 0; j < m; ++j) {
         double *vj = V + (int64_t)j * N;
         TZ *zj = Z + (int64_t)j * N;
@@ -357,48 +421,48 @@ static rs_status gmres_t(rs_bsr_s *A, rs_cpr_s *M, const double *b, double *x, c
           if (!in_queued) st = rs_cpr_apply_in(M, j > 0 ? w : b, S + (j > 0 ? S_HN : S_BETA), vj, nullptr, s);
           if (st == RS_OK) st = rs_cpr_apply_rest(M, zj, zp, s);
         }
+        in_queued = false;
         if (st != RS_OK) break;
         if ((st = rs_spmv_any(A, zj, zp, w, nullptr, s)) != RS_OK) break;
-        if ((st = run_dots(N, j + 1, V, w, part, S, S_H1, s)) != RS_OK) break;
-        if ((st = run_axpy<false>(N, j + 1, V, S + S_H1, nullptr, w, part, S, S_H2, s)) != RS_OK) break;
-        if ((st = run_axpy<true>(N, j + 1, V, S + S_H1, S + S_H2, w, part, S, S_NRM, s)) != RS_OK) break;
-        k_givens<<<1, 64, 0, s>>>(j, S, tol);
+        seq = rs_post_next(post);
+        if (j < 8) run_cgs2<8>(N, j + 1, V, w, part, S, tol, post, seq, s);
+        else if (j < 16) run_cgs2<16>(N, j + 1, V, w, part, S, tol, post, seq, s);
+        else run_cgs2<32>(N, j + 1, V, w, part, S, tol, post, seq, s);
         if (hipGetLastError() != hipSuccess) { st = RS_E_HIP; break; }
         ++iters;
         k = j + 1;
-        // the status goes to the host while the device already runs the next
-        // step's first pass, which does nothing if k_givens set the halt flag
-        // (the host stops on the same values)
-        if (hipMemcpyAsync(hb.p, S + S_STAT, sizeof(double) * 2, hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipEventRecord(es, s) != hipSuccess) { st = RS_E_HIP; break; }
+        // the device already runs the next step's first pass while the host
+        // reads the status; it does nothing if the rotations set the halt
+        // flag (the host stops on the same values)
         in_queued = j + 1 < m && iters < o.maxit;
         if (in_queued && (st = rs_cpr_apply_in(M, w, S + S_HN, vj + N, S + S_STAT + 2, s)) != RS_OK) break;
-        if (hipEventSynchronize(es) != hipSuccess) { st = RS_E_HIP; break; }
-        est = hb.p[0];
+        if ((st = rs_wait_post(post, seq, s)) != RS_OK) break;
+        est = post->v[0];
         if (!isfinite(est)) { st = RS_E_NONFINITE; break; }
-        if (hb.p[1] != 0.0) break;                               // happy breakdown
+        if (post->v[1] != 0.0) break;                            // happy breakdown
         if (est <= tol || iters >= o.maxit) break;
       }
+      in_queued = false;
       if (st != RS_OK) break;
       k_backsolve<<<1, 64, 0, s>>>(k, S);
       k_update_x<TZ><<<gN, RS_BLOCK, 0, s>>>(N, k, Z, S, x, x_zero ? 1 : 0);
       x_zero = false;
       if (hipGetLastError() != hipSuccess) { st = RS_E_HIP; break; }
     }
-    if (x_zero) k_zero<<<gN, RS_BLOCK, 0, s>>>(N, x);   // stopped before any update
+    if (x_zero) {                                // stopped before any update
+      k_zero<<<gN, RS_BLOCK, 0, s>>>(N, x);
+      timed = false;
+    }
     est = (bnorm > 0.0) ? est / bnorm : 0.0;
   } while (0);
-  if (st == RS_OK || st == RS_NOT_CONVERGED) {
-    rs_status e = rs_dilu_check(M, s);
-    if (e != RS_OK) st = e;
-  }
+  // the last cycle's start came after every sweep of the solve
+  if ((st == RS_OK || st == RS_NOT_CONVERGED) && sweeps_failed) st = RS_E_HIP;
   float ms = 0.f;
-  (void)hipEventRecord(e1, s);
+  if (!timed) (void)hipEventRecord(e1, s);
   (void)hipEventSynchronize(e1);
   (void)hipEventElapsedTime(&ms, e0, e1);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  (void)hipEventDestroy(es);
   if (info) {
     info->iters = iters;
     info->cycles = cycles;

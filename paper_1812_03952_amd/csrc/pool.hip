@@ -14,6 +14,7 @@
 #include <map>
 #include <mutex>
 #include <unordered_map>
+#include <vector>
 #include <string.h>
 
 namespace {
@@ -113,17 +114,66 @@ extern "C" void rs_pool_usage(size_t *live_bytes, size_t *cached_bytes) {
 // word) and waits for the stream at each.  A blocking stream synchronisation
 // leaves the device idle for tens of microseconds after such a read while the
 // host thread wakes up; these waits poll an event instead.  Each host thread
-// keeps one event per device and a small pinned staging buffer (never freed:
-// no HIP calls at exit).
+// keeps one event per device and a small pinned buffer: a staging area and a
+// post slot.  The buffer of a thread that ends goes to the next new one (never
+// freed: no HIP calls at exit), so there are as many as threads at one time.
 namespace {
 constexpr int WAIT_MAX_DEV = 64;
 constexpr size_t WAIT_STAGE = 256;
+struct stage_list {
+  std::mutex mu;
+  std::vector<void *> free;
+};
+stage_list &stages() {
+  static stage_list *l = new stage_list();
+  return *l;
+}
 struct host_wait {
   hipEvent_t ev[WAIT_MAX_DEV] = {};
   void *stage = nullptr;
+  ~host_wait() {
+    if (!stage) return;
+    std::lock_guard<std::mutex> lk(stages().mu);
+    stages().free.push_back(stage);
+  }
 };
 thread_local host_wait tw;
+
+rs_status get_stage() {
+  if (tw.stage) return RS_OK;
+  {
+    std::lock_guard<std::mutex> lk(stages().mu);
+    if (!stages().free.empty()) {
+      tw.stage = stages().free.back();
+      stages().free.pop_back();
+      return RS_OK;
+    }
+  }
+  void *p = nullptr;
+  RS_HIP(hipHostMalloc(&p, WAIT_STAGE + sizeof(rs_post), hipHostMallocPortable));
+  memset(p, 0, WAIT_STAGE + sizeof(rs_post));
+  tw.stage = p;
+  return RS_OK;
+}
 }  // namespace
+
+rs_status rs_post_slot(rs_post **p) {
+  RS_TRY(get_stage());
+  *p = (rs_post *)((char *)tw.stage + WAIT_STAGE);
+  return RS_OK;
+}
+
+rs_status rs_wait_post(const rs_post *p, uint64_t seq, hipStream_t s) {
+  for (unsigned spin = 1;; ++spin) {
+    if (__atomic_load_n(&p->seq, __ATOMIC_ACQUIRE) == seq) return RS_OK;
+    if (spin % 4096) continue;
+    // now and then: has the stream failed, or ended without the post?
+    const hipError_t e = hipStreamQuery(s);
+    if (e == hipErrorNotReady) continue;
+    if (e == hipSuccess && __atomic_load_n(&p->seq, __ATOMIC_ACQUIRE) == seq) return RS_OK;
+    return RS_E_HIP;
+  }
+}
 
 rs_status rs_wait(hipStream_t s) {
   int dev = 0;
@@ -147,7 +197,7 @@ rs_status rs_wait_read(void *h, const void *d, size_t bytes, hipStream_t s) {
     RS_HIP(hipStreamSynchronize(s));
     return RS_OK;
   }
-  if (!tw.stage) RS_HIP(hipHostMalloc(&tw.stage, WAIT_STAGE, hipHostMallocPortable));
+  RS_TRY(get_stage());
   RS_HIP(hipMemcpyAsync(tw.stage, d, bytes, hipMemcpyDeviceToHost, s));
   RS_TRY(rs_wait(s));
   memcpy(h, tw.stage, bytes);

@@ -29,6 +29,18 @@ void rs_pool_put(void *p, size_t bytes);
 // device memory to h and wait for them (rs_wait_read), polling an event.
 rs_status rs_wait(hipStream_t s);
 rs_status rs_wait_read(void *h, const void *d, size_t bytes, hipStream_t s);
+// Pinned host memory that a kernel posts a few values to (post_host of
+// reduce.h), one slot per host thread.  A call that uses it numbers its posts
+// with rs_post_next, waits for each with rs_wait_post before it queues the
+// next one, and leaves none in flight when it returns.
+struct rs_post {
+  double v[12];
+  uint64_t seq;        // number of the last post
+  uint64_t next;       // host only: number of the last post asked for
+};
+rs_status rs_post_slot(rs_post **p);
+static inline uint64_t rs_post_next(rs_post *p) { return ++p->next; }
+rs_status rs_wait_post(const rs_post *p, uint64_t seq, hipStream_t s);
 
 // A device allocation owned by a handle.  `bytes` is the size of the block
 // actually held (at least what was asked for).
@@ -159,12 +171,10 @@ struct rs_cpr_s {
   // GMRES work (allocated on first solve)
   int m = 0;
   dbuf V, Z, w, part, scal;
-  double *hpin = nullptr;     // pinned host status word
   // BiCGSTAB work vectors (r, r^, p, v, t in FP64; p^, s^ in the
   // preconditioner's precision), partials and scalars
   dbuf bvec, bpart, bscal;
   int bprec = 0;
-  double *bpin = nullptr;     // pinned host copy of the scalar block
   ~rs_cpr_s();
 };
 
@@ -193,6 +203,8 @@ rs_status rs_dilu_prepare(rs_cpr_s *M, hipStream_t s);
 rs_status rs_dilu_setup_run(rs_cpr_s *M, int *flag, hipStream_t s);
 template <class T> rs_status rs_dilu_apply_run(rs_cpr_s *M, const T *xp, T *out, hipStream_t s);
 rs_status rs_dilu_check(rs_cpr_s *M, hipStream_t s);
+// the error words that rs_dilu_check reads (nullptr where there is none)
+void rs_sweep_errors(const rs_cpr_s *M, const int *(&w)[2]);
 rs_status rs_ras_check_shape(const grid3 &g, int prec);
 rs_status rs_ras_setup_run(rs_cpr_s *M, int *flag, hipStream_t s);
 template <class T> rs_status rs_ras_apply_run(rs_cpr_s *M, const T *xp, T *out, hipStream_t s);
