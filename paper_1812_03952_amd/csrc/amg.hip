@@ -56,58 +56,99 @@ __device__ __forceinline__ uint64_t prio(int i, int level) {
 }
 
 // ---- scan ------------------------------------------------------------------
-__global__ void k_scan_block(const int32_t *__restrict__ in, int32_t *__restrict__ out,
-                             int32_t *__restrict__ bsum, int64_t n) {
-  __shared__ int32_t s[256];
-  int64_t base = (int64_t)blockIdx.x * 1024 + threadIdx.x * 4;
-  int32_t v[4], tsum = 0;
+// Exclusive scan of at most 2^31 counts: workgroups of 4096 entries scan their
+// own and leave their sums, and a second launch adds to each entry the sums
+// before its workgroup, which every workgroup adds up itself (4 bytes per 4096
+// entries; two launches at any length, one up to 4096).  A set word *skip
+// leaves everything as it is.
+constexpr int SCAN_T = 256, SCAN_V = 16, SCAN_N = SCAN_T * SCAN_V;
+
+struct scan_counts {
+  const int32_t *in;
+  __device__ __forceinline__ int32_t operator()(int64_t i) const { return in[i]; }
+};
+struct scan_roots {            // 1 for a root of the independent set
+  const uint8_t *state;
+  __device__ __forceinline__ int32_t operator()(int64_t i) const { return state[i] == ST_ROOT ? 1 : 0; }
+};
+
+// the workgroup's sum in every thread; ex: the sum over the threads before
+__device__ __forceinline__ int32_t scan_block(int32_t x, int32_t &ex) {
+  __shared__ int32_t sw[SCAN_T / 64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  int32_t v = x;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) { v[k] = (base + k < n) ? in[base + k] : 0; tsum += v[k]; }
-  s[threadIdx.x] = tsum;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    int32_t t = threadIdx.x >= (unsigned)off ? s[threadIdx.x - off] : 0;
-    __syncthreads();
-    s[threadIdx.x] += t;
-    __syncthreads();
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t t = __shfl_up(v, o, 64);
+    if (lane >= o) v += t;
   }
-  int32_t ex = s[threadIdx.x] - tsum;
+  if (lane == 63) sw[wv] = v;
+  __syncthreads();
+  int32_t before = 0, all = 0;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
+  for (int w = 0; w < SCAN_T / 64; ++w) {
+    if (w < wv) before += sw[w];
+    all += sw[w];
+  }
+  ex = before + v - x;
+  return all;
+}
+
+template <class S>
+__global__ __launch_bounds__(SCAN_T) void k_scan_local(S src, int32_t *__restrict__ out, int32_t *__restrict__ bsum,
+                                                       int64_t n, const int *__restrict__ skip,
+                                                       int32_t *__restrict__ total, int32_t *__restrict__ tail) {
+  if (skip && *skip) return;
+  const int64_t base = (int64_t)blockIdx.x * SCAN_N + threadIdx.x * SCAN_V;
+  int32_t v[SCAN_V], sum = 0, ex;
+#pragma unroll
+  for (int k = 0; k < SCAN_V; ++k) v[k] = base + k < n ? src(base + k) : 0;
+#pragma unroll
+  for (int k = 0; k < SCAN_V; ++k) sum += v[k];
+  const int32_t all = scan_block(sum, ex);
+#pragma unroll
+  for (int k = 0; k < SCAN_V; ++k) {
     if (base + k < n) out[base + k] = ex;
     ex += v[k];
   }
-  if (threadIdx.x == 255) bsum[blockIdx.x] = s[255];
-}
-
-__global__ void k_scan_add(int32_t *__restrict__ out, const int32_t *__restrict__ boff, int64_t n) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < n) out[t] += boff[t / 1024];
-}
-
-// out = exclusive scan of in (n entries); in may equal out.  The sum goes to
-// *total (host: the stream is synchronised) and/or *dtotal (device, stream
-// ordered); either may be null.
-rs_status scan_i32(const int32_t *in, int32_t *out, int64_t n, int64_t *total, hipStream_t s,
-                   int32_t *dtotal) {
-  int64_t nb = (n + 1023) / 1024;
-  if (nb < 1) nb = 1;
-  dbuf bs, bo;
-  RS_TRY(bs.alloc(sizeof(int32_t) * nb));
-  k_scan_block<<<(unsigned)nb, 256, 0, s>>>(in, out, bs.as<int32_t>(), n);
-  RS_HIP(hipGetLastError());
-  if (nb == 1) {
-    if (dtotal) RS_HIP(hipMemcpyAsync(dtotal, bs.p, sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-    if (total) {
-      int32_t t = 0;
-      RS_TRY(rs_wait_read(&t, bs.p, sizeof(int32_t), s));
-      *total = t;
-    }
-    return RS_OK;
+  if (threadIdx.x != 0) return;
+  bsum[blockIdx.x] = all;
+  if (gridDim.x == 1) {
+    if (total) *total = all;
+    if (tail) *tail = all;
   }
-  RS_TRY(bo.alloc(sizeof(int32_t) * nb));
-  RS_TRY(scan_i32(bs.as<int32_t>(), bo.as<int32_t>(), nb, total, s, dtotal));
-  k_scan_add<<<rs_grid(n), RS_BLOCK, 0, s>>>(out, bo.as<int32_t>(), n);
+}
+
+__global__ __launch_bounds__(SCAN_T) void k_scan_offset(int32_t *__restrict__ out, const int32_t *__restrict__ bsum,
+                                                        int64_t n, const int *__restrict__ skip,
+                                                        int32_t *__restrict__ total, int32_t *__restrict__ tail) {
+  if (skip && *skip) return;
+  int32_t x = 0, ex;
+  for (int b = threadIdx.x; b < (int)blockIdx.x; b += SCAN_T) x += bsum[b];
+  const int32_t off = scan_block(x, ex);
+  const int64_t base = (int64_t)blockIdx.x * SCAN_N;
+#pragma unroll
+  for (int k = 0; k < SCAN_V; ++k) {
+    const int64_t i = base + k * SCAN_T + threadIdx.x;
+    if (i < n) out[i] += off;
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    const int32_t all = off + bsum[blockIdx.x];
+    if (total) *total = all;
+    if (tail) *tail = all;
+  }
+}
+
+// out = exclusive scan of src (n entries; out may be src's array), the sum to
+// *total and *tail (device; either may be null).  bs: (n + 4095) / 4096 words
+// of scratch, free until the stream gets past this.
+template <class S>
+rs_status scan_i32(S src, int32_t *out, int64_t n, dbuf &bs, const int *skip, int32_t *total, int32_t *tail,
+                   hipStream_t s) {
+  const unsigned nb = rs_grid(n, SCAN_N);
+  RS_TRY(bs.alloc(sizeof(int32_t) * nb));
+  k_scan_local<<<nb, SCAN_T, 0, s>>>(src, out, bs.as<int32_t>(), n, skip, total, tail);
+  if (nb > 1) k_scan_offset<<<nb, SCAN_T, 0, s>>>(out, bs.as<int32_t>(), n, skip, total, tail);
   RS_HIP(hipGetLastError());
   return RS_OK;
 }
@@ -211,7 +252,7 @@ __device__ __forceinline__ uint64_t keyof(uint8_t st, int v, int level) {
 // predecessor left no vertex undecided (*prev == 0) has nothing to change
 // and returns at once.  prev == nullptr: the predecessor is known to have
 // left some.
-// und0 (first round of a batch only): the batch's flags, zeroed here
+// und0 (first round of a batch only): the next batch's flags, zeroed here
 __global__ void k_mis_m1(int n, int level, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
                          const uint8_t *__restrict__ strong, const uint8_t *__restrict__ state,
                          uint64_t *__restrict__ m1, const int *__restrict__ prev, int *__restrict__ und0) {
@@ -256,14 +297,6 @@ __global__ void k_mis_m2d(int n, int level, const int32_t *__restrict__ rp, cons
   }
   // one plain store per block that still has undecided vertices
   if (__syncthreads_or(left) && threadIdx.x == 0) *undecided = 1;
-}
-
-// (also zeroes the word *zero1: the aggregation's error flag)
-__global__ void k_root_flag(int n, const uint8_t *__restrict__ state, int32_t *__restrict__ f,
-                            int *__restrict__ zero1) {
-  int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v == 0) *zero1 = 0;
-  if (v < n) f[v] = state[v] == ST_ROOT ? 1 : 0;
 }
 
 // (also zeroes z[0 .. nz): the coarse level's per-row counters, nz <= n)
@@ -513,8 +546,6 @@ __global__ void k_galerkin_copy(int nc, const int32_t *__restrict__ off, const i
   if (sum == 0.0) sum = 1.0;
   dl1[I] = (T)(aii < 0.0 ? -sum : sum);
 }
-
-__global__ void k_set_last(int32_t *__restrict__ p, int64_t idx, const int32_t *__restrict__ v) { p[idx] = *v; }
 
 template <class T>
 __global__ void k_l1diag(int n, const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
@@ -1117,69 +1148,133 @@ __global__ void k_strength7_sym(int nx, int ny, int nz, const uint8_t *__restric
   state[c] = m ? ST_UND : ST_ISO;
 }
 
-// Distance-2 MIS round on the grid: m1 as k_mis_m1; m2 and the decision as
-// k_mis_m2d, in one kernel that reads only m1 and the cell's own state, so the
-// state is updated in place.  Decided cells skip m2.
-__global__ void k_mis7_m1(int nx, int ny, int nz, int level, const uint8_t *__restrict__ smask,
-                          const uint8_t *__restrict__ state, uint64_t *__restrict__ m1, const int *__restrict__ prev,
-                          int *__restrict__ und0) {
-  const int64_t n = (int64_t)nx * ny * nz, c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (und0 && c < MIS_BATCH) und0[c] = 0;
-  if (c >= n || (prev && *prev == 0)) return;
-  const cell7 e = cell7_of(c, nx, ny, nz);
-  const uint8_t sm = smask[c];
-  int64_t q[7];
-  uint8_t st[7];
-#pragma unroll
-  for (int sl = 0; sl < 7; ++sl) {
-    q[sl] = ((sm >> sl) & 1u) ? e.nb[sl] : c;
-    int64_t a = q[sl];
-    asm volatile("" : "+v"(a));   // opaque: keeps the load unconditional
-    st[sl] = state[a];
-  }
-  uint64_t m = keyof(st[3], (int)c, level);
-  bool und = st[3] == ST_UND;
-#pragma unroll
-  for (int sl = 0; sl < 7; ++sl)
-    if ((sm >> sl) & 1u) {
-      const uint64_t kk = keyof(st[sl], (int)q[sl], level);
-      m = kk > m ? kk : m;
-      und = und || st[sl] == ST_UND;
-    }
-  // m1 is read only at undecided vertices and their strong neighbours, so a
-  // vertex with no undecided one in its closed neighbourhood (strength is
-  // symmetric) skips the store
-  if (und) m1[c] = m;
+// A distance-2 MIS round on the grid: m1 as k_mis_m1, m2 and the decision as
+// k_mis_m2d, for a tile of 60 x 8 x 4 cells.  The keys of the tile and two
+// cells around it go to LDS (each hashed once per tile), then m1 of the tile
+// and one cell around it, then the decisions; the states go from st to so, so
+// that every tile sees the round's own.  A tile with nothing undecided copies
+// its states.  A wave takes whole rows, 64 keys wide, so that every index but
+// the lane's x is scalar.  On the fine level (level 0) the hash alone is the
+// key: fmix32 is a bijection, so no two cells share one, and the two cells
+// whose hashes are the marks 0 (decided) and ~0 (root) lie past the largest
+// grid (KEY32 below).
+// Bound by instruction issue and each tile's chain of loads.  The 12 rounds at
+// 200x200x100, beside the RAS factorisation: 620 us, against 960 as two passes
+// a round that hashed seven keys per cell and went through memory for m1.
+// und: set if the round left undecided cells; und0 as in k_mis_m1.
+constexpr int MX = 60, MY = 8, MZ = 4, MIS_T = 512;
+// index + 0x9e3779b9 of the cells with hash 0 and ~0 (fmix32 inverted)
+constexpr uint32_t MIS_AT0 = 0u, MIS_AT1 = 0x331da083u;
+constexpr uint32_t fmix32_c(uint32_t h) {
+  h ^= h >> 16; h *= 0x85ebca6bu; h ^= h >> 13; h *= 0xc2b2ae35u; h ^= h >> 16;
+  return h;
 }
-
-__global__ void k_mis7_m2d(int nx, int ny, int nz, int level, const uint8_t *__restrict__ smask,
-                           const uint64_t *__restrict__ m1, uint8_t *__restrict__ state,
-                           int *__restrict__ undecided, const int *__restrict__ prev) {
-  if (prev && *prev == 0) return;             // *undecided stays 0
-  const int64_t n = (int64_t)nx * ny * nz, c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int left = 0;
-  uint8_t st = ST_ISO, sm = 0;
-  if (c < n) {
-    st = state[c];
-    uint32_t t = smask[c];
-    asm volatile("" : "+v"(t));    // both loads issue before the test of st
-    sm = (uint8_t)t;
-  }
-  if (st == ST_UND) {
-    const cell7 e = cell7_of(c, nx, ny, nz);
-    uint64_t v[7];
+static_assert(fmix32_c(MIS_AT0) == 0u && fmix32_c(MIS_AT1) == ~0u, "fmix32 inverses");
+static_assert(MIS_AT0 - 0x9e3779b9u > (uint32_t)(INT32_MAX / 2) && MIS_AT1 - 0x9e3779b9u > (uint32_t)(INT32_MAX / 2),
+              "KEY32: both past the largest grid");
+__global__ __launch_bounds__(MIS_T) void k_mis7_round(int nx, int ny, int nz, const uint8_t *__restrict__ smask,
+                                                      const uint8_t *__restrict__ st, uint8_t *__restrict__ so,
+                                                      int *__restrict__ und, int *__restrict__ und0) {
+  constexpr int KY = MY + 4, KZ = MZ + 4, HY = MY + 2, HZ = MZ + 2, NW = MIS_T / 64;
+  __shared__ uint32_t key[KZ * KY][64], m1[HZ * HY][64];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (und0 && blockIdx.x == 0 && threadIdx.x < MIS_BATCH) und0[threadIdx.x] = 0;
+  const int bx = (nx + MX - 1) / MX, by = (ny + MY - 1) / MY;
+  const int x0 = (blockIdx.x % bx) * MX, y0 = (blockIdx.x / bx % by) * MY, z0 = (blockIdx.x / (bx * by)) * MZ;
+  const int nxy = nx * ny;
+  const int x = x0 - 2 + lane, xc = min(max(x, 0), nx - 1);      // the lane's column, 64 wide
+  const bool xin = x == xc, xown = xin && lane >= 2 && lane < MX + 2;
+  // row (y, z): its first cell, clamped into the grid, and whether it exists
+  auto row = [&](int y, int z, bool &in) {
+    const int yc = min(max(y, 0), ny - 1), zc = min(max(z, 0), nz - 1);
+    in = yc == y && zc == z;
+    return zc * nxy + yc * nx;
+  };
+  constexpr int OWN = MY * MZ / NW;                               // rows of the tile per wave
+  uint8_t own[OWN];
+  uint32_t msk[OWN];
+  bool any = false;
 #pragma unroll
-    for (int sl = 0; sl < 7; ++sl) v[sl] = m1[((sm >> sl) & 1u) ? e.nb[sl] : c];
-    uint64_t m = v[3];
-#pragma unroll
-    for (int sl = 0; sl < 7; ++sl)
-      if ((sm >> sl) & 1u) m = v[sl] > m ? v[sl] : m;
-    if (m == ~0ull) state[c] = ST_OUT;
-    else if (m == prio((int)c, level)) state[c] = ST_ROOT;
-    else left = 1;
+  for (int e = 0; e < OWN; ++e) {
+    const int p = wv + e * NW;
+    bool in;
+    const int c = row(y0 + p % MY, z0 + p / MY, in) + xc;
+    own[e] = st[c];
+    msk[e] = smask[c];
+    if (!(in && xown)) own[e] = ST_ISO;
+    any = any || own[e] == ST_UND;
   }
+  auto store_own = [&]() {
+#pragma unroll
+    for (int e = 0; e < OWN; ++e) {
+      const int p = wv + e * NW;
+      bool in;
+      const int c = row(y0 + p % MY, z0 + p / MY, in) + xc;
+      if (in && xown) so[c] = own[e];
+    }
+  };
+  if (!__syncthreads_or(any)) {
+    store_own();
+    return;
+  }
+  constexpr int KR = KY * KZ / NW;                                // 12 rows of keys per wave
+  uint8_t v[KR];
+#pragma unroll
+  for (int e = 0; e < KR; ++e) {
+    const int p = wv + e * NW;
+    bool in;
+    v[e] = st[row(y0 - 2 + p % KY, z0 - 2 + p / KY, in) + xc];
+  }
+#pragma unroll
+  for (int e = 0; e < KR; ++e) {
+    const int p = wv + e * NW;
+    bool in;
+    const int c = row(y0 - 2 + p % KY, z0 - 2 + p / KY, in) + xc;
+    const uint32_t h = fmix32((uint32_t)c + 0x9e3779b9u);         // prio(c, 0) without the index
+    const uint32_t k = v[e] == ST_ROOT ? ~0u : (v[e] == ST_UND ? h : 0u);
+    key[p][lane] = in && xin ? k : 0u;
+  }
+  // the maximum over a cell and its strong neighbours: the others' keys are
+  // masked to 0, and the lanes at the ends (whose results are not used) read
+  // their own
+  const int lm = max(lane - 1, 0), lp = min(lane + 1, 63);
+  auto vmax = [&](const uint32_t (*a)[64], int p, int sy, uint32_t sm) {
+    auto bit = [&](int sl) { return (uint32_t)(((int32_t)(sm << (31 - sl))) >> 31); };
+    uint32_t m = a[p][lane];
+    m = max(m, max(a[p - sy][lane] & bit(0), a[p - 1][lane] & bit(1)));
+    m = max(m, max(a[p][lm] & bit(2), a[p][lp] & bit(4)));
+    return max(m, max(a[p + 1][lane] & bit(5), a[p + sy][lane] & bit(6)));
+  };
+  constexpr int HR = (HY * HZ + NW - 1) / NW;                     // 8 rows of m1 per wave
+  uint8_t sm[HR];
+#pragma unroll
+  for (int e = 0; e < HR; ++e) {
+    const int p = min(wv + e * NW, HY * HZ - 1);
+    bool in;
+    sm[e] = smask[row(y0 - 1 + p % HY, z0 - 1 + p / HY, in) + xc];
+    if (!(in && xin)) sm[e] = 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < HR; ++e) {
+    const int p = wv + e * NW;
+    if (p < HY * HZ) m1[p][lane] = vmax(key, (p / HY + 1) * KY + p % HY + 1, KY, sm[e]);
+  }
+  __syncthreads();
+  bool left = false;
+#pragma unroll
+  for (int e = 0; e < OWN; ++e) {
+    const int p = wv + e * NW;
+    const uint32_t m = vmax(m1, (p / MY + 1) * HY + p % MY + 1, HY, msk[e]);
+    const uint32_t me = key[(p / MY + 2) * KY + p % MY + 2][lane];
+    if (own[e] != ST_UND) continue;
+    if (m == ~0u) own[e] = ST_OUT;
+    else if (m == me) own[e] = ST_ROOT;
+    else left = true;
+  }
+  store_own();
   // one plain store per block that still has undecided vertices
-  if (__syncthreads_or(left) && threadIdx.x == 0) *undecided = 1;
+  if (__syncthreads_or(left) && threadIdx.x == 0) *und = 1;
 }
 
 // (z, nz as in k_agg1)
@@ -1549,7 +1644,10 @@ static rs_status level_alloc_work(amg_level *L, int prec, int64_t guard, bool cs
   // by the second stage; zero guard planes make those reads in-bounds
   RS_TRY(L->x.alloc(es * (L->n + 1 + 2 * guard)));
   L->xoff = guard;
-  if (guard) RS_HIP(hipMemsetAsync(L->x.p, 0, es * (L->n + 1 + 2 * guard), s));
+  if (guard) {
+    RS_TRY(rs_fill32(L->x.p, 0, (int64_t)(es / 4) * guard, s));
+    RS_TRY(rs_fill32((char *)L->x.p + es * (guard + L->n), 0, (int64_t)(es / 4) * (guard + 1), s));
+  }
   RS_TRY(L->r.alloc(es * (L->n + 1)));
   // a coarse level's l1 diagonal and FP32 values come with its Galerkin copy
   if (!L->dl1.p) RS_TRY(L->dl1.alloc(es * (L->n + 1)));
@@ -1577,12 +1675,50 @@ static rs_status level0_as_coarsest(rs_cpr_s *M, hipStream_t s) {
 // Build the whole hierarchy; M->lev[0] must hold n and nnz.  The fine level
 // is set up by the structured kernels from the pressure entries by slot; its
 // CSR arrays are built only when it is also the coarsest level (or when it is
-// inspected).
-rs_status rs_amg_build(rs_cpr_s *M, hipStream_t s) {
+// inspected).  The host reads back a few words behind each batch of MIS rounds
+// (are any left, the number of roots, the error flag, the entries of the level
+// just built) and once at the end (rs_amg_finish); the temporaries of all
+// levels stay in M->setup until then, because pool memory that is given back
+// may go to work on another stream at once.
+enum {
+  W_FLAG = 0,          // aggregation error
+  W_NNZ,               // entries of the coarse level built last
+  W_NC,                // roots of the level
+  W_LU,                // singular coarsest matrix
+  W_AUX,               // a total of the smoothed product
+  W_SM,                // the second stage's set-up flags (rs_cpr_setup)
+  W_UND = 8,           // two batches' round flags
+  W_TOTAL = W_UND + 2 * MIS_BATCH
+};
+static_assert(W_TOTAL <= RS_READ_WORDS, "one read");
+
+int *rs_amg_word_sm(amg_setup *U) { return U->words.as<int>() + W_SM; }
+
+rs_status rs_amg_begin(amg_setup *U, hipStream_t s) {
+  RS_TRY(U->words.alloc(sizeof(int) * W_TOTAL));
+  return rs_fill32(U->words.p, 0, W_TOTAL, s);
+}
+
+// What the build left on the device; *sm: the second stage's flags, *err: a
+// sweep kernel's error word.  Waits for the stream.
+rs_status rs_amg_finish(rs_cpr_s *M, amg_setup *U, int *sm, hipStream_t s) {
+  int h[W_TOTAL], err = 0;
+  const int *ew[2];
+  rs_sweep_errors(M, ew);
+  RS_TRY(rs_wait_read_err(h, U->words.p, sizeof(h), ew, &err, s));
+  if (h[W_FLAG] || err) return RS_E_HIP;
+  if (h[W_LU]) return RS_E_SINGULAR;
+  if (U->counted) M->lev.back()->nnz = h[W_NNZ];
+  *sm = h[W_SM];
+  return RS_OK;
+}
+
+rs_status rs_amg_build(rs_cpr_s *M, amg_setup *U, hipStream_t s) {
   const rs_cpr_opts &o = M->o;
   int prec = M->prec;
-  dbuf flag;                            // [0] error flag, [1] coarse nnz of the level
-  RS_TRY(flag.alloc(sizeof(int) * 2));
+  int *W = U->words.as<int>();
+  int batch = 0;
+  U->counted = false;                   // the last level's nnz is still on the device
   for (int l = 0;; ++l) {
     amg_level *L = M->lev[l];
     int n = L->n;
@@ -1603,7 +1739,9 @@ rs_status rs_amg_build(rs_cpr_s *M, hipStream_t s) {
     RS_TRY(L->agg.alloc(sizeof(int32_t) * (n + 1)));
     const grid3 &g = M->A->g;
     const double *ap7 = M->D->ap7.as<double>();
-    dbuf dir;
+    U->tmp.emplace_back(new amg_tmp());
+    amg_tmp &T = *U->tmp.back();
+    dbuf &dir = T.dir;
     if (st7) {
       RS_TRY(dir.alloc(n));
       if (prec == 64)
@@ -1618,14 +1756,19 @@ rs_status rs_amg_build(rs_cpr_s *M, hipStream_t s) {
       if (prec == 32) k_cast_f32<<<rs_grid(L->nnz), RS_BLOCK, 0, s>>>(L->nnz, L->a.as<double>(), L->ap.as<float>());
     }
     RS_HIP(hipGetLastError());
-    RS_HIP(hipMemsetAsync(L->agg.p, 0xff, sizeof(int32_t) * (n + 1), s));
-    if (last) break;
-    // strength: per CSR entry, or a 7-bit mask per cell on the fine level
-    dbuf strong, state, m1, und;
+    auto no_aggregates = [&]() { return rs_fill32(L->agg.p, 0xffffffffu, n, s); };
+    if (last) {
+      RS_TRY(no_aggregates());
+      break;
+    }
+    // strength: per CSR entry (L->nnz, until it is read the bound that the
+    // level's arrays have), or a 7-bit mask per cell on the fine level
+    dbuf &strong = T.strong, &state = T.state, &state2 = T.state2, &m1 = T.m1, &id = T.id, &agg1 = T.agg1;
     if (!st7) RS_TRY(dir.alloc(L->nnz));
     RS_TRY(strong.alloc(st7 ? n : L->nnz)); RS_TRY(state.alloc(n));
-    RS_TRY(m1.alloc(sizeof(uint64_t) * n));
-    RS_TRY(und.alloc(sizeof(int) * MIS_BATCH));
+    if (st7) RS_TRY(state2.alloc(n));
+    else RS_TRY(m1.alloc(sizeof(uint64_t) * n));
+    RS_TRY(id.alloc(sizeof(int32_t) * n)); RS_TRY(agg1.alloc(sizeof(int32_t) * n));
     const int32_t *rp = L->rp.as<int32_t>(), *ci = L->ci.as<int32_t>();
     if (st7) {
       k_strength7_sym<<<rs_grid(n), RS_BLOCK, 0, s>>>(g.nx, g.ny, g.nz, dir.as<uint8_t>(), strong.as<uint8_t>(),
@@ -1635,61 +1778,69 @@ rs_status rs_amg_build(rs_cpr_s *M, hipStream_t s) {
       k_strength_sym<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, rp, ci, dir.as<uint8_t>(), strong.as<uint8_t>(), state.as<uint8_t>());
     }
     RS_HIP(hipGetLastError());
-    // distance-2 MIS rounds, MIS_BATCH per host read; und[b] = 1 when round b
-    // of the batch left undecided vertices
-    for (int round = 0;; round += MIS_BATCH) {
+    // distance-2 MIS rounds, MIS_BATCH (an even number) per host read, and the
+    // scan that numbers the roots, which does nothing while the batch's last
+    // round left undecided vertices.  Two batches' flags alternate: a batch's
+    // first round zeroes the next one's.
+    int nc = 0;
+    for (int round = 0;; round += MIS_BATCH, ++batch) {
       if (round > n + 2) return RS_E_HIP;     // progress is guaranteed; guard anyway
+      int *und = W + W_UND + (batch & 1) * MIS_BATCH, *next = W + W_UND + (~batch & 1) * MIS_BATCH;
       for (int b = 0; b < MIS_BATCH; ++b) {
-        const int *prev = b ? und.as<int>() + b - 1 : nullptr;
-        int *und0 = b ? nullptr : und.as<int>();    // zeroed by the batch's first pass
+        const int *prev = b ? und + b - 1 : nullptr;
+        int *und0 = b ? nullptr : next;
         if (st7) {
-          k_mis7_m1<<<rs_grid(n), RS_BLOCK, 0, s>>>(g.nx, g.ny, g.nz, l, strong.as<uint8_t>(), state.as<uint8_t>(),
-                                                    m1.as<uint64_t>(), prev, und0);
-          k_mis7_m2d<<<rs_grid(n), RS_BLOCK, 0, s>>>(g.nx, g.ny, g.nz, l, strong.as<uint8_t>(), m1.as<uint64_t>(),
-                                                     state.as<uint8_t>(), und.as<int>() + b, prev);
+          const unsigned tiles = (unsigned)(((g.nx + MX - 1) / MX) * ((g.ny + MY - 1) / MY)) * ((g.nz + MZ - 1) / MZ);
+          uint8_t *a = state.as<uint8_t>(), *a2 = state2.as<uint8_t>();
+          k_mis7_round<<<tiles, MIS_T, 0, s>>>(g.nx, g.ny, g.nz, strong.as<uint8_t>(), b & 1 ? a2 : a, b & 1 ? a : a2,
+                                               und + b, und0);
         } else {
           k_mis_m1<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, l, rp, ci, strong.as<uint8_t>(), state.as<uint8_t>(),
                                                    m1.as<uint64_t>(), prev, und0);
           k_mis_m2d<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, l, rp, ci, strong.as<uint8_t>(), m1.as<uint64_t>(),
-                                                    state.as<uint8_t>(), und.as<int>() + b, prev);
+                                                    state.as<uint8_t>(), und + b, prev);
         }
       }
-      RS_HIP(hipGetLastError());
-      int h = 0;
-      RS_TRY(rs_wait_read(&h, und.as<int>() + MIS_BATCH - 1, sizeof(int), s));
-      if (h == 0) break;
+      RS_TRY(scan_i32(scan_roots{state.as<uint8_t>()}, id.as<int32_t>(), n, T.bs, und + MIS_BATCH - 1, W + W_NC, nullptr, s));
+      int h[W_TOTAL];
+      RS_TRY(rs_wait_read(h, W, sizeof(h), s));
+      if (h[W_FLAG]) return RS_E_HIP;
+      if (U->counted) { L->nnz = h[W_NNZ]; U->counted = false; }
+      if (h[W_UND + (batch & 1) * MIS_BATCH + MIS_BATCH - 1] == 0) { nc = h[W_NC]; ++batch; break; }
     }
-    // aggregates
-    dbuf id, agg1;
-    RS_TRY(id.alloc(sizeof(int32_t) * n)); RS_TRY(agg1.alloc(sizeof(int32_t) * n));
-    k_root_flag<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, state.as<uint8_t>(), id.as<int32_t>(), flag.as<int>());
-    RS_HIP(hipGetLastError());
-    int64_t nc64 = 0;
-    RS_TRY(scan_i32(id.as<int32_t>(), id.as<int32_t>(), n, &nc64, s, nullptr));
-    int nc = (int)nc64;
     if (nc == 0 || nc >= n) {        // no coarsening possible: this level is the coarsest
+      RS_TRY(no_aggregates());
       if (st7) RS_TRY(level0_as_coarsest(M, s));
       break;
     }
     // per coarse row counters (nc + 1 <= n), zeroed by the first aggregation pass
-    dbuf off, skey, sval, cnt;
+    dbuf &off = T.off, &skey = T.skey, &sval = T.sval, &cnt = T.cnt;
     RS_TRY(cnt.alloc(sizeof(int32_t) * ((size_t)nc + 1)));
     if (st7) {
       k_agg1_7<<<rs_grid(n), RS_BLOCK, 0, s>>>(g.nx, g.ny, g.nz, strong.as<uint8_t>(), state.as<uint8_t>(),
                                                id.as<int32_t>(), agg1.as<int32_t>(), cnt.as<int32_t>(), nc + 1);
       k_agg2_7<<<rs_grid(n), RS_BLOCK, 0, s>>>(g.nx, g.ny, g.nz, strong.as<uint8_t>(), ap7, state.as<uint8_t>(),
-                                               agg1.as<int32_t>(), L->agg.as<int32_t>(), flag.as<int>());
+                                               agg1.as<int32_t>(), L->agg.as<int32_t>(), W + W_FLAG);
     } else {
       k_agg1<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, rp, ci, strong.as<uint8_t>(), state.as<uint8_t>(), id.as<int32_t>(),
                                              agg1.as<int32_t>(), cnt.as<int32_t>(), nc + 1);
       k_agg2<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, rp, ci, strong.as<uint8_t>(), L->a.as<double>(), state.as<uint8_t>(),
-                                             agg1.as<int32_t>(), L->agg.as<int32_t>(), flag.as<int>());
+                                             agg1.as<int32_t>(), L->agg.as<int32_t>(), W + W_FLAG);
     }
     RS_HIP(hipGetLastError());
     L->nc = nc;
-    // temporaries of the smoothed product, kept until the host read at the
-    // end of the level (the RAS set-up allocates on a side stream meanwhile)
-    dbuf rho, apoff, apcnt, apci, apv, tfill, trv, ident;
+    dbuf &rho = T.rho, &apoff = T.apoff, &apcnt = T.apcnt, &apci = T.apci, &apv = T.apv, &tfill = T.tfill, &trv = T.trv,
+         &ident = T.ident;
+    auto scan = [&](dbuf &in, dbuf &out, int64_t m, int32_t *total, int32_t *tail) {
+      return scan_i32(scan_counts{in.as<int32_t>()}, out.as<int32_t>(), m, T.bs, nullptr, total, tail, s);
+    };
+    // a scan's total on the host (negative: more than 2^31)
+    auto read_total = [&](int64_t *t) -> rs_status {
+      int h = 0;
+      RS_TRY(rs_wait_read(&h, W + W_AUX, sizeof(int), s));
+      *t = h;
+      return RS_OK;
+    };
     int64_t ncand = 0;
     if (o.smooth) {
       // smoothed prolongator: on the CSR form (built here for the fine level)
@@ -1698,7 +1849,7 @@ rs_status rs_amg_build(rs_cpr_s *M, hipStream_t s) {
       const double *ca = L->a.as<double>();
       const int64_t pcap = L->nnz + n + 1;
       RS_TRY(rho.alloc(sizeof(unsigned long long)));
-      RS_HIP(hipMemsetAsync(rho.p, 0, sizeof(unsigned long long), s));
+      RS_TRY(rs_fill32(rho.p, 0, 2, s));
       k_sa_rho<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, crp, cci, ca, rho.as<unsigned long long>());
       RS_TRY(L->pcnt.alloc(sizeof(int32_t) * ((size_t)n + 1)));
       RS_TRY(L->pci.alloc(sizeof(int32_t) * pcap));
@@ -1712,7 +1863,8 @@ rs_status rs_amg_build(rs_cpr_s *M, hipStream_t s) {
       k_sa_apcand<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, crp, cci, L->pcnt.as<int32_t>(), apcnt.as<int32_t>());
       RS_HIP(hipGetLastError());
       int64_t apt = 0;
-      RS_TRY(scan_i32(apcnt.as<int32_t>(), apoff.as<int32_t>(), n, &apt, s, nullptr));
+      RS_TRY(scan(apcnt, apoff, n, W + W_AUX, nullptr));
+      RS_TRY(read_total(&apt));
       if (apt < 0) return RS_E_NOMEM;             // more than 2^31 candidates
       RS_TRY(apci.alloc(sizeof(int32_t) * (apt + 1)));
       RS_TRY(apv.alloc(sizeof(double) * (apt + 1)));
@@ -1723,10 +1875,10 @@ rs_status rs_amg_build(rs_cpr_s *M, hipStream_t s) {
       // P^T: fine rows of each coarse column, ascending
       RS_TRY(L->tptr.alloc(sizeof(int32_t) * ((size_t)nc + 1)));
       RS_TRY(tfill.alloc(sizeof(int32_t) * ((size_t)nc + 1)));
-      RS_HIP(hipMemsetAsync(tfill.p, 0, sizeof(int32_t) * (nc + 1), s));
+      RS_TRY(rs_fill32(tfill.p, 0, (int64_t)nc + 1, s));
       k_sa_tcount<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, crp, L->pcnt.as<int32_t>(), L->pci.as<int32_t>(), cnt.as<int32_t>());
       RS_HIP(hipGetLastError());
-      RS_TRY(scan_i32(cnt.as<int32_t>(), L->tptr.as<int32_t>(), nc + 1, nullptr, s, nullptr));
+      RS_TRY(scan(cnt, L->tptr, (int64_t)nc + 1, nullptr, nullptr));
       RS_TRY(L->tri.alloc(sizeof(int32_t) * pcap));
       RS_TRY(trv.alloc(sizeof(double) * pcap));
       k_sa_tfill<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, crp, L->pcnt.as<int32_t>(), L->pci.as<int32_t>(), L->pv.as<double>(),
@@ -1741,7 +1893,8 @@ rs_status rs_amg_build(rs_cpr_s *M, hipStream_t s) {
       k_sa_ccand<<<rs_grid(nc), RS_BLOCK, 0, s>>>(nc, L->tptr.as<int32_t>(), L->tri.as<int32_t>(), apcnt.as<int32_t>(),
                                                   cnt.as<int32_t>());
       RS_HIP(hipGetLastError());
-      RS_TRY(scan_i32(cnt.as<int32_t>(), off.as<int32_t>(), nc, &ncand, s, nullptr));
+      RS_TRY(scan(cnt, off, nc, W + W_AUX, nullptr));
+      RS_TRY(read_total(&ncand));
       if (ncand < 0) return RS_E_NOMEM;
       RS_TRY(skey.alloc(sizeof(int32_t) * (ncand + 1)));
       RS_TRY(sval.alloc(sizeof(double) * (ncand + 1)));
@@ -1773,7 +1926,7 @@ rs_status rs_amg_build(rs_cpr_s *M, hipStream_t s) {
                                                       nc + 1);
       RS_HIP(hipGetLastError());
       // members: at most n (no host read of the exact count)
-      RS_TRY(scan_i32(cnt.as<int32_t>(), L->mptr.as<int32_t>(), nc + 1, nullptr, s, nullptr));
+      RS_TRY(scan(cnt, L->mptr, (int64_t)nc + 1, nullptr, nullptr));
       RS_TRY(L->mem.alloc(sizeof(int32_t) * ((size_t)n + 1)));
       k_fill_members<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, L->agg.as<int32_t>(), L->mptr.as<int32_t>(), tfill.as<int32_t>(),
                                                      L->mem.as<int32_t>());
@@ -1785,7 +1938,7 @@ rs_status rs_amg_build(rs_cpr_s *M, hipStream_t s) {
       else k_cand<<<rs_grid(nc), RS_BLOCK, 0, s>>>(nc, L->mptr.as<int32_t>(), L->mem.as<int32_t>(), rp, cnt.as<int32_t>());
       RS_HIP(hipGetLastError());
       // candidates: the members' row entries, at most this level's nnz
-      RS_TRY(scan_i32(cnt.as<int32_t>(), off.as<int32_t>(), nc, nullptr, s, nullptr));
+      RS_TRY(scan(cnt, off, nc, nullptr, nullptr));
       ncand = L->nnz;
       RS_TRY(skey.alloc(sizeof(int32_t) * (ncand + 1)));
       RS_TRY(sval.alloc(sizeof(double) * (ncand + 1)));
@@ -1803,10 +1956,11 @@ rs_status rs_amg_build(rs_cpr_s *M, hipStream_t s) {
     M->lev.push_back(C);
     C->n = nc;
     RS_TRY(C->rp.alloc(sizeof(int32_t) * (nc + 1)));
-    // coarse nnz: on the device for rp[nc], read with the error flag below;
-    // ci and a sized by the candidate bound
-    RS_TRY(scan_i32(cnt.as<int32_t>(), C->rp.as<int32_t>(), nc, nullptr, s, flag.as<int32_t>() + 1));
-    k_set_last<<<1, 1, 0, s>>>(C->rp.as<int32_t>(), nc, flag.as<int32_t>() + 1);
+    // coarse nnz: to rp[nc] and W_NNZ on the device, read behind the next
+    // level's first rounds; until then, and for the size of ci and a, the bound
+    RS_TRY(scan(cnt, C->rp, nc, W + W_NNZ, C->rp.as<int32_t>() + nc));
+    C->nnz = ncand;
+    U->counted = true;
     RS_TRY(C->ci.alloc(sizeof(int32_t) * (ncand + 1)));
     RS_TRY(C->a.alloc(sizeof(double) * (ncand + 1)));
     RS_TRY(C->dl1.alloc((prec == 64 ? sizeof(double) : sizeof(float)) * ((size_t)nc + 1)));
@@ -1820,10 +1974,6 @@ rs_status rs_amg_build(rs_cpr_s *M, hipStream_t s) {
                                                               sval.as<double>(), C->rp.as<int32_t>(), C->ci.as<int32_t>(),
                                                               C->a.as<double>(), C->ap.as<float>(), C->dl1.as<float>());
     RS_HIP(hipGetLastError());
-    int h[2] = {0, 0};
-    RS_TRY(rs_wait_read(h, flag.p, sizeof(int) * 2, s));
-    if (h[0]) return RS_E_HIP;
-    C->nnz = h[1];
   }
   M->nlev = (int)M->lev.size();
   // coarsest level
@@ -1831,20 +1981,13 @@ rs_status rs_amg_build(rs_cpr_s *M, hipStream_t s) {
   int nC = C->n;
   M->coarse_lu = nC <= o.lu_max;
   if (M->coarse_lu) {
-    dbuf G;
-    RS_TRY(G.alloc(sizeof(double) * 2 * (size_t)nC * nC + 8));
+    RS_TRY(U->G.alloc(sizeof(double) * 2 * (size_t)nC * nC + 8));
     RS_TRY(M->cinv.alloc(sizeof(double) * (size_t)nC * nC + 8));
     RS_TRY(M->cb.alloc(sizeof(double) * (nC + 1)));
     RS_TRY(M->cx.alloc(sizeof(double) * (nC + 1)));
-    RS_HIP(hipMemsetAsync(flag.p, 0, sizeof(int), s));
-    k_densify<<<rs_grid(nC), RS_BLOCK, 0, s>>>(nC, C->rp.as<int32_t>(), C->ci.as<int32_t>(), C->a.as<double>(), G.as<double>());
-    RS_TRY(dense_inverse_run(nC, G.as<double>(), M->cinv.as<double>(), flag.as<int>(), s));
-    int h = 0;
-    RS_TRY(rs_wait_read(&h, flag.p, sizeof(int), s));
-    if (h) return RS_E_SINGULAR;
-    return RS_OK;                 // the read waited for the stream
+    k_densify<<<rs_grid(nC), RS_BLOCK, 0, s>>>(nC, C->rp.as<int32_t>(), C->ci.as<int32_t>(), C->a.as<double>(), U->G.as<double>());
+    RS_TRY(dense_inverse_run(nC, U->G.as<double>(), M->cinv.as<double>(), W + W_LU, s));
   }
-  RS_TRY(rs_wait(s));
   return RS_OK;
 }
 
@@ -1987,7 +2130,7 @@ extern "C" rs_status rs_dense_inverse(int n, const double *d_a, double *d_inv, v
   dbuf G, flag;
   RS_TRY(G.alloc(sizeof(double) * 2 * (size_t)n * n));
   RS_TRY(flag.alloc(sizeof(int)));
-  RS_HIP(hipMemsetAsync(flag.p, 0, sizeof(int), s));
+  RS_TRY(rs_fill32(flag.p, 0, 1, s));
   k_augment<<<rs_grid(2 * (int64_t)n * n), RS_BLOCK, 0, s>>>(n, d_a, G.as<double>());
   RS_TRY(dense_inverse_run(n, G.as<double>(), d_inv, flag.as<int>(), s));
   int h = 0;

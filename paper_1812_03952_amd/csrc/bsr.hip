@@ -287,7 +287,7 @@ static rs_status load_values(rs_bsr_s *A, const double *d_vals, hipStream_t s) {
   int64_t n = A->g.n;
   dbuf flag;
   RS_TRY(flag.alloc(sizeof(int)));
-  RS_HIP(hipMemsetAsync(flag.p, 0, sizeof(int), s));
+  RS_TRY(rs_fill32(flag.p, 0, 1, s));
   k_to7<<<rs_grid(7 * n * 4), RS_BLOCK, 0, s>>>(n, A->pos7.as<int64_t>(), d_vals, A->a7.as<double>(),
                                                   flag.as<int>());
   RS_HIP(hipGetLastError());
@@ -321,13 +321,12 @@ extern "C" rs_status rs_bsr_create(int nx, int ny, int nz, int bs, int64_t nnzb,
     }
     dbuf flag;
     if ((st = flag.alloc(sizeof(int))) != RS_OK) break;
-    if (hipMemsetAsync(flag.p, 0, sizeof(int), s) != hipSuccess) { st = RS_E_HIP; break; }
+    if ((st = rs_fill32(flag.p, 0, 1, s)) != RS_OK) break;
     k_validate<<<rs_grid(n), RS_BLOCK, 0, s>>>(nx, ny, nz, nnzb, A->rp.as<int32_t>(), A->ci.as<int32_t>(),
                                                A->pos7.as<int64_t>(), flag.as<int>());
     int h = 0;
     if (hipGetLastError() != hipSuccess ||
-        hipMemcpyAsync(&h, flag.p, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess) { st = RS_E_HIP; break; }
+        rs_wait_read(&h, flag.p, sizeof(int), s) != RS_OK) { st = RS_E_HIP; break; }
     if (h) { st = RS_E_ARG; break; }
     st = load_values(A, d_vals, s);
   } while (0);

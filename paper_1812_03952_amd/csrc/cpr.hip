@@ -196,7 +196,10 @@ __global__ void k_vec_to_f64(int64_t m, const T *__restrict__ a, double *__restr
 }  // namespace
 
 rs_status rs_amg_level0(rs_cpr_s *M, hipStream_t s);
-rs_status rs_amg_build(rs_cpr_s *M, hipStream_t s);
+rs_status rs_amg_begin(amg_setup *U, hipStream_t s);
+rs_status rs_amg_build(rs_cpr_s *M, amg_setup *U, hipStream_t s);
+rs_status rs_amg_finish(rs_cpr_s *M, amg_setup *U, int *sm, hipStream_t s);
+int *rs_amg_word_sm(amg_setup *U);
 
 extern "C" void rs_cpr_opts_default(rs_cpr_opts *o) {
   if (!o) return;
@@ -262,7 +265,8 @@ extern "C" rs_status rs_cpr_setup(rs_bsr A, rs_dcpl D, const rs_cpr_opts *o, voi
   int64_t n = A->g.n;
   size_t es = M->prec == 64 ? sizeof(double) : sizeof(float);
   rs_status st = RS_OK;
-  dbuf flag;
+  amg_setup U;                                  // released with both streams idle
+  int *flag = nullptr;                          // the second stage's error word
   bool launched = false;
   do {
     if ((st = M->dinv2.alloc(es * 16 * n)) != RS_OK) break;
@@ -276,24 +280,24 @@ extern "C" rs_status rs_cpr_setup(rs_bsr A, rs_dcpl D, const rs_cpr_opts *o, voi
       if (M->prec == 64) k_fill0<double><<<rs_grid(nz0), RS_BLOCK, 0, s>>>(nz0, M->fzero.as<double>());
       else k_fill0<float><<<rs_grid(nz0), RS_BLOCK, 0, s>>>(nz0, M->fzero.as<float>());
     }
-    if ((st = flag.alloc(sizeof(int))) != RS_OK) break;
-    if (hipMemsetAsync(flag.p, 0, sizeof(int), s) != hipSuccess) { st = RS_E_HIP; break; }
+    if ((st = rs_amg_begin(&U, s)) != RS_OK) break;
+    flag = rs_amg_word_sm(&U);
     if (split) {
       if (hipEventRecord(ev, s) != hipSuccess || hipStreamWaitEvent(ss, ev, 0) != hipSuccess) { st = RS_E_HIP; break; }
     }
     launched = true;
     if (opts.smoother == RS_SM_BJ) {
-      if (M->prec == 64) k_bj_setup<double><<<rs_grid(n), RS_BLOCK, 0, ss>>>(n, D->t7.as<double>(), M->dinv2.as<double>(), flag.as<int>());
-      else k_bj_setup<float><<<rs_grid(n), RS_BLOCK, 0, ss>>>(n, D->t7.as<float>(), M->dinv2.as<float>(), flag.as<int>());
+      if (M->prec == 64) k_bj_setup<double><<<rs_grid(n), RS_BLOCK, 0, ss>>>(n, D->t7.as<double>(), M->dinv2.as<double>(), flag);
+      else k_bj_setup<float><<<rs_grid(n), RS_BLOCK, 0, ss>>>(n, D->t7.as<float>(), M->dinv2.as<float>(), flag);
       if (hipGetLastError() != hipSuccess) { st = RS_E_HIP; break; }
     } else if (ras) {
-      if ((st = rs_ras_setup_run(M, flag.as<int>(), ss)) != RS_OK) break;
+      if ((st = rs_ras_setup_run(M, flag, ss)) != RS_OK) break;
     } else {
       if ((st = rs_dilu_prepare(M, ss)) != RS_OK) break;
-      if ((st = rs_dilu_setup_run(M, flag.as<int>(), ss)) != RS_OK) break;
+      if ((st = rs_dilu_setup_run(M, flag, ss)) != RS_OK) break;
     }
     if ((st = rs_amg_level0(M, s)) != RS_OK) break;
-    if ((st = rs_amg_build(M, s)) != RS_OK) break;
+    if ((st = rs_amg_build(M, &U, s)) != RS_OK) break;
   } while (0);
   if (split && launched) {
     // join: the caller's stream waits for the side stream; the read of the
@@ -304,12 +308,12 @@ extern "C" rs_status rs_cpr_setup(rs_bsr A, rs_dcpl D, const rs_cpr_opts *o, voi
     }
   }
   if (st == RS_OK) {
-    int h = 0;
-    if (hipGetLastError() != hipSuccess || rs_wait_read(&h, flag.p, sizeof(int), s) != RS_OK) st = RS_E_HIP;
-    else if (h & RSF_NONFINITE) st = RS_E_NONFINITE;
-    else if (h & RSF_SINGULAR) st = RS_E_SINGULAR;
-    else if (opts.smoother == RS_SM_DILU) st = rs_dilu_check(M, s);   // its set-up's bounded waits
-  } else {
+    int h = 0;                                  // and the DILU set-up's bounded waits
+    st = hipGetLastError() != hipSuccess ? RS_E_HIP : rs_amg_finish(M, &U, &h, s);
+    if (st == RS_OK && (h & RSF_NONFINITE)) st = RS_E_NONFINITE;
+    else if (st == RS_OK && (h & RSF_SINGULAR)) st = RS_E_SINGULAR;
+  }
+  if (st != RS_OK) {
     (void)hipStreamSynchronize(s);
     if (split && launched) (void)hipStreamSynchronize(ss);
   }

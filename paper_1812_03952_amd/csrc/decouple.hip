@@ -399,7 +399,7 @@ static rs_status decouple_impl(rs_bsr_s *A, const double *vals, bool attach, int
     if ((st = D->col0.alloc(es * 32 * n)) != RS_OK) break;
     dbuf flag;
     if ((st = flag.alloc(sizeof(int))) != RS_OK) break;
-    if (hipMemsetAsync(flag.p, 0, sizeof(int), s) != hipSuccess) { st = RS_E_HIP; break; }
+    if ((st = rs_fill32(flag.p, 0, 1, s)) != RS_OK) break;
     const grid3 &g = A->g;
     if (vals && attach) A->ref = vals;
     if (vals && !attach) {

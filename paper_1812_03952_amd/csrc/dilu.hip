@@ -882,12 +882,12 @@ template rs_status rs_dilu_apply_run<float>(rs_cpr_s *, const float *, float *, 
 // error words of the pipelined sweeps (DILU bricks, RAS strips): a bounded
 // wait that timed out leaves a non-zero word
 rs_status rs_dilu_check(rs_cpr_s *M, hipStream_t s) {
-  int h[2] = {0, 0};
   const int *w[2];
   rs_sweep_errors(M, w);
-  for (int k = 0; k < 2; ++k)
-    if (w[k]) RS_TRY(rs_wait_read(&h[k], w[k], sizeof(int), s));
-  return (h[0] || h[1]) ? RS_E_HIP : RS_OK;
+  if (!w[0] && !w[1]) return RS_OK;
+  int h = 0, e = 0;
+  RS_TRY(rs_wait_read_err(&h, w[0] ? w[0] : w[1], sizeof(int), w, &e, s));
+  return e ? RS_E_HIP : RS_OK;
 }
 
 void rs_sweep_errors(const rs_cpr_s *M, const int *(&w)[2]) {

@@ -113,53 +113,50 @@ extern "C" void rs_pool_usage(size_t *live_bytes, size_t *cached_bytes) {
 // The set-up reads a few counts and flags back (an aggregate count, an error
 // word) and waits for the stream at each.  A blocking stream synchronisation
 // leaves the device idle for tens of microseconds after such a read while the
-// host thread wakes up; these waits poll an event instead.  Each host thread
-// keeps one event per device and a small pinned buffer: a staging area and a
-// post slot.  The buffer of a thread that ends goes to the next new one (never
+// host thread wakes up; these waits poll an event, or a slot of pinned memory
+// that the device stores into (9 us from the launch to the host; a copy and an
+// event take 15).  Each host thread
+// keeps one event per device and a pinned post slot.  The slot of a thread that ends goes to the next new one (never
 // freed: no HIP calls at exit), so there are as many as threads at one time.
 namespace {
 constexpr int WAIT_MAX_DEV = 64;
-constexpr size_t WAIT_STAGE = 256;
-struct stage_list {
+#include "reduce.h"
+struct slot_list {
   std::mutex mu;
-  std::vector<void *> free;
+  std::vector<rs_post *> free;
 };
-stage_list &stages() {
-  static stage_list *l = new stage_list();
+slot_list &slots() {
+  static slot_list *l = new slot_list();
   return *l;
 }
 struct host_wait {
   hipEvent_t ev[WAIT_MAX_DEV] = {};
-  void *stage = nullptr;
+  rs_post *post = nullptr;
   ~host_wait() {
-    if (!stage) return;
-    std::lock_guard<std::mutex> lk(stages().mu);
-    stages().free.push_back(stage);
+    if (!post) return;
+    std::lock_guard<std::mutex> lk(slots().mu);
+    slots().free.push_back(post);
   }
 };
 thread_local host_wait tw;
 
-rs_status get_stage() {
-  if (tw.stage) return RS_OK;
-  {
-    std::lock_guard<std::mutex> lk(stages().mu);
-    if (!stages().free.empty()) {
-      tw.stage = stages().free.back();
-      stages().free.pop_back();
-      return RS_OK;
-    }
-  }
-  void *p = nullptr;
-  RS_HIP(hipHostMalloc(&p, WAIT_STAGE + sizeof(rs_post), hipHostMallocPortable));
-  memset(p, 0, WAIT_STAGE + sizeof(rs_post));
-  tw.stage = p;
-  return RS_OK;
-}
 }  // namespace
 
-rs_status rs_post_slot(rs_post **p) {
-  RS_TRY(get_stage());
-  *p = (rs_post *)((char *)tw.stage + WAIT_STAGE);
+rs_status rs_post_slot(rs_post **out) {
+  if (!tw.post) {
+    std::lock_guard<std::mutex> lk(slots().mu);
+    if (!slots().free.empty()) {
+      tw.post = slots().free.back();
+      slots().free.pop_back();
+    }
+  }
+  if (!tw.post) {
+    void *p = nullptr;
+    RS_HIP(hipHostMalloc(&p, sizeof(rs_post), hipHostMallocPortable));
+    memset(p, 0, sizeof(rs_post));
+    tw.post = (rs_post *)p;
+  }
+  *out = tw.post;
   return RS_OK;
 }
 
@@ -191,15 +188,47 @@ rs_status rs_wait(hipStream_t s) {
   }
 }
 
+// the words and, after them, whether an error word is set, into the post's values
+__global__ void k_post_words(const uint32_t *__restrict__ d, int nw, const int *__restrict__ err0,
+                             const int *__restrict__ err1, rs_post *__restrict__ post, uint64_t seq) {
+  const int t = threadIdx.x;
+  uint32_t *o = (uint32_t *)post->v;
+  if (t < nw) __hip_atomic_store(o + t, d[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (t == 0)
+    __hip_atomic_store(o + RS_READ_WORDS, ((err0 && *err0) || (err1 && *err1)) ? 1u : 0u, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+  stores_done();
+  if (t == 0) __hip_atomic_store(&post->seq, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+rs_status rs_wait_read_err(void *h, const void *d, size_t bytes, const int *const (&errw)[2], int *err,
+                           hipStream_t s) {
+  if (bytes > sizeof(uint32_t) * RS_READ_WORDS || bytes % 4) return RS_E_ARG;
+  rs_post *post = nullptr;
+  RS_TRY(rs_post_slot(&post));
+  const uint64_t seq = rs_post_next(post);
+  k_post_words<<<1, 64, 0, s>>>((const uint32_t *)d, (int)(bytes / 4), errw[0], errw[1], post, seq);
+  RS_HIP(hipGetLastError());
+  RS_TRY(rs_wait_post(post, seq, s));
+  memcpy(h, post->v, bytes);
+  *err = (int)((const uint32_t *)post->v)[RS_READ_WORDS];
+  return RS_OK;
+}
+
 rs_status rs_wait_read(void *h, const void *d, size_t bytes, hipStream_t s) {
-  if (bytes > WAIT_STAGE) {
-    RS_HIP(hipMemcpyAsync(h, d, bytes, hipMemcpyDeviceToHost, s));
-    RS_HIP(hipStreamSynchronize(s));
-    return RS_OK;
-  }
-  RS_TRY(get_stage());
-  RS_HIP(hipMemcpyAsync(tw.stage, d, bytes, hipMemcpyDeviceToHost, s));
-  RS_TRY(rs_wait(s));
-  memcpy(h, tw.stage, bytes);
+  const int *const none[2] = {nullptr, nullptr};
+  int e = 0;
+  return rs_wait_read_err(h, d, bytes, none, &e, s);
+}
+
+__global__ void k_fill32(int64_t m, uint32_t v, uint32_t *__restrict__ a) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < m) a[t] = v;
+}
+
+rs_status rs_fill32(void *a, uint32_t v, int64_t m, hipStream_t s) {
+  if (m < 1) return RS_OK;
+  k_fill32<<<rs_grid(m), RS_BLOCK, 0, s>>>(m, v, (uint32_t *)a);
+  RS_HIP(hipGetLastError());
   return RS_OK;
 }

@@ -1174,8 +1174,8 @@ rs_status rs_ras_setup_run(rs_cpr_s *M, int *flag, hipStream_t s) {
     const size_t words = (size_t)g.nz * S * g.nx * 4 * (M->prec == 64 ? 2 : 1);
     RS_TRY(M->rxw.alloc(sizeof(uint64_t) * words));
     RS_TRY(M->rctl.alloc(sizeof(int) * 4));
-    RS_HIP(hipMemsetAsync(M->rxw.p, 0, sizeof(uint64_t) * words, s));
-    RS_HIP(hipMemsetAsync(M->rctl.p, 0, sizeof(int) * 4, s));
+    RS_TRY(rs_fill32(M->rxw.p, 0, 2 * (int64_t)words, s));
+    RS_TRY(rs_fill32(M->rctl.p, 0, 4, s));
     M->repoch = 0;
   }
   auto run = [&](auto tag) -> rs_status {

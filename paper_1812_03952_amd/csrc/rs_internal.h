@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <memory>
 #include <vector>
 #include "../../include/rsolve.h"
 
@@ -25,10 +26,15 @@ static inline hipStream_t rs_stream(void *s) { return (hipStream_t)s; }
 // cached and reused by later requests of a similar size.
 void *rs_pool_get(size_t bytes, size_t *got);   // nullptr when out of memory
 void rs_pool_put(void *p, size_t bytes);
-// Wait for the work queued on s (rs_wait), or copy bytes (at most 256) from
-// device memory to h and wait for them (rs_wait_read), polling an event.
+// Wait for the work queued on s (rs_wait, polling an event), or read a few
+// 32-bit words of device memory behind that work (rs_wait_read; err: as well
+// whether a word of rs_sweep_errors is set).
 rs_status rs_wait(hipStream_t s);
+constexpr int RS_READ_WORDS = 22;
 rs_status rs_wait_read(void *h, const void *d, size_t bytes, hipStream_t s);
+rs_status rs_wait_read_err(void *h, const void *d, size_t bytes, const int *const (&errw)[2], int *err, hipStream_t s);
+// a[0 .. m) = v by a kernel: three times cheaper to queue than hipMemsetAsync
+rs_status rs_fill32(void *a, uint32_t v, int64_t m, hipStream_t s);
 // Pinned host memory that a kernel posts a few values to (post_host of
 // reduce.h), one slot per host thread.  A call that uses it numbers its posts
 // with rs_post_next, waits for each with rs_wait_post before it queues the
@@ -136,6 +142,19 @@ struct amg_level {
   bool sa = false;
   dbuf pcnt, pci, pv, pvt, tptr, tri, trt, z;
   template <class T> T *xp() const { return x.as<T>() + xoff; }
+};
+
+// The AMG set-up's temporaries, held until its work is done: per level the
+// strength, independent set and Galerkin scratch, the dense inverse's matrix,
+// and the words that the host reads.
+struct amg_tmp {
+  dbuf dir, strong, state, state2, m1, id, agg1, bs, off, skey, sval, cnt;
+  dbuf rho, apoff, apcnt, apci, apv, tfill, trv, ident;
+};
+struct amg_setup {
+  dbuf words, G;
+  bool counted = false;
+  std::vector<std::unique_ptr<amg_tmp>> tmp;
 };
 
 struct rs_cpr_s {
