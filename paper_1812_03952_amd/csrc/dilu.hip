@@ -892,5 +892,5 @@ rs_status rs_dilu_check(rs_cpr_s *M, hipStream_t s) {
 
 void rs_sweep_errors(const rs_cpr_s *M, const int *(&w)[2]) {
   w[0] = M->pctl.p ? M->pctl.as<int>() + 1 : nullptr;
-  w[1] = M->rctl.p ? M->rctl.as<int>() + 2 : nullptr;
+  w[1] = M->rctl.p ? M->rctl.as<int>() + 5 : nullptr;
 }

@@ -10,10 +10,10 @@
 // i + j = lambda (nx + ny - 1 levels): the thread group of line j handles
 // cell (lambda - j, j) at level lambda, reads the previous level's values of
 // its own line and of line j-1 (j+1 backward) from LDS, and one barrier
-// separates the levels.  The factorisation and the FP64 sweeps give each
-// layer one workgroup, which never waits on another; the FP32 sweeps split a
-// layer into strips of lines, one workgroup each, that hand the boundary
-// line's values to the next strip level by level (see the strip sweeps).
+// separates the levels.  The factorisation gives each layer one workgroup,
+// which never waits on another; the sweeps split a layer into strips of lines,
+// one workgroup each, that hand the boundary line's values to the next strip
+// level by level.
 // The factorisation uses a quad of lanes per cell in FP64.
 //
 // The sweeps are written with D^{-1} folded in, which is the same operator
@@ -27,12 +27,11 @@
 //
 // Layout: A~ blocks by stencil slot t7[7][n][16] (slots -z -y -x self +x +y
 // +z, zeros off-grid), D^{-1} blocks dinv2[n][16]; scaled blocks
-// blk[4][n][16] (Lh_y, Lh_x, Uh_x, Uh_y) in wavefront order; vectors [n][4];
+// blk[2][n][2][16] (Lh_y, Lh_x; Uh_x, Uh_y) in wavefront order; vectors [n][4];
 // all in the preconditioner's precision.
 #include "rs_internal.h"
 #include <math.h>
 #include <algorithm>
-#include <functional>
 #include <type_traits>
 
 namespace {
@@ -63,8 +62,9 @@ __device__ __forceinline__ int64_t wf_pos(int i, int j, int nx, int ny) {
 // wavefront order, in which the cells of one anti-diagonal of the tile are
 // consecutive in the layer's wavefront order too, and written back as runs
 // of up to min(RI, RJ) cells instead of one scattered cell per quad.
-// tickets (optional): the FP32 sweeps' two ticket counters, zeroed here for
-// the forward and backward sweeps that follow on the stream.
+// tickets: the ticket counters of the sweeps that follow on the stream, zeroed
+// here.
+constexpr int RAS_TICKETS = 5, RAS_CTL = 8;   // one per sweep of an apply; the error word after them
 constexpr int RI = 16, RJ = 16;
 template <class T>
 __global__ __launch_bounds__(4 * RI * RJ) void k_ras_in_tile(int nx, int ny, int64_t n, const T *__restrict__ rt,
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(4 * RI * RJ) void k_ras_in_tile(int nx, int ny, int
                                                              const T *__restrict__ dinv2, T *__restrict__ rh,
                                                              T *__restrict__ xpw, int *__restrict__ tickets) {
   __shared__ T so[RI * RJ][4];
-  if (tickets && blockIdx.x == 0 && threadIdx.x < 2) tickets[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < RAS_TICKETS) tickets[threadIdx.x] = 0;
   __shared__ T sx[RI * RJ];
   __shared__ int sab[RI * RJ];
   const int tx = (nx + RI - 1) / RI, ty = (ny + RJ - 1) / RJ;
@@ -109,8 +109,9 @@ __global__ __launch_bounds__(4 * RI * RJ) void k_ras_in_tile(int nx, int ny, int
 }
 
 // ---- scaled blocks for the sweeps, per (cell, block row) ---------------------
-// blk[b][p] = D_c^{-1} A~_{c, nb(b)} for b = 0..3: -y, -x, +x, +y (slots 1, 2,
-// 4, 5), at the cell's wavefront position p; FP64 products rounded once.
+// blk[b / 2][p][b % 2] = D_c^{-1} A~_{c, nb(b)} for b = 0..3: -y, -x, +x, +y
+// (slots 1, 2, 4, 5), at the cell's wavefront position p: the two blocks that
+// a sweep reads lie side by side; FP64 products rounded once.
 template <class T>
 __global__ __launch_bounds__(256) void k_ras_scale(int nx, int ny, int64_t n, const T *__restrict__ t7,
                                                    const T *__restrict__ dinv2, T *__restrict__ blk) {
@@ -137,37 +138,13 @@ __global__ __launch_bounds__(256) void k_ras_scale(int nx, int ny, int64_t n, co
       o[cc] = (T)v;
     }
 #pragma unroll
-    for (int cc = 0; cc < 4; ++cc) blk[((int64_t)b * n + p) * 16 + 4 * row + cc] = o[cc];
+    for (int cc = 0; cc < 4; ++cc) blk[((b >> 1) * n + p) * 32 + 16 * (b & 1) + 4 * row + cc] = o[cc];
   }
 }
 
-// ---- sweeps ----------------------------------------------------------------
-// A sweep workgroup has 4*LW compute lanes (lines j = q + LW*u, q = lane/4,
-// U passes per level) and one writer wave.  Compute waves only load from
-// global memory and keep the loads of the next P levels in flight in
-// registers; their results go to an LDS ring of two levels.  The writer wave
-// only stores: during level lambda it copies the outputs of level lambda-1
-// from the ring to global memory.  On this architecture one counter tracks
-// both loads and stores of a wave, and with both kinds in flight a wave can
-// only wait for all of them; keeping them in different waves lets a compute
-// wave wait for just the oldest of its prefetched loads.
 template <class T> struct vec4t;
 template <> struct vec4t<float> { typedef float4 type; };
 template <> struct vec4t<double> { typedef double4 type; };
-
-// copy the outputs of level m (lines j with 0 <= m - j < nx) from an LDS ring
-// buffer [ny][4] to out: in wavefront order (WF) or natural order
-template <class T, bool WF>
-__device__ __forceinline__ void ras_write_level(int m, int nx, int ny, int64_t cl, const T *__restrict__ src,
-                                                T *__restrict__ out, int w, int nw) {
-  if (m < 0) return;
-  const int jlo = max(0, m - nx + 1), jhi = min(ny - 1, m);
-  const int64_t base = cl + (WF ? wf_off(m, nx, ny) - jlo : 0);
-  for (int j = jlo + w; j <= jhi; j += nw) {
-    const int64_t c = WF ? base + j : cl + (int64_t)j * nx + (m - j);
-    *(typename vec4t<T>::type *)(out + 4 * c) = *(const typename vec4t<T>::type *)(src + 4 * j);
-  }
-}
 
 // The loads that refill a level's registers must come after the level's last
 // use of them.  Loads from read-only restrict arguments are free to move, and
@@ -297,233 +274,76 @@ __global__ __launch_bounds__(1024) void k_ras_setup(int nx, int ny, int64_t n, i
   if (bad) atomicOr(flag, bad);
 }
 
-// wavefront index (within the grid) of line j at level lam, clamped to the
-// level's cells and the level to the layer's levels: always in bounds
-__device__ __forceinline__ int64_t wf_clamped(int64_t cl, int lam, int j, int nx, int ny) {
-  lam = min(max(lam, 0), nx + ny - 2);
-  const int jlo = wf_jlo(lam, nx), jhi = min(ny - 1, lam);
-  return cl + wf_off(lam, nx, ny) + (min(max(j, jlo), jhi) - jlo);
-}
-
-// forward, per layer: y = rh - Lh_y y_{c-nx} - Lh_x y_{c-1}
-// The level count is padded to a multiple of P and every load and LDS read is
-// issued unconditionally at clamped (in-bounds) addresses, with the terms of
-// inactive cells dropped by selects: then every path through a level issues
-// the same loads, and the compiler waits only for the level's own data.
-template <class T> struct ras_fpre { T r, a1[4], a2[4]; };
-
-template <class T, int U, int P>
-__global__ __launch_bounds__(1024) void k_ras_fwd(int nx, int ny, int64_t n, int LW, const T *__restrict__ blk,
-                                                  const T *__restrict__ rh, T *__restrict__ y) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  T *ring = (T *)smem;                                  // [2][ny][4]
-  const int q = threadIdx.x >> 2, row = threadIdx.x & 3;
-  const bool compute = (int)threadIdx.x < 4 * LW;       // wave-uniform (LW is a multiple of 16)
-  const int w = threadIdx.x - 4 * LW, nw = blockDim.x - 4 * LW;
-  const int64_t nxy = (int64_t)nx * ny, cl = nxy * blockIdx.x;
-  const int Lv = nx + ny - 1, Lpad = (Lv + P - 1) / P * P;
-  if (!compute) {
-    // the writer wave: its own level loop with one barrier per level, like
-    // the compute waves, so that no path mixes its stores with the loads
-    for (int lam = 0; lam < Lpad; ++lam) {
-      ras_write_level<T, true>(lam - 1, nx, ny, cl, ring + ((lam & 1) ^ 1) * ny * 4, y, w, nw);
-      __syncthreads();
-    }
-    ras_write_level<T, true>(Lpad - 1, nx, ny, cl, ring + ((Lpad - 1) & 1) * ny * 4, y, w, nw);
-    return;
-  }
-  const T *By = blk, *Bx = blk + n * 16;
-  ras_fpre<T> R[P][U];
-  auto load = [&](int lam, ras_fpre<T> &p, int u, T tok) {
-    int j = q + LW * u;
-    order_after(j, tok);
-    const int64_t c = wf_clamped(cl, lam, j, nx, ny);
-    p.r = rh[4 * c + row];
-    ld4v(By + c * 16 + 4 * row, p.a1);
-    ld4v(Bx + c * 16 + 4 * row, p.a2);
-  };
-#pragma unroll
-  for (int d = 0; d < P; ++d)
-#pragma unroll
-    for (int u = 0; u < U; ++u) load(d, R[d][u], u, (T)0);
-  for (int lam0 = 0; lam0 < Lpad; lam0 += P) {
-#pragma unroll
-    for (int d = 0; d < P; ++d) {
-      const int lam = lam0 + d;
-      T *cur = ring + (lam & 1) * ny * 4;
-      const T *prv = ring + ((lam & 1) ^ 1) * ny * 4;
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int j = q + LW * u, i = lam - j;
-        const bool act = j < ny && i >= 0 && i < nx;
-        const int jr = min(j, ny - 1);
-        T yy[4], yx[4];
-        ld4v(prv + 4 * max(jr - 1, 0), yy);
-        ld4v(prv + 4 * jr, yx);
-        const T ty = dot4(R[d][u].a1, yy), tx = dot4(R[d][u].a2, yx);
-        T v = R[d][u].r;
-        v = (act && j > 0) ? v - ty : v;
-        v = (act && i > 0) ? v - tx : v;
-        if (act) cur[4 * j + row] = v;
-        load(lam + P, R[d][u], u, v);
-      }
-      __syncthreads();
-    }
-  }
-}
-
-// backward, per layer: z = y - Uh_x z_{c+1} - Uh_y z_{c+nx}, output z + Pi_p x_p
-// (x_p added to unknown 0) in natural order through a second LDS ring
-template <class T> struct ras_bpre { T yc, xpc, a4[4], a5[4]; };
-
-template <class T, int U, int P>
-__global__ __launch_bounds__(1024) void k_ras_bwd(int nx, int ny, int64_t n, int LW, const T *__restrict__ blk,
-                                                  const T *__restrict__ y, const T *__restrict__ xpw,
-                                                  T *__restrict__ out) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  T *ring = (T *)smem;                                  // [2][ny][4]: z
-  T *oring = ring + 2 * ny * 4;                         // [2][ny][4]: output
-  const int q = threadIdx.x >> 2, row = threadIdx.x & 3;
-  const bool compute = (int)threadIdx.x < 4 * LW;
-  const int w = threadIdx.x - 4 * LW, nw = blockDim.x - 4 * LW;
-  const int64_t nxy = (int64_t)nx * ny, cl = nxy * blockIdx.x;
-  const int Lv = nx + ny - 1, Lpad = (Lv + P - 1) / P * P;
-  if (!compute) {
-    // step s handles level Lv-1-s; the writer copies the previous step's
-    for (int step = 0; step < Lpad; ++step) {
-      ras_write_level<T, false>(step >= 1 ? Lv - step : -1, nx, ny, cl, oring + ((step & 1) ^ 1) * ny * 4, out, w,
-                                nw);
-      __syncthreads();
-    }
-    ras_write_level<T, false>(Lv - Lpad, nx, ny, cl, oring + ((Lpad - 1) & 1) * ny * 4, out, w, nw);
-    return;
-  }
-  const T *Bx = blk + 2 * n * 16, *By = blk + 3 * n * 16;
-  ras_bpre<T> R[P][U];
-  auto load = [&](int step, ras_bpre<T> &p, int u, T tok) {
-    int j = q + LW * u;
-    order_after(j, tok);
-    const int64_t c = wf_clamped(cl, Lv - 1 - step, j, nx, ny);
-    p.yc = y[4 * c + row];
-    p.xpc = xpw[c];
-    ld4v(Bx + c * 16 + 4 * row, p.a4);
-    ld4v(By + c * 16 + 4 * row, p.a5);
-  };
-#pragma unroll
-  for (int d = 0; d < P; ++d)
-#pragma unroll
-    for (int u = 0; u < U; ++u) load(d, R[d][u], u, (T)0);
-  for (int s0 = 0; s0 < Lpad; s0 += P) {
-#pragma unroll
-    for (int d = 0; d < P; ++d) {
-      const int step = s0 + d;
-      const int lam = Lv - 1 - step;
-      const int cb = (step & 1) * ny * 4, pb = ((step & 1) ^ 1) * ny * 4;
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int j = q + LW * u, i = lam - j;
-        const bool act = j < ny && i >= 0 && i < nx;
-        const int jr = min(j, ny - 1);
-        T zx[4], zy[4];
-        ld4v(ring + pb + 4 * jr, zx);
-        ld4v(ring + pb + 4 * min(jr + 1, ny - 1), zy);
-        const T tx = dot4(R[d][u].a4, zx), ty = dot4(R[d][u].a5, zy);
-        T zc = R[d][u].yc;
-        zc = (act && i < nx - 1) ? zc - tx : zc;
-        zc = (act && j < ny - 1) ? zc - ty : zc;
-        if (act) {
-          ring[cb + 4 * j + row] = zc;
-          oring[cb + 4 * j + row] = row == 0 ? zc + R[d][u].xpc : zc;
-        }
-        load(step + P, R[d][u], u, zc);
-      }
-      __syncthreads();
-    }
-  }
-}
-
-// ---- sweeps with one lane per cell, layers split into strips (FP32) ---------
-// One lane per line handles all four block rows of its cell (per cell the
-// same arithmetic sequence as the four-lane form; a quarter of the lanes).
-// A workgroup keeps a layer's lines streamed through one CU, which bounds it
-// at that CU's memory stream, so each layer is further split into S strips
-// of H consecutive lines, one workgroup each.  A strip needs, at every level,
-// the value of the line just before it (after it, backward) computed one
-// level earlier by the neighbouring strip:
-//   - the producer's writer wave publishes its boundary line, level by level,
-//     as 64-bit words (launch tag << 32 | FP32 bits), one per block row,
-//     with device-scope stores;
-//   - the consumer's writer wave polls those words with device-scope loads
-//     until the tag matches and puts the value into a ghost slot of its LDS
-//     ring, ready for the next level;
+// ---- sweeps -----------------------------------------------------------------
+//   forward   y = rh - Lh_y y_{c-nx} - Lh_x y_{c-1}
+//   backward  z = y - Uh_x z_{c+1} - Uh_y z_{c+nx}, output z + Pi_p x_p (x_p
+//             added to unknown 0) in natural order
+// A layer is split into S strips of H consecutive lines, one workgroup each.
+// A quad of lanes owns a line; lane r owns block row r.  A strip needs, at
+// every level, the value of the line just before it (after it, backward)
+// computed one level earlier by the neighbouring strip:
+//   - the writer wave publishes its boundary line, level by level, as 64-bit
+//     words (launch tag << 32 | 32 bits of the value), with device-scope stores;
+//   - the poller wave loads the neighbour's words 16 levels at a time, polls
+//     those whose tag does not match yet, and puts each level's value into the
+//     ghost slot of the LDS ring, ready for the level;
 //   - workgroups take tickets in dependency order (every strip of a layer
 //     after the one it reads), so a workgroup only waits on workgroups that
 //     are already running; every wait is bounded, and a time-out latches an
-//     error word (ctl[2]) that the host turns into RS_E_HIP.
-// Compute waves only load; the writer wave stores (see above).
+//     error word that the host turns into RS_E_HIP.
+// The waves each have one kind of memory traffic, because one counter tracks
+// a wave's loads and stores and with both kinds in flight a wave can only wait
+// for all of them: compute waves only load, with the next P levels in flight
+// in registers; the writer only stores; the poller only loads words.
+// Bound, on small and middling layers, by the chain of a level (LDS read, four
+// dependent FMAs, LDS write, barrier) and by the instructions a wave issues
+// between two barriers, one in 4 to 5 cycles: the level's place in wavefront
+// order is a scalar that advances by a difference (ras_cursor), the two blocks
+// of a cell lie side by side, and a line's own previous value comes by DPP.
+// Both sweeps, against the kernels before these (per-lane addresses formed
+// anew each level; strips of up to 224 lines, a layer per workgroup above):
+// FP32 158 -> 104 us at 100x100x50, 393 -> 310 at 200x200x100 (1.3 GB, 4.2
+// TB/s), 905 -> 730 at 256x256x160; FP64 335 -> 283 at 161x143x67.
+// The level count is padded to a multiple of P and every load is issued
+// unconditionally at a clamped (in-bounds) address, with the terms of inactive
+// cells dropped by selects: then every path through a level issues the same
+// loads, and the compiler waits only for the level's own data.
 constexpr int RAS_SPIN_LIMIT = 1 << 20;     // polls with a short sleep: about a second
+constexpr int RAS_H = 48;                   // most lines of a strip (at most 64: the writer's lanes)
+constexpr int RAS_T = 4 * RAS_H + 128;      // most threads: compute, writer, poller
 
-__device__ __forceinline__ void ras_put(uint64_t *p, float v, uint32_t tag) {
-  __hip_atomic_store(p, ((uint64_t)tag << 32) | (uint64_t)__float_as_uint(v), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_AGENT);
-}
-// value of the word at p once its tag is `tag`; false on time-out
-__device__ __forceinline__ bool ras_get(const uint64_t *p, uint32_t tag, float &v, bool &failed) {
-  int spins = 0;
-  for (;;) {
-    uint64_t w = __hip_atomic_load(const_cast<uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((uint32_t)(w >> 32) == tag) { v = __uint_as_float((uint32_t)w); return true; }
-    if (failed || ++spins > RAS_SPIN_LIMIT) { failed = true; return false; }
-    __builtin_amdgcn_s_sleep(1);
-  }
-}
-
-// A value in FP64 crosses strips as two such words, high half first, each
-// with the tag: words of value r of line i: [W r, W r + W), W = 1 or 2.
+// A value in FP64 crosses strips as two words, high half first, each with the
+// tag: words of value r of column i: [W r, W r + W), W = 1 or 2.
 template <class T> struct ras_nw { static constexpr int W = sizeof(T) / 4; };
-__device__ __forceinline__ void ras_put_v(uint64_t *p, float v, uint32_t tag) { ras_put(p, v, tag); }
+__device__ __forceinline__ void ras_put(uint64_t *p, uint32_t v, uint32_t tag) {
+  __hip_atomic_store(p, ((uint64_t)tag << 32) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void ras_put_v(uint64_t *p, float v, uint32_t tag) { ras_put(p, __float_as_uint(v), tag); }
 __device__ __forceinline__ void ras_put_v(uint64_t *p, double v, uint32_t tag) {
   const uint64_t b = (uint64_t)__double_as_longlong(v);
-  __hip_atomic_store(p, ((uint64_t)tag << 32) | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(p + 1, ((uint64_t)tag << 32) | (b & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  ras_put(p, (uint32_t)(b >> 32), tag);
+  ras_put(p + 1, (uint32_t)b, tag);
 }
-// value from its words once every tag is `tag`; w holds the words as loaded
-// earlier, re-read (bounded) until they match; false on time-out
-__device__ __forceinline__ bool ras_get_v(const uint64_t *p, const uint64_t (&w)[1], uint32_t tag, float &v,
-                                          bool &failed) {
-  if ((uint32_t)(w[0] >> 32) == tag) { v = __uint_as_float((uint32_t)w[0]); return true; }
-  return ras_get(p, tag, v, failed);
-}
-__device__ __forceinline__ bool ras_get_v(const uint64_t *p, const uint64_t (&w)[2], uint32_t tag, double &v,
-                                          bool &failed) {
-  uint32_t h[2];
-  for (int q = 0; q < 2; ++q) {
+// the low halves of words w, loaded from p earlier, once every tag is `tag`:
+// re-read (bounded) until they match; false on time-out
+template <int W>
+__device__ __forceinline__ bool ras_get(uint64_t *p, const uint64_t (&w)[W], uint32_t tag, uint32_t (&v)[W],
+                                        bool &failed) {
+  for (int q = 0; q < W; ++q) {
     uint64_t x = w[q];
     int spins = 0;
     while ((uint32_t)(x >> 32) != tag) {
       if (failed || ++spins > RAS_SPIN_LIMIT) { failed = true; return false; }
       __builtin_amdgcn_s_sleep(1);
-      x = __hip_atomic_load(const_cast<uint64_t *>(p + q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      x = __hip_atomic_load(p + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    h[q] = (uint32_t)x;
+    v[q] = (uint32_t)x;
   }
-  v = __longlong_as_double((long long)(((uint64_t)h[0] << 32) | h[1]));
   return true;
 }
-
-// store the outputs of level lam (own lines [j0, j1)) from an LDS ring
-// buffer [H+2][4] (slot of line j: j - j0 + 1) to out, in wavefront order
-// (WF) or natural order
-template <bool WF, class T = float>
-__device__ __forceinline__ void ras_write_strip(int lam, int nx, int ny, int j0, int j1, int64_t cl,
-                                                const T *__restrict__ src, T *__restrict__ out, int w, int nw) {
-  if (lam < 0 || lam > nx + ny - 2) return;
-  const int jlo = max(j0, lam - nx + 1), jhi = min(j1 - 1, lam);
-  const int64_t base = WF ? cl + wf_off(lam, nx, ny) - max(0, lam - nx + 1) : 0;
-  for (int j = jlo + w; j <= jhi; j += nw) {
-    const int64_t c = WF ? base + j : cl + (int64_t)j * nx + (lam - j);
-    *(typename vec4t<T>::type *)(out + 4 * c) = *(const typename vec4t<T>::type *)(src + 4 * (j - j0 + 1));
-  }
+__device__ __forceinline__ float ras_value(const uint32_t (&v)[1]) { return __uint_as_float(v[0]); }
+__device__ __forceinline__ double ras_value(const uint32_t (&v)[2]) {
+  return __longlong_as_double((long long)(((uint64_t)v[0] << 32) | v[1]));
 }
 
 // word of the boundary value (row r) of strip s of layer k at column i
@@ -531,473 +351,258 @@ __device__ __forceinline__ int64_t ras_xword(int k, int s, int S, int nx, int i)
   return (((int64_t)k * S + s) * nx + i) * 4;
 }
 
-template <class T> struct ras_f1 { T r[4], a1[16], a2[16]; };
-
-template <int U, int P>
-__global__ __launch_bounds__(320) void k_ras_fwd1(int nx, int ny, int nz, int S, int H, int64_t n, int LW,
-                                                  const float *__restrict__ blk, const float *__restrict__ rh,
-                                                  float *__restrict__ y, int *__restrict__ ctl,
-                                                  uint64_t *__restrict__ xw, uint32_t tag) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  float *ring = (float *)smem;                          // [2][H+2][4]
-  __shared__ int s_t;
-  __shared__ float gh[32][4];                           // ghost line j0-1, by level mod 32
-  const int tid = threadIdx.x;
-  if (tid == 0) s_t = atomicAdd(&ctl[0], 1);
-  __syncthreads();
-  const int s = s_t / nz, k = s_t - (s_t / nz) * nz;
-  const int j0 = s * H, j1 = min(ny, j0 + H), RS = H + 2;
-  const bool compute = tid < LW;                        // wave-uniform (LW is a multiple of 64)
-  const int64_t nxy = (int64_t)nx * ny, cl = nxy * k;
-  const int Lw = nx + (j1 - j0) - 1, Lpad = (Lw + P - 1) / P * P;   // levels j0 .. j0+Lw-1
-  if (!compute) {
-    const int w = tid - LW, nw = blockDim.x - LW;
-    bool failed = false;
-    // ghost line j0-1 for local level m (cell i = m) goes to gh[m % 32]; the
-    // writer loads 16 levels at a time (64 lanes: level offset, block row),
-    // issued 8 levels before the first of them is needed and checked one
-    // level before it, so the neighbour's words are normally published by
-    // the time they are loaded and the load latency is hidden behind 7
-    // levels; a word not yet published is polled
-    auto issue16 = [&](int m16, uint64_t &slot) {
-      const int m = m16 + (w >> 2), r = w & 3;
-      if (s == 0 || w >= 64 || m >= nx) return;
-      slot = __hip_atomic_load(xw + ras_xword(k, s - 1, S, nx, m) + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    auto finish16 = [&](int m16, uint64_t slot) {
-      const int m = m16 + (w >> 2), r = w & 3;
-      if (s == 0 || w >= 64 || m >= nx) return;
-      float v;
-      if ((uint32_t)(slot >> 32) == tag) v = __uint_as_float((uint32_t)slot);
-      else if (!ras_get(xw + ras_xword(k, s - 1, S, nx, m) + r, tag, v, failed)) atomicOr(&ctl[2], 1);
-      gh[m & 31][r] = v;
-    };
-    // own last line j1-1 at local level m (cell i = m + j0 - (j1-1)), buffer m&1
-    auto publish = [&](int m) {
-      if (s == S - 1 || w >= 4 || m < 0) return;
-      const int i = m + j0 - (j1 - 1);
-      if (i < 0 || i >= nx) return;
-      ras_put(xw + ras_xword(k, s, S, nx, i) + w, ring[(m & 1) * RS * 4 + (j1 - j0) * 4 + w], tag);
-    };
-    uint64_t pend = 0;
-    issue16(0, pend);
-    finish16(0, pend);
-    __syncthreads();
-    for (int m = 0; m < Lpad; ++m) {
-      if ((m & 15) == 8) issue16(m + 8, pend);          // the next batch, 8 levels ahead
-      ras_write_strip<true>(j0 + m - 1, nx, ny, j0, j1, cl, ring + ((m + 1) & 1) * RS * 4, y, w, nw);
-      publish(m - 1);
-      if ((m & 15) == 15) finish16(m + 1, pend);        // levels m+1 .. m+16
-      __syncthreads();
-    }
-    ras_write_strip<true>(j0 + Lpad - 1, nx, ny, j0, j1, cl, ring + ((Lpad + 1) & 1) * RS * 4, y, w, nw);
-    publish(Lpad - 1);
-    return;
+// Place of a level in wavefront order, all scalar: line j's cell of level lam
+// is at base + j, for the lines [jlo, jhi] of the level; levels past the
+// layer's ends stay at its last (first) level.
+struct ras_cursor {
+  int lam, jlo, jhi;
+  int64_t base;
+  __device__ __forceinline__ void set(int64_t cl, int l, int nx, int ny) {
+    lam = l;
+    jlo = max(0, l - nx + 1);
+    jhi = min(ny - 1, l);
+    base = cl + wf_off(l, nx, ny) - jlo;
   }
-  __syncthreads();
-  const float *By = blk, *Bx = blk + n * 16;
-  ras_f1<float> R[P][U];
-  auto load = [&](int m, ras_f1<float> &p, int u, float tok) {
-    int j = j0 + tid + LW * u;
-    order_after(j, tok);
-    const int64_t c = wf_clamped(cl, j0 + m, j, nx, ny);
-    ld4v(rh + 4 * c, p.r);
+  __device__ __forceinline__ void up(int nx, int ny) {
+    if (lam >= nx + ny - 2) return;
+    ++lam;
+    const int lo = max(0, lam - nx + 1);
+    base += jhi + 1 - lo;
+    jlo = lo;
+    jhi = min(ny - 1, lam);
+  }
+  __device__ __forceinline__ void down(int nx, int ny) {
+    if (lam <= 0) return;
+    --lam;
+    const int hi = min(ny - 1, lam);
+    base += jlo - hi - 1;
+    jlo = max(0, lam - nx + 1);
+    jhi = hi;
+  }
+};
+
+// u = sum_m a[m] v_m, the 4-vector v spread over the quad, as dot4
+template <class T> __device__ __forceinline__ T quad_dot(const T (&a)[4], T v) {
+  T u = 0;
+  u = fma(a[0], qb<0>(v), u);
+  u = fma(a[1], qb<1>(v), u);
+  u = fma(a[2], qb<2>(v), u);
+  return fma(a[3], qb<3>(v), u);
+}
+
+// The poller wave: words of the neighbour's boundary line, 16 steps at a time
+// (64 lanes: step offset, block row), loaded 10 steps before the first of them
+// is needed and checked two steps before it.  Word i = i0 + di * step, if in
+// [0, nx); xw: the neighbour's words, nullptr for none.  Value of step m to
+// slot `slot` of the ring buffer that step m reads.
+template <class T>
+__device__ __forceinline__ void ras_poll(int w, int steps, int i0, int di, int nx, uint64_t *xw, uint32_t tag,
+                                         T (*gh)[4], T *ring, int RS, int slot, int *err) {
+  constexpr int W = ras_nw<T>::W;
+  bool failed = false;
+  const int r = w & 3;
+  uint64_t pend[W] = {};
+  auto issue16 = [&](int m16) {
+    const int i = i0 + di * (m16 + (w >> 2));
+    if (!xw || i < 0 || i >= nx) return;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      float t4[4];
-      ld4v(By + c * 16 + 4 * q, t4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) p.a1[4 * q + e] = t4[e];
-      ld4v(Bx + c * 16 + 4 * q, t4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) p.a2[4 * q + e] = t4[e];
-    }
+    for (int q = 0; q < W; ++q)
+      pend[q] = __hip_atomic_load(xw + W * (4 * (int64_t)i + r) + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  // slot d of R holds level m0 + d; the slot of the previous level is
-  // refilled at the start of each level (before its LDS reads, so that the
-  // load issue overlaps their latency), keeping P-1 levels in flight
-#pragma unroll
-  for (int d = 0; d < P - 1; ++d)
-#pragma unroll
-    for (int u = 0; u < U; ++u) load(d, R[d][u], u, 0.f);
-  float tok[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) tok[u] = 0.f;
-  for (int m0 = 0; m0 < Lpad; m0 += P) {
-#pragma unroll
-    for (int d = 0; d < P; ++d) {
-      const int m = m0 + d, lam = j0 + m;
-      float *cur = ring + (m & 1) * RS * 4;
-      const float *prv = ring + ((m + 1) & 1) * RS * 4;
-#pragma unroll
-      for (int u = 0; u < U; ++u) load(m + P - 1, R[(d + P - 1) % P][u], u, tok[u]);
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int j = j0 + tid + LW * u, i = lam - j;
-        const bool act = j < j1 && i >= 0 && i < nx;
-        const int sl = min(j, j1 - 1) - j0 + 1;         // slot of line j
-        float yy[4], yx[4], v[4];
-        ld4v(sl == 1 ? &gh[m & 31][0] : prv + 4 * (sl - 1), yy);   // line j0-1: the ghost
-        ld4v(prv + 4 * sl, yx);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float a1r[4] = {R[d][u].a1[4 * r], R[d][u].a1[4 * r + 1], R[d][u].a1[4 * r + 2], R[d][u].a1[4 * r + 3]};
-          float a2r[4] = {R[d][u].a2[4 * r], R[d][u].a2[4 * r + 1], R[d][u].a2[4 * r + 2], R[d][u].a2[4 * r + 3]};
-          const float ty = dot4(a1r, yy), tx = dot4(a2r, yx);
-          float vr = R[d][u].r[r];
-          vr = (act && j > 0) ? vr - ty : vr;
-          vr = (act && i > 0) ? vr - tx : vr;
-          v[r] = vr;
-        }
-        if (act) *(float4 *)(cur + 4 * sl) = make_float4(v[0], v[1], v[2], v[3]);
-        tok[u] = v[3];
-      }
-      __syncthreads();
-    }
+  auto finish16 = [&](int m16) {
+    const int m = m16 + (w >> 2), i = i0 + di * m;
+    if (!xw || i < 0 || i >= nx) return;
+    uint32_t v[W] = {};
+    if (!ras_get<W>(xw + W * (4 * (int64_t)i + r), pend, tag, v, failed)) atomicOr(err, 1);
+    gh[m & 31][r] = ras_value(v);
+  };
+  T val = 0;                                            // the next step's, read one step ahead
+  auto hand = [&](int m) {                              // to the buffer that step m reads
+    if (w < 4) ring[((m + 1) & 1) * RS * 4 + 4 * slot + w] = val;
+    val = gh[(m + 1) & 31][r];
+  };
+  issue16(0);
+  finish16(0);
+  val = gh[0][r];
+  hand(0);
+  __syncthreads();
+  for (int m = 0; m < steps; ++m) {
+    if ((m & 15) == 6) issue16(m + 10);
+    if ((m & 15) == 14) finish16(m + 2);
+    hand(m + 1);
+    __syncthreads();
   }
 }
 
-template <class T> struct ras_b1 { T yc[4], xpc, a4[16], a5[16]; };
+template <class T> struct ras_fpre { T r, a1[4], a2[4]; };
 
-template <int U, int P>
-__global__ __launch_bounds__(320) void k_ras_bwd1(int nx, int ny, int nz, int S, int H, int64_t n, int LW,
-                                                  const float *__restrict__ blk, const float *__restrict__ y,
-                                                  const float *__restrict__ xpw, float *__restrict__ out,
-                                                  int *__restrict__ ctl, uint64_t *__restrict__ xw, uint32_t tag) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  float *ring = (float *)smem;                          // [2][H+2][4]: z
-  __shared__ int s_t;
-  __shared__ float gh[32][4];                           // ghost line j1, by step mod 32
-  const int tid = threadIdx.x;
-  if (tid == 0) s_t = atomicAdd(&ctl[1], 1);
-  __syncthreads();
-  const int st = s_t / nz, k = s_t - st * nz, s = S - 1 - st;   // last strip first
-  const int j0 = s * H, j1 = min(ny, j0 + H), RS = H + 2, nl = j1 - j0;
-  float *oring = ring + 2 * RS * 4;                     // [2][H+2][4]: output
-  const bool compute = tid < LW;
-  const int64_t nxy = (int64_t)nx * ny, cl = nxy * k;
-  const int Lw = nx + nl - 1, Lpad = (Lw + P - 1) / P * P;
-  const int ltop = j1 - 1 + nx - 1;                     // step m handles level ltop - m
-  if (!compute) {
-    const int w = tid - LW, nw = blockDim.x - LW;
-    bool failed = false;
-    // ghost line j1 for step m (cell i = ltop - m - (j1-1)) goes to gh[m % 32],
-    // loaded 16 steps at a time as in the forward sweep
-    auto issue16 = [&](int m16, uint64_t &slot) {
-      const int m = m16 + (w >> 2), r = w & 3;
-      const int i = ltop - m - (j1 - 1);
-      if (s == S - 1 || w >= 64 || i < 0 || i >= nx) return;
-      slot = __hip_atomic_load(xw + ras_xword(k, s + 1, S, nx, i) + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    auto finish16 = [&](int m16, uint64_t slot) {
-      const int m = m16 + (w >> 2), r = w & 3;
-      const int i = ltop - m - (j1 - 1);
-      if (s == S - 1 || w >= 64 || i < 0 || i >= nx) return;
-      float v;
-      if ((uint32_t)(slot >> 32) == tag) v = __uint_as_float((uint32_t)slot);
-      else if (!ras_get(xw + ras_xword(k, s + 1, S, nx, i) + r, tag, v, failed)) atomicOr(&ctl[2], 1);
-      gh[m & 31][r] = v;
-    };
-    // own first line j0 at step m (cell i = ltop - m - j0), buffer m&1, slot 1
-    auto publish = [&](int m) {
-      if (s == 0 || w >= 4 || m < 0) return;
-      const int i = ltop - m - j0;
-      if (i < 0 || i >= nx) return;
-      ras_put(xw + ras_xword(k, s, S, nx, i) + w, ring[(m & 1) * RS * 4 + 4 + w], tag);
-    };
-    uint64_t pend = 0;
-    issue16(0, pend);
-    finish16(0, pend);
-    __syncthreads();
-    for (int m = 0; m < Lpad; ++m) {
-      if ((m & 15) == 8) issue16(m + 8, pend);          // the next batch, 8 levels ahead
-      if (m >= 1) ras_write_strip<false>(ltop - m + 1, nx, ny, j0, j1, cl, oring + ((m + 1) & 1) * RS * 4, out, w, nw);
-      publish(m - 1);
-      if ((m & 15) == 15) finish16(m + 1, pend);        // steps m+1 .. m+16
-      __syncthreads();
-    }
-    ras_write_strip<false>(ltop - Lpad + 1, nx, ny, j0, j1, cl, oring + ((Lpad + 1) & 1) * RS * 4, out, w, nw);
-    publish(Lpad - 1);
-    return;
-  }
-  __syncthreads();
-  const float *Bx = blk + 2 * n * 16, *By = blk + 3 * n * 16;
-  ras_b1<float> R[P][U];
-  auto load = [&](int m, ras_b1<float> &p, int u, float tok) {
-    int j = j0 + tid + LW * u;
-    order_after(j, tok);
-    const int64_t c = wf_clamped(cl, ltop - m, j, nx, ny);
-    ld4v(y + 4 * c, p.yc);
-    p.xpc = xpw[c];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      float t4[4];
-      ld4v(Bx + c * 16 + 4 * q, t4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) p.a4[4 * q + e] = t4[e];
-      ld4v(By + c * 16 + 4 * q, t4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) p.a5[4 * q + e] = t4[e];
-    }
-  };
-#pragma unroll
-  for (int d = 0; d < P - 1; ++d)
-#pragma unroll
-    for (int u = 0; u < U; ++u) load(d, R[d][u], u, 0.f);
-  float tok[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) tok[u] = 0.f;
-  for (int m0 = 0; m0 < Lpad; m0 += P) {
-#pragma unroll
-    for (int d = 0; d < P; ++d) {
-      const int m = m0 + d, lam = ltop - m;
-      const int cb = (m & 1) * RS * 4, pb = ((m + 1) & 1) * RS * 4;
-#pragma unroll
-      for (int u = 0; u < U; ++u) load(m + P - 1, R[(d + P - 1) % P][u], u, tok[u]);
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int j = j0 + tid + LW * u, i = lam - j;
-        const bool act = j < j1 && i >= 0 && i < nx;
-        const int sl = min(j, j1 - 1) - j0 + 1;
-        float zx[4], zy[4], z[4];
-        ld4v(ring + pb + 4 * sl, zx);
-        ld4v(sl == nl ? &gh[m & 31][0] : ring + pb + 4 * (sl + 1), zy);   // line j1: the ghost
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float a4r[4] = {R[d][u].a4[4 * r], R[d][u].a4[4 * r + 1], R[d][u].a4[4 * r + 2], R[d][u].a4[4 * r + 3]};
-          float a5r[4] = {R[d][u].a5[4 * r], R[d][u].a5[4 * r + 1], R[d][u].a5[4 * r + 2], R[d][u].a5[4 * r + 3]};
-          const float tx = dot4(a4r, zx), ty = dot4(a5r, zy);
-          float zr = R[d][u].yc[r];
-          zr = (act && i < nx - 1) ? zr - tx : zr;
-          zr = (act && j < ny - 1) ? zr - ty : zr;
-          z[r] = zr;
-        }
-        if (act) {
-          *(float4 *)(ring + cb + 4 * sl) = make_float4(z[0], z[1], z[2], z[3]);
-          *(float4 *)(oring + cb + 4 * sl) = make_float4(z[0] + R[d][u].xpc, z[1], z[2], z[3]);
-        }
-        tok[u] = z[3];
-      }
-      __syncthreads();
-    }
-  }
-}
-
-// ---- sweeps with a quad of lanes per cell on strips (FP32 and FP64) ---------
-// The strips, tickets and boundary words of the sweeps above, with the
-// compute of the one-workgroup-per-layer sweeps: lane r of a cell's quad owns
-// block row r and keeps its rows of the next P levels in flight in registers
-// (three loads per level: its rh or y entry and its rows of the two scaled
-// blocks, plus x_p backward), so a level's loads are spread over four times
-// as many lanes as with one lane per line.  The waves each have one kind of
-// memory traffic: compute waves only load; the writer wave only stores
-// (outputs and published boundary words); a poller wave only loads the
-// neighbour strip's words, so no wait for a load ever waits for a store.
-// Strips of up to 224 lines (one pass).
 template <class T, int P>
-__global__ __launch_bounds__(1024) void k_ras_fwd3(int nx, int ny, int nz, int S, int H, int64_t n, int LWq,
+__global__ __launch_bounds__(RAS_T) void k_ras_fwd(int nx, int ny, int nz, int S, int H, int64_t n, int NC,
                                                    const T *__restrict__ blk, const T *__restrict__ rh,
-                                                   T *__restrict__ y, int *__restrict__ ctl,
+                                                   T *__restrict__ y, int *__restrict__ ticket, int *__restrict__ err,
                                                    uint64_t *__restrict__ xw, uint32_t tag) {
   extern __shared__ __align__(16) unsigned char smem[];
-  T *ring = (T *)smem;                                  // [2][H+2][4]
+  T *ring = (T *)smem;                                  // [2][H+2][4]: slot of line j: j - j0 + 1, slot 0 the ghost
   __shared__ int s_t;
-  __shared__ T gh[32][4];                               // ghost line j0-1, by level mod 32
-  const int tid = threadIdx.x, NC = 4 * LWq;
-  constexpr int W = ras_nw<T>::W;                       // boundary words per value
-  if (tid == 0) s_t = atomicAdd(&ctl[0], 1);
+  __shared__ T gh[32][4];                               // ghost line j0-1, by step mod 32
+  const int tid = threadIdx.x;
+  constexpr int W = ras_nw<T>::W;
+  if (tid == 0) s_t = atomicAdd(ticket, 1);
   __syncthreads();
-  const int s = s_t / nz, k = s_t - (s_t / nz) * nz;
+  const int tk = __builtin_amdgcn_readfirstlane(s_t);
+  const int s = tk / nz, k = tk - s * nz;
   const int j0 = s * H, j1 = min(ny, j0 + H), RS = H + 2;
   const int64_t nxy = (int64_t)nx * ny, cl = nxy * k;
-  const int Lw = nx + (j1 - j0) - 1, Lpad = (Lw + P - 1) / P * P;
+  const int Lw = nx + (j1 - j0) - 1, Lpad = (Lw + P - 1) / P * P;    // levels j0 .. j0 + Lw - 1
   if (tid >= NC + 64) {
-    // poller wave
-    const int w = tid - NC - 64;
-    bool failed = false;
-    auto wp = [&](int m, int r) { return xw + W * (ras_xword(k, s - 1, S, nx, m) + r); };
-    auto issue16 = [&](int m16, uint64_t (&slot)[W]) {
-      const int m = m16 + (w >> 2), r = w & 3;
-      if (s == 0 || m >= nx) return;
-#pragma unroll
-      for (int q = 0; q < W; ++q)
-        slot[q] = __hip_atomic_load(wp(m, r) + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    auto finish16 = [&](int m16, const uint64_t (&slot)[W]) {
-      const int m = m16 + (w >> 2), r = w & 3;
-      if (s == 0 || m >= nx) return;
-      T v = 0;
-      if (!ras_get_v(wp(m, r), slot, tag, v, failed)) atomicOr(&ctl[2], 1);
-      gh[m & 31][r] = v;
-    };
-    uint64_t pend[W] = {};
-    issue16(0, pend);
-    finish16(0, pend);
-    __syncthreads();
-    for (int m = 0; m < Lpad; ++m) {
-      if ((m & 15) == 8) issue16(m + 8, pend);
-      if ((m & 15) == 15) finish16(m + 1, pend);
-      __syncthreads();
-    }
+    ras_poll<T>(tid - NC - 64, Lpad, 0, 1, nx, s > 0 ? xw + W * ras_xword(k, s - 1, S, nx, 0) : nullptr, tag, gh, ring,
+                RS, 0, err);
     return;
   }
+  ras_cursor cur;
+  cur.set(cl, j0, nx, ny);
   if (tid >= NC) {
-    // writer wave: stores only
-    const int w = tid - NC, nw = 64;
-    auto publish = [&](int m) {
-      if (s == S - 1 || w >= 4 || m < 0) return;
-      const int i = m + j0 - (j1 - 1);
-      if (i < 0 || i >= nx) return;
-      ras_put_v(xw + W * (ras_xword(k, s, S, nx, i) + w), ring[(m & 1) * RS * 4 + (j1 - j0) * 4 + w], tag);
-    };
+    const int w = tid - NC, j = j0 + w, jl = j1 - 1, wl = min(w, jl - j0) + 1;
+    uint64_t *xp = s < S - 1 ? xw + W * (ras_xword(k, s, S, nx, 0) + w) : nullptr;
     __syncthreads();
-    for (int m = 0; m < Lpad; ++m) {
-      ras_write_strip<true, T>(j0 + m - 1, nx, ny, j0, j1, cl, ring + ((m + 1) & 1) * RS * 4, y, w, nw);
-      publish(m - 1);
+    for (int m = 1; m <= Lpad; ++m) {                   // the outputs of step m - 1
       __syncthreads();
+      const T *src = ring + ((m + 1) & 1) * RS * 4;
+      const int lam = j0 + m - 1;
+      const typename vec4t<T>::type o = *(const typename vec4t<T>::type *)(src + 4 * wl);
+      const T e = src[4 * (jl - j0 + 1) + (w & 3)];
+      const int i = lam - jl;
+      if (xp && w < 4 && i >= 0 && i < nx) ras_put_v(xp + W * 4 * (int64_t)i, e, tag);
+      if (j < j1 && (unsigned)(lam - j) < (unsigned)nx) *(typename vec4t<T>::type *)(y + 4 * (cur.base + j)) = o;
+      cur.up(nx, ny);
     }
-    ras_write_strip<true, T>(j0 + Lpad - 1, nx, ny, j0, j1, cl, ring + ((Lpad + 1) & 1) * RS * 4, y, w, nw);
-    publish(Lpad - 1);
     return;
   }
-  __syncthreads();
-  const int row = tid & 3, j = j0 + (tid >> 2);
-  const int sl = min(j, j1 - 1) - j0 + 1;               // slot of line j in the ring
-  const T *By = blk, *Bx = blk + n * 16;
+  const int row = tid & 3, q = tid >> 2, j = j0 + q;
+  const int sl = min(q, j1 - 1 - j0) + 1;
+  const int jn = j < j1 ? nx : 0;                       // no column is active on a line past the strip
+  T *slot = ring + 4 * sl;
   ras_fpre<T> R[P];
-  auto load = [&](int m, ras_fpre<T> &p, T tok) {
+  auto load = [&](ras_fpre<T> &p, T tok) {
     int jj = j;
     order_after(jj, tok);
-    const int64_t c = wf_clamped(cl, j0 + m, jj, nx, ny);
-    p.r = rh[4 * c + row];
-    ld4v(By + c * 16 + 4 * row, p.a1);
-    ld4v(Bx + c * 16 + 4 * row, p.a2);
+    const uint32_t at = (uint32_t)min(max(jj, cur.jlo), cur.jhi);
+    const T *b = blk + 32 * cur.base, *v = rh + 4 * cur.base;
+    p.r = v[4u * at + row];
+    ld4v(b + (32u * at + 4 * row), p.a1);
+    ld4v(b + (32u * at + 16 + 4 * row), p.a2);
+    cur.up(nx, ny);
   };
 #pragma unroll
-  for (int d = 0; d < P; ++d) load(d, R[d], (T)0);
+  for (int d = 0; d < P - 1; ++d) load(R[d], (T)0);
+  __syncthreads();
+  T v = 0;
   for (int m0 = 0; m0 < Lpad; m0 += P) {
 #pragma unroll
     for (int d = 0; d < P; ++d) {
-      const int m = m0 + d, i = j0 + m - j;
-      const bool act = j < j1 && i >= 0 && i < nx;
-      T *cur = ring + (m & 1) * RS * 4;
-      const T *prv = ring + ((m + 1) & 1) * RS * 4;
-      T yy[4], yx[4];
-      ld4v(sl == 1 ? &gh[m & 31][0] : prv + 4 * (sl - 1), yy);   // line j0-1: the ghost
-      ld4v(prv + 4 * sl, yx);
-      const T ty = dot4(R[d].a1, yy), tx = dot4(R[d].a2, yx);
-      T v = R[d].r;
-      v = (act && j > 0) ? v - ty : v;
-      v = (act && i > 0) ? v - tx : v;
-      if (act) cur[4 * sl + row] = v;
-      load(m + P, R[d], v);
+      const int i = j0 + m0 + d - j;
+      T yy[4];
+      ld4v(slot + ((d + 1) & 1) * RS * 4 - 4, yy);      // the line before, or the ghost
+      load(R[(d + P - 1) % P], v);                      // into the previous level's, while the read is under way
+      const T ty = dot4(R[d].a1, yy), tx = quad_dot(R[d].a2, v);
+      v = R[d].r;
+      v = j > 0 ? v - ty : v;
+      v = i > 0 ? v - tx : v;
+      if ((unsigned)i < (unsigned)jn) slot[(d & 1) * RS * 4 + row] = v;
       __syncthreads();
     }
   }
 }
 
+template <class T> struct ras_bpre { T yc, xpc, a4[4], a5[4]; };
+
 template <class T, int P>
-__global__ __launch_bounds__(1024) void k_ras_bwd3(int nx, int ny, int nz, int S, int H, int64_t n, int LWq,
+__global__ __launch_bounds__(RAS_T) void k_ras_bwd(int nx, int ny, int nz, int S, int H, int64_t n, int NC,
                                                    const T *__restrict__ blk, const T *__restrict__ y,
                                                    const T *__restrict__ xpw, T *__restrict__ out,
-                                                   int *__restrict__ ctl, uint64_t *__restrict__ xw, uint32_t tag) {
+                                                   int *__restrict__ ticket, int *__restrict__ err,
+                                                   uint64_t *__restrict__ xw, uint32_t tag) {
   extern __shared__ __align__(16) unsigned char smem[];
-  T *ring = (T *)smem;                                  // [2][H+2][4]: z
+  T *ring = (T *)smem;                                  // [2][H+2][4]: z, slot j1 - j0 + 1 the ghost
   __shared__ int s_t;
   __shared__ T gh[32][4];                               // ghost line j1, by step mod 32
-  const int tid = threadIdx.x, NC = 4 * LWq;
-  constexpr int W = ras_nw<T>::W;                       // boundary words per value
-  if (tid == 0) s_t = atomicAdd(&ctl[1], 1);
+  const int tid = threadIdx.x;
+  constexpr int W = ras_nw<T>::W;
+  if (tid == 0) s_t = atomicAdd(ticket, 1);
   __syncthreads();
-  const int st = s_t / nz, k = s_t - st * nz, s = S - 1 - st;   // last strip first
+  const int tk = __builtin_amdgcn_readfirstlane(s_t);
+  const int st = tk / nz, k = tk - st * nz, s = S - 1 - st;     // last strip first
   const int j0 = s * H, j1 = min(ny, j0 + H), RS = H + 2, nl = j1 - j0;
-  T *oring = ring + 2 * RS * 4;                         // [2][H+2][4]: output
+  T *ob = ring + 2 * RS * 4;                            // [H][16][4]: output of line j, by column mod 16
   const int64_t nxy = (int64_t)nx * ny, cl = nxy * k;
   const int Lw = nx + nl - 1, Lpad = (Lw + P - 1) / P * P;
   const int ltop = j1 - 1 + nx - 1;                     // step m handles level ltop - m
   if (tid >= NC + 64) {
-    const int w = tid - NC - 64;
-    bool failed = false;
-    auto wp = [&](int i, int r) { return xw + W * (ras_xword(k, s + 1, S, nx, i) + r); };
-    auto issue16 = [&](int m16, uint64_t (&slot)[W]) {
-      const int m = m16 + (w >> 2), r = w & 3;
-      const int i = ltop - m - (j1 - 1);
-      if (s == S - 1 || i < 0 || i >= nx) return;
-#pragma unroll
-      for (int q = 0; q < W; ++q)
-        slot[q] = __hip_atomic_load(wp(i, r) + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    auto finish16 = [&](int m16, const uint64_t (&slot)[W]) {
-      const int m = m16 + (w >> 2), r = w & 3;
-      const int i = ltop - m - (j1 - 1);
-      if (s == S - 1 || i < 0 || i >= nx) return;
-      T v = 0;
-      if (!ras_get_v(wp(i, r), slot, tag, v, failed)) atomicOr(&ctl[2], 1);
-      gh[m & 31][r] = v;
-    };
-    uint64_t pend[W] = {};
-    issue16(0, pend);
-    finish16(0, pend);
-    __syncthreads();
-    for (int m = 0; m < Lpad; ++m) {
-      if ((m & 15) == 8) issue16(m + 8, pend);
-      if ((m & 15) == 15) finish16(m + 1, pend);
-      __syncthreads();
-    }
+    ras_poll<T>(tid - NC - 64, Lpad, nx - 1, -1, nx, s < S - 1 ? xw + W * ras_xword(k, s + 1, S, nx, 0) : nullptr, tag,
+                gh, ring, RS, nl + 1, err);
     return;
   }
   if (tid >= NC) {
-    const int w = tid - NC, nw = 64;
-    auto publish = [&](int m) {
-      if (s == 0 || w >= 4 || m < 0) return;
-      const int i = ltop - m - j0;
-      if (i < 0 || i >= nx) return;
-      ras_put_v(xw + W * (ras_xword(k, s, S, nx, i) + w), ring[(m & 1) * RS * 4 + 4 + w], tag);
-    };
+    // A line's output advances by one cell a level, so eight lanes write eight
+    // cells of a line in a row (128 or 256 bytes) at the level that completes
+    // them, for an eighth of the lines each: stored level by level, 16 bytes to
+    // each line's row, the sweep took 192 us in FP64 at 161x143x67 instead of
+    // 145 (FP32: 100 and 79).
+    const int w = tid - NC, sub = w & 7;
+    uint64_t *xp = s > 0 ? xw + W * (ras_xword(k, s, S, nx, 0) + w) : nullptr;
     __syncthreads();
-    for (int m = 0; m < Lpad; ++m) {
-      if (m >= 1) ras_write_strip<false, T>(ltop - m + 1, nx, ny, j0, j1, cl, oring + ((m + 1) & 1) * RS * 4, out, w, nw);
-      publish(m - 1);
+    for (int m = 1; m <= Lpad; ++m) {                   // the outputs of step m - 1
       __syncthreads();
+      const int lam = ltop - m + 1;
+      const int q = (((lam - j0) & 7) + (w & ~7)), jq = min(q, nl - 1);
+      const int i0 = lam - j0 - q, io = i0 + sub;       // a multiple of 8, and this lane's column
+      const typename vec4t<T>::type z4 = *(const typename vec4t<T>::type *)(ob + (jq * 16 + (io & 15)) * 4);
+      const T e = ring[((m + 1) & 1) * RS * 4 + 4 + (w & 3)];
+      const int i = lam - j0;
+      if (xp && w < 4 && i >= 0 && i < nx) ras_put_v(xp + W * 4 * (int64_t)i, e, tag);
+      if (q < nl && i0 >= 0 && io < nx)
+        *(typename vec4t<T>::type *)(out + 4 * (cl + (int64_t)(j0 + q) * nx + io)) = z4;
     }
-    ras_write_strip<false, T>(ltop - Lpad + 1, nx, ny, j0, j1, cl, oring + ((Lpad + 1) & 1) * RS * 4, out, w, nw);
-    publish(Lpad - 1);
     return;
   }
-  __syncthreads();
-  const int row = tid & 3, j = j0 + (tid >> 2);
-  const int sl = min(j, j1 - 1) - j0 + 1;
-  const T *Bx = blk + 2 * n * 16, *By = blk + 3 * n * 16;
+  ras_cursor cur;
+  cur.set(cl, ltop, nx, ny);
+  const int row = tid & 3, q = tid >> 2, j = j0 + q;
+  const int sl = min(q, nl - 1) + 1;
+  const int jn = j < j1 ? nx : 0;
+  const T *bb = blk + 32 * n;
+  T *slot = ring + 4 * sl, *oq = ob + (sl - 1) * 64 + row;
   ras_bpre<T> R[P];
-  auto load = [&](int m, ras_bpre<T> &p, T tok) {
+  auto load = [&](ras_bpre<T> &p, T tok) {
     int jj = j;
     order_after(jj, tok);
-    const int64_t c = wf_clamped(cl, ltop - m, jj, nx, ny);
-    p.yc = y[4 * c + row];
-    p.xpc = xpw[c];
-    ld4v(Bx + c * 16 + 4 * row, p.a4);
-    ld4v(By + c * 16 + 4 * row, p.a5);
+    const uint32_t at = (uint32_t)min(max(jj, cur.jlo), cur.jhi);
+    const T *b = bb + 32 * cur.base, *v = y + 4 * cur.base, *x = xpw + cur.base;
+    p.yc = v[4u * at + row];
+    p.xpc = x[at];
+    ld4v(b + (32u * at + 4 * row), p.a4);
+    ld4v(b + (32u * at + 16 + 4 * row), p.a5);
+    cur.down(nx, ny);
   };
 #pragma unroll
-  for (int d = 0; d < P; ++d) load(d, R[d], (T)0);
+  for (int d = 0; d < P - 1; ++d) load(R[d], (T)0);
+  __syncthreads();
+  T z = 0;
   for (int m0 = 0; m0 < Lpad; m0 += P) {
 #pragma unroll
     for (int d = 0; d < P; ++d) {
-      const int m = m0 + d, i = ltop - m - j;
-      const bool act = j < j1 && i >= 0 && i < nx;
-      const int cb = (m & 1) * RS * 4, pb = ((m + 1) & 1) * RS * 4;
-      T zx[4], zy[4];
-      ld4v(ring + pb + 4 * sl, zx);
-      ld4v(sl == nl ? &gh[m & 31][0] : ring + pb + 4 * (sl + 1), zy);   // line j1: the ghost
-      const T tx = dot4(R[d].a4, zx), ty = dot4(R[d].a5, zy);
-      T zc = R[d].yc;
-      zc = (act && i < nx - 1) ? zc - tx : zc;
-      zc = (act && j < ny - 1) ? zc - ty : zc;
-      if (act) {
-        ring[cb + 4 * sl + row] = zc;
-        oring[cb + 4 * sl + row] = row == 0 ? zc + R[d].xpc : zc;
+      const int i = ltop - m0 - d - j;
+      T zy[4];
+      ld4v(slot + ((d + 1) & 1) * RS * 4 + 4, zy);      // the line after, or the ghost
+      load(R[(d + P - 1) % P], z);
+      const T tx = quad_dot(R[d].a4, z), ty = dot4(R[d].a5, zy);
+      z = R[d].yc;
+      z = i < nx - 1 ? z - tx : z;
+      z = j < ny - 1 ? z - ty : z;
+      if ((unsigned)i < (unsigned)jn) {
+        slot[(d & 1) * RS * 4 + row] = z;
+        oq[(i & 15) * 4] = row == 0 ? z + R[d].xpc : z;
       }
-      load(m + P, R[d], zc);
       __syncthreads();
     }
   }
@@ -1116,28 +721,29 @@ __global__ void k_ras_zero(int64_t m, T *__restrict__ v) {
   if (t < m) v[t] = (T)0;
 }
 
-__global__ void k_ras_reset(int *__restrict__ ctl) {
-  if (threadIdx.x < 2) ctl[threadIdx.x] = 0;
-}
-
-// launch shape of the sweeps: LW lines per pass (a multiple of 16, so whole
-// waves), U passes per level
-struct sweep_shape { int lw, u; };
-static sweep_shape ras_sweep_shape(int ny) {
-  int u = 1;
-  while ((ny + u - 1) / u > 240) u *= 2;
-  int lw = (ny + u - 1) / u;
-  lw = (lw + 15) / 16 * 16;
-  return {lw, u};
+// Strips per layer: at most RAS_H = 48 lines each.  Of 16 to 96 lines, 48 (three
+// compute waves) measured fastest or within 3 % of it in FP32 everywhere and in
+// FP64 on large grids: both sweeps at 200x200x100 take 339 us in FP32, against
+// 406 with 32 lines and 384 with 64, and 759 against 842 and 779 at
+// 256x256x160.  In FP64 a strip's operands bind it at what one CU takes in, so
+// strips of 32 lines are faster while each has a CU of its own and the layer
+// is split anyway: 142 us against 160 at 100x100x50, but 377 against 324 at
+// 161x143x67 (335 strips) and 56 against 48 at 60x40x30 (one strip).
+struct ras_shape { int S, H; };
+static ras_shape ras_strips(const grid3 &g, int prec) {
+  int H = RAS_H;
+  if (prec == 64 && g.ny > RAS_H && (int64_t)g.nz * ((g.ny + 31) / 32) <= 256) H = 32;
+  const int S = (g.ny + H - 1) / H;
+  H = (g.ny + S - 1) / S;
+  return {(g.ny + H - 1) / H, H};                       // every strip non-empty
 }
 
 }  // namespace
 
 // ---------------------------------------------------------------------------
 rs_status rs_ras_check_shape(const grid3 &g, int prec) {
-  // sweeps: at most 240 lines per pass and 2 passes (FP64) or 4 (FP32);
-  // LDS: the factorisation keeps one D^{-1} block per line, the backward
-  // sweep four 4-vectors per line, both within 64 KiB
+  // the factorisation: at most 240 lines per pass and 2 passes (FP64) or 4
+  // (FP32), and one D^{-1} block per line in LDS, within 64 KiB
   int max_ny = prec == 64 ? 480 : 960;
   if (g.ny < 1 || g.ny > max_ny || g.nx < 1 || g.nz < 1) return RS_E_ARG;
   return RS_OK;
@@ -1166,16 +772,13 @@ rs_status rs_ras_setup_run(rs_cpr_s *M, int *flag, hipStream_t s) {
     RS_TRY(M->rzero.alloc(es * (size_t)g.n));
   }
   {
-    // strips per layer: enough workgroups for the CUs, at least 32 lines each
-    int S = std::max(1, std::min(256 / std::max(g.nz, 1), (g.ny + 31) / 32));
-    int H = (g.ny + S - 1) / S;
-    S = (g.ny + H - 1) / H;                          // every strip non-empty
-    M->rs_strips = S; M->rs_h = H;
-    const size_t words = (size_t)g.nz * S * g.nx * 4 * (M->prec == 64 ? 2 : 1);
+    const ras_shape h = ras_strips(g, M->prec);
+    M->rs_strips = h.S; M->rs_h = h.H;
+    const size_t words = (size_t)g.nz * h.S * g.nx * 4 * (M->prec == 64 ? 2 : 1);
     RS_TRY(M->rxw.alloc(sizeof(uint64_t) * words));
-    RS_TRY(M->rctl.alloc(sizeof(int) * 4));
+    RS_TRY(M->rctl.alloc(sizeof(int) * RAS_CTL));
     RS_TRY(rs_fill32(M->rxw.p, 0, 2 * (int64_t)words, s));
-    RS_TRY(rs_fill32(M->rctl.p, 0, 4, s));
+    RS_TRY(rs_fill32(M->rctl.p, 0, RAS_CTL, s));
     M->repoch = 0;
   }
   auto run = [&](auto tag) -> rs_status {
@@ -1232,70 +835,34 @@ rs_status rs_ras_apply_run(rs_cpr_s *M, const T *xp, T *out, hipStream_t s) {
   const T *P0 = ov1 ? M->rdv0.as<T>() : M->dinv2.as<T>();
   {
     const int64_t tiles = (int64_t)g.nz * ((g.nx + RI - 1) / RI) * ((g.ny + RJ - 1) / RJ);
-    // the tickets of the sweeps below are zeroed here (overlap 0); the
-    // overlapping form sweeps several times and zeroes them before each
-    int *tk = !ov1 ? M->rctl.as<int>() : nullptr;
+    // the tickets of the sweeps below are zeroed here
+    int *tk = M->rctl.as<int>();
     k_ras_in_tile<T><<<(unsigned)tiles, 4 * RI * RJ, 0, s>>>(g.nx, g.ny, g.n, M->rt.as<T>(), D->col0.as<T>(), xp,
                                                              P0, rh, xpw, tk);
   }
   RS_HIP(hipGetLastError());
-  const sweep_shape sh = ras_sweep_shape(g.ny);
-  // compute lanes (at most 960) + one writer wave
-  const int nt = 4 * sh.lw + 64;
-  const size_t ring_bytes = sizeof(T) * 8 * (size_t)g.ny;     // two levels of [ny][4]
-  // one forward sweep over all layers: blocks blk, rhs r (wavefront), result yo (wavefront)
-  std::function<void(const T *, const T *, T *)> fwd;
-  // one backward sweep: result + x_p (x_p in wavefront order) in natural order
-  std::function<void(const T *, const T *, const T *, T *)> bwd;
-  // strips of H lines (the tickets restart at every launch)
+  // Levels in flight, and with them the workgroups that share a CU: few of them
+  // stream the operands of a large grid faster than many (at 200x200x100, FP32,
+  // the forward sweep takes 144 us with 16 levels and one workgroup, 183 with
+  // 12 and three; the backward one 150 with 12 levels and two, by the LDS asked
+  // for, 156 with three and 171 with 10 levels).
+  constexpr int PF = sizeof(T) == 4 ? 16 : 8, PB = sizeof(T) == 4 ? 12 : 6;
+  constexpr size_t two_per_cu = 56000;
   const int S = M->rs_strips, H = M->rs_h;
-  int *ctl = M->rctl.as<int>();
-  uint64_t *xw = M->rxw.as<uint64_t>();
   const unsigned nwg = (unsigned)(g.nz * S);
-  if (H <= 224) {
-    // strips of at most 224 lines: a quad of lanes per cell (one pass)
-    const int lwq = (H + 15) / 16 * 16, ntq = 4 * lwq + 128;
-    const size_t rb3 = sizeof(T) * 8 * (size_t)(H + 2);
-    fwd = [=](const T *blk, const T *r, T *yo) {
-      if (ov1) k_ras_reset<<<1, 64, 0, s>>>(ctl);
-      const uint32_t tag = ++M->repoch;
-      k_ras_fwd3<T, 4><<<nwg, ntq, rb3, s>>>(g.nx, g.ny, g.nz, S, H, g.n, lwq, blk, r, yo, ctl, xw, tag);
-    };
-    bwd = [=](const T *blk, const T *yi, const T *xw_p, T *o) {
-      if (ov1) k_ras_reset<<<1, 64, 0, s>>>(ctl);
-      const uint32_t tag = ++M->repoch;
-      k_ras_bwd3<T, 4><<<nwg, ntq, 2 * rb3, s>>>(g.nx, g.ny, g.nz, S, H, g.n, lwq, blk, yi, xw_p, o, ctl, xw, tag);
-    };
-  } else if constexpr (sizeof(T) == 4) {
-    // taller strips (FP32): one lane per line (at most 256 per pass, U passes)
-    const int u1 = H <= 256 ? 1 : (H <= 512 ? 2 : 4);
-    const int lw1 = ((H + u1 - 1) / u1 + 63) / 64 * 64, nt1 = lw1 + 64;
-    const size_t rb = sizeof(float) * 8 * (size_t)(H + 2);
-    fwd = [=](const T *blk, const T *r, T *yo) {
-      if (ov1) k_ras_reset<<<1, 64, 0, s>>>(ctl);
-      const uint32_t tag = ++M->repoch;
-      if (u1 == 1) k_ras_fwd1<1, 5><<<nwg, nt1, rb, s>>>(g.nx, g.ny, g.nz, S, H, g.n, lw1, blk, r, yo, ctl, xw, tag);
-      else if (u1 == 2) k_ras_fwd1<2, 3><<<nwg, nt1, rb, s>>>(g.nx, g.ny, g.nz, S, H, g.n, lw1, blk, r, yo, ctl, xw, tag);
-      else k_ras_fwd1<4, 2><<<nwg, nt1, rb, s>>>(g.nx, g.ny, g.nz, S, H, g.n, lw1, blk, r, yo, ctl, xw, tag);
-    };
-    bwd = [=](const T *blk, const T *yi, const T *xw_p, T *o) {
-      if (ov1) k_ras_reset<<<1, 64, 0, s>>>(ctl);
-      const uint32_t tag = ++M->repoch;
-      if (u1 == 1) k_ras_bwd1<1, 5><<<nwg, nt1, 2 * rb, s>>>(g.nx, g.ny, g.nz, S, H, g.n, lw1, blk, yi, xw_p, o, ctl, xw, tag);
-      else if (u1 == 2) k_ras_bwd1<2, 3><<<nwg, nt1, 2 * rb, s>>>(g.nx, g.ny, g.nz, S, H, g.n, lw1, blk, yi, xw_p, o, ctl, xw, tag);
-      else k_ras_bwd1<4, 2><<<nwg, nt1, 2 * rb, s>>>(g.nx, g.ny, g.nz, S, H, g.n, lw1, blk, yi, xw_p, o, ctl, xw, tag);
-    };
-  } else {
-    // taller layers (FP64): one workgroup per layer, a quad of lanes per cell
-    fwd = [=](const T *blk, const T *r, T *yo) {
-      if (sh.u == 1) k_ras_fwd<T, 1, 4><<<g.nz, nt, ring_bytes, s>>>(g.nx, g.ny, g.n, sh.lw, blk, r, yo);
-      else k_ras_fwd<T, 2, 2><<<g.nz, nt, ring_bytes, s>>>(g.nx, g.ny, g.n, sh.lw, blk, r, yo);
-    };
-    bwd = [=](const T *blk, const T *yi, const T *xw_p, T *o) {
-      if (sh.u == 1) k_ras_bwd<T, 1, 4><<<g.nz, nt, 2 * ring_bytes, s>>>(g.nx, g.ny, g.n, sh.lw, blk, yi, xw_p, o);
-      else k_ras_bwd<T, 2, 2><<<g.nz, nt, 2 * ring_bytes, s>>>(g.nx, g.ny, g.n, sh.lw, blk, yi, xw_p, o);
-    };
-  }
+  const int NC = (H + 15) / 16 * 64, nt = NC + 128;    // compute lanes in whole waves, writer, poller
+  const size_t ring = sizeof(T) * 8 * (size_t)(H + 2);
+  int *ticket = M->rctl.as<int>(), *err = ticket + RAS_TICKETS;
+  uint64_t *xw = M->rxw.as<uint64_t>();
+  // one forward sweep over all layers: blocks blk, rhs r, result yo (wavefront order)
+  auto fwd = [&](const T *blk, const T *r, T *yo) {
+    k_ras_fwd<T, PF><<<nwg, nt, ring, s>>>(g.nx, g.ny, g.nz, S, H, g.n, NC, blk, r, yo, ticket++, err, xw, ++M->repoch);
+  };
+  // one backward sweep: result + x_p (x_p in wavefront order) in natural order
+  auto bwd = [&](const T *blk, const T *yi, const T *x, T *o) {
+    k_ras_bwd<T, PB><<<nwg, nt, std::max(ring + sizeof(T) * 64 * (size_t)H, two_per_cu), s>>>(g.nx, g.ny, g.nz, S, H, g.n, NC, blk, yi, x, o, ticket++, err, xw,
+                                               ++M->repoch);
+  };
   const T *blk = M->rblk.as<T>();
   if (!ov1) {
     fwd(blk, rh, y);

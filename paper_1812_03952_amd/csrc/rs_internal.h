@@ -175,8 +175,8 @@ struct rs_cpr_s {
   uint32_t pepoch = 0;
   dbuf pdone, pctl, pxch, pblk, pxp;
   // RAS sweeps: scaled blocks and x_p in wavefront order; strips per layer,
-  // their boundary exchange words, [fwd ticket, bwd ticket, error] and the
-  // tag of the last sweep
+  // their boundary exchange words, [a ticket per sweep, error] and the tag of
+  // the last sweep
   dbuf rblk, rxp, rxw, rctl;
   int rs_strips = 1, rs_h = 0;
   // RAS with overlap 1: layer factors P0 (dinv2 holds P1, the owned ones),
