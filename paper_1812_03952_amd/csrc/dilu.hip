@@ -282,10 +282,10 @@ __global__ __launch_bounds__(256) void k_dilu_rhs(int nx, int ny, int nz, int NJ
 // as long as its CU takes to bring the operands in (about 45 GB/s a CU from
 // HBM: 0.39 us in FP32 and 0.75 in FP64 with 64 cells), and for every brick on
 // the way from corner to corner the way of a face value through memory, 2 to
-// 3 us.  Forward and backward, FP32 at 200x200x100: 480 and 520 us (1395 and
+// 3 us.  Forward and backward, FP32 at 200x200x100: 459 and 458 us (1395 and
 // 1206 with bricks of 4 x 4 lines whose waves took the levels in turn, polled
 // their faces themselves and read the grid's order; 690 and 740 with these
-// waves on the grid's order); FP64 at 100x100x50: 210 and 217 (567 and 577).
+// waves on the grid's order); FP64 at 100x100x50: 199 and 199 (567 and 577).
 template <class T> __device__ __forceinline__ void poll_faces(
     int lane, int L, int nx, bool has, int shift, const uint64_t *__restrict__ src, bool rev, T *__restrict__ slot0,
     T *__restrict__ slot1, uint32_t tag, int *__restrict__ err) {
@@ -502,7 +502,8 @@ __global__ __launch_bounds__(4 * BJ * BK + 128) void k_bwd_pipe(int nx, int ny, 
                                                   const T *__restrict__ xpb, T *__restrict__ out) {
   constexpr int NC = 4 * BJ * BK, RN = ring_lines<BK>, BS = brick_geo<BK>::BS;
   __shared__ __align__(32) T ring[2][RN][4];       // line (jl, kl) at kl RG + jl
-  __shared__ __align__(32) T oring[2][BJ * BK][4];        // the level's output: z + Pi_p x_p, by rank
+  constexpr int OB = 16 * 4 + 4;                          // padded: the lines of a level start in different banks
+  __shared__ __align__(32) T ob[BJ * BK][OB];             // output z + Pi_p x_p of line (jl, kl), by column mod 16
   __shared__ int s_t;
   const int tid = threadIdx.x;
   if (tid == 0) s_t = atomicAdd(ticket, 1);
@@ -530,18 +531,22 @@ __global__ __launch_bounds__(4 * BJ * BK + 128) void k_bwd_pipe(int nx, int ny, 
     const bool yf = lane < 4 * BK;
     const int pos = yf ? lane >> 2 : min((lane >> 2) - BK, BJ - 1), fj = yf ? 0 : pos, fk = yf ? pos : 0;
     const bool pub = lane < 4 * (BJ + BK) && (yf ? J > 0 && pos < g.bk : K > 0 && pos < g.bj);
-    int jl = 0, kl = 0;
-    if (lane < g.nl) g.line(lane, jl, kl);
-    const T *f0 = &ring[0][fk * RG + fj][lane & 3], *o0 = &oring[0][min(lane, BJ * BK - 1)][0];
+    const T *f0 = &ring[0][fk * RG + fj][lane & 3];
     uint64_t *dst = xch + xslot<T>(b, yf ? 0 : 1, pos, 0, nx, lane & 3);
-    T *o = out + 4 * ((int64_t)(K * BK + kl) * ny + J * BJ + jl) * nx;
+    // a line's output advances by one cell a level: eight lanes write eight
+    // cells of a row together at the level that completes them, which one line
+    // of every kl does (16 bytes to each line's row at every level: 512 us
+    // instead of 458 in FP32 at 200x200x100)
+    const int kl = lane >> 3, sub = lane & 7;
+    T *o = out + 4 * ((int64_t)(K * BK + kl) * ny + J * BJ) * nx;
     write_levels<T>(L, [&](int m) {
-      const int i = top - m - fj - fk, c = top - m - jl - kl;
+      const int i = top - m - fj - fk;
+      const int jl = (top - m - kl) & 7, i0 = top - m - kl - jl, io = i0 + sub;
       const T fv = f0[(m & 1) * RN * 4];
       T ov[4];
-      ld4v(o0 + (m & 1) * BJ * BK * 4, ov);
+      ld4v(&ob[(kl & (BK - 1)) * BJ + jl][(io & 15) * 4], ov);
       if (pub && i >= 0 && i < nx) xw<T>::put(dst + (int64_t)i * 4 * xw<T>::W, fv, tag);
-      if (lane < g.nl && c >= 0 && c < nx) st4v(o + 4 * c, ov);
+      if (jl < g.bj && kl < g.bk && i0 >= 0 && io < nx) st4v(o + 4 * ((int64_t)jl * nx + io), ov);
     });
     return;
   }
@@ -550,6 +555,7 @@ __global__ __launch_bounds__(4 * BJ * BK + 128) void k_bwd_pipe(int nx, int ny, 
   if (q < g.nl) g.line(q, jl, kl);
   const bool hz = K * BK + kl < nz - 1, hy = J * BJ + jl < ny - 1;
   const int slot = kl * RG + jl;
+  T *oq = &ob[kl * BJ + jl][row];
   T xpc[P];
   walk<T, BK> lw;                                           // the level that loads next
   lw.begin_top(g, y, pb, top);
@@ -590,7 +596,7 @@ __global__ __launch_bounds__(4 * BJ * BK + 128) void k_bwd_pipe(int nx, int ny, 
       const T zc = R[d].v - w;
       if (act) {
         ring[m & 1][slot][row] = zc;
-        oring[m & 1][q][row] = row == 0 ? zc + xpc[d] : zc;
+        oq[(i & 15) * 4] = row == 0 ? zc + xpc[d] : zc;
       }
       load(R[d], xpc[d], zc);
     }
