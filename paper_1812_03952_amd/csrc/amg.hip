@@ -39,6 +39,7 @@
 #include <mutex>
 
 namespace {
+#include "reduce.h"
 
 enum : uint8_t { ST_UND = 0, ST_ROOT = 1, ST_OUT = 2, ST_ISO = 3 };
 
@@ -243,6 +244,19 @@ __device__ __forceinline__ cell7 cell7_of(int64_t c, int nx, int ny, int nz) {
 }
 
 constexpr int MIS_BATCH = 4;   // MIS rounds per host read
+
+// the set-up's words on the device, which the host reads (rs_amg_build)
+enum {
+  W_FLAG = 0,          // aggregation error
+  W_NNZ,               // entries of the coarse level built last
+  W_NC,                // roots of the level
+  W_LU,                // singular coarsest matrix
+  W_AUX,               // a total of the smoothed product
+  W_SM,                // the second stage's set-up flags (rs_cpr_setup)
+  W_UND = 8,           // two batches' round flags
+  W_TOTAL = W_UND + 2 * MIS_BATCH
+};
+static_assert(W_TOTAL <= RS_READ_WORDS, "one read");
 
 __device__ __forceinline__ uint64_t keyof(uint8_t st, int v, int level) {
   return st == ST_ROOT ? ~0ull : (st == ST_UND ? prio(v, level) : 0ull);
@@ -511,17 +525,177 @@ __global__ __launch_bounds__(GAL_BLOCK) void k_galerkin(int nc, const int32_t *_
   cnt[I] = m;
 }
 
-// Also the coarse level's l1 diagonal (as k_l1diag, the same additions in
-// the same order) and, when cap is given, its FP32 values (as k_cast_f32),
-// so the coarse level needs no pass of its own for them.
+// The same rows with 16 lanes (a DPP row) per coarse row, for levels whose
+// rows do not fill the chip with a thread each: there k_galerkin's time is one
+// row's chain, some 60 candidates times a list search in LDS (54 us at 500
+// rows).  Lane l of the row's group holds the list entries l and 16 + l; 16
+// candidates are loaded at a time, one per lane, and handed round in order
+// (broadcast in the DPP row): the lane whose key matches adds the value, or,
+// if none does, the next free lane takes it.  The additions to an entry are
+// those of k_galerkin in the same order (an entry that a candidate misses adds
+// 0.0, which leaves it as it is: it is never -0.0).  The rank of its key is an
+// entry's place in the row.  Rows with more than 32 columns take gal_row on
+// the global scratch, in the group's first lane.
+// Against a thread per row: 9.5 us for 42 at 600 rows of the fine level, 45 for
+// 65 at 76 thousand, 294 for 250 at 611 thousand, where the groups'
+// instructions (20 per candidate and four rows) fill the chip; on coarser
+// levels 13 for 47 at 5.6 thousand and 30 for 61 at 45 thousand.
+constexpr int GAL_LANES_MAX = 1 << 18;
+template <int C> __device__ __forceinline__ int row_bcast(int x) {
+  return __builtin_amdgcn_mov_dpp(x, 0x150 + C, 0xf, 0xf, true);
+}
+struct gal_list {
+  int k0 = -2, k1 = -2, m = 0;                          // keys (none: -2), entries of the row
+  double v0 = 0.0, v1 = 0.0;
+  template <int C> __device__ __forceinline__ void put(int J, double a, int lane) {
+    const int j = row_bcast<C>(J);
+    const double x = __hiloint2double(row_bcast<C>(__double2hiint(a)), row_bcast<C>(__double2loint(a)));
+    const bool e0 = k0 == j, e1 = k1 == j;
+    v0 = v0 + (e0 ? x : 0.0);
+    v1 = v1 + (e1 ? x : 0.0);
+    const uint64_t hit = __ballot(e0 || e1);
+    if (j >= 0 && ((uint32_t)(hit >> (threadIdx.x & 48)) & 0xffffu) == 0) {   // the same for the group
+      if (m == lane) { k0 = j; v0 = 0.0 + x; }
+      if (m == lane + 16) { k1 = j; v1 = 0.0 + x; }
+      ++m;
+    }
+  }
+  template <int C> __device__ __forceinline__ void count(int a0, int a1, int &r0, int &r1) const {
+    const int b0 = row_bcast<C>(a0), b1 = row_bcast<C>(a1);
+    r0 += (b0 < a0) + (b1 < a0);
+    r1 += (b0 < a1) + (b1 < a1);
+  }
+  __device__ __forceinline__ void ranks(int lane, int &r0, int &r1) const {
+    const int a0 = lane < m ? k0 : INT32_MAX, a1 = lane + 16 < m ? k1 : INT32_MAX;
+    r0 = r1 = 0;
+    count<0>(a0, a1, r0, r1); count<1>(a0, a1, r0, r1); count<2>(a0, a1, r0, r1); count<3>(a0, a1, r0, r1);
+    count<4>(a0, a1, r0, r1); count<5>(a0, a1, r0, r1); count<6>(a0, a1, r0, r1); count<7>(a0, a1, r0, r1);
+    count<8>(a0, a1, r0, r1); count<9>(a0, a1, r0, r1); count<10>(a0, a1, r0, r1); count<11>(a0, a1, r0, r1);
+    count<12>(a0, a1, r0, r1); count<13>(a0, a1, r0, r1); count<14>(a0, a1, r0, r1); count<15>(a0, a1, r0, r1);
+  }
+};
+
+// the candidates of a row source, 16 at a time
+__device__ __forceinline__ void gal_rows(const rows_7 &w, int x0, int x1, int lane, const int32_t *__restrict__ mem,
+                                         const int32_t *__restrict__ agg, gal_list &g) {
+  // two members per step, their slots in lanes 0-6 and 8-14; the next step's
+  // loads are in flight while a step's candidates are put
+  const int sl = lane & 7;
+  const int64_t n = (int64_t)w.nx * w.ny * w.nz;
+  auto get = [&](int x2, int &J, double &a) {
+    const int x = x2 + (lane >> 3), i = mem[max(min(x, x1 - 1), 0)];
+    const cell7 e = cell7_of(i, w.nx, w.ny, w.nz);
+    bool in = false;
+    int64_t q = i;
+#pragma unroll
+    for (int t = 0; t < 7; ++t)
+      if (sl == t && e.in[t]) { in = true; q = e.nb[t]; }
+    const int J0 = agg[q];
+    a = w.ap7[(int64_t)min(sl, 6) * n + i];
+    J = x < x1 && in ? J0 : -1;
+  };
+  int J, Jn = -1;
+  double a, an = 0.0;
+  get(x0, J, a);
+  for (int x = x0; __ballot(x < x1); x += 2) {          // groups that are done put nothing
+    get(x + 2, Jn, an);
+    g.put<0>(J, a, lane); g.put<1>(J, a, lane); g.put<2>(J, a, lane); g.put<3>(J, a, lane);
+    g.put<4>(J, a, lane); g.put<5>(J, a, lane); g.put<6>(J, a, lane);
+    g.put<8>(J, a, lane); g.put<9>(J, a, lane); g.put<10>(J, a, lane); g.put<11>(J, a, lane);
+    g.put<12>(J, a, lane); g.put<13>(J, a, lane); g.put<14>(J, a, lane);
+    J = Jn;
+    a = an;
+  }
+}
+__device__ __forceinline__ void gal_rows(const rows_csr &w, int x0, int x1, int lane, const int32_t *__restrict__ mem,
+                                         const int32_t *__restrict__ agg, gal_list &g) {
+  // 16 entries of a member's row per step; entries are loaded two steps and
+  // their columns' aggregates one step before they are put
+  int x = x0, p = 0, pe = 0;                            // the next step's member, entries left of its row
+  auto open = [&]() {
+    const int i = mem[max(min(x, x1 - 1), 0)];
+    p = w.rp[i];
+    pe = x < x1 ? w.rp[i + 1] : p;
+  };
+  auto entries = [&](int &c, double &a, int &last) {    // of the next step; c = -1: none
+    const bool in = p + lane < pe;
+    const int at = max(min(p + lane, pe - 1), 0);
+    c = w.ci[at];
+    a = w.a[at];
+    if (!in) c = -1;
+    last = pe - p;
+    p += 16;
+    if (p >= pe && x < x1) {
+      ++x;
+      open();
+    }
+  };
+  open();
+  int c1, c2, n1, n2, n3;
+  double a1, a2, a3;
+  entries(c1, a1, n1);
+  entries(c2, a2, n2);
+  int J = c1 >= 0 ? agg[c1] : -1;
+  while (__ballot(n1 > 0 || n2 > 0 || x < x1)) {
+    int c3;
+    entries(c3, a3, n3);
+    const int Jn = agg[max(c2, 0)];
+    g.put<0>(J, a1, lane); g.put<1>(J, a1, lane); g.put<2>(J, a1, lane); g.put<3>(J, a1, lane);
+    g.put<4>(J, a1, lane); g.put<5>(J, a1, lane); g.put<6>(J, a1, lane); g.put<7>(J, a1, lane);
+    if (__ballot(n1 > 8)) {
+      g.put<8>(J, a1, lane); g.put<9>(J, a1, lane); g.put<10>(J, a1, lane); g.put<11>(J, a1, lane);
+      g.put<12>(J, a1, lane); g.put<13>(J, a1, lane); g.put<14>(J, a1, lane); g.put<15>(J, a1, lane);
+    }
+    J = c2 >= 0 ? Jn : -1;
+    a1 = a2; n1 = n2;
+    c2 = c3; a2 = a3; n2 = n3;
+  }
+}
+
+// nc: the number of coarse rows, or (d_nc given) its bound while the number is
+// still on the device, where a level that does not coarsen (0 or n) is left alone
+template <class R>
+__global__ __launch_bounds__(256) void k_galerkin_lanes(int nc, const int *__restrict__ d_nc,
+                                                        const int32_t *__restrict__ mptr,
+                                                        const int32_t *__restrict__ mem, R rows,
+                                                        const int32_t *__restrict__ agg,
+                                                        const int32_t *__restrict__ off, int32_t *__restrict__ skey,
+                                                        double *__restrict__ sval, int32_t *__restrict__ cnt) {
+  if (d_nc) {
+    const int d = *d_nc;
+    if (d >= nc) return;
+    nc = d;
+  }
+  const int lane = threadIdx.x & 15, I = (blockIdx.x * 256 + threadIdx.x) >> 4;
+  const int Ic = min(I, nc - 1);
+  if (nc < 1 || (int)(blockIdx.x * 16) >= nc) return;   // the same for the workgroup
+  const bool own = I < nc;
+  const int x0 = mptr[Ic], x1 = own ? mptr[Ic + 1] : x0, base = off[Ic], ncand = cnt[Ic];
+  gal_list g;
+  gal_rows(rows, x0, x1, lane, mem, agg, g);
+  int r0, r1;
+  g.ranks(lane, r0, r1);
+  if (!own) return;
+  if (g.m <= 32) {
+    if (lane < g.m) { skey[base + r0] = g.k0; sval[base + r0] = g.v0; }
+    if (lane + 16 < g.m) { skey[base + r1] = g.k1; sval[base + r1] = g.v1; }
+    if (lane == 0) cnt[I] = g.m;
+  } else if (lane == 0) {
+    int m = 0;
+    gal_row(I, mptr, mem, rows, agg, [&](int q) -> int32_t & { return skey[base + q]; },
+            [&](int q) -> double & { return sval[base + q]; }, ncand, m);
+    cnt[I] = m;
+  }
+}
+
+// Row I of the coarse level, m entries, from the scratch at b to o.  Also the
+// coarse level's l1 diagonal (as k_l1diag, the same additions in the same
+// order) and, when cap is given, its FP32 values (as k_cast_f32), so the
+// coarse level needs no pass of its own for them.
 template <class T>
-__global__ void k_galerkin_copy(int nc, const int32_t *__restrict__ off, const int32_t *__restrict__ skey,
-                                const double *__restrict__ sval, const int32_t *__restrict__ crp,
-                                int32_t *__restrict__ cci, double *__restrict__ ca, float *__restrict__ cap,
-                                T *__restrict__ dl1) {
-  int I = blockIdx.x * blockDim.x + threadIdx.x;
-  if (I >= nc) return;
-  int b = off[I], o = crp[I], m = crp[I + 1] - crp[I];
+__device__ __forceinline__ void gal_copy_row(int I, int m, int b, int o, const int32_t *__restrict__ skey,
+                                             const double *__restrict__ sval, int32_t *__restrict__ cci,
+                                             double *__restrict__ ca, float *__restrict__ cap, T *__restrict__ dl1) {
   double sum = 0.0, aii = 0.0;
   for (int sb = 0; sb < m; sb += 8) {            // eight entries' loads in flight at once
     int32_t kv[8];
@@ -545,6 +719,16 @@ __global__ void k_galerkin_copy(int nc, const int32_t *__restrict__ off, const i
   }
   if (sum == 0.0) sum = 1.0;
   dl1[I] = (T)(aii < 0.0 ? -sum : sum);
+}
+
+template <class T>
+__global__ void k_galerkin_copy(int nc, const int32_t *__restrict__ off, const int32_t *__restrict__ skey,
+                                const double *__restrict__ sval, const int32_t *__restrict__ crp,
+                                int32_t *__restrict__ cci, double *__restrict__ ca, float *__restrict__ cap,
+                                T *__restrict__ dl1) {
+  int I = blockIdx.x * blockDim.x + threadIdx.x;
+  if (I >= nc) return;
+  gal_copy_row<T>(I, crp[I + 1] - crp[I], off[I], crp[I], skey, sval, cci, ca, cap, dl1);
 }
 
 template <class T>
@@ -1632,6 +1816,306 @@ __global__ __launch_bounds__(256) void k_vc_post7z(int n, int nx, int nxy, const
   x[i] = z[i] + (b[i] - s) / d[i];
 }
 
+// ---- a small level in one launch ---------------------------------------------
+// Strength, independent set, aggregates, their members and the Galerkin
+// product's offsets of a level of at most SMALL_N rows by one workgroup, with
+// the states, keys and aggregates in LDS.  As separate launches this is some
+// twenty of them and two to four host reads, 3 us and 9 us each, where none has
+// work for a microsecond.  The whole preconditioner set-up at 20x20x10 (levels of
+// 4000 and 600 rows) takes 215 us, 371 before this and k_galerkin_lanes; this
+// kernel 46 us of it on the fine level and 13 to 48 on coarser ones.  At more
+// rows its one CU would be slower than the launches.
+// The results are those of the kernels above (the same tests, sums and orders).
+// Keys are hashes alone, as in k_mis7_round; the host sees to it that the two
+// marks are no row's hash (small_keys_ok).
+// ST7: the fine level, neighbours by slot and dmask (from k_fine7); else CSR,
+// with dir and strong as scratch of one byte per entry.
+constexpr int SMALL_N = 8192, SMALL_T = 1024, SMALL_V = SMALL_N / SMALL_T;
+
+template <bool ST7>
+__global__ __launch_bounds__(SMALL_T) void k_small_level(int n, int level, int nx, int ny, int nz,
+                                                         const double *__restrict__ ap7,
+                                                         const uint8_t *__restrict__ dmask,
+                                                         const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
+                                                         const double *__restrict__ a, double theta, double mrs,
+                                                         uint8_t *dir, uint8_t *strong, int32_t *__restrict__ agg,
+                                                         int32_t *__restrict__ mptr, int32_t *__restrict__ mem,
+                                                         int32_t *__restrict__ cnt, int32_t *__restrict__ off,
+                                                         int *__restrict__ W, rs_post *__restrict__ post, uint64_t seq) {
+  __shared__ uint32_t A[SMALL_N], B[SMALL_N];
+  __shared__ uint8_t st[SMALL_N], sm[ST7 ? SMALL_N : 1];
+  __shared__ uint16_t ml[SMALL_N];
+  __shared__ int part[SMALL_T / 64];
+  const int t = threadIdx.x, nxy = nx * ny;
+  // f(v) for the thread's rows
+  auto rows = [&](auto f) {
+    for (int v = t; v < n; v += SMALL_T) f(v);
+  };
+  // f(entry, neighbour) over the strong neighbours of v in column order, and
+  // over all the row's entries when `all`; stops when f returns false
+  auto each = [&](int v, auto f) {
+    if constexpr (ST7) {
+      const uint32_t m = sm[v];
+      const int d[7] = {-nxy, -nx, -1, 0, 1, nx, nxy};
+#pragma unroll
+      for (int sl = 0; sl < 7; ++sl)
+        if (((m >> sl) & 1u) && !f(sl, v + d[sl])) return;
+    } else {
+      const int p0 = rp[v], p1 = rp[v + 1];
+      for (int p = p0; p < p1; p += 4) {                // four entries' loads at once
+        int c[4];
+        uint8_t g[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int q = min(p + k, p1 - 1);
+          c[k] = ci[q];
+          g[k] = strong[q];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (p + k < p1 && g[k] && !f(p + k, c[k])) return;
+      }
+    }
+  };
+  // exclusive scan of x over the threads, the sum in `all`
+  auto scan = [&](int x, int &all) {
+    const int lane = t & 63, wv = t >> 6;
+    int v = x;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(v, o, 64);
+      if (lane >= o) v += u;
+    }
+    __syncthreads();                                    // part may still be read
+    if (lane == 63) part[wv] = v;
+    __syncthreads();
+    int before = 0;
+    all = 0;
+#pragma unroll
+    for (int w = 0; w < SMALL_T / 64; ++w) {
+      before += w < wv ? part[w] : 0;
+      all += part[w];
+    }
+    return before + v - x;
+  };
+  // ---- strength and the first states
+  if constexpr (ST7) {
+    rows([&](int c) {
+      const cell7 e = cell7_of(c, nx, ny, nz);
+      const uint8_t o = dmask[c];
+      uint8_t m = 0;
+#pragma unroll
+      for (int sl = 0; sl < 7; ++sl) {
+        const uint8_t d = dmask[e.in[sl] ? e.nb[sl] : c];
+        if (e.in[sl] && sl != 3 && (((o >> sl) & 1u) || ((d >> (6 - sl)) & 1u))) m |= (uint8_t)(1u << sl);
+      }
+      sm[c] = m;
+      st[c] = m ? ST_UND : ST_ISO;
+    });
+  } else {
+    rows([&](int i) {
+      const int p0 = rp[i], p1 = rp[i + 1];
+      double aii = 0.0, nm = 0.0, sum = 0.0;
+      for (int p = p0; p < p1; ++p) {
+        const double v = a[p];
+        sum = sum + v;
+        if (ci[p] == i) aii = v;
+        else if (-v > nm) nm = -v;
+      }
+      const bool weak = fabs(sum) > mrs * fabs(aii) || !(nm > 0.0);
+      const double thr = theta * nm;
+      for (int p = p0; p < p1; ++p) dir[p] = (!weak && ci[p] != i && -a[p] >= thr) ? 1 : 0;
+    });
+    __syncthreads();
+    rows([&](int i) {
+      int deg = 0;
+      for (int p = rp[i]; p < rp[i + 1]; ++p) {
+        const int j = ci[p];
+        uint8_t v = 0;
+        if (j != i) {
+          const int q = find_col(rp, ci, j, i);
+          v = dir[p] | (q >= 0 ? dir[q] : (uint8_t)0);
+        }
+        strong[p] = v;
+        deg += v;
+      }
+      st[i] = deg ? ST_UND : ST_ISO;
+    });
+  }
+  __syncthreads();
+  // ---- independent set: keys in A, their maxima over a neighbourhood in B
+  const uint32_t salt = 0x9e3779b9u * (uint32_t)(level + 1);
+  rows([&](int v) { A[v] = st[v] == ST_UND ? fmix32((uint32_t)v + salt) : 0u; });
+  __syncthreads();
+  for (;;) {
+    rows([&](int v) {
+      uint32_t m = A[v];
+      each(v, [&](int, int w) { m = max(m, A[w]); return true; });
+      B[v] = m;
+    });
+    __syncthreads();
+    bool left = false;
+    uint32_t now[SMALL_V];                              // A is read by this pass: changed after it
+#pragma unroll
+    for (int k = 0; k < SMALL_V; ++k) {
+      const int v = t + k * SMALL_T;
+      if (v >= n) continue;
+      now[k] = A[v];
+      if (st[v] != ST_UND) continue;
+      uint32_t m = B[v];
+      each(v, [&](int, int w) { m = max(m, B[w]); return true; });
+      if (m == ~0u) { st[v] = ST_OUT; now[k] = 0u; }
+      else if (m == now[k]) { st[v] = ST_ROOT; now[k] = ~0u; }
+      else left = true;
+    }
+    if (!__syncthreads_or(left)) break;
+#pragma unroll
+    for (int k = 0; k < SMALL_V; ++k)
+      if (t + k * SMALL_T < n) A[t + k * SMALL_T] = now[k];
+    __syncthreads();
+  }
+  // ---- roots numbered in A (SMALL_V consecutive rows per thread)
+  int nc = 0, x = 0;
+#pragma unroll
+  for (int k = 0; k < SMALL_V; ++k) x += t * SMALL_V + k < n && st[t * SMALL_V + k] == ST_ROOT ? 1 : 0;
+  x = scan(x, nc);
+#pragma unroll
+  for (int k = 0; k < SMALL_V; ++k) {
+    const int v = t * SMALL_V + k;
+    if (v >= n) continue;
+    A[v] = (uint32_t)x;
+    x += st[v] == ST_ROOT ? 1 : 0;
+  }
+  __syncthreads();
+  // the host takes it from here
+  if (t == 0) {
+    W[W_NC] = nc;
+    const double o[3] = {(double)W[W_FLAG], (double)W[W_NNZ], (double)nc};
+    post_host(post, seq, o, 3);
+  }
+  if (nc == 0 || nc >= n) return;
+  // ---- aggregates: first pass in B, then agg (and A)
+  rows([&](int v) {
+    int g = -1;
+    if (st[v] == ST_ROOT) g = (int)A[v];
+    else if (st[v] != ST_ISO)
+      each(v, [&](int, int w) {
+        if (st[w] != ST_ROOT) return true;
+        g = (int)A[w];
+        return false;
+      });
+    B[v] = (uint32_t)g;
+  });
+  __syncthreads();
+  rows([&](int v) {
+    int g = (int)B[v];
+    if (g < 0 && st[v] != ST_ISO) {
+      double bw = -1.0;
+      each(v, [&](int p, int w) {
+        const int ag = (int)B[w];
+        if (ag < 0) return true;
+        const double x2 = fabs(ST7 ? ap7[(int64_t)p * n + v] : a[p]);
+        if (x2 > bw || (x2 == bw && ag < g)) { bw = x2; g = ag; }
+        return true;
+      });
+      if (g < 0) atomicOr(W + W_FLAG, 1);   // cannot happen for a maximal distance-2 set
+    }
+    A[v] = (uint32_t)g;
+    agg[v] = g;
+  });
+  __syncthreads();
+  // ---- members: counts in B, their scan, the lists sorted in ml
+  for (int v = t; v < nc; v += SMALL_T) B[v] = 0;
+  __syncthreads();
+  rows([&](int v) { if ((int)A[v] >= 0) atomicAdd(&B[A[v]], 1u); });
+  __syncthreads();
+  int all = 0;
+  x = 0;
+#pragma unroll
+  for (int k = 0; k < SMALL_V; ++k) x += t * SMALL_V + k < nc ? (int)B[t * SMALL_V + k] : 0;
+  x = scan(x, all);
+#pragma unroll
+  for (int k = 0; k < SMALL_V; ++k) {
+    const int v = t * SMALL_V + k;
+    if (v >= nc) continue;
+    const int c = (int)B[v];
+    B[v] = (uint32_t)x;
+    mptr[v] = x;
+    x += c;
+  }
+  if (t == 0) mptr[nc] = all;
+  __syncthreads();
+  rows([&](int v) { if ((int)A[v] >= 0) ml[atomicAdd(&B[A[v]], 1u)] = (uint16_t)v; });
+  __syncthreads();
+  // list I: ml[B[I - 1], B[I]); its rows' entries, the row's candidates
+  for (int I = t; I < nc; I += SMALL_T) {
+    const int b = I ? (int)B[I - 1] : 0, e = (int)B[I];
+    for (int y = b + 1; y < e; ++y) {
+      const uint16_t v = ml[y];
+      int z = y - 1;
+      while (z >= b && ml[z] > v) { ml[z + 1] = ml[z]; --z; }
+      ml[z + 1] = v;
+    }
+    int c = 0;
+    for (int y = b; y < e; ++y) {
+      const int v = ml[y];
+      mem[y] = v;
+      if constexpr (ST7) {
+        const cell7 q = cell7_of(v, nx, ny, nz);
+#pragma unroll
+        for (int sl = 0; sl < 7; ++sl) c += q.in[sl] ? 1 : 0;
+      } else {
+        c += rp[v + 1] - rp[v];
+      }
+    }
+    cnt[I] = c;
+    A[I] = (uint32_t)c;
+  }
+  __syncthreads();
+  x = 0;
+#pragma unroll
+  for (int k = 0; k < SMALL_V; ++k) x += t * SMALL_V + k < nc ? (int)A[t * SMALL_V + k] : 0;
+  x = scan(x, all);
+#pragma unroll
+  for (int k = 0; k < SMALL_V; ++k) {
+    const int v = t * SMALL_V + k;
+    if (v >= nc) continue;
+    off[v] = x;
+    x += (int)A[v];
+  }
+}
+
+// k_galerkin_copy for a small level, with the scan of the row lengths: every
+// workgroup adds up the lengths before its rows
+template <class T>
+__global__ __launch_bounds__(256) void k_small_copy(int n, int *__restrict__ W, const int32_t *__restrict__ cnt,
+                                                    const int32_t *__restrict__ off, const int32_t *__restrict__ skey,
+                                                    const double *__restrict__ sval, int32_t *__restrict__ crp,
+                                                    int32_t *__restrict__ cci, double *__restrict__ ca,
+                                                    float *__restrict__ cap, T *__restrict__ dl1) {
+  const int nc = W[W_NC], b0 = blockIdx.x * SCAN_T;
+  if (nc >= n || b0 >= nc) return;
+  int x = 0, ex;
+  for (int i = threadIdx.x; i < b0; i += SCAN_T) x += cnt[i];
+  const int before = scan_block(x, ex);
+  const int I = b0 + threadIdx.x, m = I < nc ? cnt[I] : 0;
+  __syncthreads();
+  scan_block(m, ex);
+  if (I >= nc) return;
+  const int o = before + ex;
+  crp[I] = o;
+  if (I == nc - 1) {
+    crp[nc] = o + m;
+    W[W_NNZ] = o + m;
+  }
+  gal_copy_row<T>(I, m, off[I], o, skey, sval, cci, ca, cap, dl1);
+}
+
+static bool small_keys_ok(int n, int level) {
+  const uint32_t salt = 0x9e3779b9u * (uint32_t)(level + 1);
+  return n <= SMALL_N && MIS_AT0 - salt >= (uint32_t)n && MIS_AT1 - salt >= (uint32_t)n;
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -1680,18 +2164,6 @@ static rs_status level0_as_coarsest(rs_cpr_s *M, hipStream_t s) {
 // just built) and once at the end (rs_amg_finish); the temporaries of all
 // levels stay in M->setup until then, because pool memory that is given back
 // may go to work on another stream at once.
-enum {
-  W_FLAG = 0,          // aggregation error
-  W_NNZ,               // entries of the coarse level built last
-  W_NC,                // roots of the level
-  W_LU,                // singular coarsest matrix
-  W_AUX,               // a total of the smoothed product
-  W_SM,                // the second stage's set-up flags (rs_cpr_setup)
-  W_UND = 8,           // two batches' round flags
-  W_TOTAL = W_UND + 2 * MIS_BATCH
-};
-static_assert(W_TOTAL <= RS_READ_WORDS, "one read");
-
 int *rs_amg_word_sm(amg_setup *U) { return U->words.as<int>() + W_SM; }
 
 rs_status rs_amg_begin(amg_setup *U, hipStream_t s) {
@@ -1710,6 +2182,74 @@ rs_status rs_amg_finish(rs_cpr_s *M, amg_setup *U, int *sm, hipStream_t s) {
   if (h[W_LU]) return RS_E_SINGULAR;
   if (U->counted) M->lev.back()->nnz = h[W_NNZ];
   *sm = h[W_SM];
+  return RS_OK;
+}
+
+// One level of at most SMALL_N rows (T.dir: its directed strengths on the fine
+// level): three launches, all sized by n, and a host read of the number of
+// aggregates that waits for the first of them only.
+static rs_status small_level(rs_cpr_s *M, amg_setup *U, amg_tmp &T, int l, bool st7, bool *coarsened, hipStream_t s) {
+  const rs_cpr_opts &o = M->o;
+  const grid3 &g = M->A->g;
+  amg_level *L = M->lev[l];
+  const int n = L->n, *d_nc = U->words.as<int>() + W_NC;
+  const int64_t ncand = L->nnz;                 // or its bound
+  int *W = U->words.as<int>();
+  const double *ap7 = M->D->ap7.as<double>();
+  const int32_t *rp = L->rp.as<int32_t>(), *ci = L->ci.as<int32_t>();
+  if (!st7) {
+    RS_TRY(T.dir.alloc(ncand));
+    RS_TRY(T.strong.alloc(ncand));
+  }
+  RS_TRY(T.cnt.alloc(sizeof(int32_t) * ((size_t)n + 1)));
+  RS_TRY(T.off.alloc(sizeof(int32_t) * ((size_t)n + 1)));
+  RS_TRY(T.skey.alloc(sizeof(int32_t) * (ncand + 1)));
+  RS_TRY(T.sval.alloc(sizeof(double) * (ncand + 1)));
+  RS_TRY(L->mptr.alloc(sizeof(int32_t) * ((size_t)n + 1)));
+  RS_TRY(L->mem.alloc(sizeof(int32_t) * ((size_t)n + 1)));
+  rs_post *post = nullptr;
+  RS_TRY(rs_post_slot(&post));
+  const uint64_t seq = rs_post_next(post);
+  int32_t *agg = L->agg.as<int32_t>(), *mptr = L->mptr.as<int32_t>(), *mem = L->mem.as<int32_t>();
+  int32_t *cnt = T.cnt.as<int32_t>(), *off = T.off.as<int32_t>(), *skey = T.skey.as<int32_t>();
+  double *sval = T.sval.as<double>();
+  if (st7) {
+    k_small_level<true><<<1, SMALL_T, 0, s>>>(n, l, g.nx, g.ny, g.nz, ap7, T.dir.as<uint8_t>(), nullptr, nullptr, nullptr,
+                                              o.theta, o.max_row_sum, nullptr, nullptr, agg, mptr, mem, cnt, off, W, post,
+                                              seq);
+    k_galerkin_lanes<rows_7><<<rs_grid(n, 16), 256, 0, s>>>(n, d_nc, mptr, mem, rows_7{g.nx, g.ny, g.nz, ap7}, agg, off,
+                                                            skey, sval, cnt);
+  } else {
+    k_small_level<false><<<1, SMALL_T, 0, s>>>(n, l, 0, 0, 0, nullptr, nullptr, rp, ci, L->a.as<double>(), o.theta,
+                                               o.max_row_sum, T.dir.as<uint8_t>(), T.strong.as<uint8_t>(), agg, mptr, mem,
+                                               cnt, off, W, post, seq);
+    k_galerkin_lanes<rows_csr><<<rs_grid(n, 16), 256, 0, s>>>(n, d_nc, mptr, mem, rows_csr{rp, ci, L->a.as<double>()}, agg,
+                                                              off, skey, sval, cnt);
+  }
+  std::unique_ptr<amg_level> C(new amg_level());
+  RS_TRY(C->rp.alloc(sizeof(int32_t) * ((size_t)n + 1)));
+  RS_TRY(C->ci.alloc(sizeof(int32_t) * (ncand + 1)));
+  RS_TRY(C->a.alloc(sizeof(double) * (ncand + 1)));
+  RS_TRY(C->dl1.alloc((M->prec == 64 ? sizeof(double) : sizeof(float)) * ((size_t)n + 1)));
+  if (M->prec == 32) RS_TRY(C->ap.alloc(sizeof(float) * (ncand + 1)));
+  if (M->prec == 64)
+    k_small_copy<double><<<rs_grid(n), SCAN_T, 0, s>>>(n, W, cnt, off, skey, sval, C->rp.as<int32_t>(), C->ci.as<int32_t>(),
+                                                       C->a.as<double>(), nullptr, C->dl1.as<double>());
+  else
+    k_small_copy<float><<<rs_grid(n), SCAN_T, 0, s>>>(n, W, cnt, off, skey, sval, C->rp.as<int32_t>(), C->ci.as<int32_t>(),
+                                                      C->a.as<double>(), C->ap.as<float>(), C->dl1.as<float>());
+  RS_HIP(hipGetLastError());
+  RS_TRY(rs_wait_post(post, seq, s));
+  if (post->v[0] != 0.0) return RS_E_HIP;
+  if (U->counted) { L->nnz = (int64_t)post->v[1]; U->counted = false; }
+  const int nc = (int)post->v[2];
+  *coarsened = nc > 0 && nc < n;
+  if (!*coarsened) return RS_OK;                // the launches above leave everything alone
+  L->nc = nc;
+  C->n = nc;
+  C->nnz = ncand;
+  U->counted = true;
+  M->lev.push_back(C.release());
   return RS_OK;
 }
 
@@ -1761,6 +2301,15 @@ rs_status rs_amg_build(rs_cpr_s *M, amg_setup *U, hipStream_t s) {
       RS_TRY(no_aggregates());
       break;
     }
+    const int32_t *rp = L->rp.as<int32_t>(), *ci = L->ci.as<int32_t>();
+    if (!o.smooth && small_keys_ok(n, l)) {
+      bool coarsened = false;
+      RS_TRY(small_level(M, U, T, l, st7, &coarsened, s));
+      if (coarsened) continue;
+      RS_TRY(no_aggregates());
+      if (st7) RS_TRY(level0_as_coarsest(M, s));
+      break;
+    }
     // strength: per CSR entry (L->nnz, until it is read the bound that the
     // level's arrays have), or a 7-bit mask per cell on the fine level
     dbuf &strong = T.strong, &state = T.state, &state2 = T.state2, &m1 = T.m1, &id = T.id, &agg1 = T.agg1;
@@ -1769,7 +2318,6 @@ rs_status rs_amg_build(rs_cpr_s *M, amg_setup *U, hipStream_t s) {
     if (st7) RS_TRY(state2.alloc(n));
     else RS_TRY(m1.alloc(sizeof(uint64_t) * n));
     RS_TRY(id.alloc(sizeof(int32_t) * n)); RS_TRY(agg1.alloc(sizeof(int32_t) * n));
-    const int32_t *rp = L->rp.as<int32_t>(), *ci = L->ci.as<int32_t>();
     if (st7) {
       k_strength7_sym<<<rs_grid(n), RS_BLOCK, 0, s>>>(g.nx, g.ny, g.nz, dir.as<uint8_t>(), strong.as<uint8_t>(),
                                                       state.as<uint8_t>());
@@ -1942,9 +2490,17 @@ rs_status rs_amg_build(rs_cpr_s *M, amg_setup *U, hipStream_t s) {
       ncand = L->nnz;
       RS_TRY(skey.alloc(sizeof(int32_t) * (ncand + 1)));
       RS_TRY(sval.alloc(sizeof(double) * (ncand + 1)));
-      if (st7)
+      if (st7 && nc <= GAL_LANES_MAX)
+        k_galerkin_lanes<rows_7><<<rs_grid(nc, 16), 256, 0, s>>>(
+            nc, nullptr, L->mptr.as<int32_t>(), L->mem.as<int32_t>(), rows_7{g.nx, g.ny, g.nz, ap7}, L->agg.as<int32_t>(),
+            off.as<int32_t>(), skey.as<int32_t>(), sval.as<double>(), cnt.as<int32_t>());
+      else if (st7)
         k_galerkin<rows_7><<<rs_grid(nc, GAL_BLOCK), GAL_BLOCK, 0, s>>>(
             nc, L->mptr.as<int32_t>(), L->mem.as<int32_t>(), rows_7{g.nx, g.ny, g.nz, ap7}, L->agg.as<int32_t>(),
+            off.as<int32_t>(), skey.as<int32_t>(), sval.as<double>(), cnt.as<int32_t>());
+      else if (nc <= GAL_LANES_MAX)
+        k_galerkin_lanes<rows_csr><<<rs_grid(nc, 16), 256, 0, s>>>(
+            nc, nullptr, L->mptr.as<int32_t>(), L->mem.as<int32_t>(), rows_csr{rp, ci, L->a.as<double>()}, L->agg.as<int32_t>(),
             off.as<int32_t>(), skey.as<int32_t>(), sval.as<double>(), cnt.as<int32_t>());
       else
         k_galerkin<rows_csr><<<rs_grid(nc, GAL_BLOCK), GAL_BLOCK, 0, s>>>(
