@@ -40,6 +40,7 @@ namespace {
 #pragma clang fp contract(fast)
 #include "quad4.h"
 #include "quadinv.h"
+#include "reduce.h"
 
 // ---- wavefront order --------------------------------------------------------
 // Number of cells (i, j) of an nx x ny layer with i + j < lambda.
@@ -661,6 +662,178 @@ __global__ __launch_bounds__(256) void k_ras_zdiag(int64_t n, int64_t nxy, const
   }
 }
 
+// The three factorisations of overlap 1 in one launch: workgroup (stage, layer)
+// factors a layer as k_ras_setup does, with the diagonal reduced by the Schur
+// term of the layer below in the factors of the stage before (k_ras_zdiag's
+// operations and rounding), a few levels behind the workgroup that forms them.
+//   - the writer wave of a stage that another one reads stores its blocks at
+//     device scope and publishes the number of finished levels;
+//   - the poller wave waits (bounded) until the levels below are there;
+//   - the compute waves load the block rows of the layer below at device scope.
+// Tickets go stage by stage, so a workgroup only waits on one that is already
+// running.  One after another the stages leave most CUs idle (nz workgroups
+// each) and take their chains' sum.  All three, against three launches of
+// k_ras_setup and two of k_ras_zdiag: FP32 538 us for 1337 at 120x90x40, 1067
+// for 2261 at 161x143x67, 1938 for 3305 at 180x220x60; FP64 631 for 1445, 1489
+// for 2636 and 3402 for 4057.  (With the writer's lanes on a cell each instead
+// of on consecutive words FP64 took 964, 3110 and 5409.)
+constexpr int RAS1_DONE = 32;                           // ints from one level count to the next: a cache line each
+template <class T> __device__ __forceinline__ void ld_row_dev(const T *p, T (&o)[4]) {
+  constexpr int N = 4 * sizeof(T) / 8;
+  uint64_t w[N];
+#pragma unroll
+  for (int e = 0; e < N; ++e)
+    w[e] = __hip_atomic_load(reinterpret_cast<uint64_t *>(const_cast<T *>(p)) + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __builtin_memcpy(o, w, sizeof(o));
+}
+// MT: most threads, so that shorter layers have more registers.
+template <class T, int MT>
+__global__ __launch_bounds__(MT) void k_ras1_setup(int nx, int ny, int nz, int64_t n, int LW,
+                                                     const T *__restrict__ t7, T *P0, T *P1, T *P2,
+                                                     int *__restrict__ flag, int *__restrict__ ticket, int *done,
+                                                     int *__restrict__ err) {
+#pragma clang fp contract(off)
+  extern __shared__ __align__(16) unsigned char smem[];
+  T *ring = (T *)smem;                                  // [ny][16]
+  __shared__ int s_t;
+  const int tid = threadIdx.x, NC = 4 * LW;
+  if (tid == 0) s_t = atomicAdd(ticket, 1);
+  __syncthreads();
+  const int tk = __builtin_amdgcn_readfirstlane(s_t);
+  const int stage = tk / nz, k = tk - stage * nz;
+  T *dinv = stage == 0 ? P0 : (stage == 1 ? P1 : P2);
+  const T *below = stage == 1 ? P0 : P1;
+  const bool chained = stage > 0 && k > 0;              // the same for the workgroup
+  int *mine = done + (int64_t)tk * RAS1_DONE;
+  const int64_t nxy = (int64_t)nx * ny, cl = nxy * k;
+  const int Lv = nx + ny - 1;
+  if (tid >= NC + 64) {                                 // poller: two levels ahead of the compute waves' loads
+    const int *at = done + (int64_t)(chained ? tk - nz - 1 : tk) * RAS1_DONE;
+    int have = chained ? 0 : Lv;
+    bool failed = false;
+    auto need = [&](int m) {
+      m = min(m, Lv);
+      int spins = 0;
+      while (have < m && !failed) {
+        have = __hip_atomic_load(const_cast<int *>(at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (have >= m) break;
+        if (++spins > RAS_SPIN_LIMIT) {
+          failed = true;
+          if (tid == NC + 64) atomicOr(err, 1);
+        }
+        __builtin_amdgcn_s_sleep(1);
+      }
+    };
+    need(2);
+    __syncthreads();
+    for (int lam = 0; lam < Lv; ++lam) {
+      need(lam + 3);
+      __syncthreads();
+      __syncthreads();
+    }
+    return;
+  }
+  if (tid >= NC) {                                      // writer
+    const int w = tid - NC;
+    auto write_level = [&](int m) {
+      if (m < 0) return;
+      const int jlo = max(0, m - nx + 1), jhi = min(ny - 1, m);
+      if (stage < 2) {                                  // 8 bytes a lane, a cell's words side by side
+        constexpr int N = 16 * sizeof(T) / 8;
+        const uint64_t *v = (const uint64_t *)ring;
+        for (int x = jlo * N + w; x < (jhi + 1) * N; x += 64) {
+          const int j = x / N, e = x - j * N;
+          __hip_atomic_store(reinterpret_cast<uint64_t *>(dinv + (cl + (int64_t)j * nx + (m - j)) * 16) + e, v[x],
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        return;
+      }
+      for (int j = jlo + w; j <= jhi; j += 64) {
+        T *o = dinv + (cl + (int64_t)j * nx + (m - j)) * 16;
+#pragma unroll
+        for (int e = 0; e < 16; e += 4)
+          *(typename vec4t<T>::type *)(o + e) = *(const typename vec4t<T>::type *)(ring + j * 16 + e);
+      }
+    };
+    auto publish = [&](int m) {                         // levels below m are stored
+      if (stage == 2) return;
+      stores_done();
+      if (w == 0 && m > 0) __hip_atomic_store(mine, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    __syncthreads();
+    for (int lam = 0; lam < Lv; ++lam) {
+      publish(lam - 1);                                 // the stores of the level before last
+      write_level(lam - 1);
+      __syncthreads();
+      __syncthreads();
+    }
+    publish(Lv - 1);
+    write_level(Lv - 1);
+    publish(Lv);
+    return;
+  }
+  const int q = tid >> 2, r = tid & 3, wq = (tid & 63) & ~3;
+  const int j = min(q, ny - 1);
+  struct rows { T v[8][4]; };
+  // this lane's row of A~_cc, A~_{c,c-nx}, A~_{c,c-1}, A~_{c-nx,c}, A~_{c-1,c}
+  // and, chained, of A~_{c,c-nxy}, A~_{c-nxy,c} and D^{-1} below, one level ahead
+  auto load = [&](int lam, rows &p) {
+    const int i = min(max(lam - j, 0), nx - 1);
+    const int64_t c = cl + (int64_t)j * nx + i;
+    const int64_t qy = j > 0 ? c - nx : c, qx = i > 0 ? c - 1 : c;
+    ld4v(t7 + (3 * n + c) * 16 + 4 * r, p.v[0]);
+    ld4v(t7 + (n + c) * 16 + 4 * r, p.v[1]);
+    ld4v(t7 + (2 * n + c) * 16 + 4 * r, p.v[2]);
+    ld4v(t7 + (5 * n + qy) * 16 + 4 * r, p.v[3]);
+    ld4v(t7 + (4 * n + qx) * 16 + 4 * r, p.v[4]);
+    if (chained) {
+      ld4v(t7 + c * 16 + 4 * r, p.v[5]);
+      ld4v(t7 + (6 * n + c - nxy) * 16 + 4 * r, p.v[6]);
+      ld_row_dev(below + (c - nxy) * 16 + 4 * r, p.v[7]);
+    }
+  };
+  __syncthreads();
+  rows p;
+  load(0, p);
+  int bad = 0;
+  for (int lam = 0; lam < Lv; ++lam) {
+    const int i = lam - q;
+    const bool act = q < ny && i >= 0 && i < nx;        // the same for the four lanes of the cell
+    T orow[4] = {0, 0, 0, 0};
+    int ok = r;
+    if (act) {
+      double Lr[4], Rr[4];
+#pragma unroll
+      for (int cc = 0; cc < 4; ++cc) Lr[cc] = (double)p.v[0][cc];
+      if (chained) {
+        quad_schur<T>(Lr, p.v[7], p.v[6], p.v[5]);
+#pragma unroll
+        for (int cc = 0; cc < 4; ++cc) Lr[cc] = (double)(T)Lr[cc];   // stored as T between the stages
+      }
+      T dq[4];                                          // -y, then -x (ascending column)
+      if (q > 0) {
+        ld4v(ring + (q - 1) * 16 + 4 * r, dq);
+        quad_schur<T>(Lr, dq, p.v[3], p.v[1]);
+      }
+      if (i > 0) {
+        ld4v(ring + q * 16 + 4 * r, dq);
+        quad_schur<T>(Lr, dq, p.v[4], p.v[2]);
+      }
+      bad |= quad_inverse(Lr, Rr, r, wq, ok);
+#pragma unroll
+      for (int cc = 0; cc < 4; ++cc) orow[cc] = (T)Rr[cc];
+    }
+    if (lam + 1 < Lv) load(lam + 1, p);
+    __syncthreads();                                    // level lam-1 reads done
+    if (act) {
+#pragma unroll
+      for (int cc = 0; cc < 4; ++cc) ring[q * 16 + 4 * ok + cc] = orow[cc];
+    }
+    __syncthreads();                                    // level lam visible
+  }
+  if (bad) atomicOr(flag, bad);
+}
+
 // rh = P^{-1} (r~ - A~[:,0] x_p - A~_{c,c-nxy} yb_{c-nxy}) in wavefront order,
 // with yb the forward result of the layer below (wavefront order) and no
 // z term on the first layer; x_p carries nx*ny zero guards on each side.
@@ -800,6 +973,23 @@ rs_status rs_ras_setup_run(rs_cpr_s *M, int *flag, hipStream_t s) {
     if (!ov1) {
       factor(nullptr, M->dinv2.as<T>());
       scale(M->dinv2.as<T>(), M->rblk.as<T>());
+    } else if (4 * lw + 128 <= 1024 && u == 1) {        // up to 224 lines: compute, writer and poller waves fit
+      // P0 (plain layers), P1 (middle of each extension, the owned cells':
+      // dinv2), P2 (top of each extension), chained
+      int *ctl = M->rctl.as<int>();
+      RS_TRY(M->rdone.alloc(sizeof(int) * (3 * (size_t)g.nz * RAS1_DONE)));
+      RS_TRY(rs_fill32(M->rdone.p, 0, 3 * (int64_t)g.nz * RAS1_DONE, s));
+      auto chain = [&](auto kernel) {
+        kernel<<<3 * g.nz, 4 * lw + 128, lds, s>>>(g.nx, g.ny, g.nz, g.n, lw, t7, M->rdv0.as<T>(), M->dinv2.as<T>(),
+                                                   M->rdv2.as<T>(), flag, ctl, M->rdone.as<int>(), ctl + RAS_TICKETS);
+      };
+      if (4 * lw + 128 <= 512) chain(k_ras1_setup<T, 512>);
+      else if (4 * lw + 128 <= 768) chain(k_ras1_setup<T, 768>);
+      else chain(k_ras1_setup<T, 1024>);
+      scale(M->rdv0.as<T>(), M->rblk.as<T>());
+      scale(M->dinv2.as<T>(), M->rblk1.as<T>());
+      scale(M->rdv2.as<T>(), M->rblk2.as<T>());
+      k_ras_zero<T><<<rs_grid(g.n), RS_BLOCK, 0, s>>>(g.n, M->rzero.as<T>());
     } else {
       // P0 (plain layers), P1 (middle of each extension, the owned cells':
       // dinv2), P2 (top of each extension).  The reduced diagonals E live in
