@@ -688,47 +688,57 @@ __global__ __launch_bounds__(256) void k_galerkin_lanes(int nc, const int *__res
   }
 }
 
-// Row I of the coarse level, m entries, from the scratch at b to o.  Also the
-// coarse level's l1 diagonal (as k_l1diag, the same additions in the same
-// order) and, when cap is given, its FP32 values (as k_cast_f32), so the
-// coarse level needs no pass of its own for them.
+// Row I of the coarse level, m entries, from the scratch at b to o, by the 16
+// lanes of a DPP row.  Also the coarse level's l1 diagonal (as k_l1diag, the
+// same additions in the same order; adding 0.0 for an entry that is not there
+// leaves the sum) and, when cap is given, its FP32 values (as k_cast_f32), so
+// the coarse level needs no pass of its own for them.  Bound by memory: 611
+// thousand rows take 63 us, 101 with a thread per row.
 template <class T>
-__device__ __forceinline__ void gal_copy_row(int I, int m, int b, int o, const int32_t *__restrict__ skey,
+__device__ __forceinline__ void gal_copy_row(int I, int m, int b, int o, int lane, const int32_t *__restrict__ skey,
                                              const double *__restrict__ sval, int32_t *__restrict__ cci,
                                              double *__restrict__ ca, float *__restrict__ cap, T *__restrict__ dl1) {
   double sum = 0.0, aii = 0.0;
-  for (int sb = 0; sb < m; sb += 8) {            // eight entries' loads in flight at once
-    int32_t kv[8];
-    double vv[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      int e = sb + k < m ? sb + k : 0;
-      asm volatile("" : "+v"(e));
-      kv[k] = skey[b + e];
-      vv[k] = sval[b + e];
+  for (int sb = 0; __ballot(sb < m); sb += 16) {
+    const int e = sb + lane;
+    const bool in = e < m;
+    const int k = in ? skey[b + e] : -1;
+    const double v = in ? sval[b + e] : 0.0;
+    if (in) {
+      cci[o + e] = k;
+      ca[o + e] = v;
+      if (cap) cap[o + e] = (float)v;
     }
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-      if (sb + k < m) {
-        cci[o + sb + k] = kv[k];
-        ca[o + sb + k] = vv[k];
-        if (cap) cap[o + sb + k] = (float)vv[k];
-        sum = sum + fabs(vv[k]);
-        if (kv[k] == I) aii = vv[k];
-      }
+    auto add = [&](auto c) {
+      const double x = __hiloint2double(row_bcast<decltype(c)::value>(__double2hiint(v)),
+                                        row_bcast<decltype(c)::value>(__double2loint(v)));
+      sum = sum + fabs(x);
+      if (row_bcast<decltype(c)::value>(k) == I) aii = x;
+    };
+    add(std::integral_constant<int, 0>{}); add(std::integral_constant<int, 1>{}); add(std::integral_constant<int, 2>{});
+    add(std::integral_constant<int, 3>{}); add(std::integral_constant<int, 4>{}); add(std::integral_constant<int, 5>{});
+    add(std::integral_constant<int, 6>{}); add(std::integral_constant<int, 7>{});
+    if (__ballot(sb + 8 < m)) {
+      add(std::integral_constant<int, 8>{}); add(std::integral_constant<int, 9>{});
+      add(std::integral_constant<int, 10>{}); add(std::integral_constant<int, 11>{});
+      add(std::integral_constant<int, 12>{}); add(std::integral_constant<int, 13>{});
+      add(std::integral_constant<int, 14>{}); add(std::integral_constant<int, 15>{});
+    }
   }
   if (sum == 0.0) sum = 1.0;
-  dl1[I] = (T)(aii < 0.0 ? -sum : sum);
+  if (lane == 0 && I >= 0) dl1[I] = (T)(aii < 0.0 ? -sum : sum);
 }
 
 template <class T>
-__global__ void k_galerkin_copy(int nc, const int32_t *__restrict__ off, const int32_t *__restrict__ skey,
-                                const double *__restrict__ sval, const int32_t *__restrict__ crp,
-                                int32_t *__restrict__ cci, double *__restrict__ ca, float *__restrict__ cap,
-                                T *__restrict__ dl1) {
-  int I = blockIdx.x * blockDim.x + threadIdx.x;
-  if (I >= nc) return;
-  gal_copy_row<T>(I, crp[I + 1] - crp[I], off[I], crp[I], skey, sval, cci, ca, cap, dl1);
+__global__ __launch_bounds__(256) void k_galerkin_copy(int nc, const int32_t *__restrict__ off,
+                                                       const int32_t *__restrict__ skey,
+                                                       const double *__restrict__ sval, const int32_t *__restrict__ crp,
+                                                       int32_t *__restrict__ cci, double *__restrict__ ca,
+                                                       float *__restrict__ cap, T *__restrict__ dl1) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int row = (int)(t >> 4), I = row < nc ? row : -1, Ic = max(min(row, nc - 1), 0);
+  const int o = crp[Ic], m = I >= 0 ? crp[Ic + 1] - o : 0;
+  gal_copy_row<T>(I, m, off[Ic], o, (int)(t & 15), skey, sval, cci, ca, cap, dl1);
 }
 
 template <class T>
@@ -1316,8 +1326,10 @@ __global__ void k_fine7(int nx, int ny, int nz, const double *__restrict__ ap7, 
 
 // symmetrised: smask bit s = dmask(c) bit s | dmask(nbr) bit 6-s
 __global__ void k_strength7_sym(int nx, int ny, int nz, const uint8_t *__restrict__ dmask,
-                                uint8_t *__restrict__ smask, uint8_t *__restrict__ state) {
+                                uint8_t *__restrict__ smask, uint8_t *__restrict__ state,
+                                uint8_t *__restrict__ settled, int tiles) {
   const int64_t n = (int64_t)nx * ny * nz, c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (c < tiles) settled[c] = 0;                // the rounds' tiles, fewer than cells
   if (c >= n) return;
   const cell7 e = cell7_of(c, nx, ny, nz);
   uint8_t d[7];
@@ -1337,7 +1349,7 @@ __global__ void k_strength7_sym(int nx, int ny, int nz, const uint8_t *__restric
 // cells around it go to LDS (each hashed once per tile), then m1 of the tile
 // and one cell around it, then the decisions; the states go from st to so, so
 // that every tile sees the round's own.  A tile with nothing undecided copies
-// its states.  A wave takes whole rows, 64 keys wide, so that every index but
+// its states once and is settled.  A wave takes whole rows, 64 keys wide, so that every index but
 // the lane's x is scalar.  On the fine level (level 0) the hash alone is the
 // key: fmix32 is a bijection, so no two cells share one, and the two cells
 // whose hashes are the marks 0 (decided) and ~0 (root) lie past the largest
@@ -1345,7 +1357,7 @@ __global__ void k_strength7_sym(int nx, int ny, int nz, const uint8_t *__restric
 // Bound by instruction issue and each tile's chain of loads.  The 12 rounds at
 // 200x200x100, beside the RAS factorisation: 620 us, against 960 as two passes
 // a round that hashed seven keys per cell and went through memory for m1.
-// und: set if the round left undecided cells; und0 as in k_mis_m1.
+// und: set if the round left undecided cells; settled: per tile, zero at first.
 constexpr int MX = 60, MY = 8, MZ = 4, MIS_T = 512;
 // index + 0x9e3779b9 of the cells with hash 0 and ~0 (fmix32 inverted)
 constexpr uint32_t MIS_AT0 = 0u, MIS_AT1 = 0x331da083u;
@@ -1358,11 +1370,13 @@ static_assert(MIS_AT0 - 0x9e3779b9u > (uint32_t)(INT32_MAX / 2) && MIS_AT1 - 0x9
               "KEY32: both past the largest grid");
 __global__ __launch_bounds__(MIS_T) void k_mis7_round(int nx, int ny, int nz, const uint8_t *__restrict__ smask,
                                                       const uint8_t *__restrict__ st, uint8_t *__restrict__ so,
-                                                      int *__restrict__ und, int *__restrict__ und0) {
+                                                      int *__restrict__ und, int *__restrict__ und0,
+                                                      uint8_t *__restrict__ settled) {
+  if (und0 && blockIdx.x == 0 && threadIdx.x < MIS_BATCH) und0[threadIdx.x] = 0;
+  if (settled[blockIdx.x]) return;                                // nothing undecided, and both buffers agree
   constexpr int KY = MY + 4, KZ = MZ + 4, HY = MY + 2, HZ = MZ + 2, NW = MIS_T / 64;
   __shared__ uint32_t key[KZ * KY][64], m1[HZ * HY][64];
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (und0 && blockIdx.x == 0 && threadIdx.x < MIS_BATCH) und0[threadIdx.x] = 0;
   const int bx = (nx + MX - 1) / MX, by = (ny + MY - 1) / MY;
   const int x0 = (blockIdx.x % bx) * MX, y0 = (blockIdx.x / bx % by) * MY, z0 = (blockIdx.x / (bx * by)) * MZ;
   const int nxy = nx * ny;
@@ -1399,6 +1413,7 @@ __global__ __launch_bounds__(MIS_T) void k_mis7_round(int nx, int ny, int nz, co
   };
   if (!__syncthreads_or(any)) {
     store_own();
+    if (threadIdx.x == 0) settled[blockIdx.x] = 1;
     return;
   }
   constexpr int KR = KY * KZ / NW;                                // 12 rows of keys per wave
@@ -1461,11 +1476,10 @@ __global__ __launch_bounds__(MIS_T) void k_mis7_round(int nx, int ny, int nz, co
   if (__syncthreads_or(left) && threadIdx.x == 0) *und = 1;
 }
 
-// (z, nz as in k_agg1)
+// (also the root cell of each aggregate)
 __global__ void k_agg1_7(int nx, int ny, int nz, const uint8_t *__restrict__ smask, const uint8_t *__restrict__ state,
-                         const int32_t *__restrict__ id, int32_t *__restrict__ agg1, int32_t *__restrict__ z, int nzr) {
+                         const int32_t *__restrict__ id, int32_t *__restrict__ agg1, int32_t *__restrict__ root) {
   const int64_t n = (int64_t)nx * ny * nz, c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (c < nzr) z[c] = 0;
   if (c >= n) return;
   const cell7 e = cell7_of(c, nx, ny, nz);
   int g = -1;
@@ -1478,7 +1492,7 @@ __global__ void k_agg1_7(int nx, int ny, int nz, const uint8_t *__restrict__ sma
     st[sl] = state[q];
     ids[sl] = id[q];
   }
-  if (st[3] == ST_ROOT) g = ids[3];
+  if (st[3] == ST_ROOT) root[g = ids[3]] = (int32_t)c;
   else if (st[3] != ST_ISO)
 #pragma unroll
     for (int sl = 6; sl >= 0; --sl)               // the first root in slot order wins
@@ -1516,17 +1530,57 @@ __global__ void k_agg2_7(int nx, int ny, int nz, const uint8_t *__restrict__ sma
   agg[c] = g;
 }
 
-__global__ void k_cand7(int nc, int nx, int ny, int nz, const int32_t *__restrict__ mptr, const int32_t *__restrict__ mem,
-                        int32_t *__restrict__ cand) {
+// The members of each aggregate on the grid: cells within two steps of its
+// root (roots take their neighbours, the rest join a neighbour's), so a thread
+// per aggregate looks at the 25 of them, in ascending order.  FILL false: their
+// number and that of their rows' entries; true: the list at mptr.  Counting and
+// filling over all cells with atomics, sorting the lists and counting the
+// entries took 174 us at 200x200x100; this takes 32.
+template <bool FILL>
+__global__ __launch_bounds__(256) void k_members7(int nc, int nx, int ny, int nz, const int32_t *__restrict__ root,
+                                                  const int32_t *__restrict__ agg, int32_t *__restrict__ cnt,
+                                                  int32_t *__restrict__ cand, const int32_t *__restrict__ mptr,
+                                                  int32_t *__restrict__ mem) {
   const int I = blockIdx.x * blockDim.x + threadIdx.x;
   if (I >= nc) return;
-  int cnt = 0;
-  for (int x = mptr[I]; x < mptr[I + 1]; ++x) {
-    const cell7 e = cell7_of(mem[x], nx, ny, nz);
+  const int c = root[I], nxy = nx * ny, k = c / nxy, j = (c - k * nxy) / nx, i = c - k * nxy - j * nx;
+  int at = FILL ? mptr[I] : 0, m = 0, e = 0;
 #pragma unroll
-    for (int sl = 0; sl < 7; ++sl) cnt += e.in[sl] ? 1 : 0;
+  for (int dz = -2; dz <= 2; ++dz) {
+    const int ry = 2 - (dz < 0 ? -dz : dz);
+    int g[13];                                          // one plane's loads at once
+    int w = 0;
+#pragma unroll
+    for (int dy = -ry; dy <= ry; ++dy) {
+      const int rx = ry - (dy < 0 ? -dy : dy);
+#pragma unroll
+      for (int dx = -rx; dx <= rx; ++dx, ++w) {
+        const bool in = (unsigned)(i + dx) < (unsigned)nx && (unsigned)(j + dy) < (unsigned)ny &&
+                        (unsigned)(k + dz) < (unsigned)nz;
+        const int a = agg[in ? c + dz * nxy + dy * nx + dx : c];
+        g[w] = in ? a : -1;
+      }
+    }
+    w = 0;
+#pragma unroll
+    for (int dy = -ry; dy <= ry; ++dy) {
+      const int rx = ry - (dy < 0 ? -dy : dy);
+#pragma unroll
+      for (int dx = -rx; dx <= rx; ++dx, ++w) {
+        if (g[w] != I) continue;
+        if (FILL) {
+          mem[at++] = c + dz * nxy + dy * nx + dx;
+        } else {
+          ++m;
+          e += 1 + (i + dx > 0) + (i + dx < nx - 1) + (j + dy > 0) + (j + dy < ny - 1) + (k + dz > 0) + (k + dz < nz - 1);
+        }
+      }
+    }
   }
-  cand[I] = cnt;
+  if (!FILL) {
+    cnt[I] = m;
+    cand[I] = e;
+  }
 }
 
 // x = Cinv b, one wave per row.
@@ -2086,29 +2140,28 @@ __global__ __launch_bounds__(SMALL_T) void k_small_level(int n, int level, int n
 }
 
 // k_galerkin_copy for a small level, with the scan of the row lengths: every
-// workgroup adds up the lengths before its rows
+// workgroup (16 rows) adds up the lengths before its own
 template <class T>
 __global__ __launch_bounds__(256) void k_small_copy(int n, int *__restrict__ W, const int32_t *__restrict__ cnt,
                                                     const int32_t *__restrict__ off, const int32_t *__restrict__ skey,
                                                     const double *__restrict__ sval, int32_t *__restrict__ crp,
                                                     int32_t *__restrict__ cci, double *__restrict__ ca,
                                                     float *__restrict__ cap, T *__restrict__ dl1) {
-  const int nc = W[W_NC], b0 = blockIdx.x * SCAN_T;
+  const int nc = W[W_NC], b0 = blockIdx.x * 16, lane = threadIdx.x & 15, q = threadIdx.x >> 4;
   if (nc >= n || b0 >= nc) return;
   int x = 0, ex;
   for (int i = threadIdx.x; i < b0; i += SCAN_T) x += cnt[i];
-  const int before = scan_block(x, ex);
-  const int I = b0 + threadIdx.x, m = I < nc ? cnt[I] : 0;
-  __syncthreads();
-  scan_block(m, ex);
-  if (I >= nc) return;
-  const int o = before + ex;
-  crp[I] = o;
-  if (I == nc - 1) {
-    crp[nc] = o + m;
-    W[W_NNZ] = o + m;
+  int o = scan_block(x, ex);
+  for (int k = 0; k < q; ++k) o += cnt[min(b0 + k, nc - 1)];
+  const int I = b0 + q < nc ? b0 + q : -1, m = I >= 0 ? cnt[I] : 0;
+  if (I >= 0 && lane == 0) {
+    crp[I] = o;
+    if (I == nc - 1) {
+      crp[nc] = o + m;
+      W[W_NNZ] = o + m;
+    }
   }
-  gal_copy_row<T>(I, m, off[I], o, skey, sval, cci, ca, cap, dl1);
+  gal_copy_row<T>(I, m, off[max(I, 0)], o, lane, skey, sval, cci, ca, cap, dl1);
 }
 
 static bool small_keys_ok(int n, int level) {
@@ -2233,10 +2286,10 @@ static rs_status small_level(rs_cpr_s *M, amg_setup *U, amg_tmp &T, int l, bool 
   RS_TRY(C->dl1.alloc((M->prec == 64 ? sizeof(double) : sizeof(float)) * ((size_t)n + 1)));
   if (M->prec == 32) RS_TRY(C->ap.alloc(sizeof(float) * (ncand + 1)));
   if (M->prec == 64)
-    k_small_copy<double><<<rs_grid(n), SCAN_T, 0, s>>>(n, W, cnt, off, skey, sval, C->rp.as<int32_t>(), C->ci.as<int32_t>(),
+    k_small_copy<double><<<rs_grid(n, 16), SCAN_T, 0, s>>>(n, W, cnt, off, skey, sval, C->rp.as<int32_t>(), C->ci.as<int32_t>(),
                                                        C->a.as<double>(), nullptr, C->dl1.as<double>());
   else
-    k_small_copy<float><<<rs_grid(n), SCAN_T, 0, s>>>(n, W, cnt, off, skey, sval, C->rp.as<int32_t>(), C->ci.as<int32_t>(),
+    k_small_copy<float><<<rs_grid(n, 16), SCAN_T, 0, s>>>(n, W, cnt, off, skey, sval, C->rp.as<int32_t>(), C->ci.as<int32_t>(),
                                                       C->a.as<double>(), C->ap.as<float>(), C->dl1.as<float>());
   RS_HIP(hipGetLastError());
   RS_TRY(rs_wait_post(post, seq, s));
@@ -2318,9 +2371,11 @@ rs_status rs_amg_build(rs_cpr_s *M, amg_setup *U, hipStream_t s) {
     if (st7) RS_TRY(state2.alloc(n));
     else RS_TRY(m1.alloc(sizeof(uint64_t) * n));
     RS_TRY(id.alloc(sizeof(int32_t) * n)); RS_TRY(agg1.alloc(sizeof(int32_t) * n));
+    const unsigned tiles = (unsigned)(((g.nx + MX - 1) / MX) * ((g.ny + MY - 1) / MY)) * ((g.nz + MZ - 1) / MZ);
     if (st7) {
+      RS_TRY(T.settled.alloc(tiles));
       k_strength7_sym<<<rs_grid(n), RS_BLOCK, 0, s>>>(g.nx, g.ny, g.nz, dir.as<uint8_t>(), strong.as<uint8_t>(),
-                                                      state.as<uint8_t>());
+                                                      state.as<uint8_t>(), T.settled.as<uint8_t>(), (int)tiles);
     } else {
       k_strength_dir<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, rp, ci, L->a.as<double>(), o.theta, o.max_row_sum, dir.as<uint8_t>());
       k_strength_sym<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, rp, ci, dir.as<uint8_t>(), strong.as<uint8_t>(), state.as<uint8_t>());
@@ -2338,10 +2393,9 @@ rs_status rs_amg_build(rs_cpr_s *M, amg_setup *U, hipStream_t s) {
         const int *prev = b ? und + b - 1 : nullptr;
         int *und0 = b ? nullptr : next;
         if (st7) {
-          const unsigned tiles = (unsigned)(((g.nx + MX - 1) / MX) * ((g.ny + MY - 1) / MY)) * ((g.nz + MZ - 1) / MZ);
           uint8_t *a = state.as<uint8_t>(), *a2 = state2.as<uint8_t>();
           k_mis7_round<<<tiles, MIS_T, 0, s>>>(g.nx, g.ny, g.nz, strong.as<uint8_t>(), b & 1 ? a2 : a, b & 1 ? a : a2,
-                                               und + b, und0);
+                                               und + b, und0, T.settled.as<uint8_t>());
         } else {
           k_mis_m1<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, l, rp, ci, strong.as<uint8_t>(), state.as<uint8_t>(),
                                                    m1.as<uint64_t>(), prev, und0);
@@ -2361,12 +2415,14 @@ rs_status rs_amg_build(rs_cpr_s *M, amg_setup *U, hipStream_t s) {
       if (st7) RS_TRY(level0_as_coarsest(M, s));
       break;
     }
-    // per coarse row counters (nc + 1 <= n), zeroed by the first aggregation pass
+    // per coarse row counters (nc + 1 <= n), zeroed by the first CSR aggregation pass
     dbuf &off = T.off, &skey = T.skey, &sval = T.sval, &cnt = T.cnt;
     RS_TRY(cnt.alloc(sizeof(int32_t) * ((size_t)nc + 1)));
     if (st7) {
+      RS_TRY(T.root.alloc(sizeof(int32_t) * nc));
       k_agg1_7<<<rs_grid(n), RS_BLOCK, 0, s>>>(g.nx, g.ny, g.nz, strong.as<uint8_t>(), state.as<uint8_t>(),
-                                               id.as<int32_t>(), agg1.as<int32_t>(), cnt.as<int32_t>(), nc + 1);
+                                               id.as<int32_t>(), agg1.as<int32_t>(), T.root.as<int32_t>());
+      if (o.smooth) RS_TRY(rs_fill32(cnt.p, 0, (int64_t)nc + 1, s));
       k_agg2_7<<<rs_grid(n), RS_BLOCK, 0, s>>>(g.nx, g.ny, g.nz, strong.as<uint8_t>(), ap7, state.as<uint8_t>(),
                                                agg1.as<int32_t>(), L->agg.as<int32_t>(), W + W_FLAG);
     } else {
@@ -2467,25 +2523,31 @@ rs_status rs_amg_build(rs_cpr_s *M, amg_setup *U, hipStream_t s) {
       RS_HIP(hipGetLastError());
       L->sa = true;
     } else {
-      // members of each aggregate, ascending
+      // members of each aggregate, ascending; candidates of the Galerkin
+      // product: the members' row entries, at most this level's nnz
       RS_TRY(L->mptr.alloc(sizeof(int32_t) * (nc + 1)));
-      RS_TRY(tfill.alloc(sizeof(int32_t) * ((size_t)nc + 1)));
-      k_count_members<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, L->agg.as<int32_t>(), cnt.as<int32_t>(), tfill.as<int32_t>(),
-                                                      nc + 1);
-      RS_HIP(hipGetLastError());
-      // members: at most n (no host read of the exact count)
-      RS_TRY(scan(cnt, L->mptr, (int64_t)nc + 1, nullptr, nullptr));
       RS_TRY(L->mem.alloc(sizeof(int32_t) * ((size_t)n + 1)));
-      k_fill_members<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, L->agg.as<int32_t>(), L->mptr.as<int32_t>(), tfill.as<int32_t>(),
-                                                     L->mem.as<int32_t>());
-      k_sort_members<<<rs_grid(nc), RS_BLOCK, 0, s>>>(nc, L->mptr.as<int32_t>(), L->mem.as<int32_t>());
-      RS_HIP(hipGetLastError());
-      // Galerkin product
       RS_TRY(off.alloc(sizeof(int32_t) * (nc + 1)));
-      if (st7) k_cand7<<<rs_grid(nc), RS_BLOCK, 0, s>>>(nc, g.nx, g.ny, g.nz, L->mptr.as<int32_t>(), L->mem.as<int32_t>(), cnt.as<int32_t>());
-      else k_cand<<<rs_grid(nc), RS_BLOCK, 0, s>>>(nc, L->mptr.as<int32_t>(), L->mem.as<int32_t>(), rp, cnt.as<int32_t>());
+      if (st7) {
+        // agg1 is free again: the members' numbers
+        k_members7<false><<<rs_grid(nc), RS_BLOCK, 0, s>>>(nc, g.nx, g.ny, g.nz, T.root.as<int32_t>(), L->agg.as<int32_t>(),
+                                                           agg1.as<int32_t>(), cnt.as<int32_t>(), nullptr, nullptr);
+        RS_HIP(hipGetLastError());
+        RS_TRY(scan(agg1, L->mptr, nc, nullptr, L->mptr.as<int32_t>() + nc));
+        k_members7<true><<<rs_grid(nc), RS_BLOCK, 0, s>>>(nc, g.nx, g.ny, g.nz, T.root.as<int32_t>(), L->agg.as<int32_t>(),
+                                                          nullptr, nullptr, L->mptr.as<int32_t>(), L->mem.as<int32_t>());
+      } else {
+        RS_TRY(tfill.alloc(sizeof(int32_t) * ((size_t)nc + 1)));
+        k_count_members<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, L->agg.as<int32_t>(), cnt.as<int32_t>(), tfill.as<int32_t>(),
+                                                        nc + 1);
+        RS_HIP(hipGetLastError());
+        RS_TRY(scan(cnt, L->mptr, (int64_t)nc + 1, nullptr, nullptr));
+        k_fill_members<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, L->agg.as<int32_t>(), L->mptr.as<int32_t>(), tfill.as<int32_t>(),
+                                                       L->mem.as<int32_t>());
+        k_sort_members<<<rs_grid(nc), RS_BLOCK, 0, s>>>(nc, L->mptr.as<int32_t>(), L->mem.as<int32_t>());
+        k_cand<<<rs_grid(nc), RS_BLOCK, 0, s>>>(nc, L->mptr.as<int32_t>(), L->mem.as<int32_t>(), rp, cnt.as<int32_t>());
+      }
       RS_HIP(hipGetLastError());
-      // candidates: the members' row entries, at most this level's nnz
       RS_TRY(scan(cnt, off, nc, nullptr, nullptr));
       ncand = L->nnz;
       RS_TRY(skey.alloc(sizeof(int32_t) * (ncand + 1)));
@@ -2522,11 +2584,11 @@ rs_status rs_amg_build(rs_cpr_s *M, amg_setup *U, hipStream_t s) {
     RS_TRY(C->dl1.alloc((prec == 64 ? sizeof(double) : sizeof(float)) * ((size_t)nc + 1)));
     if (prec == 32) RS_TRY(C->ap.alloc(sizeof(float) * (ncand + 1)));
     if (prec == 64)
-      k_galerkin_copy<double><<<rs_grid(nc), RS_BLOCK, 0, s>>>(nc, off.as<int32_t>(), skey.as<int32_t>(),
+      k_galerkin_copy<double><<<rs_grid(16 * (int64_t)nc), 256, 0, s>>>(nc, off.as<int32_t>(), skey.as<int32_t>(),
                                                                sval.as<double>(), C->rp.as<int32_t>(), C->ci.as<int32_t>(),
                                                                C->a.as<double>(), nullptr, C->dl1.as<double>());
     else
-      k_galerkin_copy<float><<<rs_grid(nc), RS_BLOCK, 0, s>>>(nc, off.as<int32_t>(), skey.as<int32_t>(),
+      k_galerkin_copy<float><<<rs_grid(16 * (int64_t)nc), 256, 0, s>>>(nc, off.as<int32_t>(), skey.as<int32_t>(),
                                                               sval.as<double>(), C->rp.as<int32_t>(), C->ci.as<int32_t>(),
                                                               C->a.as<double>(), C->ap.as<float>(), C->dl1.as<float>());
     RS_HIP(hipGetLastError());

@@ -148,7 +148,7 @@ struct amg_level {
 // strength, independent set and Galerkin scratch, the dense inverse's matrix,
 // and the words that the host reads.
 struct amg_tmp {
-  dbuf dir, strong, state, state2, m1, id, agg1, bs, off, skey, sval, cnt;
+  dbuf dir, strong, state, state2, settled, m1, id, agg1, root, bs, off, skey, sval, cnt;
   dbuf rho, apoff, apcnt, apci, apv, tfill, trv, ident;
 };
 struct amg_setup {
