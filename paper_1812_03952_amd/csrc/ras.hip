@@ -285,7 +285,7 @@ __global__ __launch_bounds__(1024) void k_ras_setup(int nx, int ny, int64_t n, i
 // computed one level earlier by the neighbouring strip:
 //   - the writer wave publishes its boundary line, level by level, as 64-bit
 //     words (launch tag << 32 | 32 bits of the value), with device-scope stores;
-//   - the poller wave loads the neighbour's words 16 levels at a time, polls
+//   - the poller wave loads the neighbour's words 8 levels at a time, polls
 //     those whose tag does not match yet, and puts each level's value into the
 //     ghost slot of the LDS ring, ready for the level;
 //   - workgroups take tickets in dependency order (every strip of a layer
@@ -303,8 +303,8 @@ __global__ __launch_bounds__(1024) void k_ras_setup(int nx, int ny, int64_t n, i
 // of a cell lie side by side, and a line's own previous value comes by DPP.
 // Both sweeps, against the kernels before these (per-lane addresses formed
 // anew each level; strips of up to 224 lines, a layer per workgroup above):
-// FP32 158 -> 104 us at 100x100x50, 393 -> 310 at 200x200x100 (1.3 GB, 4.2
-// TB/s), 905 -> 730 at 256x256x160; FP64 335 -> 283 at 161x143x67.
+// FP32 158 -> 98 us at 100x100x50, 393 -> 294 at 200x200x100 (1.3 GB, 4.4
+// TB/s), 905 -> 745 at 256x256x160; FP64 335 -> 267 at 161x143x67.
 // The level count is padded to a multiple of P and every load is issued
 // unconditionally at a clamped (in-bounds) address, with the terms of inactive
 // cells dropped by selects: then every path through a level issues the same
@@ -391,9 +391,12 @@ template <class T> __device__ __forceinline__ T quad_dot(const T (&a)[4], T v) {
   return fma(a[3], qb<3>(v), u);
 }
 
-// The poller wave: words of the neighbour's boundary line, 16 steps at a time
-// (64 lanes: step offset, block row), loaded 10 steps before the first of them
-// is needed and checked two steps before it.  Word i = i0 + di * step, if in
+// The poller wave: words of the neighbour's boundary line, 8 steps at a time
+// (32 lanes: step offset, block row), loaded 5 steps before the first of them
+// is needed and checked two steps before it.  A strip so runs 9 steps behind
+// its neighbour's line; with 16 at a time, 17: both sweeps at 100x100x50 in
+// FP64 120 us against 134, at 200x200x100 in FP32 294 against 311 (loaded 7
+// steps before: the same).  Word i = i0 + di * step, if in
 // [0, nx); xw: the neighbour's words, nullptr for none.  Value of step m to
 // slot `slot` of the ring buffer that step m reads.
 template <class T>
@@ -403,16 +406,16 @@ __device__ __forceinline__ void ras_poll(int w, int steps, int i0, int di, int n
   bool failed = false;
   const int r = w & 3;
   uint64_t pend[W] = {};
-  auto issue16 = [&](int m16) {
-    const int i = i0 + di * (m16 + (w >> 2));
-    if (!xw || i < 0 || i >= nx) return;
+  auto issue8 = [&](int m8) {
+    const int i = i0 + di * (m8 + (w >> 2));
+    if (!xw || w >= 32 || i < 0 || i >= nx) return;
 #pragma unroll
     for (int q = 0; q < W; ++q)
       pend[q] = __hip_atomic_load(xw + W * (4 * (int64_t)i + r) + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  auto finish16 = [&](int m16) {
-    const int m = m16 + (w >> 2), i = i0 + di * m;
-    if (!xw || i < 0 || i >= nx) return;
+  auto finish8 = [&](int m8) {
+    const int m = m8 + (w >> 2), i = i0 + di * m;
+    if (!xw || w >= 32 || i < 0 || i >= nx) return;
     uint32_t v[W] = {};
     if (!ras_get<W>(xw + W * (4 * (int64_t)i + r), pend, tag, v, failed)) atomicOr(err, 1);
     gh[m & 31][r] = ras_value(v);
@@ -422,14 +425,14 @@ __device__ __forceinline__ void ras_poll(int w, int steps, int i0, int di, int n
     if (w < 4) ring[((m + 1) & 1) * RS * 4 + 4 * slot + w] = val;
     val = gh[(m + 1) & 31][r];
   };
-  issue16(0);
-  finish16(0);
+  issue8(0);
+  finish8(0);
   val = gh[0][r];
   hand(0);
   __syncthreads();
   for (int m = 0; m < steps; ++m) {
-    if ((m & 15) == 6) issue16(m + 10);
-    if ((m & 15) == 14) finish16(m + 2);
+    if ((m & 7) == 3) issue8(m + 5);
+    if ((m & 7) == 6) finish8(m + 2);
     hand(m + 1);
     __syncthreads();
   }
