@@ -27,6 +27,15 @@ class SolveSpec:
         self.last_adjoint_info = None
 
 
+def _from_zero(opts):
+    """The GMRES options with zero_guess set (a copy: the caller's stay as they
+    are).  Both solves below start from 0, and saying so saves each a product
+    with A and a norm (0.1 ms a solve at 100x100x50) for bitwise the same x."""
+    o = rs.gmres_opts() if opts is None else rs.GmresOpts.from_buffer_copy(opts)
+    o.zero_guess = 1
+    return o
+
+
 class SolveFn(torch.autograd.Function):
     """x = A(vals)^{-1} b by CPR-preconditioned GMRES."""
 
@@ -36,7 +45,7 @@ class SolveFn(torch.autograd.Function):
         D = rs.decouple(A, spec.method, spec.prec)
         M = rs.cpr_setup(A, D, spec.cpr)
         x = torch.zeros_like(b)
-        spec.last_info = rs.gmres_solve(A, M, b.detach().contiguous(), x, spec.gmres)
+        spec.last_info = rs.gmres_solve(A, M, b.detach().contiguous(), x, _from_zero(spec.gmres))
         ctx.A, ctx.spec = A, spec
         ctx.save_for_backward(x)
         return x
@@ -47,7 +56,7 @@ class SolveFn(torch.autograd.Function):
         A, spec = ctx.A, ctx.spec
         lam = torch.zeros_like(x)
         spec.last_adjoint_info = rs.adjoint_solve(A, gx.contiguous(), lam, spec.method, spec.prec,
-                                                  spec.cpr, spec.gmres)
+                                                  spec.cpr, _from_zero(spec.gmres))
         G = None
         if ctx.needs_input_grad[0]:
             G = torch.empty(16 * A.nnzb, dtype=torch.float64, device=x.device)
