@@ -914,6 +914,18 @@ static ras_shape ras_strips(const grid3 &g, int prec) {
   return {(g.ny + H - 1) / H, H};                       // every strip non-empty
 }
 
+// Whether overlap 1 chains its three factorisations: layers of at most 224 lines
+// (compute, writer and poller waves fit), and 3 nz workgroups that share CUs at
+// most in pairs, or, above 160 lines, whose 13 waves and more leave a CU no room
+// (and FP64 too few registers), not at all.  All three, chained against one
+// after another: 100x100x190 (570 workgroups) 1577 us for 1519 in FP32,
+// 161x143x160 (480) 2243 for 2611 and 3252 for 3560 in FP64, 200x200x100 (300)
+// 3644 for 3597 and 6337 for 4546, 200x200x60 (180) 1844 for 3339 and 3117 for
+// 3975.
+static bool ras1_chained(const grid3 &g, int u, int lw) {
+  return u == 1 && 4 * lw + 128 <= 1024 && 3 * (int64_t)g.nz <= (lw <= 160 ? 512 : 256);
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -976,7 +988,7 @@ rs_status rs_ras_setup_run(rs_cpr_s *M, int *flag, hipStream_t s) {
     if (!ov1) {
       factor(nullptr, M->dinv2.as<T>());
       scale(M->dinv2.as<T>(), M->rblk.as<T>());
-    } else if (4 * lw + 128 <= 1024 && u == 1) {        // up to 224 lines: compute, writer and poller waves fit
+    } else if (ras1_chained(g, u, lw)) {
       // P0 (plain layers), P1 (middle of each extension, the owned cells':
       // dinv2), P2 (top of each extension), chained
       int *ctl = M->rctl.as<int>();

@@ -1,5 +1,6 @@
 """The chained factorisation of RAS with overlap 1 at the edges of its launch
-variants (96, 160 and 224 lines a layer, and one more of each), with one, two
+variants (96, 160 and 224 lines a layer, and one more of each) and of its rule
+(170 layers, 85 of more than 160 lines, and one more of each), with one, two
 and many layers, single columns and rows: the owned factors bitwise against the
 oracle's, the apply (which uses all three stages' factors) as the overlapping
 RAS tests compare it."""
@@ -15,7 +16,7 @@ from paper_1812_03952_amd import rsolve as rs
 pytestmark = pytest.mark.gpu
 
 DIMS = [(1, 1, 1), (1, 1, 2), (3, 96, 3), (3, 97, 2), (2, 160, 2), (2, 161, 3), (2, 224, 2), (2, 225, 2), (40, 3, 60),
-        (5, 7, 130)]
+        (5, 7, 130), (3, 5, 170), (3, 5, 171), (1, 161, 85), (1, 161, 86)]
 
 
 @pytest.mark.parametrize("method", [rs.ABF, rs.FRS])
