@@ -284,7 +284,10 @@ __global__ void k_mis_m1(int n, int level, const int32_t *__restrict__ rp, const
       m = k > m ? k : m;
       und = und || sw == ST_UND;
     }
-  if (und) m1[u] = m;                            // as in k_mis7_m1
+  // m1 is read only at undecided vertices and their strong neighbours, so a
+  // vertex with no undecided one in its closed neighbourhood (strength is
+  // symmetric) skips the store
+  if (und) m1[u] = m;
 }
 
 // the distance-2 maximum of an undecided vertex (the largest m1 over its

@@ -110,16 +110,16 @@ extern "C" void rs_pool_usage(size_t *live_bytes, size_t *cached_bytes) {
 }
 
 // ---- short host waits --------------------------------------------------------
-// The set-up reads a few counts and flags back (an aggregate count, an error
-// word) and waits for the stream at each.  A blocking stream synchronisation
-// leaves the device idle for tens of microseconds after such a read while the
-// host thread wakes up; these waits poll an event, or a slot of pinned memory
-// that the device stores into (9 us from the launch to the host; a copy and an
-// event take 15).  Each host thread
-// keeps one event per device and a pinned post slot.  The slot of a thread that ends goes to the next new one (never
-// freed: no HIP calls at exit), so there are as many as threads at one time.
+// The set-up reads a few counts and flags back (a number of aggregates, an
+// error word) and waits for the stream at each, and the Krylov loops read a
+// status per step.  A blocking stream synchronisation leaves the device idle
+// for tens of microseconds after such a read while the host thread wakes up, a
+// copy and a polled event take 15; instead the device stores the words into
+// pinned memory that the host polls (9 us from the launch).  Each host thread
+// has one such slot; the slot of a thread that ends goes to the next new one
+// (never freed: no HIP calls at exit), so there are as many as threads at one
+// time.
 namespace {
-constexpr int WAIT_MAX_DEV = 64;
 #include "reduce.h"
 struct slot_list {
   std::mutex mu;
@@ -130,7 +130,6 @@ slot_list &slots() {
   return *l;
 }
 struct host_wait {
-  hipEvent_t ev[WAIT_MAX_DEV] = {};
   rs_post *post = nullptr;
   ~host_wait() {
     if (!post) return;
@@ -152,7 +151,7 @@ rs_status rs_post_slot(rs_post **out) {
   }
   if (!tw.post) {
     void *p = nullptr;
-    RS_HIP(hipHostMalloc(&p, sizeof(rs_post), hipHostMallocPortable));
+    RS_HIP(hipHostMalloc(&p, sizeof(rs_post), hipHostMallocPortable | hipHostMallocCoherent));
     memset(p, 0, sizeof(rs_post));
     tw.post = (rs_post *)p;
   }
@@ -169,22 +168,6 @@ rs_status rs_wait_post(const rs_post *p, uint64_t seq, hipStream_t s) {
     if (e == hipErrorNotReady) continue;
     if (e == hipSuccess && __atomic_load_n(&p->seq, __ATOMIC_ACQUIRE) == seq) return RS_OK;
     return RS_E_HIP;
-  }
-}
-
-rs_status rs_wait(hipStream_t s) {
-  int dev = 0;
-  RS_HIP(hipGetDevice(&dev));
-  if (dev < 0 || dev >= WAIT_MAX_DEV) {
-    RS_HIP(hipStreamSynchronize(s));
-    return RS_OK;
-  }
-  if (!tw.ev[dev]) RS_HIP(hipEventCreateWithFlags(&tw.ev[dev], hipEventDisableTiming));
-  RS_HIP(hipEventRecord(tw.ev[dev], s));
-  for (;;) {
-    const hipError_t e = hipEventQuery(tw.ev[dev]);
-    if (e == hipSuccess) return RS_OK;
-    if (e != hipErrorNotReady) return RS_E_HIP;
   }
 }
 

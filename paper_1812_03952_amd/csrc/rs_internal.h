@@ -26,10 +26,8 @@ static inline hipStream_t rs_stream(void *s) { return (hipStream_t)s; }
 // cached and reused by later requests of a similar size.
 void *rs_pool_get(size_t bytes, size_t *got);   // nullptr when out of memory
 void rs_pool_put(void *p, size_t bytes);
-// Wait for the work queued on s (rs_wait, polling an event), or read a few
-// 32-bit words of device memory behind that work (rs_wait_read; err: as well
-// whether a word of rs_sweep_errors is set).
-rs_status rs_wait(hipStream_t s);
+// Read a few 32-bit words of device memory behind the work queued on s
+// (rs_wait_read; err: as well whether a word of rs_sweep_errors is set).
 constexpr int RS_READ_WORDS = 22;
 rs_status rs_wait_read(void *h, const void *d, size_t bytes, hipStream_t s);
 rs_status rs_wait_read_err(void *h, const void *d, size_t bytes, const int *const (&errw)[2], int *err, hipStream_t s);
