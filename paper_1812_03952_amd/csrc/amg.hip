@@ -827,61 +827,6 @@ __global__ void k_gj_elim(int n, int k, double *__restrict__ G) {
   G[(int64_t)r * 2 * n + c] -= f * G[(int64_t)k * 2 * n + c];
 }
 
-// The same elimination for small n in one workgroup, three barriers per
-// column: the pivot (largest |value|, lowest row on ties) is reduced per wave
-// with shuffles and then across the waves from LDS; the row swap and the
-// scaling of the pivot row are one pass (each thread owns whole columns);
-// then the elimination.  Every entry gets the same operations as in the
-// two-launch form.
-constexpr int GJ_FUSED_MAX = 256;
-__global__ __launch_bounds__(1024) void k_gj_fused(int n, double *__restrict__ G, int *__restrict__ bad) {
-  __shared__ double sv[16], sp[16];
-  __shared__ int si[16];
-  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wv = tid >> 6, nwv = nt >> 6;
-  const int64_t ld = 2 * (int64_t)n;
-  const int tpr = max(1, nt / n);             // threads per row in the elimination
-  const int rstep = nt / tpr, r0 = tid / tpr, c0 = tid - r0 * tpr;
-  for (int k = 0; k < n; ++k) {
-    // pivot: |value| compared, the signed value carried along
-    double best = -1.0, bval = 0.0;
-    int bi = k;
-    for (int r = k + tid; r < n; r += nt) {
-      double x = G[(int64_t)r * ld + k], v = fabs(x);
-      if (v > best) { best = v; bval = x; bi = r; }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      double ov = __shfl_down(best, off, 64), ox = __shfl_down(bval, off, 64);
-      int oi = __shfl_down(bi, off, 64);
-      if (ov > best || (ov == best && oi < bi)) { best = ov; bval = ox; bi = oi; }
-    }
-    if (lane == 0) { sv[wv] = best; sp[wv] = bval; si[wv] = bi; }
-    __syncthreads();
-    best = sv[0]; bval = sp[0]; bi = si[0];
-    for (int w = 1; w < nwv; ++w)
-      if (sv[w] > best || (sv[w] == best && si[w] < bi)) { best = sv[w]; bval = sp[w]; bi = si[w]; }
-    const int piv = bi;
-    double *rk = G + (int64_t)k * ld, *rpv = G + (int64_t)piv * ld;
-    const double pv = bval;
-    if (tid == 0 && !(fabs(pv) > 0.0)) atomicOr(bad, 1);
-    const double inv = 1.0 / pv;
-    for (int c = tid; c < ld; c += nt) {
-      const double vk = rk[c], vp = rpv[c];
-      if (piv != k) rpv[c] = vk;
-      rk[c] = (c == k) ? 1.0 : vp * inv;
-    }
-    __syncthreads();
-    // thread -> (rows r0 + rstep*m, columns c0 + tpr*q): no divisions per entry
-    for (int r = r0; r < n && tid < rstep * tpr; r += rstep) {
-      if (r == k) continue;
-      const double f = G[(int64_t)r * ld + k];
-      double *gr = G + (int64_t)r * ld;
-      for (int c = k + 1 + c0; c < ld; c += tpr) gr[c] -= f * rk[c];
-    }
-    __syncthreads();
-  }
-}
-
 // Coarsest levels up to GJ_BLK_MAX rows are inverted in one workgroup with
 // the n x n matrix in registers, by in-place Gauss-Jordan with implicit
 // partial pivoting: rows never move; at step k the pivot is the largest
@@ -890,10 +835,13 @@ __global__ __launch_bounds__(1024) void k_gj_fused(int n, double *__restrict__ G
 // this step creates.  Thread (rg, cg) owns rows rg + nrg*i and columns
 // cg + ncg*j of an R x Q tile, so column k = kc + ncg*j0 always sits in
 // register slot j0, a compile-time index once the loop over j0 is unrolled.
+// Row rg + nrg*i is slot rg + PR*i of the pivot search, so slots are in row
+// order, their LDS offsets are immediates and PR >= nrg gives the tile of a
+// slot without a division.
 // Per step:
 //   - the owners of column k publish it to LDS (value, and |value| or -1
 //     for used rows);
-//   - every wave reduces max |value| with DPP and takes the lowest row
+//   - every wave reduces max |value| with DPP and takes the lowest slot
 //     holding it from a ballot, and its signed value with a readlane;
 //   - the owners set column k to e_p (the identity column of pivot row p);
 //   - the pivot row's threads publish that row times 1/pivot and zero it;
@@ -902,7 +850,15 @@ __global__ __launch_bounds__(1024) void k_gj_fused(int n, double *__restrict__ G
 // the same products and fused multiply-adds, in the same order.
 // With p_k the pivot row of step k, the final tile X gives
 // inverse[k][p_k'] = X[p_k][k'], which the last pass scatters.
-constexpr int GJ_BLK_MAX = 156;
+// Bound by the chain of a step (publish, barrier, search, division, publish,
+// barrier, update: 1.2 us at n = 64) and, as n grows, by the update's FMAs
+// on one CU.  The matrix must stay in registers: with it in global memory
+// the update's two passes over n x 2n entries made the inverse 3.1 ms at
+// n = 157, 5.6 at 192, 8.0 at 224 and 11.9 at 256, and 0.30, 0.40, 0.60 and
+// 1.36 ms here (host call included; 0.16 ms at n = 108, 0.29 at 156).  256
+// rows are the whole register file of a CU, so the largest tile keeps RL of
+// its rows in LDS, each thread's entries at its own place.
+constexpr int GJ_BLK_MAX = 256;
 template <int CTRL, int RM>
 __device__ __forceinline__ double gj_dpp_max(double x) {
   const int a0 = __double2loint(x), a1 = __double2hiint(x);
@@ -910,29 +866,42 @@ __device__ __forceinline__ double gj_dpp_max(double x) {
                                     __builtin_amdgcn_update_dpp(a0, a0, CTRL, RM, 0xf, false));
   return fmax(x, o);
 }
-template <int NT, int R, int Q>
+template <int NT, int R, int Q, int PR, int RL>
 __global__ __launch_bounds__(NT) void k_gj_blk(int n, int ld, const double *__restrict__ G0, double *__restrict__ cinv,
                                                int *__restrict__ bad) {
-  __shared__ double colk[2][GJ_BLK_MAX + 8], cabs[2][GJ_BLK_MAX + 8], prow[GJ_BLK_MAX + 8];
-  __shared__ int pivrow[GJ_BLK_MAX];
+  constexpr int PQ = 32, NW = (R * PR + 63) / 64;   // column pitch, slots per lane of the pivot search
+  constexpr int RR = R - RL;                        // rows in registers; the other RL are in LDS
+  __shared__ double colk[2][64 * NW], cabs[2][64 * NW], prow[Q * PQ];
+  __shared__ double gl[RL ? RL : 1][RL ? Q : 1][RL ? NT : 1];
+  __shared__ int pivrow[GJ_BLK_MAX], slotk[64 * NW];   // row of step k, step of a slot
   const int tid = threadIdx.x, lane = tid & 63;
   const int nrg = (n + R - 1) / R, ncg = (n + Q - 1) / Q;
   const int rg = tid / ncg, cg = tid - rg * ncg;
   const bool act = rg < nrg;
-  double g[R][Q];
-  bool used[R];
-  int pos[R];
+  double g[RR][Q];
+  auto get = [&](int i, int j) { return i < RR ? g[i][j] : gl[i - RR][j][tid]; };
+  auto put = [&](int i, int j, double v) {
+    if (i < RR) g[i][j] = v;
+    else gl[i - RR][j][tid] = v;
+  };
+  unsigned used = 0;                                // bit i: row i of the tile is no candidate any more
+  for (int t = tid; t < 64 * NW; t += NT) {         // slots that no row has
+    colk[0][t] = colk[1][t] = 0.0;
+    cabs[0][t] = cabs[1][t] = -1.0;
+    slotk[t] = 0;
+  }
 #pragma unroll
   for (int i = 0; i < R; ++i) {
-    used[i] = false;
-    pos[i] = 0;
     const int row = rg + nrg * i;
+    if (row >= n) used |= 1u << i;
 #pragma unroll
     for (int j = 0; j < Q; ++j) {
       const int col = cg + ncg * j;
-      g[i][j] = (act && row < n && col < n) ? G0[(int64_t)row * ld + col] : 0.0;
+      put(i, j, (act && row < n && col < n) ? G0[row * ld + col] : 0.0);
     }
+    if (R * Q > 24) __builtin_amdgcn_sched_barrier(0);
   }
+  __syncthreads();
   int b = 0;  // colk / cabs double buffer: step k+1 publishes while step k's f reads finish
 #pragma unroll
   for (int j0 = 0; j0 < Q; ++j0) {
@@ -942,22 +911,22 @@ __global__ __launch_bounds__(NT) void k_gj_blk(int n, int ld, const double *__re
       if (act && cg == kc) {
 #pragma unroll
         for (int i = 0; i < R; ++i) {
-          const int row = rg + nrg * i;
-          colk[b][row] = g[i][j0];
-          cabs[b][row] = (used[i] || row >= n) ? -1.0 : fabs(g[i][j0]);
+          const double v = get(i, j0);
+          colk[b][rg + PR * i] = v;
+          cabs[b][rg + PR * i] = (used >> i & 1) ? -1.0 : fabs(v);
         }
       }
       __syncthreads();
-      // pivot: rows lane, lane+64, lane+128
-      double a[3], v[3];
+      // pivot: slots lane, lane + 64, ...
+      double a[NW], v[NW];
 #pragma unroll
-      for (int m = 0; m < 3; ++m) {
-        const int rr = lane + 64 * m;
-        a[m] = -1.0;
-        v[m] = 0.0;
-        if (rr < n) { a[m] = cabs[b][rr]; v[m] = colk[b][rr]; }
+      for (int m = 0; m < NW; ++m) {
+        a[m] = cabs[b][lane + 64 * m];
+        v[m] = colk[b][lane + 64 * m];
       }
-      double mx = fmax(a[0], fmax(a[1], a[2]));
+      double mx = a[0];
+#pragma unroll
+      for (int m = 1; m < NW; ++m) mx = fmax(mx, a[m]);
       mx = gj_dpp_max<0xB1, 0xf>(mx);   // quad_perm [1,0,3,2]
       mx = gj_dpp_max<0x4E, 0xf>(mx);   // quad_perm [2,3,0,1]
       mx = gj_dpp_max<0x141, 0xf>(mx);  // row_half_mirror
@@ -966,10 +935,10 @@ __global__ __launch_bounds__(NT) void k_gj_blk(int n, int ld, const double *__re
       mx = gj_dpp_max<0x143, 0xc>(mx);  // row_bcast:31 into rows 2, 3
       const double gm = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(mx), 63),
                                          __builtin_amdgcn_readlane(__double2loint(mx), 63));
-      int p = n - 1;
+      int p = 0;
       double pv = 0.0;
 #pragma unroll
-      for (int m = 2; m >= 0; --m) {
+      for (int m = NW - 1; m >= 0; --m) {
         const unsigned long long bm = __ballot(a[m] == gm);
         if (bm) {
           const int l = __ffsll(bm) - 1;
@@ -978,39 +947,41 @@ __global__ __launch_bounds__(NT) void k_gj_blk(int n, int ld, const double *__re
                                 __builtin_amdgcn_readlane(__double2loint(v[m]), l));
         }
       }
-      if (tid == 0 && !(fabs(pv) > 0.0)) atomicOr(bad, 1);
+      const int ip = p / PR, rgp = p - PR * ip;
+      if (tid == 0) {
+        if (!(gm > 0.0)) atomicOr(bad, 1);          // only zeros or NaN left
+        pivrow[k] = min(rgp + nrg * ip, n - 1);     // no row's slot: only in a flagged matrix
+        slotk[p] = k;
+      }
       const double inv = 1.0 / pv;
+      const bool mine = act && rg == rgp;           // row ip of this tile is the pivot row
       if (act && cg == kc) {
 #pragma unroll
-        for (int i = 0; i < R; ++i) g[i][j0] = (rg + nrg * i == p) ? 1.0 : 0.0;
+        for (int i = 0; i < R; ++i) put(i, j0, (mine && i == ip) ? 1.0 : 0.0);
       }
-      const int rgp = p % nrg, ip = p / nrg;
-      if (act && rg == rgp) {
+      if (mine) {
+        used |= 1u << ip;
 #pragma unroll
         for (int i = 0; i < R; ++i)
           if (i == ip) {
 #pragma unroll
             for (int j = 0; j < Q; ++j) {
-              prow[cg + ncg * j] = g[i][j] * inv;
-              g[i][j] = 0.0;
+              prow[cg + PQ * j] = get(i, j) * inv;
+              put(i, j, 0.0);
             }
           }
       }
-      if (tid == 0) pivrow[k] = p;
-#pragma unroll
-      for (int i = 0; i < R; ++i)
-        if (rg + nrg * i == p) {
-          used[i] = true;
-          pos[i] = k;
-        }
       __syncthreads();
       if (act) {
+        double pr[Q];
+#pragma unroll
+        for (int j = 0; j < Q; ++j) pr[j] = prow[cg + PQ * j];
 #pragma unroll
         for (int i = 0; i < R; ++i) {
-          const int row = rg + nrg * i;
-          const double f = (row == p) ? -1.0 : colk[b][row];
+          const double f = (mine && i == ip) ? -1.0 : colk[b][rg + PR * i];
 #pragma unroll
-          for (int j = 0; j < Q; ++j) g[i][j] = fma(-f, prow[cg + ncg * j], g[i][j]);
+          for (int j = 0; j < Q; ++j) put(i, j, fma(-f, pr[j], get(i, j)));
+          if (R * Q > 24) __builtin_amdgcn_sched_barrier(0);   // a row at a time: the registers are full
         }
       }
       b ^= 1;
@@ -1024,16 +995,27 @@ __global__ __launch_bounds__(NT) void k_gj_blk(int n, int ld, const double *__re
 #pragma unroll
       for (int j = 0; j < Q; ++j) {
         const int col = cg + ncg * j;
-        if (row < n && col < n) cinv[(int64_t)pos[i] * n + pivrow[col]] = g[i][j];
+        if (row < n && col < n) cinv[slotk[rg + PR * i] * n + pivrow[col]] = get(i, j);
       }
+      if (R * Q > 24) __builtin_amdgcn_sched_barrier(0);
     }
   }
 }
 
-// Tiles of k_gj_blk: R x Q per thread with 1024 threads (2 x 6 up to n = 108,
-// 4 x 6 up to 156).
-static bool gj_blk_fits(int n, int R, int Q) {
-  return n <= GJ_BLK_MAX && (int64_t)((n + R - 1) / R) * ((n + Q - 1) / Q) <= 1024;
+// k_gj_blk on an R x Q tile per thread, if n rows fit.  Callers go from the
+// smallest tile up: at n = 102 tiles of 2 x 6, 4 x 6 and 10 x 10 (1024, 512
+// and 256 threads) took 0.163, 0.164 and 0.273 ms, at n = 145 those of
+// 4 x 6, 8 x 7 and 10 x 10 took 0.276, 0.300 and 0.402.  Past 192 rows the
+// tile leaves 1024 threads too few registers: at n = 193 and 224 tiles of
+// 14 x 7 on 512 threads take 0.47 and 0.60 ms, those of 16 x 8 (four rows
+// in LDS) 0.90 and 1.12, and 8 x 8 on 1024 (two in LDS) 0.92 and 1.22; at
+// n = 256 the latter two 1.36 and 1.59.
+template <int NT, int R, int Q, int PR, int RL>
+static bool gj_blk(int n, const double *G, double *cinv, int *flag, hipStream_t s) {
+  const int nrg = (n + R - 1) / R, ncg = (n + Q - 1) / Q;
+  if (n > GJ_BLK_MAX || nrg > PR || ncg > 32 || nrg * ncg > NT) return false;
+  k_gj_blk<NT, R, Q, PR, RL><<<1, NT, 0, s>>>(n, 2 * n, G, cinv, flag);
+  return true;
 }
 
 __global__ void k_extract_inv(int n, const double *__restrict__ G, double *__restrict__ inv) {
@@ -1047,19 +1029,16 @@ __global__ void k_extract_inv(int n, const double *__restrict__ G, double *__res
 // right half the identity; G is overwritten) into cinv (n x n), by the path
 // that fits n.  A zero pivot sets *flag.
 static rs_status dense_inverse_run(int n, double *G, double *cinv, int *flag, hipStream_t s) {
-  if (gj_blk_fits(n, 2, 6)) {
-    k_gj_blk<1024, 2, 6><<<1, 1024, 0, s>>>(n, 2 * n, G, cinv, flag);
-  } else if (gj_blk_fits(n, 4, 6)) {
-    k_gj_blk<1024, 4, 6><<<1, 1024, 0, s>>>(n, 2 * n, G, cinv, flag);
-  } else {
-    if (n <= GJ_FUSED_MAX) {
-      k_gj_fused<<<1, 1024, 0, s>>>(n, G, flag);
-    } else {
-      for (int k = 0; k < n; ++k) {
-        k_gj_pivot<<<1, 256, 0, s>>>(n, k, G, flag);
-        int64_t work = (int64_t)n * (2 * (int64_t)n - (k + 1));
-        if (work > 0) k_gj_elim<<<rs_grid(work), RS_BLOCK, 0, s>>>(n, k, G);
-      }
+  const bool done = gj_blk<1024, 2, 6, 64, 0>(n, G, cinv, flag, s) ||    // to 108 rows
+                    gj_blk<1024, 4, 6, 40, 0>(n, G, cinv, flag, s) ||    // 156
+                    gj_blk<1024, 6, 6, 32, 0>(n, G, cinv, flag, s) ||    // 192
+                    gj_blk<512, 14, 7, 16, 0>(n, G, cinv, flag, s) ||    // 224
+                    gj_blk<512, 16, 8, 16, 4>(n, G, cinv, flag, s);      // 256
+  if (!done) {
+    for (int k = 0; k < n; ++k) {
+      k_gj_pivot<<<1, 256, 0, s>>>(n, k, G, flag);
+      int64_t work = (int64_t)n * (2 * (int64_t)n - (k + 1));
+      if (work > 0) k_gj_elim<<<rs_grid(work), RS_BLOCK, 0, s>>>(n, k, G);
     }
     k_extract_inv<<<rs_grid((int64_t)n * n), RS_BLOCK, 0, s>>>(n, G, cinv);
   }
