@@ -855,9 +855,11 @@ __global__ void k_gj_elim(int n, int k, double *__restrict__ G) {
 // on one CU.  The matrix must stay in registers: with it in global memory
 // the update's two passes over n x 2n entries made the inverse 3.1 ms at
 // n = 157, 5.6 at 192, 8.0 at 224 and 11.9 at 256, and 0.30, 0.40, 0.60 and
-// 1.36 ms here (host call included; 0.16 ms at n = 108, 0.29 at 156).  256
+// 1.03 ms here (host call included; 0.16 ms at n = 108, 0.29 at 156).  256
 // rows are the whole register file of a CU, so the largest tile keeps RL of
-// its rows in LDS, each thread's entries at its own place.
+// its rows in LDS, each thread's entries at its own place.  Those rows have
+// rolled loops of their own: unrolled with the others, their loads were
+// moved up and spilled 25 registers (1.36 ms at n = 256, 1.17 at 225; 0.90).
 constexpr int GJ_BLK_MAX = 256;
 template <int CTRL, int RM>
 __device__ __forceinline__ double gj_dpp_max(double x) {
@@ -962,14 +964,21 @@ __global__ __launch_bounds__(NT) void k_gj_blk(int n, int ld, const double *__re
       if (mine) {
         used |= 1u << ip;
 #pragma unroll
-        for (int i = 0; i < R; ++i)
+        for (int i = 0; i < RR; ++i)
           if (i == ip) {
 #pragma unroll
             for (int j = 0; j < Q; ++j) {
-              prow[cg + PQ * j] = get(i, j) * inv;
-              put(i, j, 0.0);
+              prow[cg + PQ * j] = g[i][j] * inv;
+              g[i][j] = 0.0;
             }
           }
+        if (RL && ip >= RR) {
+#pragma unroll 1
+          for (int j = 0; j < Q; ++j) {
+            prow[cg + PQ * j] = gl[ip - RR][j][tid] * inv;
+            gl[ip - RR][j][tid] = 0.0;
+          }
+        }
       }
       __syncthreads();
       if (act) {
@@ -977,11 +986,17 @@ __global__ __launch_bounds__(NT) void k_gj_blk(int n, int ld, const double *__re
 #pragma unroll
         for (int j = 0; j < Q; ++j) pr[j] = prow[cg + PQ * j];
 #pragma unroll
-        for (int i = 0; i < R; ++i) {
+        for (int i = 0; i < RR; ++i) {
           const double f = (mine && i == ip) ? -1.0 : colk[b][rg + PR * i];
 #pragma unroll
-          for (int j = 0; j < Q; ++j) put(i, j, fma(-f, pr[j], get(i, j)));
+          for (int j = 0; j < Q; ++j) g[i][j] = fma(-f, pr[j], g[i][j]);
           if (R * Q > 24) __builtin_amdgcn_sched_barrier(0);   // a row at a time: the registers are full
+        }
+#pragma unroll 1
+        for (int i = RR; i < R; ++i) {
+          const double f = (mine && i == ip) ? -1.0 : colk[b][rg + PR * i];
+#pragma unroll
+          for (int j = 0; j < Q; ++j) gl[i - RR][j][tid] = fma(-f, pr[j], gl[i - RR][j][tid]);
         }
       }
       b ^= 1;
@@ -1008,8 +1023,8 @@ __global__ __launch_bounds__(NT) void k_gj_blk(int n, int ld, const double *__re
 // 4 x 6, 8 x 7 and 10 x 10 took 0.276, 0.300 and 0.402.  Past 192 rows the
 // tile leaves 1024 threads too few registers: at n = 193 and 224 tiles of
 // 14 x 7 on 512 threads take 0.47 and 0.60 ms, those of 16 x 8 (four rows
-// in LDS) 0.90 and 1.12, and 8 x 8 on 1024 (two in LDS) 0.92 and 1.22; at
-// n = 256 the latter two 1.36 and 1.59.
+// in LDS) at n = 225 0.90 and at 256 1.03, and 8 x 8 on 1024 (two in LDS)
+// 1.10 and 1.35.
 template <int NT, int R, int Q, int PR, int RL>
 static bool gj_blk(int n, const double *G, double *cinv, int *flag, hipStream_t s) {
   const int nrg = (n + R - 1) / R, ncg = (n + Q - 1) / Q;
