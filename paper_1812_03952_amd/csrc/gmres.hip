@@ -321,7 +321,8 @@ static rs_status gmres_t(rs_bsr_s *A, rs_cpr_s *M, const double *b, double *x, c
                          rs_solve_info *info, hipStream_t s) {
   int64_t N = 4 * A->g.n;
   int m = o.restart;
-  if (M->m != m || !M->V.p) {
+  if (M->m != m) {
+    M->m = 0;                                    // no workspace until every part of it is there
     RS_TRY(M->V.alloc(sizeof(double) * N * (m + 1)));
     RS_TRY(M->Z.alloc(sizeof(TZ) * N * m));
     RS_TRY(M->w.alloc(sizeof(double) * N));
