@@ -403,16 +403,21 @@ __global__ __launch_bounds__(256) void k_thermal(int nx, int ny, int nz, tpar q,
   if (res) res[4 * c + r] = R;
 }
 
-// wells must be ascending and unique, inside the grid (one workgroup, which
-// writes the flag whatever it finds)
+// wells must be ascending and unique, inside the grid.  One workgroup writes
+// the flag whatever it finds; several (of a thread per well) set a zeroed one.
 __global__ __launch_bounds__(1024) void k_thermal_wells_check(int64_t n, int nw, const int32_t *__restrict__ wcell,
                                                                int *__restrict__ bad) {
   int b = 0;
-  for (int t = threadIdx.x; t < nw; t += 1024)
+  for (int t = blockIdx.x * 1024 + threadIdx.x; t < nw; t += gridDim.x * 1024)
     if (wcell[t] < 0 || wcell[t] >= n || (t > 0 && wcell[t - 1] >= wcell[t])) b = 1;
   b = __syncthreads_or(b);
-  if (threadIdx.x == 0) *bad = b;
+  if (threadIdx.x == 0 && (b || gridDim.x == 1)) *bad = b;
 }
+// Most wells that one workgroup checks; beyond, its steps of 1024 wells take
+// longer than a launch that zeroes the flag.  Residual of 100x100x32 cells, one
+// workgroup and many: 116 and 118 us with 16 thousand wells, 133 and 120 with
+// 65 thousand, 283 and 128 with 320 thousand.
+constexpr int WELLS_ONE_WG = 16384;
 
 // (p, N_w, N_o, T) from (p, S_w, S_o, T): N = phi rho S
 __global__ void k_thermal_state(int64_t n, rs_thermal_params q, const double *__restrict__ p,
@@ -471,7 +476,9 @@ extern "C" rs_status rs_thermal_assemble(int nx, int ny, int nz, const rs_therma
   if (nw > 0) {
     dbuf flag;
     RS_TRY(flag.alloc(sizeof(int)));
-    k_thermal_wells_check<<<1, 1024, 0, s>>>(n, nw, d_wcell, flag.as<int>());
+    const bool one = nw <= WELLS_ONE_WG;
+    if (!one) RS_TRY(rs_fill32(flag.p, 0, 1, s));
+    k_thermal_wells_check<<<one ? 1 : rs_grid(nw, 1024), 1024, 0, s>>>(n, nw, d_wcell, flag.as<int>());
     int h = 0;
     RS_HIP(hipGetLastError());
     RS_TRY(rs_wait_read(&h, flag.p, sizeof(int), s));
