@@ -75,6 +75,15 @@ static inline unsigned rs_grid(int64_t work, int block = RS_BLOCK) {
   return (unsigned)g;
 }
 
+// A launch of many workgroups: HIP takes fewer than 2^32 threads along an axis,
+// so past 2^21 workgroups (of at most 1024) they stand in rows of that many.
+// rs_wg: a workgroup's number, past the last one in the last row.
+static inline dim3 rs_wgs(int64_t wgs) {
+  constexpr int64_t ROW = 1 << 21;
+  return wgs <= ROW ? dim3((unsigned)(wgs < 1 ? 1 : wgs)) : dim3((unsigned)ROW, (unsigned)((wgs + ROW - 1) / ROW));
+}
+__device__ __forceinline__ uint32_t rs_wg() { return blockIdx.x + gridDim.x * blockIdx.y; }
+
 // ---- grid geometry --------------------------------------------------------
 // The 7 stencil slots in ascending column order: -z -y -x self +x +y +z.
 struct grid3 {

@@ -10,10 +10,11 @@
 // upstream fluid part); the model, its constants and their sources are
 // listed with rs_thermal_assemble in rsolve.h.
 //
-// A workgroup takes a tile of 8 x 4 x 2 cells: it evaluates the properties of
-// the tile's cells and of the cells around it once, into LDS, and then forms
-// the block rows and the residual with a quad of lanes per cell, lane r for
-// equation r, so that a block is written as one 128-byte run.  No two lanes
+// A workgroup takes a tile of 64 cells (8 x 4 x 2 but on thin grids): it
+// evaluates the properties of the tile's cells and of the cells around it once,
+// into LDS, and then forms the block rows and the residual with a quad of lanes
+// per cell, lane r for equation r, so that a block is written as one 128-byte
+// run.  No two lanes
 // write the same place.  The face flow seen from either side is the same
 // number (up to sign): the upstream cell is the one of higher pressure, on a
 // tie the lower-numbered one, whichever cell computes it.
@@ -210,29 +211,37 @@ __device__ double cell_energy(const tpar &q, const double *__restrict__ u4) {
 }
 
 // Tile of a workgroup, and the LDS index of its cells and the ones around it:
-// own cells, then the faces -x, +x, -y, +y, -z, +z.
-constexpr int TX = 8, TY = 4, TZ = 2, TN = TX * TY * TZ;
-constexpr int HX = TN, HY = HX + 2 * TY * TZ, HZ = HY + 2 * TX * TZ, HN = HZ + 2 * TX * TY;
-static_assert(HN + TN + TY * TZ <= 256 && 4 * TN == 256, "one evaluation or search and one block row per thread");
-__device__ __forceinline__ void tile_cell(int t, int &a, int &b, int &d) {
-  if (t < HX) {
-    a = t % TX; b = t / TX % TY; d = t / (TX * TY);
-  } else if (t < HY) {
-    const int f = t - HX, e = f % (TY * TZ);
-    a = f < TY * TZ ? -1 : TX; b = e % TY; d = e / TY;
-  } else if (t < HZ) {
-    const int f = t - HY, e = f % (TX * TZ);
-    b = f < TX * TZ ? -1 : TY; a = e % TX; d = e / TX;
-  } else {
-    const int f = t - HZ, e = f % (TX * TY);
-    d = f < TX * TY ? -1 : TZ; a = e % TX; b = e / TX;
+// own cells, then the faces -x, +x, -y, +y, -z, +z.  Along an axis with one
+// cell in the tile the grid has one too, and there are no faces.
+template <int TX_, int TY_, int TZ_> struct tile {
+  static constexpr int TX = TX_, TY = TY_, TZ = TZ_, TN = TX * TY * TZ;
+  static constexpr int HX = TN, HY = HX + (TX > 1 ? 2 * TY * TZ : 0), HZ = HY + (TY > 1 ? 2 * TX * TZ : 0);
+  static constexpr int HN = HZ + (TZ > 1 ? 2 * TX * TY : 0);
+  static_assert(HN + TN + TY * TZ <= 256 && 4 * TN == 256, "one evaluation or search and one block row per thread");
+  static int64_t count(int nx, int ny, int nz) {
+    return (int64_t)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY) * ((nz + TZ - 1) / TZ);
   }
-}
+  __device__ static __forceinline__ void cell(int t, int &a, int &b, int &d) {
+    if (t < HX) {
+      a = t % TX; b = t / TX % TY; d = t / (TX * TY);
+    } else if (t < HY) {
+      const int f = t - HX, e = f % (TY * TZ);
+      a = f < TY * TZ ? -1 : TX; b = e % TY; d = e / TY;
+    } else if (t < HZ) {
+      const int f = t - HY, e = f % (TX * TZ);
+      b = f < TX * TZ ? -1 : TY; a = e % TX; d = e / TX;
+    } else {
+      const int f = t - HZ, e = f % (TX * TY);
+      d = f < TX * TY ? -1 : TZ; a = e % TX; b = e / TX;
+    }
+  }
+};
 
 // 2300 instructions per 16 cells and a chain of loads, evaluation, faces and
 // stores; the blocks written (441 MB at 100x100x50) would take 90 us.  There:
 // 169 us, 426 us with one thread per cell that evaluated its six neighbours
 // as well and searched the tables in constant memory.
+template <class TILE>
 __global__ __launch_bounds__(256) void k_thermal(int nx, int ny, int nz, tpar q,
                                                  const double *__restrict__ kx, const double *__restrict__ ky,
                                                  const double *__restrict__ kz, const double *__restrict__ u,
@@ -240,14 +249,17 @@ __global__ __launch_bounds__(256) void k_thermal(int nx, int ny, int nz, tpar q,
                                                  const int32_t *__restrict__ wcell, const int32_t *__restrict__ wkind,
                                                  const double *__restrict__ wval, double *__restrict__ vals,
                                                  double *__restrict__ res) {
+  constexpr int TX = TILE::TX, TY = TILE::TY, TZ = TILE::TZ, TN = TILE::TN;
+  constexpr int HX = TILE::HX, HY = TILE::HY, HZ = TILE::HZ, HN = TILE::HN;
   __shared__ double prop[HN][C_N + 1], own[TN][O_N];
   __shared__ int first_well[TY * TZ];
   __shared__ swt_t swt;
   __shared__ wvis_t wvis;
   const int64_t nxy = (int64_t)nx * ny;
   const int tid = threadIdx.x, tx = (nx + TX - 1) / TX, ty = (ny + TY - 1) / TY;
-  const int bt = blockIdx.x / tx, i0 = (int)(blockIdx.x - (unsigned)bt * tx) * TX;
+  const int wg = (int)rs_wg(), bt = wg / tx, i0 = (wg - bt * tx) * TX;
   const int k0 = bt / ty * TZ, j0 = (bt - bt / ty * ty) * TY;
+  if (k0 >= nz) return;                                 // past the last tile
   // What the second half needs of global memory is asked for first: the
   // workgroup's time is latencies one after another.
   const int r = tid & 3, l = tid >> 2, a = l % TX, b = l / TX % TY, d = l / (TX * TY);
@@ -277,7 +289,7 @@ __global__ __launch_bounds__(256) void k_thermal(int nx, int ny, int nz, tpar q,
   const bool old = tid >= HN;
   {
     int ta, tb, td;
-    tile_cell(old ? min(tid - HN, TN - 1) : tid, ta, tb, td);
+    TILE::cell(old ? min(tid - HN, TN - 1) : tid, ta, tb, td);
     const int ti = i0 + ta, tj = j0 + tb, tk = k0 + td;
     if (ti >= 0 && ti < nx && tj >= 0 && tj < ny && tk >= 0 && tk < nz && tid < HN + TN) {
       eval = true;
@@ -484,9 +496,22 @@ extern "C" rs_status rs_thermal_assemble(int nx, int ny, int nz, const rs_therma
     RS_TRY(rs_wait_read(&h, flag.p, sizeof(int), s));
     if (h) return RS_E_ARG;
   }
-  const int64_t tiles = (int64_t)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY) * ((nz + TZ - 1) / TZ);
-  k_thermal<<<(unsigned)tiles, 256, 0, s>>>(nx, ny, nz, tpar(*q), d_kx, d_ky, d_kz, d_u, d_uold, nw, d_wcell, d_wkind, d_wval,
-                                            d_vals, d_res);
+  // Tiles of 8 x 4 x 2 cells, and on a grid one cell thick in x, where they
+  // would hold 8 cells, or in two directions, tiles in its own shape.  Where it
+  // is thick in x they are fast enough: 500x1x500 198 us, 700x700x1 194 (200 and
+  // 333 with a thread per cell).  Others, with tiles of 8 x 4 x 2, a thread per
+  // cell and now: 1x400x700 419, 225 and 83 us; 300000x1x1 314, 167 and 83;
+  // 1x300000x1 643, 159 and 78; 1x1x300000 1597, 168 and 82.
+  auto run = [&](auto t) {
+    using TILE = decltype(t);
+    k_thermal<TILE><<<rs_wgs(TILE::count(nx, ny, nz)), 256, 0, s>>>(nx, ny, nz, tpar(*q), d_kx, d_ky, d_kz, d_u, d_uold,
+                                                                      nw, d_wcell, d_wkind, d_wval, d_vals, d_res);
+  };
+  if (ny == 1 && nz == 1) run(tile<64, 1, 1>{});
+  else if (nx == 1 && nz == 1) run(tile<1, 64, 1>{});
+  else if (nx == 1 && ny == 1) run(tile<1, 1, 64>{});
+  else if (nx == 1) run(tile<1, 8, 8>{});
+  else run(tile<8, 4, 2>{});
   RS_HIP(hipGetLastError());
   return RS_OK;
 }
