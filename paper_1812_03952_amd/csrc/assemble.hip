@@ -160,28 +160,42 @@ __device__ __forceinline__ double row_sum(double v) {
 // G : dA/dT is the face's, the same from either side: a workgroup takes a tile
 // of cells, forms it once for each face of the tile (16 lanes a face: four
 // blocks of G, two of M), and sums the faces of its cells from LDS.  The
-// tile's outer faces are formed by two tiles (1.19 times the faces in all).
-// 100x100x50: 279 us, 1493 us with one thread a cell that formed every face
-// twice.
-constexpr int TX = 16, TY = 4, TZ = 4;
-constexpr int FX = (TX + 1) * TY * TZ, FY = TX * (TY + 1) * TZ, FZ = TX * TY * (TZ + 1);
+// tile's outer faces are formed by two tiles (1.29 times the faces in all).
+// A workgroup's faces are a chain of loads, 16 of them side by side, so a tile
+// has few cells: with 8 x 4 x 2 of them 15.7 us at 20x20x20 and 210 at
+// 100x100x50, with 16 x 4 x 4 54 and 232, with one thread a cell that formed
+// every face twice 40 and 1492.
+// Along an axis with one cell in the tile the grid has one too: no faces there.
+template <int TX_, int TY_, int TZ_> struct tile {
+  static constexpr int TX = TX_, TY = TY_, TZ = TZ_;
+  static constexpr int OX = TX > 1, OY = TY > 1, OZ = TZ > 1;           // cells around the tile
+  static constexpr int FX = OX * (TX + 1) * TY * TZ, FY = OY * TX * (TY + 1) * TZ, FZ = OZ * TX * TY * (TZ + 1);
+  static_assert(TX * TY * TZ == 64, "a wave's lanes at the end");
+  static int64_t count(int nx, int ny, int nz) {
+    return (int64_t)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY) * ((nz + TZ - 1) / TZ);
+  }
+};
 
+template <class TILE>
 __global__ __launch_bounds__(256) void k_grad_logk(int nx, int ny, int nz, const double *__restrict__ logk, double kvkh,
                                                     double tscale, const double *__restrict__ Mf,
                                                     const double *__restrict__ Mb, int nw,
                                                     const int32_t *__restrict__ wc, const double *__restrict__ wu,
                                                     const int32_t *__restrict__ rp, const double *__restrict__ G,
                                                     double *__restrict__ g) {
+  constexpr int TX = TILE::TX, TY = TILE::TY, TZ = TILE::TZ, OX = TILE::OX, OY = TILE::OY, OZ = TILE::OZ;
+  constexpr int FX = TILE::FX, FY = TILE::FY, FZ = TILE::FZ, KX = TX + 2 * OX, KY = TY + 2 * OY, KZ = TZ + 2 * OZ;
   __shared__ double ef[FX + FY + FZ];
-  __shared__ double kk[TZ + 2][TY + 2][TX + 2];
+  __shared__ double kk[KZ][KY][KX];
   const int64_t nxy = (int64_t)nx * ny, n = nxy * nz;
   const int tx = (nx + TX - 1) / TX, ty = (ny + TY - 1) / TY;
-  const int bt = blockIdx.x / tx, i0 = (int)(blockIdx.x - (unsigned)bt * tx) * TX;
+  const int wg = (int)rs_wg(), bt = wg / tx, i0 = (wg - bt * tx) * TX;
   const int k0 = bt / ty * TZ, j0 = (bt - bt / ty * ty) * TY;
+  if (k0 >= nz) return;                                 // past the last tile
   // permeabilities of the tile and its neighbours
-  for (int t = threadIdx.x; t < (TX + 2) * (TY + 2) * (TZ + 2); t += 256) {
-    const int a = t % (TX + 2), b = t / (TX + 2) % (TY + 2), d = t / ((TX + 2) * (TY + 2));
-    const int i = i0 + a - 1, j = j0 + b - 1, k = k0 + d - 1;
+  for (int t = threadIdx.x; t < KX * KY * KZ; t += 256) {
+    const int a = t % KX, b = t / KX % KY, d = t / (KX * KY);
+    const int i = i0 + a - OX, j = j0 + b - OY, k = k0 + d - OZ;
     if (i >= 0 && i < nx && j >= 0 && j < ny && k >= 0 && k < nz) kk[d][b][a] = exp(logk[i + nx * (j + (int64_t)ny * k)]);
   }
   // faces: below cell (a, b, d) of the tile along the axis
@@ -206,12 +220,12 @@ __global__ __launch_bounds__(256) void k_grad_logk(int nx, int ny, int nz, const
     if (e == 0) ef[f] = v;
   }
   __syncthreads();
-  const int a = threadIdx.x & 15, b = (threadIdx.x >> 4) & 3, d = threadIdx.x >> 6;
+  const int a = threadIdx.x % TX, b = threadIdx.x / TX % TY, d = threadIdx.x / (TX * TY);
   const int i = i0 + a, j = j0 + b, k = k0 + d;
-  if (i >= nx || j >= ny || k >= nz) return;
+  if (d >= TZ || i >= nx || j >= ny || k >= nz) return;   // the first wave takes the cells
   const int64_t c = i + nx * (j + (int64_t)ny * k);
   const unsigned in = slots_in(i, j, k, nx, ny, nz);
-  const double kc = kk[d + 1][b + 1][a + 1];
+  const double kc = kk[d + OZ][b + OY][a + OX];
   double acc = 0.0;
 #pragma unroll
   for (int s = 0; s < 7; ++s) {
@@ -221,7 +235,7 @@ __global__ __launch_bounds__(256) void k_grad_logk(int nx, int ny, int nz, const
     const int f = axis == 0 ? fa + (TX + 1) * (fb + TY * fd)
                             : (axis == 1 ? FX + fa + TX * (fb + (TY + 1) * fd) : FX + FY + fa + TX * (fb + TY * fd));
     const int sg = up ? 1 : -1;
-    const double kq = kk[d + 1 + (axis == 2) * sg][b + 1 + (axis == 1) * sg][a + 1 + (axis == 0) * sg];
+    const double kq = kk[d + OZ + (axis == 2) * sg][b + OY + (axis == 1) * sg][a + OX + (axis == 0) * sg];
     const double sc = tscale * (axis == 2 ? kvkh : 1.0);
     const double den = (kc + kq) * (kc + kq);
     const double dT = sc * 2.0 * kc * kq * kq / den;
@@ -267,9 +281,21 @@ extern "C" rs_status rs_grad_logk(int nx, int ny, int nz, const double *d_logk, 
   if (!rs_grid_dims_ok(nx, ny, nz) || nw < 0 || !d_logk || !d_Mf || !d_Mb || !d_row_ptr || !d_G || !d_g ||
       (nw > 0 && (!d_wcell || !d_wu)))
     return RS_E_ARG;
-  const int64_t tiles = (int64_t)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY) * ((nz + TZ - 1) / TZ);
-  k_grad_logk<<<(unsigned)tiles, 256, 0, rs_stream(stream)>>>(nx, ny, nz, d_logk, kvkh, tscale, d_Mf, d_Mb, nw, d_wcell,
-                                                              d_wu, d_row_ptr, d_G, d_g);
+  auto run = [&](auto t) {
+    using TILE = decltype(t);
+    k_grad_logk<TILE><<<rs_wgs(TILE::count(nx, ny, nz)), 256, 0, rs_stream(stream)>>>(
+        nx, ny, nz, d_logk, kvkh, tscale, d_Mf, d_Mb, nw, d_wcell, d_wu, d_row_ptr, d_G, d_g);
+  };
+  // Grids one cell thick in y, in x, or in two directions take tiles in their
+  // own shape.  With a thread per cell, tiles of 16 x 4 x 4 and now: 500x1x500
+  // 482, 124 and 67 us; 1x400x700 566, 585 and 73; 300000x1x1 268, 395 and 37;
+  // 1x300000x1 275, 1494 and 35; 1x1x300000 285, 1619 and 43.
+  if (ny == 1 && nz == 1) run(tile<64, 1, 1>{});
+  else if (nx == 1 && nz == 1) run(tile<1, 64, 1>{});
+  else if (nx == 1 && ny == 1) run(tile<1, 1, 64>{});
+  else if (nx == 1) run(tile<1, 8, 8>{});
+  else if (ny == 1) run(tile<8, 1, 8>{});
+  else run(tile<8, 4, 2>{});
   RS_HIP(hipGetLastError());
   return RS_OK;
 }

@@ -1,8 +1,10 @@
-"""Grids a cell or two thick: the tiles that the thermal assembly takes on them,
-at their edges, against the oracle, and a launch of more than 2^32 threads."""
+"""Grids a cell or two thick: the tiles that the thermal assembly and the
+gradient take on them, and the gradient's of 8 x 4 x 2 cells, at their edges,
+against the oracle, and a launch of more than 2^32 threads."""
 import pytest
 import torch
 
+import test_gpu_grad_tiles as tg
 import test_gpu_thermal as tt
 from paper_1812_03952_amd import rsolve as rs
 
@@ -15,6 +17,15 @@ PLANES = [(1, 8, 8), (1, 9, 17), (1, 23, 2), (1, 2, 70), (2, 1, 65), (5, 9, 1)]
 @pytest.mark.parametrize("dims", COLUMNS + PLANES)
 def test_thermal_matches_oracle(dims):
     tt.test_assembly_matches_oracle(dims)
+
+
+GRAD = [(64, 1, 1), (65, 1, 1), (1, 64, 1), (1, 131, 1), (1, 1, 65), (1, 8, 8), (1, 9, 17), (8, 1, 8), (9, 1, 17),
+        (8, 4, 2), (9, 5, 3), (24, 8, 5)]
+
+
+@pytest.mark.parametrize("dims", GRAD)
+def test_gradient_matches_oracle(dims):
+    tg.test_assembly_and_gradient_tiles(dims)
 
 
 def test_thermal_past_2_32_threads():
@@ -40,3 +51,4 @@ def test_thermal_past_2_32_threads():
     assert torch.equal(big[0], small[0]) and torch.equal(big[-1], small[2])
     assert (big[1:-1] == small[1]).all()
     rs.pool_trim()
+
