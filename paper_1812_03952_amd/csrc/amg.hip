@@ -1473,6 +1473,81 @@ __global__ __launch_bounds__(MIS_T) void k_mis7_round(int nx, int ny, int nz, co
   if (__syncthreads_or(left) && threadIdx.x == 0) *und = 1;
 }
 
+// The round as two passes with a thread per cell, as k_mis_m1 and k_mis_m2d:
+// for grids whose tiles would be mostly empty (mis7_tiled).
+__global__ void k_mis7_m1(int nx, int ny, int nz, int level, const uint8_t *__restrict__ smask,
+                          const uint8_t *__restrict__ state, uint64_t *__restrict__ m1, const int *__restrict__ prev,
+                          int *__restrict__ und0) {
+  const int64_t n = (int64_t)nx * ny * nz, c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (und0 && c < MIS_BATCH) und0[c] = 0;
+  if (c >= n || (prev && *prev == 0)) return;
+  const cell7 e = cell7_of(c, nx, ny, nz);
+  const uint8_t sm = smask[c];
+  int64_t q[7];
+  uint8_t st[7];
+#pragma unroll
+  for (int sl = 0; sl < 7; ++sl) {
+    q[sl] = ((sm >> sl) & 1u) ? e.nb[sl] : c;
+    int64_t a = q[sl];
+    asm volatile("" : "+v"(a));   // opaque: keeps the load unconditional
+    st[sl] = state[a];
+  }
+  uint64_t m = keyof(st[3], (int)c, level);
+  bool und = st[3] == ST_UND;
+#pragma unroll
+  for (int sl = 0; sl < 7; ++sl)
+    if ((sm >> sl) & 1u) {
+      const uint64_t kk = keyof(st[sl], (int)q[sl], level);
+      m = kk > m ? kk : m;
+      und = und || st[sl] == ST_UND;
+    }
+  // m1 is read only at undecided vertices and their strong neighbours, so a
+  // vertex with no undecided one in its closed neighbourhood (strength is
+  // symmetric) skips the store
+  if (und) m1[c] = m;
+}
+
+__global__ void k_mis7_m2d(int nx, int ny, int nz, int level, const uint8_t *__restrict__ smask,
+                           const uint64_t *__restrict__ m1, uint8_t *__restrict__ state,
+                           int *__restrict__ undecided, const int *__restrict__ prev) {
+  if (prev && *prev == 0) return;             // *undecided stays 0
+  const int64_t n = (int64_t)nx * ny * nz, c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int left = 0;
+  uint8_t st = ST_ISO, sm = 0;
+  if (c < n) {
+    st = state[c];
+    uint32_t t = smask[c];
+    asm volatile("" : "+v"(t));    // both loads issue before the test of st
+    sm = (uint8_t)t;
+  }
+  if (st == ST_UND) {
+    const cell7 e = cell7_of(c, nx, ny, nz);
+    uint64_t v[7];
+#pragma unroll
+    for (int sl = 0; sl < 7; ++sl) v[sl] = m1[((sm >> sl) & 1u) ? e.nb[sl] : c];
+    uint64_t m = v[3];
+#pragma unroll
+    for (int sl = 0; sl < 7; ++sl)
+      if ((sm >> sl) & 1u) m = v[sl] > m ? v[sl] : m;
+    if (m == ~0ull) state[c] = ST_OUT;
+    else if (m == prio((int)c, level)) state[c] = ST_ROOT;
+    else left = 1;
+  }
+  // one plain store per block that still has undecided vertices
+  if (__syncthreads_or(left) && threadIdx.x == 0) *undecided = 1;
+}
+
+// Tiles, while at least one cell in three of theirs is on the grid.  The whole
+// set-up with block Jacobi, by two passes a round and by tiles: 700x350x2 (one
+// in 2.1) 601 and 572 us, 20x150x150 (3.0) 646 and 621; 16x160x160 (3.8) 623
+// and 633, 700x700x1 (4.1) 510 and 546, 8x200x200 (7.5) 518 and 545, 1x400x700
+// (60) 415 and 655, 1x1x300000 (1920) 140 and 460.
+constexpr int64_t MIS_FILL = 3;
+static int64_t mis7_tiles(const grid3 &g) {
+  return (int64_t)((g.nx + MX - 1) / MX) * ((g.ny + MY - 1) / MY) * ((g.nz + MZ - 1) / MZ);
+}
+static bool mis7_tiled(const grid3 &g) { return mis7_tiles(g) * (MX * MY * MZ) <= MIS_FILL * g.n; }
+
 // (also the root cell of each aggregate)
 __global__ void k_agg1_7(int nx, int ny, int nz, const uint8_t *__restrict__ smask, const uint8_t *__restrict__ state,
                          const int32_t *__restrict__ id, int32_t *__restrict__ agg1, int32_t *__restrict__ root) {
@@ -2365,10 +2440,11 @@ rs_status rs_amg_build(rs_cpr_s *M, amg_setup *U, hipStream_t s) {
     dbuf &strong = T.strong, &state = T.state, &state2 = T.state2, &m1 = T.m1, &id = T.id, &agg1 = T.agg1;
     if (!st7) RS_TRY(dir.alloc(L->nnz));
     RS_TRY(strong.alloc(st7 ? n : L->nnz)); RS_TRY(state.alloc(n));
-    if (st7) RS_TRY(state2.alloc(n));
+    const bool tiled = st7 && mis7_tiled(g);
+    if (tiled) RS_TRY(state2.alloc(n));
     else RS_TRY(m1.alloc(sizeof(uint64_t) * n));
     RS_TRY(id.alloc(sizeof(int32_t) * n)); RS_TRY(agg1.alloc(sizeof(int32_t) * n));
-    const unsigned tiles = (unsigned)(((g.nx + MX - 1) / MX) * ((g.ny + MY - 1) / MY)) * ((g.nz + MZ - 1) / MZ);
+    const int64_t tiles = tiled ? mis7_tiles(g) : 0;
     if (st7) {
       RS_TRY(T.settled.alloc(tiles));
       k_strength7_sym<<<rs_grid(n), RS_BLOCK, 0, s>>>(g.nx, g.ny, g.nz, dir.as<uint8_t>(), strong.as<uint8_t>(),
@@ -2389,10 +2465,15 @@ rs_status rs_amg_build(rs_cpr_s *M, amg_setup *U, hipStream_t s) {
       for (int b = 0; b < MIS_BATCH; ++b) {
         const int *prev = b ? und + b - 1 : nullptr;
         int *und0 = b ? nullptr : next;
-        if (st7) {
+        if (tiled) {
           uint8_t *a = state.as<uint8_t>(), *a2 = state2.as<uint8_t>();
-          k_mis7_round<<<tiles, MIS_T, 0, s>>>(g.nx, g.ny, g.nz, strong.as<uint8_t>(), b & 1 ? a2 : a, b & 1 ? a : a2,
+          k_mis7_round<<<(unsigned)tiles, MIS_T, 0, s>>>(g.nx, g.ny, g.nz, strong.as<uint8_t>(), b & 1 ? a2 : a, b & 1 ? a : a2,
                                                und + b, und0, T.settled.as<uint8_t>());
+        } else if (st7) {
+          k_mis7_m1<<<rs_grid(n), RS_BLOCK, 0, s>>>(g.nx, g.ny, g.nz, l, strong.as<uint8_t>(), state.as<uint8_t>(),
+                                                    m1.as<uint64_t>(), prev, und0);
+          k_mis7_m2d<<<rs_grid(n), RS_BLOCK, 0, s>>>(g.nx, g.ny, g.nz, l, strong.as<uint8_t>(), m1.as<uint64_t>(),
+                                                     state.as<uint8_t>(), und + b, prev);
         } else {
           k_mis_m1<<<rs_grid(n), RS_BLOCK, 0, s>>>(n, l, rp, ci, strong.as<uint8_t>(), state.as<uint8_t>(),
                                                    m1.as<uint64_t>(), prev, und0);
