@@ -407,8 +407,11 @@ extern "C" rs_status rs_cpr_apply(rs_cpr M, const double *d_r, double *d_z, void
   RS_TRY(cpr_apply_t<float>(M, d_r, tmp.as<float>(), s));
   k_vec_to_f64<float><<<rs_grid(m), RS_BLOCK, 0, s>>>(m, tmp.as<float>(), d_z);
   RS_HIP(hipGetLastError());
-  RS_HIP(hipStreamSynchronize(s));   // tmp is freed on return
-  return rs_dilu_check(M, s);
+  // tmp is freed on return: the read of a sweep's error word waits for the
+  // stream, and is the only wait where there is one
+  const rs_status st = rs_dilu_check(M, s);
+  if (M->o.smoother == RS_SM_BJ || st != RS_OK) RS_HIP(hipStreamSynchronize(s));
+  return st;
 }
 
 extern "C" rs_status rs_cpr_smoother_get(rs_cpr M, double *h_dinv2) {
