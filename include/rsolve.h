@@ -67,7 +67,9 @@ typedef enum {
 #define RS_FRS_ABF 3    /* two-stage FRS then ABF (same section); equals ABF
                            in exact arithmetic                               */
 #define RS_SM_BJ 0      /* second stage: block Jacobi over cells (RAS, overlap 0, one cell each) */
-#define RS_SM_DILU 1    /* second stage: block ILU(0) of the whole matrix, natural order        */
+#define RS_SM_DILU 1    /* second stage: block ILU(0) of the whole matrix, natural order; needs
+                           nx * ceil(ny/4) * ceil(nz/4) < 2^24 with FP32 storage, 2^23 with
+                           FP64, else RS_E_ARG                                             */
 #define RS_SM_RAS 2     /* second stage: RAS, overlap 0, one xy-layer per subdomain, block
                            ILU(0) in each (Section "Preconditioners"); needs ny <= 480 with
                            FP64 storage, ny <= 960 with FP32, else RS_E_ARG               */

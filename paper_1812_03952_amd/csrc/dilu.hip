@@ -805,6 +805,14 @@ __global__ __launch_bounds__(6 * 64) void k_setup_pipe(int nx, int ny, int nz, i
 }  // namespace
 
 // ---------------------------------------------------------------------------
+// The grids that rs_cpr_setup documents for DILU.  (The bound comes from face
+// words of bricks of 4 x 4 lines within 4 GiB; bricks are larger now and
+// nothing of that size is allocated.)
+rs_status rs_dilu_check_shape(const grid3 &g, int prec) {
+  const int64_t c = (int64_t)((g.ny + 3) / 4) * ((g.nz + 3) / 4) * g.nx;
+  return c < (prec == 64 ? 1 << 23 : 1 << 24) ? RS_OK : RS_E_ARG;
+}
+
 rs_status rs_dilu_prepare(rs_cpr_s *M, hipStream_t s) {
   const grid3 &g = M->A->g;
   // Bricks of 8 x 4 lines while they are few enough for one a CU, 8 x 8 beyond:
@@ -825,9 +833,6 @@ rs_status rs_dilu_prepare(rs_cpr_s *M, hipStream_t s) {
   RS_TRY(M->pctl.alloc(sizeof(int) * 4));     // [0] ticket, [1] error, [2] second ticket
   // face exchange: 2 faces x 8 lines x nx cells x 4 values x (1 or 2) words
   const size_t words = nb * 2 * BJ * g.nx * 4 * (M->prec == 64 ? 2 : 1);
-  // grids beyond this are refused
-  const size_t nb4 = (size_t)((g.ny + 3) / 4) * ((g.nz + 3) / 4);
-  if (sizeof(uint64_t) * nb4 * 8 * g.nx * 4 * (M->prec == 64 ? 2 : 1) >= 0xffffffffull) return RS_E_ARG;
   RS_TRY(M->pxch.alloc(sizeof(uint64_t) * words));
   const size_t most = std::max(words, nbs);
   k_pipe_clear<<<rs_grid(most), RS_BLOCK, 0, s>>>((int64_t)words, M->pxch.as<uint64_t>(), (int)nbs, M->pdone.as<int>(),
@@ -884,7 +889,6 @@ rs_status rs_dilu_apply_run(rs_cpr_s *M, const T *xp, T *out, hipStream_t s) {
 template rs_status rs_dilu_apply_run<double>(rs_cpr_s *, const double *, double *, hipStream_t);
 template rs_status rs_dilu_apply_run<float>(rs_cpr_s *, const float *, float *, hipStream_t);
 
-// error word of the pipelined kernels (time-out of a bounded wait)
 // error words of the pipelined sweeps (DILU bricks, RAS strips): a bounded
 // wait that timed out leaves a non-zero word
 rs_status rs_dilu_check(rs_cpr_s *M, hipStream_t s) {

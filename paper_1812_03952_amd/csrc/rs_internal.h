@@ -225,6 +225,7 @@ rs_status rs_cpr_apply_in(rs_cpr_s *M, const double *w, const double *d_h, doubl
 rs_status rs_cpr_apply_rest(rs_cpr_s *M, void *z, int zprec, hipStream_t s);
 rs_status rs_vcycle_run(rs_cpr_s *M, hipStream_t s);
 rs_status rs_transpose7(const rs_bsr_s *A, rs_bsr_s *At, hipStream_t s);
+rs_status rs_dilu_check_shape(const grid3 &g, int prec);
 rs_status rs_dilu_prepare(rs_cpr_s *M, hipStream_t s);
 rs_status rs_dilu_setup_run(rs_cpr_s *M, int *flag, hipStream_t s);
 template <class T> rs_status rs_dilu_apply_run(rs_cpr_s *M, const T *xp, T *out, hipStream_t s);

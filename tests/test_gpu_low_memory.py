@@ -1,5 +1,7 @@
 """Calls that meet the end of device memory: what they report, and that the
 handle they ran on still works."""
+from contextlib import contextmanager
+
 import pytest
 import torch
 
@@ -11,18 +13,24 @@ pytestmark = pytest.mark.gpu
 GiB = 1 << 30
 
 
-def leave_free(target):
-    """Take device memory until about `target` bytes of it are free."""
+@contextmanager
+def free_memory(target):
+    """About `target` bytes of device memory free, the rest taken."""
     torch.cuda.synchronize()
     rs.pool_trim()
     torch.cuda.empty_cache()
     held = []
-    for _ in range(64):
-        left = torch.cuda.mem_get_info()[0] - target
-        if left < (4 << 20):
-            break
-        held.append(torch.empty(min(left, 16 * GiB) >> 21 << 21, dtype=torch.uint8, device="cuda"))
-    return held
+    try:
+        for _ in range(64):
+            left = torch.cuda.mem_get_info()[0] - target
+            if left < (4 << 20):
+                break
+            held.append(torch.empty(min(left, 16 * GiB) >> 21 << 21, dtype=torch.uint8, device="cuda"))
+        yield
+    finally:
+        held.clear()
+        torch.cuda.empty_cache()
+        rs.pool_trim()
 
 
 def test_gmres_restart_that_does_not_fit():
@@ -38,11 +46,29 @@ def test_gmres_restart_that_does_not_fit():
     basis, z = 8 * N * 33, 8 * N * 32
     # room for the basis and for half of the preconditioned vectors; what the
     # short restart held (9 vectors) comes back to the pool meanwhile
-    held = leave_free(basis + z // 2 - 9 * 8 * N)
-    info = rs.gmres_solve(A, M, dp.b, x1, rs.gmres_opts(restart=32, rtol=1e-10), check=False)
-    assert info["return"] == -3
-    assert rs.gmres_solve(A, M, dp.b, x1, short)["return"] == 0
-    assert torch.equal(x0, x1)
-    del held
-    torch.cuda.empty_cache()
+    with free_memory(basis + z // 2 - 9 * 8 * N):
+        info = rs.gmres_solve(A, M, dp.b, x1, rs.gmres_opts(restart=32, rtol=1e-10), check=False)
+        assert info["return"] == -3
+        assert rs.gmres_solve(A, M, dp.b, x1, short)["return"] == 0
+        assert torch.equal(x0, x1)
     assert rs.gmres_solve(A, M, dp.b, x1, rs.gmres_opts(restart=32, rtol=1e-10))["return"] == 0
+
+
+def test_dilu_refuses_a_grid_before_it_takes_memory():
+    """A column of 2^25 cells in FP64, where the set-up takes 2^25 - 4."""
+    nz = 1 << 25
+    rp, ci = rs.pattern(1, 1, nz)
+    vals = torch.zeros(16 * ci.numel(), dtype=torch.float64, device="cuda").view(-1, 16)
+    row = torch.repeat_interleave(torch.arange(nz, device="cuda"), torch.diff(rp).long())
+    vals[ci == row] = torch.eye(4, dtype=torch.float64, device="cuda").reshape(1, 16)
+    del row
+    A = rs.bsr_create(1, 1, nz, rp, ci, vals.view(-1))
+    D = rs.decouple(A, rs.ABF, 64)
+    before = sum(rs.pool_usage())
+    with pytest.raises(rs.RsError) as e:
+        rs.cpr_setup(A, D)
+    assert e.value.status == -1
+    assert sum(rs.pool_usage()) == before
+    del A, D, rp, ci, vals
+    torch.cuda.empty_cache()
+    rs.pool_trim()
