@@ -218,9 +218,11 @@ static rs_status bicgstab_t(rs_bsr_s *A, rs_cpr_s *M, const double *b, double *x
   const unsigned nsp = rs_spmv_blocks(A);
   const int zp = sizeof(TZ) == 8 ? 64 : 32;
   if (M->bprec != zp || !M->bvec.p) {
-    RS_TRY(M->bvec.alloc(sizeof(double) * N * 5 + sizeof(TZ) * N * 2));
-    RS_TRY(M->bpart.alloc(sizeof(double) * (2 * (size_t)nsp + 2 * RED_NB)));
-    RS_TRY(M->bscal.alloc(sizeof(double) * B_TOTAL));
+    RS_TRY(rs_yield(M, [&]() -> rs_status {
+      RS_TRY(M->bvec.alloc(sizeof(double) * N * 5 + sizeof(TZ) * N * 2));
+      RS_TRY(M->bpart.alloc(sizeof(double) * (2 * (size_t)nsp + 2 * RED_NB)));
+      return M->bscal.alloc(sizeof(double) * B_TOTAL);
+    }));
     M->bprec = zp;
   }
   double *r = M->bvec.as<double>(), *rh = r + N, *p = rh + N, *v = p + N, *tv = v + N;

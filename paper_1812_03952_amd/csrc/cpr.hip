@@ -241,11 +241,7 @@ static hipStream_t side_stream() {
 // other, but only on workgroups that took their ticket before them and so
 // are already running, whatever else the device runs.)  Both streams are
 // idle again when this returns, on every path.
-extern "C" rs_status rs_cpr_setup(rs_bsr A, rs_dcpl D, const rs_cpr_opts *o, void *stream, rs_cpr *out) {
-  if (!A || !D || !out || D->A != A) return RS_E_ARG;
-  *out = nullptr;
-  rs_cpr_opts opts;
-  if (o) opts = *o; else rs_cpr_opts_default(&opts);
+static rs_status cpr_setup(rs_bsr A, rs_dcpl D, const rs_cpr_opts &opts, bool pcopy, void *stream, rs_cpr *out) {
   const bool ras = opts.smoother == RS_SM_RAS || opts.smoother == RS_SM_RAS1;
   if ((opts.smoother != RS_SM_BJ && opts.smoother != RS_SM_DILU && !ras) ||
       (ras && rs_ras_check_shape(A->g, D->prec) != RS_OK) ||
@@ -263,6 +259,7 @@ extern "C" rs_status rs_cpr_setup(rs_bsr A, rs_dcpl D, const rs_cpr_opts *o, voi
   const bool split = ss != s;
   rs_cpr_s *M = new rs_cpr_s();
   M->A = A; M->D = D; M->o = opts; M->prec = D->prec;
+  M->pcopy = pcopy;
   int64_t n = A->g.n;
   size_t es = M->prec == 64 ? sizeof(double) : sizeof(float);
   rs_status st = RS_OK;
@@ -322,6 +319,16 @@ extern "C" rs_status rs_cpr_setup(rs_bsr A, rs_dcpl D, const rs_cpr_opts *o, voi
   if (st != RS_OK) { delete M; return st; }
   *out = M;
   return RS_OK;
+}
+
+extern "C" rs_status rs_cpr_setup(rs_bsr A, rs_dcpl D, const rs_cpr_opts *o, void *stream, rs_cpr *out) {
+  if (!A || !D || !out || D->A != A) return RS_E_ARG;
+  *out = nullptr;
+  rs_cpr_opts opts;
+  if (o) opts = *o; else rs_cpr_opts_default(&opts);
+  const rs_status st = cpr_setup(A, D, opts, true, stream, out);
+  // without the memory for all of it: DILU without its copy in brick order
+  return st == RS_E_NOMEM && opts.smoother == RS_SM_DILU ? cpr_setup(A, D, opts, false, stream, out) : st;
 }
 
 template <class T>
@@ -404,7 +411,7 @@ extern "C" rs_status rs_cpr_apply(rs_cpr M, const double *d_r, double *d_z, void
   }
   int64_t m = 4 * M->A->g.n;
   dbuf tmp;
-  RS_TRY(tmp.alloc(sizeof(float) * m));
+  RS_TRY(rs_yield(M, [&] { return tmp.alloc(sizeof(float) * m); }));
   RS_TRY(cpr_apply_t<float>(M, d_r, tmp.as<float>(), s));
   k_vec_to_f64<float><<<rs_grid(m), RS_BLOCK, 0, s>>>(m, tmp.as<float>(), d_z);
   RS_HIP(hipGetLastError());

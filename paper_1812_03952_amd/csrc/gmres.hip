@@ -323,11 +323,13 @@ static rs_status gmres_t(rs_bsr_s *A, rs_cpr_s *M, const double *b, double *x, c
   int m = o.restart;
   if (M->m != m) {
     M->m = 0;                                    // no workspace until every part of it is there
-    RS_TRY(M->V.alloc(sizeof(double) * N * (m + 1)));
-    RS_TRY(M->Z.alloc(sizeof(TZ) * N * m));
-    RS_TRY(M->w.alloc(sizeof(double) * N));
-    RS_TRY(M->part.alloc(sizeof(double) * RED_NB * 33));
-    RS_TRY(M->scal.alloc(sizeof(double) * S_TOTAL));
+    RS_TRY(rs_yield(M, [&]() -> rs_status {
+      RS_TRY(M->V.alloc(sizeof(double) * N * (m + 1)));
+      RS_TRY(M->Z.alloc(sizeof(TZ) * N * m));
+      RS_TRY(M->w.alloc(sizeof(double) * N));
+      RS_TRY(M->part.alloc(sizeof(double) * RED_NB * 33));
+      return M->scal.alloc(sizeof(double) * S_TOTAL);
+    }));
     M->m = m;
   }
   double *V = M->V.as<double>(), *w = M->w.as<double>(), *part = M->part.as<double>(), *S = M->scal.as<double>();

@@ -181,6 +181,7 @@ struct rs_cpr_s {
   int pbk = 8, pnj = 0, pnk = 0;
   uint32_t pepoch = 0;
   dbuf pdone, pctl, pxch, pblk, pxp;
+  bool pcopy = true;         // the set-up is to allocate pblk
   // RAS sweeps: scaled blocks and x_p in wavefront order; strips per layer,
   // their boundary exchange words, [a ticket per sweep, error] and the tag of
   // the last sweep
@@ -203,6 +204,18 @@ struct rs_cpr_s {
   int bprec = 0;
   ~rs_cpr_s();
 };
+
+// The allocations of a solve or an apply with M: where memory ends, DILU's copy
+// of its blocks in brick order gives way to them (the sweeps then read the
+// grid's order).
+template <class F> static inline rs_status rs_yield(rs_cpr_s *M, F &&alloc) {
+  rs_status st = alloc();
+  if (st != RS_E_NOMEM || !M->pblk.p) return st;
+  RS_HIP(hipDeviceSynchronize());
+  M->pblk.release();
+  return alloc();
+}
+
 
 // ---- internal entry points shared between translation units ---------------
 rs_status rs_spmv_any(const rs_bsr_s *A, const void *x, int xprec, double *y,
