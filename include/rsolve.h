@@ -386,8 +386,8 @@ rs_status rs_cpr_level_p(rs_cpr M, int l, int64_t *h_nnz, int32_t *h_rp, int32_t
 /* Second-stage block inverses (16*n doubles, upcast if FP32). */
 rs_status rs_cpr_smoother_get(rs_cpr M, double *h_dinv2);
 /* Inverse of a dense n x n FP64 matrix (row-major, device) by the kernels
- * that invert the coarsest AMG level (Gauss-Jordan with partial pivoting:
- * register tiles up to n = 156, one workgroup up to 256, one launch pair per
+ * that invert the coarsest AMG level (Gauss-Jordan with partial pivoting: one
+ * workgroup with the matrix in registers up to n = 256, one launch pair per
  * column beyond); 16 n^2 bytes of scratch.  A zero pivot gives
  * RS_E_SINGULAR. */
 rs_status rs_dense_inverse(int n, const double *d_a, double *d_inv, void *stream);

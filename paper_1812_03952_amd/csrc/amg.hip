@@ -22,9 +22,9 @@
 //              neighbouring first-pass aggregate with the largest |a_ij|,
 //              ties to the lowest id; vertices with no strength edge stay
 //              unaggregated.
-//   Galerkin   A_c = P^T A P for piecewise-constant P, one thread per coarse
-//              row, summing members in increasing fine index and each
-//              member's row in column order.  Only additions are involved, so
+//   Galerkin   A_c = P^T A P for piecewise-constant P, 16 lanes per coarse row
+//              (a thread past GAL_LANES_MAX rows), summing members in
+//              increasing fine index and each member's row in column order.  Only additions are involved, so
 //              coarse matrices are bitwise reproducible.
 //   cycle      l1-Jacobi (d_i = sgn(a_ii) sum_j |a_ij|), one sweep before and
 //              one after the coarse correction; dense FP64 inverse at the
@@ -1949,8 +1949,11 @@ __global__ __launch_bounds__(256) void k_vc_post7z(int n, int nx, int nxy, const
 // twenty of them and two to four host reads, 3 us and 9 us each, where none has
 // work for a microsecond.  The whole preconditioner set-up at 20x20x10 (levels of
 // 4000 and 600 rows) takes 215 us, 371 before this and k_galerkin_lanes; this
-// kernel 46 us of it on the fine level and 13 to 48 on coarser ones.  At more
-// rows its one CU would be slower than the launches.
+// kernel 46 us of it on the fine level and 13 to 48 on coarser ones.  Up to 8192
+// rows, 96 KB of LDS: with 4096 the set-ups (block Jacobi) of 20x20x20, 45x45x4
+// and 90x90x1 take 367, 381 and 385 us for 330, 353 and 333 (without this kernel
+// 435, 421 and 439), and that of 100x100x50, whose third level has 5.6 thousand
+// rows, 710 for 657.
 // The results are those of the kernels above (the same tests, sums and orders).
 // Keys are hashes alone, as in k_mis7_round; the host sees to it that the two
 // marks are no row's hash (small_keys_ok).
@@ -2287,8 +2290,8 @@ static rs_status level0_as_coarsest(rs_cpr_s *M, hipStream_t s) {
 // inspected).  The host reads back a few words behind each batch of MIS rounds
 // (are any left, the number of roots, the error flag, the entries of the level
 // just built) and once at the end (rs_amg_finish); the temporaries of all
-// levels stay in M->setup until then, because pool memory that is given back
-// may go to work on another stream at once.
+// levels stay in the amg_setup until then (rs_cpr_setup's own), because pool
+// memory that is given back may go to work on another stream at once.
 int *rs_amg_word_sm(amg_setup *U) { return U->words.as<int>() + W_SM; }
 
 rs_status rs_amg_begin(amg_setup *U, hipStream_t s) {

@@ -222,7 +222,7 @@ rs_cpr_s::~rs_cpr_s() {
 extern "C" void rs_cpr_destroy(rs_cpr M) { delete M; }
 
 // One non-blocking stream per device, at the default priority, for set-up
-// work that does not depend on the AMG set-up (block Jacobi, layer RAS).
+// work that does not depend on the AMG set-up (the second stage's).
 // nullptr if it cannot be created (the work then stays on the caller's stream).
 static hipStream_t side_stream() {
   static std::mutex mu;

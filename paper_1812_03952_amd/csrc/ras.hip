@@ -303,8 +303,8 @@ __global__ __launch_bounds__(1024) void k_ras_setup(int nx, int ny, int64_t n, i
 // of a cell lie side by side, and a line's own previous value comes by DPP.
 // Both sweeps, against the kernels before these (per-lane addresses formed
 // anew each level; strips of up to 224 lines, a layer per workgroup above):
-// FP32 158 -> 98 us at 100x100x50, 393 -> 294 at 200x200x100 (1.3 GB, 4.4
-// TB/s), 905 -> 745 at 256x256x160; FP64 335 -> 267 at 161x143x67.
+// FP32 157 -> 97 us at 100x100x50, 398 -> 323 at 200x200x100 (1.3 GB, 4.0
+// TB/s), 930 -> 800 at 256x256x160; FP64 342 -> 277 at 161x143x67.
 // The level count is padded to a multiple of P and every load is issued
 // unconditionally at a clamped (in-bounds) address, with the terms of inactive
 // cells dropped by selects: then every path through a level issues the same
@@ -394,9 +394,9 @@ template <class T> __device__ __forceinline__ T quad_dot(const T (&a)[4], T v) {
 // The poller wave: words of the neighbour's boundary line, 8 steps at a time
 // (32 lanes: step offset, block row), loaded 5 steps before the first of them
 // is needed and checked two steps before it.  A strip so runs 9 steps behind
-// its neighbour's line; with 16 at a time, 17: both sweeps at 100x100x50 in
-// FP64 120 us against 134, at 200x200x100 in FP32 294 against 311 (loaded 7
-// steps before: the same).  Word i = i0 + di * step, if in
+// its neighbour's line; with 16 at a time, 17, and both sweeps took 12 % longer
+// at 100x100x50 in FP64, 6 % at 200x200x100 in FP32 (loaded 7 steps before: the
+// same).  Word i = i0 + di * step, if in
 // [0, nx); xw: the neighbour's words, nullptr for none.  Value of step m to
 // slot `slot` of the ring buffer that step m reads.
 template <class T>
@@ -550,8 +550,8 @@ __global__ __launch_bounds__(RAS_T) void k_ras_bwd(int nx, int ny, int nz, int S
     // A line's output advances by one cell a level, so eight lanes write eight
     // cells of a line in a row (128 or 256 bytes) at the level that completes
     // them, for an eighth of the lines each: stored level by level, 16 bytes to
-    // each line's row, the sweep took 192 us in FP64 at 161x143x67 instead of
-    // 145 (FP32: 100 and 79).
+    // each line's row, the sweep took a third longer in FP64 at 161x143x67, a
+    // quarter in FP32.
     const int w = tid - NC, sub = w & 7;
     uint64_t *xp = s > 0 ? xw + W * (ras_xword(k, s, S, nx, 0) + w) : nullptr;
     __syncthreads();
@@ -898,13 +898,14 @@ __global__ void k_ras_zero(int64_t m, T *__restrict__ v) {
 }
 
 // Strips per layer: at most RAS_H = 48 lines each.  Of 16 to 96 lines, 48 (three
-// compute waves) measured fastest or within 3 % of it in FP32 everywhere and in
-// FP64 on large grids: both sweeps at 200x200x100 take 339 us in FP32, against
-// 406 with 32 lines and 384 with 64, and 759 against 842 and 779 at
-// 256x256x160.  In FP64 a strip's operands bind it at what one CU takes in, so
-// strips of 32 lines are faster while each has a CU of its own and the layer
-// is split anyway: 142 us against 160 at 100x100x50, but 377 against 324 at
-// 161x143x67 (335 strips) and 56 against 48 at 60x40x30 (one strip).
+// compute waves) measured fastest or within 4 % of it in FP32 everywhere and in
+// FP64 on large grids: both sweeps at 200x200x100 take 323 us in FP32, against
+// 366 with 32 lines and 347 with 64, and 800 against 789 and 777 at
+// 256x256x160; in FP64 613 against 711 and 681 at 200x200x100.  In FP64 a
+// strip's operands bind it at what one CU takes in, so strips of 32 lines are
+// faster while each has a CU of its own and the layer is split anyway: 122 us
+// against 138 at 100x100x50, but 342 against 277 at 161x143x67 (335 strips) and
+// 54 against 50 at 60x40x30 (one strip).
 struct ras_shape { int S, H; };
 static ras_shape ras_strips(const grid3 &g, int prec) {
   int H = RAS_H;
@@ -1047,10 +1048,10 @@ rs_status rs_ras_apply_run(rs_cpr_s *M, const T *xp, T *out, hipStream_t s) {
   }
   RS_HIP(hipGetLastError());
   // Levels in flight, and with them the workgroups that share a CU: few of them
-  // stream the operands of a large grid faster than many (at 200x200x100, FP32,
-  // the forward sweep takes 144 us with 16 levels and one workgroup, 183 with
-  // 12 and three; the backward one 150 with 12 levels and two, by the LDS asked
-  // for, 156 with three and 171 with 10 levels).
+  // stream the operands of a large grid faster than many.  At 200x200x100, FP32,
+  // the forward sweep with 12 levels and three workgroups takes 27 % longer than
+  // with 16 levels and one; the backward one has 12 levels and two, by the LDS
+  // asked for, and takes 4 % longer with three and 14 % with 10 levels.
   constexpr int PF = sizeof(T) == 4 ? 16 : 8, PB = sizeof(T) == 4 ? 12 : 6;
   constexpr size_t two_per_cu = 56000;
   const int S = M->rs_strips, H = M->rs_h;
