@@ -285,15 +285,12 @@ static int64_t grid_nnzb(int nx, int ny, int nz) {
 static rs_status load_values(rs_bsr_s *A, const double *d_vals, hipStream_t s) {
   if ((uintptr_t)d_vals & 15) return RS_E_ARG;         // block rows are read 16 bytes at a time
   int64_t n = A->g.n;
-  dbuf flag;
-  RS_TRY(flag.alloc(sizeof(int)));
-  RS_TRY(rs_fill32(flag.p, 0, 1, s));
-  k_to7<<<rs_grid(7 * n * 4), RS_BLOCK, 0, s>>>(n, A->pos7.as<int64_t>(), d_vals, A->a7.as<double>(),
-                                                  flag.as<int>());
+  int *flag = A->flag.as<int>();
+  k_to7<<<rs_grid(7 * n * 4), RS_BLOCK, 0, s>>>(n, A->pos7.as<int64_t>(), d_vals, A->a7.as<double>(), flag);
   RS_HIP(hipGetLastError());
   int h = 0;
   A->ref = nullptr;                     // A holds its own copy again
-  RS_TRY(rs_wait_read(&h, flag.p, sizeof(int), s));
+  RS_TRY(rs_wait_take(&h, flag, s));
   return h ? RS_E_NONFINITE : RS_OK;
 }
 
@@ -319,14 +316,13 @@ extern "C" rs_status rs_bsr_create(int nx, int ny, int nz, int bs, int64_t nnzb,
         hipMemcpyAsync(A->ci.p, d_col_idx, sizeof(int32_t) * nnzb, hipMemcpyDeviceToDevice, s) != hipSuccess) {
       st = RS_E_HIP; break;
     }
-    dbuf flag;
-    if ((st = flag.alloc(sizeof(int))) != RS_OK) break;
-    if ((st = rs_fill32(flag.p, 0, 1, s)) != RS_OK) break;
+    if ((st = A->flag.alloc(sizeof(int))) != RS_OK) break;
+    if ((st = rs_fill32(A->flag.p, 0, 1, s)) != RS_OK) break;
     k_validate<<<rs_grid(n), RS_BLOCK, 0, s>>>(nx, ny, nz, nnzb, A->rp.as<int32_t>(), A->ci.as<int32_t>(),
-                                               A->pos7.as<int64_t>(), flag.as<int>());
+                                               A->pos7.as<int64_t>(), A->flag.as<int>());
     int h = 0;
     if (hipGetLastError() != hipSuccess ||
-        rs_wait_read(&h, flag.p, sizeof(int), s) != RS_OK) { st = RS_E_HIP; break; }
+        rs_wait_take(&h, A->flag.as<int>(), s) != RS_OK) { st = RS_E_HIP; break; }
     if (h) { st = RS_E_ARG; break; }
     st = load_values(A, d_vals, s);
   } while (0);
@@ -426,6 +422,8 @@ rs_status rs_transpose7(const rs_bsr_s *A, rs_bsr_s *At, hipStream_t s) {
   RS_TRY(At->ci.alloc(sizeof(int32_t) * A->nnzb));
   RS_TRY(At->pos7.alloc(sizeof(int64_t) * 7 * n));
   RS_TRY(At->a7.alloc(sizeof(double) * 7 * n * 16));
+  RS_TRY(At->flag.alloc(sizeof(int)));
+  RS_TRY(rs_fill32(At->flag.p, 0, 1, s));
   RS_HIP(hipMemcpyAsync(At->rp.p, A->rp.p, sizeof(int32_t) * (n + 1), hipMemcpyDeviceToDevice, s));
   RS_HIP(hipMemcpyAsync(At->ci.p, A->ci.p, sizeof(int32_t) * A->nnzb, hipMemcpyDeviceToDevice, s));
   RS_HIP(hipMemcpyAsync(At->pos7.p, A->pos7.p, sizeof(int64_t) * 7 * n, hipMemcpyDeviceToDevice, s));

@@ -397,22 +397,20 @@ static rs_status decouple_impl(rs_bsr_s *A, const double *vals, bool attach, int
     if ((st = D->dinv.alloc(es * n * 16)) != RS_OK) break;
     if ((st = D->ap7.alloc(sizeof(double) * 7 * n)) != RS_OK) break;
     if ((st = D->col0.alloc(es * 32 * n)) != RS_OK) break;
-    dbuf flag;
-    if ((st = flag.alloc(sizeof(int))) != RS_OK) break;
-    if ((st = rs_fill32(flag.p, 0, 1, s)) != RS_OK) break;
+    int *flag = A->flag.as<int>();
     const grid3 &g = A->g;
     if (vals && attach) A->ref = vals;
     if (vals && !attach) {
-      launch_decouple(method, prec, n, srcu{vals, A->pos7.as<int64_t>(), A->a7.as<double>(), n}, D, flag.as<int>(), s);
+      launch_decouple(method, prec, n, srcu{vals, A->pos7.as<int64_t>(), A->a7.as<double>(), n}, D, flag, s);
       A->ref = nullptr;
     } else if (A->ref) {
       // attached values are checked for finiteness when they arrive
       const srcr src{A->ref, (uint32_t)g.nx, (uint32_t)g.ny, (uint32_t)g.nz, vals != nullptr};
-      launch_decouple(method, prec, n, src, D, flag.as<int>(), s);
+      launch_decouple(method, prec, n, src, D, flag, s);
     } else {
-      launch_decouple(method, prec, n, src7{A->a7.as<double>(), n}, D, flag.as<int>(), s);
+      launch_decouple(method, prec, n, src7{A->a7.as<double>(), n}, D, flag, s);
     }
-    if (hipGetLastError() != hipSuccess || rs_wait_read(&h, flag.p, sizeof(int), s) != RS_OK) {
+    if (hipGetLastError() != hipSuccess || rs_wait_take(&h, flag, s) != RS_OK) {
       st = RS_E_HIP;
       break;
     }

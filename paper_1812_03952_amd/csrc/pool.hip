@@ -171,12 +171,17 @@ rs_status rs_wait_post(const rs_post *p, uint64_t seq, hipStream_t s) {
   }
 }
 
-// the words and, after them, whether an error word is set, into the post's values
-__global__ void k_post_words(const uint32_t *__restrict__ d, int nw, const int *__restrict__ err0,
-                             const int *__restrict__ err1, rs_post *__restrict__ post, uint64_t seq) {
+// the words and, after them, whether an error word is set, into the post's
+// values; take: the words are zero afterwards
+__global__ void k_post_words(uint32_t *d, int nw, int take, const int *err0, const int *err1,
+                             rs_post *__restrict__ post, uint64_t seq) {
   const int t = threadIdx.x;
   uint32_t *o = (uint32_t *)post->v;
-  if (t < nw) __hip_atomic_store(o + t, d[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (t < nw) {
+    __hip_atomic_store(o + t, d[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    // at agent scope: done before the post, whatever stream the next call takes
+    if (take) __hip_atomic_store(d + t, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   if (t == 0)
     __hip_atomic_store(o + RS_READ_WORDS, ((err0 && *err0) || (err1 && *err1)) ? 1u : 0u, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_SYSTEM);
@@ -184,13 +189,13 @@ __global__ void k_post_words(const uint32_t *__restrict__ d, int nw, const int *
   if (t == 0) __hip_atomic_store(&post->seq, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-rs_status rs_wait_read_err(void *h, const void *d, size_t bytes, const int *const (&errw)[2], int *err,
-                           hipStream_t s) {
+static rs_status wait_words(void *h, uint32_t *d, size_t bytes, bool take, const int *const (&errw)[2], int *err,
+                            hipStream_t s) {
   if (bytes > sizeof(uint32_t) * RS_READ_WORDS || bytes % 4) return RS_E_ARG;
   rs_post *post = nullptr;
   RS_TRY(rs_post_slot(&post));
   const uint64_t seq = rs_post_next(post);
-  k_post_words<<<1, 64, 0, s>>>((const uint32_t *)d, (int)(bytes / 4), errw[0], errw[1], post, seq);
+  k_post_words<<<1, 64, 0, s>>>(d, (int)(bytes / 4), take ? 1 : 0, errw[0], errw[1], post, seq);
   RS_HIP(hipGetLastError());
   RS_TRY(rs_wait_post(post, seq, s));
   memcpy(h, post->v, bytes);
@@ -198,10 +203,21 @@ rs_status rs_wait_read_err(void *h, const void *d, size_t bytes, const int *cons
   return RS_OK;
 }
 
+rs_status rs_wait_read_err(void *h, const void *d, size_t bytes, const int *const (&errw)[2], int *err,
+                           hipStream_t s) {
+  return wait_words(h, (uint32_t *)d, bytes, false, errw, err, s);
+}
+
 rs_status rs_wait_read(void *h, const void *d, size_t bytes, hipStream_t s) {
   const int *const none[2] = {nullptr, nullptr};
   int e = 0;
   return rs_wait_read_err(h, d, bytes, none, &e, s);
+}
+
+rs_status rs_wait_take(int *h, int *d, hipStream_t s) {
+  const int *const none[2] = {nullptr, nullptr};
+  int e = 0;
+  return wait_words(h, (uint32_t *)d, sizeof(int), true, none, &e, s);
 }
 
 __global__ void k_fill32(int64_t m, uint32_t v, uint32_t *__restrict__ a) {

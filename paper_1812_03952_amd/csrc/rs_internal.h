@@ -30,6 +30,8 @@ void rs_pool_put(void *p, size_t bytes);
 // (rs_wait_read; err: as well whether a word of rs_sweep_errors is set).
 constexpr int RS_READ_WORDS = 22;
 rs_status rs_wait_read(void *h, const void *d, size_t bytes, hipStream_t s);
+// Read an error word and leave it zero for the next call.
+rs_status rs_wait_take(int *h, int *d, hipStream_t s);
 rs_status rs_wait_read_err(void *h, const void *d, size_t bytes, const int *const (&errw)[2], int *err, hipStream_t s);
 // a[0 .. m) = v by a kernel: three times cheaper to queue than hipMemsetAsync
 rs_status rs_fill32(void *a, uint32_t v, int64_t m, hipStream_t s);
@@ -110,6 +112,8 @@ struct rs_bsr_s {
   // attached values (caller layout, rs_bsr_attach_decouple): when set, the
   // values of A are read there and a7 is stale
   const double *ref = nullptr;
+  // error word of the calls that take or decouple values; zero between calls
+  dbuf flag;
   // adjoint cache
   rs_bsr_s *at = nullptr;
   rs_dcpl_s *at_d = nullptr;
